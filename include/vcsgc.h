@@ -493,7 +493,7 @@ vcsgc_status vcsgc_mlp_grad(vcsgc_mlp *m, const double *desc_dev, const double *
  * device memory (code under HIP graph capture, training loops that forbid
  * allocation): the same forward and backward kernels on n <= 4096 samples,
  * with the batch's workspace in a fixed device array of the library
- * (about 7.6 MB per device, held until the process ends) instead of the
+ * (about 4.9 MB per device, held until the process ends) instead of the
  * network's own buffers, which vcsgc_mlp_grad grows with hipMalloc.
  * desc_dev[n][10] (FP64) and dE_dev[n] (eV) are inputs; grad_dev receives the
  * 4929 gradient values (parameter order of vcsgc_mlp_set_params) and

@@ -23,16 +23,16 @@ struct vcsgc_mlp {
   float *g = nullptr;     // gradient [4929]
   float *m1 = nullptr, *m2 = nullptr;  // Adam moments
   __bf16 *w1b = nullptr;  // [64][32]
-  __bf16 *w2b = nullptr;  // [64][64]
+  __bf16 *w2b = nullptr;  // [64][64], then its transpose
   float *w3r = nullptr;   // [64] bf16-rounded w3
   float mu[10], sd[10];
   float out_mu = 0.f, out_sd = 1.f;
   int64_t adam_t = 0;
   // training scratch for batch size cap
   int64_t cap = 0;
-  float *Z = nullptr, *T = nullptr, *A1 = nullptr, *H1 = nullptr, *A2 = nullptr, *H2 = nullptr;
-  float *Y = nullptr, *dY = nullptr, *dA2 = nullptr, *dH1 = nullptr, *dA1 = nullptr;
-  double *red = nullptr;  // loss / statistics partials
+  unsigned char *work = nullptr;
+  double *red = nullptr;  // per-sample squared errors
+  double *mom = nullptr;  // normalization: block totals, then mean and sd per column
   std::string err;
 };
 
@@ -62,7 +62,10 @@ __global__ void k_mlp_refresh(const float *__restrict__ p, __bf16 *w1b, __bf16 *
     const int n = t / MLP_KP, k = t % MLP_KP;
     w1b[t] = to_bf16(k < MLP_IN ? p[OFF_W1 + n * MLP_IN + k] : 0.0f);
   }
-  if (t < MLP_H * MLP_H) w2b[t] = to_bf16(p[OFF_W2 + t]);
+  if (t < MLP_H * MLP_H) {
+    w2b[t] = to_bf16(p[OFF_W2 + t]);
+    w2b[MLP_H * MLP_H + t % MLP_H * MLP_H + t / MLP_H] = to_bf16(p[OFF_W2 + t]);
+  }
   if (t < MLP_H) w3r[t] = bf16_round(p[OFF_W3 + t]);
 }
 
@@ -92,117 +95,345 @@ __global__ void __launch_bounds__(BLOCK) k_mlp_infer(MlpDev md, int64_t n,
 // ---------------------------------------------------------------------------
 // training
 // ---------------------------------------------------------------------------
-// C[M][N] = sum_k bf16(A(m,k)) bf16(B(k,n)), FP32 accumulation on the MFMA;
-// A(m,k) = A[m*sam + k*sak], B(k,n) = B[k*sbk + n*sbn]; one 16x16 tile per
-// wave, out-of-range operands read as zero.
-__global__ void __launch_bounds__(BLOCK)
-    k_gemm_bf16(int M, int N, int K, const float *__restrict__ A, int64_t sam, int64_t sak,
-                const float *__restrict__ B, int64_t sbk, int64_t sbn, float *C, int64_t ldc) {
-  const int lane = threadIdx.x & 63;
-  const int tile = blockIdx.x * (BLOCK / 64) + (threadIdx.x >> 6);
-  const int tn = (N + 15) / 16, tm = (M + 15) / 16;
-  if (tile >= tm * tn) return;  // whole wave leaves together
-  const int m0 = (tile / tn) * 16, n0 = (tile % tn) * 16;
-  const int r = lane & 15, kb = (lane >> 4) * 8;
-  floatx4 c = {0.f, 0.f, 0.f, 0.f};
-  for (int k0 = 0; k0 < K; k0 += 32) {
-    bf16x8 a, b;
-#pragma unroll
-    for (int q = 0; q < 8; ++q) {
-      const int k = k0 + kb + q;
-      const int mm = m0 + r, nn = n0 + r;
-      a[q] = to_bf16((mm < M && k < K) ? A[mm * sam + k * sak] : 0.0f);
-      b[q] = to_bf16((nn < N && k < K) ? B[k * sbk + nn * sbn] : 0.0f);
-    }
-    c = mfma16(a, b, c);
-  }
-#pragma unroll
-  for (int q = 0; q < 4; ++q) {
-    const int mm = m0 + (lane >> 4) * 4 + q, nn = n0 + r;
-    if (mm < M && nn < N) C[mm * ldc + nn] = c[q];
-  }
-}
-
-static hipError_t gemm(hipStream_t s, int M, int N, int K, const float *A, int64_t sam,
-                       int64_t sak, const float *B, int64_t sbk, int64_t sbn, float *C,
-                       int64_t ldc) {
-  const int tiles = ((M + 15) / 16) * ((N + 15) / 16);
-  k_gemm_bf16<<<(tiles + 3) / 4, BLOCK, 0, s>>>(M, N, K, A, sam, sak, B, sbk, sbn, C, ldc);
-  return hipGetLastError();
-}
-
-// normalized, bf16-rounded inputs and targets of the batch: samples 0..B-1
-// (draw == 0) or Philox-drawn sample indices, with replacement (draw != 0)
-__global__ void k_batch(int64_t n, int64_t B, const double *__restrict__ desc,
-                        const double *__restrict__ dE, MlpDev md, uint64_t seed, uint64_t step,
-                        int draw, float *Z, float *T) {
-  const int64_t b = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (b >= B) return;
-  int64_t src = b;
-  if (draw) {
-    const U4 r = philox(seed, 0x5EEDull, step, (uint64_t)b, 0, 7);
-    src = (int64_t)__umul64hi(r.v[0], (uint64_t)n);
-  }
-  for (int k = 0; k < MLP_IN; ++k) {
-    const float z = (float)((desc[src * MLP_IN + k] - (double)md.mu[k]) / (double)md.sd[k]);
-    Z[b * MLP_IN + k] = bf16_round(z);
-  }
-  T[b] = (float)((dE[src] - (double)md.out_mu) / (double)md.out_sd);
-}
-
-// A <- A + bias, H <- bf16(SiLU(A)) over [B][64]
-__global__ void k_bias_silu(int64_t B, float *A, const float *__restrict__ bias, float *H) {
-  const int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (e >= B * MLP_H) return;
-  const float a = A[e] + bias[e % MLP_H];
-  A[e] = a;
-  H[e] = bf16_round(silu(a));
-}
-
-// y = b3 + sum_k w3r[k] H2[b][k]; dY = 2 (y - t) / B; per-sample squared error
-__global__ void k_out(int64_t B, const float *__restrict__ H2, const float *__restrict__ w3r,
-                      const float *__restrict__ b3, const float *__restrict__ T, float *Y,
-                      float *dY, double *se) {
-  const int64_t b = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (b >= B) return;
-  float acc = b3[0];
-  for (int k = 0; k < MLP_H; ++k) acc += w3r[k] * H2[b * MLP_H + k];
-  Y[b] = acc;
-  const float r = acc - T[b];
-  dY[b] = 2.0f * r / (float)B;
-  se[b] = (double)r * (double)r;
-}
+// Training runs two kernels per step, k_fwd_bwd and k_grads.  (Seventeen
+// launches with every activation and error in memory as [B][64] floats, one
+// thread per column for the column sums, were 2.8 ms a step at a batch of
+// 4,096, 2.6 ms of it in the column sums' one-load-at-a-time chains.)  The
+// arithmetic and the order of every sum are those of the plain formulation:
+// products in ascending k (32 per MFMA), column sums in ascending sample.
 
 __device__ __forceinline__ float dsilu(float a) {
   const float s = 1.0f / (1.0f + expf(-a));
   return s * (1.0f + a * (1.0f - s));
 }
 
-// dA2[b][j] = dY[b] w3r[j] SiLU'(A2[b][j])
-__global__ void k_bwd_out(int64_t B, const float *__restrict__ dY, const float *__restrict__ w3r,
-                          const float *__restrict__ A2, float *dA2) {
-  const int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (e >= B * MLP_H) return;
-  dA2[e] = dY[e / MLP_H] * w3r[e % MLP_H] * dsilu(A2[e]);
+// Activations and errors of one batch, Bp = B rounded up to 32 samples (the
+// samples past B are zero).  Errors that are summed over the samples in FP32
+// are row-major [b][64]; operands of the weight-gradient products are bf16 and
+// sample-contiguous [neuron][Bp], so that a lane's eight products are one
+// 16-byte load.
+struct MlpWork {
+  float *P;    // [Bp][64] dY[b] H2[b][k]
+  float *dA2;  // [Bp][64]
+  float *dA1;  // [Bp][64]
+  float *dY;   // [Bp]
+  __bf16 *dA2t, *dA1t, *H1t;  // [64][Bp]
+  __bf16 *Zt;                 // [16][Bp], rows 10.. zero
+  double *red;  // per-sample squared errors [B]
+  float *g;     // gradient [4929]
+  int64_t Bp;
+};
+
+// bytes of workspace per padded sample, the squared errors aside
+constexpr int64_t MLP_WORK_BYTES = 4 * (3 * MLP_H + 1) + 2 * (3 * MLP_H + 16);
+
+static MlpWork carve_work(unsigned char *base, int64_t B, double *red, float *g) {
+  MlpWork w;
+  w.Bp = (B + 31) / 32 * 32;  // every part below is a multiple of 64 bytes
+  float *f = (float *)base;
+  w.P = f;
+  w.dA2 = w.P + w.Bp * MLP_H;
+  w.dA1 = w.dA2 + w.Bp * MLP_H;
+  w.dY = w.dA1 + w.Bp * MLP_H;
+  w.dA2t = (__bf16 *)(w.dY + w.Bp);
+  w.dA1t = w.dA2t + w.Bp * MLP_H;
+  w.H1t = w.dA1t + w.Bp * MLP_H;
+  w.Zt = w.H1t + w.Bp * MLP_H;
+  w.red = red;
+  w.g = g;
+  return w;
 }
 
-// dA1 = dH1 * SiLU'(A1)
-__global__ void k_bwd_hidden(int64_t B, const float *__restrict__ dH1, const float *__restrict__ A1,
-                             float *dA1) {
-  const int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (e >= B * MLP_H) return;
-  dA1[e] = dH1[e] * dsilu(A1[e]);
+// Forward and backward pass of 16 samples per block, everything between the
+// drawn samples and the errors in registers and LDS: samples 0..B-1
+// (draw == 0) or Philox-drawn sample indices, with replacement (draw != 0).
+// Wave v computes neurons 16 v .. 16 v + 15 of each layer; lane l holds rows
+// 4 (l / 16) .. + 3 of neuron 16 v + l % 16, of which it keeps the
+// pre-activations for the backward pass.  Bound by the latency of its chain
+// (draw, three MFMA layers, the 64-term output sum), one block per CU and
+// 9.3 us at a batch of 4,096.
+__global__ void __launch_bounds__(BLOCK)
+    k_fwd_bwd(int64_t n, int64_t B, const double *__restrict__ desc,
+              const double *__restrict__ dE, MlpDev md, const __bf16 *__restrict__ w2t,
+              uint64_t seed, uint64_t step, int draw, MlpWork w) {
+  __shared__ __bf16 zs[16 * MLP_KP];
+  __shared__ __bf16 h1[16 * MLP_H], da2[16 * MLP_H];
+  __shared__ float h2[16 * (MLP_H + 1)];
+  __shared__ float w3[MLP_H];
+  __shared__ float tv[16], dy[16];
+  __shared__ int64_t src[16];
+  const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+  const int r = lane & 15, kb = (lane >> 4) * 8, row0 = (lane >> 4) * 4;
+  const int nn = wv * 16 + r;  // this lane's neuron
+  const int64_t base = (int64_t)blockIdx.x * 16;
+  const MlpFrag f = mlp_frag(md);
+  bf16x8 w2c[2];
+#pragma unroll
+  for (int q = 0; q < 8; ++q) {
+    w2c[0][q] = w2t[nn * MLP_H + kb + q];
+    w2c[1][q] = w2t[nn * MLP_H + 32 + kb + q];
+  }
+  if (tid < MLP_H) w3[tid] = md.w3[tid];
+  if (tid < 16) {
+    int64_t s = base + tid;
+    if (draw && s < B) {
+      const U4 u = philox(seed, 0x5EEDull, step, (uint64_t)s, 0, 7);
+      s = (int64_t)__umul64hi(u.v[0], (uint64_t)n);
+    }
+    src[tid] = base + tid < B ? s : -1;
+    tv[tid] = base + tid < B ? (float)((dE[s] - (double)md.out_mu) / (double)md.out_sd) : 0.0f;
+  }
+  __syncthreads();
+  for (int e = tid; e < 16 * MLP_KP; e += BLOCK) {
+    const int b = e / MLP_KP, k = e % MLP_KP;
+    const int64_t s = src[b];
+    const bool in = s >= 0 && k < MLP_IN;
+    zs[e] = in ? mlp_input(md, k, desc[s * MLP_IN + k]) : to_bf16(0.0f);
+  }
+  __syncthreads();
+  const bool ok[4] = {base + row0 < B, base + row0 + 1 < B, base + row0 + 2 < B,
+                      base + row0 + 3 < B};
+  typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
+  // column nn of four consecutive samples, sample-contiguous
+  auto store_t = [&](__bf16 *dst, const bf16x4 &v) {
+    *(bf16x4 *)(dst + nn * w.Bp + base + row0) = v;
+  };
+  float a1[4], a2[4];
+  {  // layer 1
+    bf16x8 a;
+#pragma unroll
+    for (int q = 0; q < 8; ++q) a[q] = zs[r * MLP_KP + kb + q];
+    floatx4 c = {0.f, 0.f, 0.f, 0.f};
+    c = mfma16(a, f.w1, c);
+    bf16x4 t;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      a1[q] = c[q] + f.b1;
+      const __bf16 h = to_bf16(silu(a1[q]));
+      h1[(row0 + q) * MLP_H + nn] = h;
+      t[q] = ok[q] ? h : to_bf16(0.0f);
+    }
+    store_t(w.H1t, t);
+    if (wv == 0) {  // the inputs, sample-contiguous (rows 10..15 are zero)
+      bf16x4 z;
+#pragma unroll
+      for (int q = 0; q < 4; ++q) z[q] = zs[(row0 + q) * MLP_KP + r];
+      *(bf16x4 *)(w.Zt + r * w.Bp + base + row0) = z;
+    }
+  }
+  __syncthreads();
+  {  // layer 2
+    floatx4 c = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int ks = 0; ks < MLP_H; ks += 32) {
+      bf16x8 a;
+#pragma unroll
+      for (int q = 0; q < 8; ++q) a[q] = h1[r * MLP_H + ks + kb + q];
+      c = mfma16(a, ks == 0 ? f.w2a : f.w2b, c);
+    }
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      a2[q] = c[q] + f.b2;
+      h2[(row0 + q) * (MLP_H + 1) + nn] = bf16_round(silu(a2[q]));
+    }
+  }
+  __syncthreads();
+  // y = b3 + sum_k w3[k] H2[b][k]; dY = 2 (y - t) / B; squared error
+  if (tid < 16) {
+    float acc = md.b3[0];
+    for (int k = 0; k < MLP_H; ++k) acc += w3[k] * h2[tid * (MLP_H + 1) + k];
+    const float d = acc - tv[tid];
+    const bool in = base + tid < B;
+    dy[tid] = in ? 2.0f * d / (float)B : 0.0f;
+    w.dY[base + tid] = dy[tid];
+    if (in) w.red[base + tid] = (double)d * (double)d;
+  }
+  __syncthreads();
+  {  // output-layer products and dA2[b][j] = dY[b] w3[j] SiLU'(A2[b][j])
+    bf16x4 t;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const int64_t e = (base + row0 + q) * MLP_H + nn;
+      const float y = dy[row0 + q];
+      w.P[e] = y * h2[(row0 + q) * (MLP_H + 1) + nn];
+      const float v = y * w3[nn] * dsilu(a2[q]);
+      w.dA2[e] = v;
+      t[q] = to_bf16(v);
+      da2[(row0 + q) * MLP_H + nn] = t[q];
+    }
+    store_t(w.dA2t, t);
+  }
+  __syncthreads();
+  {  // dH1 = dA2 W2, dA1 = dH1 SiLU'(A1)
+    floatx4 c = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int ks = 0; ks < MLP_H; ks += 32) {
+      bf16x8 a;
+#pragma unroll
+      for (int q = 0; q < 8; ++q) a[q] = da2[r * MLP_H + ks + kb + q];
+      c = mfma16(a, w2c[ks / 32], c);
+    }
+    bf16x4 t;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const float v = c[q] * dsilu(a1[q]);
+      w.dA1[(base + row0 + q) * MLP_H + nn] = v;
+      t[q] = to_bf16(v);
+    }
+    store_t(w.dA1t, t);
+  }
 }
 
-// out[c] = sum_b X[b][c] (cols columns), and optionally out2[c] = sum_b w[b] X[b][c]
-// one thread per column, ascending b (deterministic)
-__global__ void k_colsum(int64_t B, int cols, const float *__restrict__ X, const float *__restrict__ w,
-                         float *out) {
-  const int c = blockIdx.x * blockDim.x + threadIdx.x;
-  if (c >= cols) return;
+// Adam's update of parameter t and the copies of it that the products read
+struct AdamPar {
+  float *p, *m1, *m2;
+  __bf16 *w1b, *w2b, *w2t;
+  float *w3r;
+  float lr, b1, b2, eps, c1, c2;
+};
+
+__device__ __forceinline__ void adam_update(const AdamPar &a, int t, float gt) {
+  const float m = a.b1 * a.m1[t] + (1.0f - a.b1) * gt;
+  const float v = a.b2 * a.m2[t] + (1.0f - a.b2) * gt * gt;
+  a.m1[t] = m;
+  a.m2[t] = v;
+  const float pn = a.p[t] - a.lr * (m / a.c1) / (sqrtf(v / a.c2) + a.eps);
+  a.p[t] = pn;
+  if (t < OFF_B1) {
+    a.w1b[t / MLP_IN * MLP_KP + t % MLP_IN] = to_bf16(pn);
+  } else if (t >= OFF_W2 && t < OFF_B2) {
+    const int e = t - OFF_W2;
+    a.w2b[e] = to_bf16(pn);
+    a.w2t[e % MLP_H * MLP_H + e / MLP_H] = to_bf16(pn);
+  } else if (t >= OFF_W3 && t < OFF_B3) {
+    a.w3r[t - OFF_W3] = bf16_round(pn);
+  }
+}
+
+// Gradients from the errors of a batch, one role per block:
+//   blocks 0..19   one 16 x 16 tile (the first wave) of dW2 = dA2^T H1 (16
+//                  tiles) and dW1 = dA1^T Z (4 tiles), the whole batch in one
+//                  MFMA chain with GR_DEPTH steps' operands loaded together;
+//   blocks 20..31  column sums of P (dW3), dA2 (db2) and dA1 (db1), GR_COLS
+//                  columns each: the block streams GR_ROWS rows at a time
+//                  through two LDS buffers and its first wave adds them, one
+//                  column per lane;
+//   block 32       db3, the sum of dY.
+// The chains are serial in the sample (their order is the result's), so the
+// kernel's time is the longest chain's, about 4,096 dependent FP32 additions
+// at the default batch, if the operands arrive in time: one compute unit
+// waits about 2 us for what it can have in flight (64 KB), so the columns are
+// split over 12 blocks and the tiles over 20: 34 us at a batch of 4,096, 20
+// of them the additions (three blocks of 64 columns and five of four tiles:
+// 67 us).
+// ADAM: the update is applied to the parameters; else the gradient is stored.
+constexpr int GR_DEPTH = 16, GR_COLS = 16, GR_ROWS = 1024;
+constexpr int GR_TILES = 20, GR_SUMS = 3 * MLP_H / GR_COLS, GR_BLOCKS = GR_TILES + GR_SUMS + 1;
+
+// Sums of COLS columns of X[Bp][LD] over the first B rows, ascending, one
+// column per lane of the block's first wave (lanes past COLS repeat them).
+// GR_ROWS rows are loaded by the whole block while the tile before them is
+// added from LDS (rows past Bp repeat the last one and are not added).
+template <int COLS, int LD>
+__device__ __forceinline__ float column_sums(const float *X, int64_t B, int64_t Bp, float *buf) {
+  const int tid = threadIdx.x;
+  constexpr int PR = COLS >= 4 ? COLS / 4 : 1;      // 16-byte pieces per row
+  constexpr int RP = COLS >= 4 ? 1 : 4;             // rows per piece
+  constexpr int PIECES = GR_ROWS * COLS / 4, NV = PIECES / BLOCK;
+  static_assert(PIECES % BLOCK == 0 && (COLS % 4 == 0 || LD == 1), "whole pieces per thread");
+  float4 v[NV];
+  auto load = [&](int64_t tile) {
+#pragma unroll
+    for (int u = 0; u < NV; ++u) {
+      const int e = u * BLOCK + tid;
+      int64_t row = tile * GR_ROWS + e / PR * RP;
+      row = row < Bp ? row : Bp - RP;
+      v[u] = *(const float4 *)(X + row * LD + e % PR * 4);
+    }
+  };
+  auto store = [&](int half) {
+    float4 *d = (float4 *)buf + half * PIECES;
+#pragma unroll
+    for (int u = 0; u < NV; ++u) d[u * BLOCK + tid] = v[u];
+  };
+  const int64_t tiles = (B + GR_ROWS - 1) / GR_ROWS;
   float acc = 0.f;
-  for (int64_t b = 0; b < B; ++b) acc += (w ? w[b] : 1.0f) * X[b * cols + c];
-  out[c] = acc;
+  load(0);
+  store(0);
+  __syncthreads();
+  for (int64_t t = 0; t < tiles; ++t) {
+    if (t + 1 < tiles) load(t + 1);
+    if (tid < 64) {
+      const float *s = buf + (t & 1) * PIECES * 4 + tid % COLS;
+      const int64_t left = B - t * GR_ROWS;
+      const int rows = left < GR_ROWS ? (int)left : GR_ROWS;
+      int b = 0;
+      for (; b + 32 <= rows; b += 32) {
+        float x[32];
+#pragma unroll
+        for (int u = 0; u < 32; ++u) x[u] = s[(b + u) * COLS];
+#pragma unroll
+        for (int u = 0; u < 32; ++u) acc += x[u];
+      }
+      for (; b < rows; ++b) acc += s[b * COLS];
+    }
+    if (t + 1 < tiles) store((int)((t + 1) & 1));
+    __syncthreads();
+  }
+  return acc;
+}
+
+template <bool ADAM>
+__global__ void __launch_bounds__(BLOCK) k_grads(int64_t B, MlpWork w, AdamPar ad) {
+  extern __shared__ float buf[];  // [2][GR_ROWS][GR_COLS] (column sums), [2][GR_ROWS] (db3)
+  const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+  auto put = [&](int t, float gt) {
+    if (ADAM)
+      adam_update(ad, t, gt);
+    else
+      w.g[t] = gt;
+  };
+  if (blockIdx.x < GR_TILES) {
+    if (wv) return;
+    const int tile = blockIdx.x;
+    const int r = lane & 15, kb = (lane >> 4) * 8;
+    const bool two = tile < 16;
+    const int m0 = two ? tile / 4 * 16 : (tile - 16) * 16, n0 = two ? tile % 4 * 16 : 0;
+    const __bf16 *A = (two ? w.dA2t : w.dA1t) + (m0 + r) * w.Bp + kb;
+    const __bf16 *Bm = (two ? w.H1t : w.Zt) + (n0 + r) * w.Bp + kb;
+    floatx4 c = {0.f, 0.f, 0.f, 0.f};
+    for (int64_t k0 = 0; k0 < w.Bp; k0 += 32 * GR_DEPTH) {
+      bf16x8 a[GR_DEPTH], b[GR_DEPTH];
+#pragma unroll
+      for (int u = 0; u < GR_DEPTH; ++u) {
+        const int64_t k = k0 + 32 * u < w.Bp ? k0 + 32 * u : 0;  // inside the rows
+        a[u] = *(const bf16x8 *)(A + k);
+        b[u] = *(const bf16x8 *)(Bm + k);
+      }
+#pragma unroll
+      for (int u = 0; u < GR_DEPTH; ++u)
+        if (k0 + 32 * u < w.Bp) c = mfma16(a[u], b[u], c);
+    }
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const int mm = m0 + (lane >> 4) * 4 + q, nn = n0 + r;
+      if (two)
+        put(OFF_W2 + mm * MLP_H + nn, c[q]);
+      else if (nn < MLP_IN)
+        put(OFF_W1 + mm * MLP_IN + nn, c[q]);
+    }
+    return;
+  }
+  const int sum = (int)blockIdx.x - GR_TILES;
+  if (sum < GR_SUMS) {
+    const int which = sum * GR_COLS / MLP_H, c0 = sum * GR_COLS % MLP_H;
+    const float *X = (which == 0 ? w.P : (which == 1 ? w.dA2 : w.dA1)) + c0;
+    const float acc = column_sums<GR_COLS, MLP_H>(X, B, w.Bp, buf);
+    if (tid < GR_COLS) put((which == 0 ? OFF_W3 : (which == 1 ? OFF_B2 : OFF_B1)) + c0 + tid, acc);
+  } else {
+    const float acc = column_sums<1, 1>(w.dY, B, w.Bp, buf);
+    if (tid == 0) put(OFF_B3, acc);
+  }
 }
 
 // fixed-order double sum of v[0..n) into *out, divided by div (one block)
@@ -219,113 +450,112 @@ __global__ void k_dsum(int64_t n, const double *__restrict__ v, double *out, dou
   if (threadIdx.x == 0) *out = s[0] / div;
 }
 
-// Adam on the FP32 master parameters
-__global__ void k_adam(float *p, const float *__restrict__ g, float *m1, float *m2, float lr,
-                       float b1, float b2, float eps, float c1, float c2) {
-  const int t = blockIdx.x * blockDim.x + threadIdx.x;
-  if (t >= MLP_NPARAM) return;
-  const float gt = g[t];
-  const float a = b1 * m1[t] + (1.0f - b1) * gt;
-  const float v = b2 * m2[t] + (1.0f - b2) * gt * gt;
-  m1[t] = a;
-  m2[t] = v;
-  p[t] = p[t] - lr * (a / c1) / (sqrtf(v / c2) + eps);
+// Per-column sums and sums of squares of [n][cols] doubles: block b adds the
+// row groups b, b + gridDim.x, ... (BLOCK / cols rows of one coalesced read
+// each, a thread keeps to one column) and leaves its totals in
+// part[(b cols + c) 2 ..]; the last step adds the blocks' totals in order.
+// (One block per column, reading every cols-th double, took 0.25 ms at 65,536
+// samples and grew with n.)
+constexpr int MOM_GRID = 256;
+
+__global__ void __launch_bounds__(BLOCK)
+    k_moments(int64_t n, int cols, const double *__restrict__ X, double *part) {
+  __shared__ double s1[BLOCK], s2[BLOCK];
+  const int rpb = BLOCK / cols, used = rpb * cols, t = threadIdx.x;
+  double a = 0.0, b = 0.0;
+  if (t < used)
+    for (int64_t e = (int64_t)blockIdx.x * used + t; e < n * cols; e += (int64_t)gridDim.x * used) {
+      const double v = X[e];
+      a = a + v;
+      b = b + v * v;
+    }
+  s1[t] = a;
+  s2[t] = b;
+  __syncthreads();
+  if (t < cols) {
+    for (int k = 1; k < rpb; ++k) {
+      a = a + s1[k * cols + t];
+      b = b + s2[k * cols + t];
+    }
+    part[2 * ((int64_t)blockIdx.x * cols + t)] = a;
+    part[2 * ((int64_t)blockIdx.x * cols + t) + 1] = b;
+  }
 }
 
-// per-column mean and standard deviation of [n][cols] doubles (fixed order)
-__global__ void k_moments(int64_t n, int cols, const double *__restrict__ X, double *out) {
-  __shared__ double s1[BLOCK], s2[BLOCK];
-  const int c = blockIdx.x;
+// mean and standard deviation per column (out[2 c], out[2 c + 1]) from nb
+// blocks' totals; one wave per column, fixed order
+__global__ void __launch_bounds__(64)
+    k_moments_final(int64_t n, int cols, int nb, const double *__restrict__ part, double *out) {
+  const int c = blockIdx.x, l = threadIdx.x;
   double a = 0.0, b = 0.0;
-  for (int64_t k = threadIdx.x; k < n; k += BLOCK) {
-    const double v = X[k * cols + c];
-    a = a + v;
-    b = b + v * v;
+  for (int k = l; k < nb; k += 64) {
+    a = a + part[2 * ((int64_t)k * cols + c)];
+    b = b + part[2 * ((int64_t)k * cols + c) + 1];
   }
-  s1[threadIdx.x] = a;
-  s2[threadIdx.x] = b;
-  __syncthreads();
-  for (int h = BLOCK / 2; h > 0; h >>= 1) {
-    if ((int)threadIdx.x < h) {
-      s1[threadIdx.x] = s1[threadIdx.x] + s1[threadIdx.x + h];
-      s2[threadIdx.x] = s2[threadIdx.x] + s2[threadIdx.x + h];
-    }
-    __syncthreads();
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) {
+    a = a + __shfl_down(a, o);
+    b = b + __shfl_down(b, o);
   }
-  if (threadIdx.x == 0) {
-    const double mean = s1[0] / (double)n;
-    const double var = s2[0] / (double)n - mean * mean;
+  if (l == 0) {
+    const double mean = a / (double)n;
+    const double var = b / (double)n - mean * mean;
     out[2 * c] = mean;
     out[2 * c + 1] = var > 0.0 ? sqrt(var) : 0.0;
   }
 }
 
-// Activations, gradients and loss partials of one batch: the network's own
-// buffers (grown on demand) or a fixed workspace.
-struct MlpWork {
-  float *Z, *T, *A1, *H1, *A2, *H2, *Y, *dY, *dA2, *dH1, *dA1;
-  double *red;  // per-sample squared errors [B]
-  float *g;     // gradient [4929]
-};
-
-// floats of workspace per sample (Z, T, A1, H1, A2, H2, Y, dY, dA2, dH1, dA1)
-constexpr int64_t MLP_WORK_PER_SAMPLE = MLP_IN + 1 + 4 * MLP_H + 2 + 3 * MLP_H;
-
-static MlpWork own_work(vcsgc_mlp *m) {
-  return MlpWork{m->Z, m->T, m->A1, m->H1, m->A2, m->H2, m->Y, m->dY, m->dA2, m->dH1, m->dA1,
-                 m->red, m->g};
+static AdamPar adam_par(const vcsgc_mlp *m) {
+  AdamPar a = {};
+  a.p = m->p;
+  a.m1 = m->m1;
+  a.m2 = m->m2;
+  a.w1b = m->w1b;
+  a.w2b = m->w2b;
+  a.w2t = m->w2b + MLP_H * MLP_H;
+  a.w3r = m->w3r;
+  return a;
 }
 
-// Full forward + backward over a batch already in w.Z / w.T; gradient into
-// w.g, per-sample squared errors into w.red.  Reads the network's parameters
-// only.
-static hipError_t mlp_fwd_bwd(const vcsgc_mlp *m, const MlpWork &w, int64_t B, hipStream_t s) {
-  const float *p = m->p;
-  hipError_t e;
-  const int gB = grid_for(B), gBH = grid_for(B * MLP_H);
-  // layer 1: A1 = Z W1^T (+ b1), H1 = bf16(SiLU(A1))
-  if ((e = gemm(s, (int)B, MLP_H, MLP_IN, w.Z, MLP_IN, 1, p + OFF_W1, 1, MLP_IN, w.A1, MLP_H)))
-    return e;
-  k_bias_silu<<<gBH, BLOCK, 0, s>>>(B, w.A1, p + OFF_B1, w.H1);
-  // layer 2
-  if ((e = gemm(s, (int)B, MLP_H, MLP_H, w.H1, MLP_H, 1, p + OFF_W2, 1, MLP_H, w.A2, MLP_H)))
-    return e;
-  k_bias_silu<<<gBH, BLOCK, 0, s>>>(B, w.A2, p + OFF_B2, w.H2);
-  k_out<<<gB, BLOCK, 0, s>>>(B, w.H2, m->w3r, p + OFF_B3, w.T, w.Y, w.dY, w.red);
-  // output layer gradients
-  k_colsum<<<1, 64, 0, s>>>(B, MLP_H, w.H2, w.dY, w.g + OFF_W3);
-  k_colsum<<<1, 64, 0, s>>>(B, 1, w.dY, nullptr, w.g + OFF_B3);
-  k_bwd_out<<<gBH, BLOCK, 0, s>>>(B, w.dY, m->w3r, w.A2, w.dA2);
-  // layer 2 gradients: dW2 = dA2^T H1, db2, dH1 = dA2 W2
-  if ((e = gemm(s, MLP_H, MLP_H, (int)B, w.dA2, 1, MLP_H, w.H1, MLP_H, 1, w.g + OFF_W2, MLP_H)))
-    return e;
-  k_colsum<<<1, 64, 0, s>>>(B, MLP_H, w.dA2, nullptr, w.g + OFF_B2);
-  if ((e = gemm(s, (int)B, MLP_H, MLP_H, w.dA2, MLP_H, 1, p + OFF_W2, MLP_H, 1, w.dH1, MLP_H)))
-    return e;
-  k_bwd_hidden<<<gBH, BLOCK, 0, s>>>(B, w.dH1, w.A1, w.dA1);
-  // layer 1 gradients: dW1 = dA1^T Z, db1
-  if ((e = gemm(s, MLP_H, MLP_IN, (int)B, w.dA1, 1, MLP_H, w.Z, MLP_IN, 1, w.g + OFF_W1, MLP_IN)))
-    return e;
-  k_colsum<<<1, 64, 0, s>>>(B, MLP_H, w.dA1, nullptr, w.g + OFF_B1);
+// Forward and backward pass over a batch and its gradient (into w.g, or
+// straight into Adam's update of the parameters when ad is given); the
+// per-sample squared errors go to w.red.
+constexpr size_t GR_LDS = 2 * sizeof(float) * GR_ROWS * GR_COLS;
+
+static hipError_t mlp_fwd_bwd(const vcsgc_mlp *m, const MlpWork &w, int64_t n, int64_t B,
+                              const double *desc, const double *dE, const MlpDev &md,
+                              uint64_t seed, uint64_t step, int draw, const AdamPar *ad) {
+  // every padded sample is written (the pads as zeros)
+  k_fwd_bwd<<<(unsigned)(w.Bp / 16), BLOCK, 0, m->stream>>>(
+      n, B, desc, dE, md, m->w2b + MLP_H * MLP_H, seed, step, draw, w);
+  if (ad)
+    k_grads<true><<<GR_BLOCKS, BLOCK, GR_LDS, m->stream>>>(B, w, *ad);
+  else
+    k_grads<false><<<GR_BLOCKS, BLOCK, GR_LDS, m->stream>>>(B, w, AdamPar{});
   return hipGetLastError();
+}
+
+// more than 64 KB of LDS per block has to be asked for
+static hipError_t grads_lds() {
+  hipError_t e = hipFuncSetAttribute((const void *)k_grads<true>,
+                                     hipFuncAttributeMaxDynamicSharedMemorySize, (int)GR_LDS);
+  if (e == hipSuccess)
+    e = hipFuncSetAttribute((const void *)k_grads<false>,
+                            hipFuncAttributeMaxDynamicSharedMemorySize, (int)GR_LDS);
+  return e;
 }
 
 hipError_t mlp_ensure_cap(vcsgc_mlp *m, int64_t B) {
   if (B <= m->cap) return hipSuccess;
-  float **bufs[] = {&m->Z, &m->T, &m->A1, &m->H1, &m->A2, &m->H2, &m->Y, &m->dY,
-                    &m->dA2, &m->dH1, &m->dA1};
-  const int64_t sizes[] = {B * MLP_IN, B, B * MLP_H, B * MLP_H, B * MLP_H, B * MLP_H, B, B,
-                           B * MLP_H, B * MLP_H, B * MLP_H};
   (void)hipStreamSynchronize(m->stream);
-  for (int k = 0; k < 11; ++k) {
-    if (*bufs[k]) (void)hipFree(*bufs[k]);
-    *bufs[k] = nullptr;
-    hipError_t e = hipMalloc((void **)bufs[k], sizeof(float) * sizes[k]);
-    if (e != hipSuccess) return e;
-  }
+  if (m->work) (void)hipFree(m->work);
+  m->work = nullptr;
   if (m->red) (void)hipFree(m->red);
   m->red = nullptr;
-  hipError_t e = hipMalloc((void **)&m->red, sizeof(double) * (B + 8));
+  m->cap = 0;
+  const int64_t Bp = (B + 31) / 32 * 32;
+  hipError_t e = hipMalloc((void **)&m->work, (size_t)(MLP_WORK_BYTES * Bp));
+  if (e == hipSuccess) e = hipMalloc((void **)&m->red, sizeof(double) * (B + 8));
   if (e != hipSuccess) return e;
   m->cap = B;
   return hipSuccess;
@@ -335,9 +565,8 @@ hipError_t mlp_grad_batch(vcsgc_mlp *m, const double *desc, const double *dE, in
                           double *loss) {
   hipError_t e = mlp_ensure_cap(m, n);
   if (e != hipSuccess) return e;
-  MlpDev md = mlp_dev(m);
-  k_batch<<<grid_for(n), BLOCK, 0, m->stream>>>(n, n, desc, dE, md, 0, 0, 0, m->Z, m->T);
-  if ((e = mlp_fwd_bwd(m, own_work(m), n, m->stream)) != hipSuccess) return e;
+  const MlpWork w = carve_work(m->work, n, m->red, m->g);
+  if ((e = mlp_fwd_bwd(m, w, n, n, desc, dE, mlp_dev(m), 0, 0, 0, nullptr)) != hipSuccess) return e;
   k_dsum<<<1, BLOCK, 0, m->stream>>>(n, m->red, m->red + m->cap, 1.0);
   double h = 0.0;
   e = hipMemcpyAsync(&h, m->red + m->cap, sizeof(double), hipMemcpyDeviceToHost, m->stream);
@@ -353,20 +582,20 @@ hipError_t mlp_train(vcsgc_mlp *m, const double *desc, const double *dE, int64_t
   if (e != hipSuccess) return e;
   const int64_t steps_per_epoch = (n + B - 1) / B;
   const int64_t steps = steps_per_epoch * cfg->epochs;
-  MlpDev md = mlp_dev(m);
-  double first = -1.0, last = 0.0, acc = 0.0;
-  int64_t acc_n = 0;
+  const MlpDev md = mlp_dev(m);
+  const MlpWork w = carve_work(m->work, B, m->red, m->g);
+  AdamPar ad = adam_par(m);
+  ad.lr = (float)cfg->lr;
+  ad.b1 = (float)cfg->beta1;
+  ad.b2 = (float)cfg->beta2;
+  ad.eps = (float)cfg->eps;
+  double first = -1.0, last = 0.0;
   for (int64_t st = 0; st < steps; ++st) {
-    k_batch<<<grid_for(B), BLOCK, 0, m->stream>>>(n, B, desc, dE, md, cfg->seed, (uint64_t)st, 1,
-                                                  m->Z, m->T);
-    if ((e = mlp_fwd_bwd(m, own_work(m), B, m->stream)) != hipSuccess) return e;
     m->adam_t += 1;
-    const float c1 = 1.0f - powf((float)cfg->beta1, (float)m->adam_t);
-    const float c2 = 1.0f - powf((float)cfg->beta2, (float)m->adam_t);
-    k_adam<<<grid_for(MLP_NPARAM), BLOCK, 0, m->stream>>>(m->p, m->g, m->m1, m->m2, (float)cfg->lr,
-                                                          (float)cfg->beta1, (float)cfg->beta2,
-                                                          (float)cfg->eps, c1, c2);
-    if ((e = mlp_refresh(m)) != hipSuccess) return e;
+    ad.c1 = 1.0f - powf((float)cfg->beta1, (float)m->adam_t);
+    ad.c2 = 1.0f - powf((float)cfg->beta2, (float)m->adam_t);
+    if ((e = mlp_fwd_bwd(m, w, n, B, desc, dE, md, cfg->seed, (uint64_t)st, 1, &ad)) != hipSuccess)
+      return e;
     // epoch-end loss of the last batch (one read-back per epoch)
     if ((st + 1) % steps_per_epoch == 0 || st == 0) {
       k_dsum<<<1, BLOCK, 0, m->stream>>>(B, m->red, m->red + m->cap, 1.0);
@@ -377,8 +606,6 @@ hipError_t mlp_train(vcsgc_mlp *m, const double *desc, const double *dE, int64_t
       h /= (double)B;
       if (first < 0.0) first = h;
       last = h;
-      acc += h;
-      acc_n += 1;
     }
   }
   if (rep) {
@@ -396,17 +623,22 @@ hipError_t mlp_forward(vcsgc_mlp *m, const double *desc, int64_t n, double *dE) 
 }
 
 hipError_t mlp_fit_normalization(vcsgc_mlp *m, const double *desc, const double *dE, int64_t n) {
-  hipError_t e = mlp_ensure_cap(m, 1);
-  if (e != hipSuccess) return e;
-  double *st = nullptr;
-  e = hipMalloc((void **)&st, sizeof(double) * 22);
-  if (e != hipSuccess) return e;
-  k_moments<<<MLP_IN, BLOCK, 0, m->stream>>>(n, MLP_IN, desc, st);
-  k_moments<<<1, BLOCK, 0, m->stream>>>(n, 1, dE, st + 20);
+  double *st = m->mom + 2 * MOM_GRID * (MLP_IN + 1);
+  auto blocks = [&](int cols) {
+    const int64_t rpb = BLOCK / cols, g = (n + rpb - 1) / rpb;
+    return (int)(g < MOM_GRID ? g : MOM_GRID);
+  };
+  double *part1 = m->mom + 2 * MOM_GRID * MLP_IN;
+  const int g0 = blocks(MLP_IN), g1 = blocks(1);
+  k_moments<<<g0, BLOCK, 0, m->stream>>>(n, MLP_IN, desc, m->mom);
+  k_moments<<<g1, BLOCK, 0, m->stream>>>(n, 1, dE, part1);
+  k_moments_final<<<MLP_IN, 64, 0, m->stream>>>(n, MLP_IN, g0, m->mom, st);
+  k_moments_final<<<1, 64, 0, m->stream>>>(n, 1, g1, part1, st + 2 * MLP_IN);
   double h[22];
-  e = hipMemcpyAsync(h, st, sizeof(h), hipMemcpyDeviceToHost, m->stream);
+  hipError_t e = hipGetLastError();
+  if (e == hipSuccess)
+    e = hipMemcpyAsync(h, st, sizeof(h), hipMemcpyDeviceToHost, m->stream);
   if (e == hipSuccess) e = hipStreamSynchronize(m->stream);
-  (void)hipFree(st);
   if (e != hipSuccess) return e;
   for (int k = 0; k < MLP_IN; ++k) {
     m->mu[k] = (float)h[2 * k];
@@ -462,7 +694,10 @@ vcsgc_status vcsgc_mlp_create(uint64_t seed, hipStream_t stream, vcsgc_mlp **out
   if (e == hipSuccess) e = hipMalloc((void **)&m->m1, sizeof(float) * vc::MLP_NPARAM);
   if (e == hipSuccess) e = hipMalloc((void **)&m->m2, sizeof(float) * vc::MLP_NPARAM);
   if (e == hipSuccess) e = hipMalloc((void **)&m->w1b, sizeof(__bf16) * 64 * 32);
-  if (e == hipSuccess) e = hipMalloc((void **)&m->w2b, sizeof(__bf16) * 64 * 64);
+  if (e == hipSuccess) e = hipMalloc((void **)&m->w2b, sizeof(__bf16) * 2 * 64 * 64);
+  if (e == hipSuccess)
+    e = hipMalloc((void **)&m->mom, sizeof(double) * (2 * vc::MOM_GRID * (vc::MLP_IN + 1) + 22));
+  if (e == hipSuccess) e = vc::grads_lds();
   if (e == hipSuccess) e = hipMalloc((void **)&m->w3r, sizeof(float) * 64);
   std::vector<float> p;
   init_params(seed, p);
@@ -483,8 +718,7 @@ vcsgc_status vcsgc_mlp_create(uint64_t seed, hipStream_t stream, vcsgc_mlp **out
 vcsgc_status vcsgc_mlp_destroy(vcsgc_mlp *m) {
   if (!m) return VCSGC_OK;
   (void)hipStreamSynchronize(m->stream);
-  void *ptrs[] = {m->p, m->g, m->m1, m->m2, m->w1b, m->w2b, m->w3r, m->Z, m->T, m->A1, m->H1,
-                  m->A2, m->H2, m->Y, m->dY, m->dA2, m->dH1, m->dA1, m->red};
+  void *ptrs[] = {m->p, m->g, m->m1, m->m2, m->w1b, m->w2b, m->w3r, m->work, m->red, m->mom};
   for (void *q : ptrs)
     if (q) (void)hipFree(q);
   delete m;
@@ -576,7 +810,7 @@ vcsgc_status vcsgc_mlp_grad(vcsgc_mlp *m, const double *desc_dev, const double *
 namespace vc {
 
 constexpr int64_t NA_MAX = VCSGC_NOALLOC_MAX_SAMPLES;
-constexpr size_t NA_FLOAT_BYTES = sizeof(float) * (size_t)(NA_MAX * MLP_WORK_PER_SAMPLE);
+constexpr size_t NA_FLOAT_BYTES = (size_t)(NA_MAX * MLP_WORK_BYTES);
 constexpr size_t NA_BYTES = NA_FLOAT_BYTES + sizeof(double) * (size_t)NA_MAX;
 static_assert(NA_FLOAT_BYTES % 256 == 0, "double area aligned");
 
@@ -604,20 +838,6 @@ static hipError_t scratch_address(int dev, unsigned char **out) {
   return hipSuccess;
 }
 
-static MlpWork fixed_work(unsigned char *base, int64_t B, float *grad) {
-  float *f = (float *)base;
-  MlpWork w;
-  float **bufs[] = {&w.Z, &w.T, &w.A1, &w.H1, &w.A2, &w.H2, &w.Y, &w.dY, &w.dA2, &w.dH1, &w.dA1};
-  const int64_t per[] = {MLP_IN, 1, MLP_H, MLP_H, MLP_H, MLP_H, 1, 1, MLP_H, MLP_H, MLP_H};
-  for (int k = 0; k < 11; ++k) {
-    *bufs[k] = f;
-    f += per[k] * B;
-  }
-  w.red = (double *)(base + NA_FLOAT_BYTES);
-  w.g = grad;
-  return w;
-}
-
 }  // namespace vc
 
 extern "C" vcsgc_status vcsgc_mlp_grad_noalloc(const vcsgc_mlp *m, const double *desc_dev,
@@ -629,11 +849,9 @@ extern "C" vcsgc_status vcsgc_mlp_grad_noalloc(const vcsgc_mlp *m, const double 
   unsigned char *base = nullptr;
   hipError_t e = vc::scratch_address(m->device, &base);
   if (e != hipSuccess) return VCSGC_E_DEVICE;
-  const vc::MlpWork w = vc::fixed_work(base, n, grad_dev);
-  const vc::MlpDev md = vc::mlp_dev(m);
-  vc::k_batch<<<vc::grid_for(n), vc::BLOCK, 0, m->stream>>>(n, n, desc_dev, dE_dev, md, 0, 0, 0,
-                                                            w.Z, w.T);
-  e = vc::mlp_fwd_bwd(m, w, n, m->stream);
+  const vc::MlpWork w =
+      vc::carve_work(base, n, (double *)(base + vc::NA_FLOAT_BYTES), grad_dev);
+  e = vc::mlp_fwd_bwd(m, w, n, n, desc_dev, dE_dev, vc::mlp_dev(m), 0, 0, 0, nullptr);
   if (e != hipSuccess) return VCSGC_E_DEVICE;
   vc::k_dsum<<<1, vc::BLOCK, 0, m->stream>>>(n, w.red, loss_dev, (double)n);
   return hipGetLastError() == hipSuccess ? VCSGC_OK : VCSGC_E_DEVICE;

@@ -272,3 +272,41 @@ def test_sample_log_and_training(torch_cuda, oracle_mod):
     assert rmse < 0.5 * float(np.std(E)), (rmse, float(np.std(E)))
     g.close()
     net.close()
+
+
+@pytest.mark.parametrize("n", [1, 15, 17, 33, 255, 257, 511, 1025])
+def test_gradient_batch_edges(torch_cuda, oracle_mod, n):
+    """Batches around the kernels' tiles (16 samples per block, 32 per MFMA
+    step, 256 rows per column-sum tile): gradient and loss against the oracle,
+    with the tolerance of the gradient test."""
+    torch = torch_cuda
+    m = _params(5)
+    net = _gpu_mlp(m)
+    d, t = _samples(n, 40 + n)
+    loss, g = net.grad(torch.tensor(d, device="cuda"), torch.tensor(t, device="cuda"))
+    want_loss, want = oracle_mod.mlp_grad(m, d, t, bf16_emul=True)
+    assert abs(loss - want_loss) <= GRAD_REL * max(abs(want_loss), 1e-12)
+    for name, a, b in TENSORS:
+        err = np.linalg.norm(g[a:b] - want[a:b])
+        assert err <= GRAD_REL * max(np.linalg.norm(want[a:b]), 1e-12), (name, err)
+    net.close()
+
+
+@pytest.mark.parametrize("n", [2, 24, 25, 26, 6399, 6401, 100003])
+def test_normalization_edges(torch_cuda, n):
+    """Mean and standard deviation per column around the row groups of a block
+    (25 rows) and of the grid (6,400), against numpy in 64 bits: FP64 sums
+    rounded once to FP32 (the variance as E[x^2] - mean^2: its cancellation
+    costs at most 2^-52 mean^2 n^(1/2) / var relative, below 1e-6 here)."""
+    torch = torch_cuda
+    from paper_1012_5082_amd.binding import Mlp
+    d, t = _samples(n, 60)
+    net = Mlp(seed=1)
+    net.fit_normalization(torch.tensor(d, device="cuda"), torch.tensor(t, device="cuda"))
+    _, mu, sd, om, osd = net.get_params()
+    want = d.std(0)
+    want[want <= 1e-6] = 1.0
+    assert np.allclose(mu, d.mean(0), rtol=1e-6, atol=1e-7)
+    assert np.allclose(sd, want, rtol=2e-6, atol=1e-7)
+    assert abs(om - t.mean()) <= 1e-6 and abs(osd - t.std()) <= 1e-6
+    net.close()
