@@ -236,10 +236,11 @@ vcsgc_status vcsgc_sweep_batch(vcsgc_ctx *ctx, const double *dmu0, const double 
  *               only; trials_per_group in [1, 16], capped at half the stages
  *               of a sweep; with trial or stage logs on, or fewer than two
  *               stages per sweep, it runs as strategy 2);
- *   trials_per_group: strategies 0 and 1: active cells handled by each
- *            16-lane trial group per stage in the persistent kernel (sets
- *            the number of workgroups per replica; raised automatically if
- *            the grid would not fit); strategy 3: stages per batch.
+ *   trials_per_group: strategies 0 and 1: divides the number of workgroups
+ *            of a replica in the persistent kernel, and with it the stages
+ *            tried per batch (a replica that fits one compute unit's LDS
+ *            always has one; raised automatically if the grid would not
+ *            fit); strategy 3: stages per batch.
  * Synchronizes the stream. */
 vcsgc_status vcsgc_set_tuning(vcsgc_ctx *ctx, int32_t strategy, int32_t trials_per_group);
 /* Current tuning and the persistent grid size (any output may be NULL). */

@@ -3,8 +3,7 @@
 Candidates: for single systems the stage pipeline ("stage", one kernel per
 stage) and the batched stage pipeline ("batch", 2, 3, 4, 8 or 16 stages
 tried per kernel); for all, the graph-captured persistent launch with 1, 2,
-4 or 8 active cells per 16-lane trial group per stage (which sets the number
-of workgroups per replica).  Results do not depend on the choice: every
+4 or 8 as the divisor of the workgroups per replica.  Results do not depend on the choice: every
 candidate produces the same chain, so the sweeps made while tuning are real
 sweeps of the chain.  The winner is cached in a JSON file keyed by the GPU
 architecture, the problem shape (replicas, sites and active cells per stage,

@@ -169,33 +169,60 @@ vcsgc_status refresh_md(vcsgc_ctx *c) {
   }
 }
 
-// Workgroups of the persistent sweep: replica r gets about
-// ncpc / (groups per workgroup * trials_per_group) of them (at least one);
-// replicas with 8 or more get a multiple of 8 starting at a multiple of 8 so
-// that their shares can be laid out XCD by XCD.  The grid must fit the
-// co-resident capacity; trials_per_group doubles until it does.
+// Workgroups of the persistent sweep.  A replica whose densities and species
+// (nine bytes per atom) fit the LDS of one workgroup runs in one: its stages
+// then need no device barrier.  The others get trial groups for
+// PERSIST_SPEC / trials_per_group stages of their active cells per batch (at
+// least one workgroup, a multiple of 8 starting at a multiple of 8 from 8 on,
+// so that their shares can be laid out XCD by XCD).  The grid must fit the
+// co-resident capacity, which the LDS of the largest resident replica
+// lowers: first fewer stages are tried per batch, then the LDS bound of
+// residence is lowered (one, two, three workgroups per CU, none resident),
+// then trials_per_group doubles.
+constexpr int PERSIST_SPEC = 8;
+constexpr int64_t PERSIST_MAX = 1 << 20;  // active cells and workgroups of a replica, at most
+
 vcsgc_status assign_workgroups(vcsgc_ctx *c) {
-  int dev_cu = 0, per_cu = 0;
+  int dev_cu = 0, lds_cu = 0;
   VC_CHECK(c, hipDeviceGetAttribute(&dev_cu, hipDeviceAttributeMultiprocessorCount, c->device),
            "device query");
-  VC_CHECK(c, vc::persist_max_blocks(&per_cu, c->pot.tab != 0), "occupancy query");
-  const int cap = dev_cu * (per_cu > 0 ? per_cu : 1);
+  VC_CHECK(c, hipDeviceGetAttribute(&lds_cu, hipDeviceAttributeMaxSharedMemoryPerMultiprocessor,
+                                    c->device),
+           "device query");
   const int R = (int)c->reps.size();
-  if (R > cap) return fail(c, VCSGC_E_INVALID_ARG, "more replicas than co-resident workgroups");
   int tpg = c->trials_per_group < 1 ? 1 : c->trials_per_group;
-  for (;;) {
-    std::vector<int> want(R);
-    int64_t total = 0;
-    for (int k = 0; k < R; ++k) {
-      const int64_t per = (int64_t)vc::persist_groups() * tpg;
-      int64_t g = (c->reps[k].ncpc + per - 1) / per;
-      if (g < 1) g = 1;
-      if (g >= 8) g = (g + 7) / 8 * 8;
-      want[k] = (int)g;
-      total += g;
-    }
-    if (total <= cap || tpg >= (1 << 20)) {
-      if (total > cap) return fail(c, VCSGC_E_INVALID_ARG, "persistent grid does not fit");
+  for (;; tpg *= 2) {
+    for (int step = 0; step < 16; ++step) {
+      const int split = 1 + step / 4, spec = PERSIST_SPEC >> (step % 4);
+      // LDS of a workgroup with the static part and some slack left out
+      const size_t room = split <= 3 ? (size_t)lds_cu / split - 1024 : 0;
+      std::vector<int> want(R);
+      std::vector<char> res(R);
+      int64_t total = 0, chunk = 1, nres = 0;
+      for (int k = 0; k < R; ++k) {
+        const RepHost &r = c->reps[k];
+        if (r.ncpc > PERSIST_MAX)
+          return fail(c, VCSGC_E_INVALID_ARG, "too many cells for the persistent sweep");
+        res[k] = vc::persist_lds_need(r.ncpc, r.n, nullptr) <= room;
+        const int64_t per = (int64_t)vc::persist_groups() * tpg;
+        int64_t g = res[k] ? 1 : (spec * r.ncpc + per - 1) / per;
+        if (g < 1) g = 1;
+        if (g >= 8) g = (g + 7) / 8 * 8;
+        want[k] = (int)g;
+        total += g;
+        chunk = std::max<int64_t>(chunk, (r.ncpc + g - 1) / g);
+        if (res[k]) nres = std::max<int64_t>(nres, r.n);
+      }
+      int ndraw = 0, per_cu = 0;
+      const size_t lds = vc::persist_lds_need(chunk, nres, &ndraw);
+      if (lds > (size_t)lds_cu - 1024) continue;
+      VC_CHECK(c, vc::persist_max_blocks(&per_cu, c->pot.tab != 0, lds, (size_t)lds_cu - 1024), "occupancy query");
+      const int64_t cap = (int64_t)dev_cu * per_cu;
+      if (total > cap) {
+        if (R > cap && step == 15)
+          return fail(c, VCSGC_E_INVALID_ARG, "more replicas than co-resident workgroups");
+        continue;
+      }
       // large replicas first (aligned), then the single-digit ones
       std::vector<int> order(R);
       for (int k = 0; k < R; ++k) order[k] = k;
@@ -206,6 +233,7 @@ vcsgc_status assign_workgroups(vcsgc_ctx *c) {
       for (int k : order) {
         c->reps[k].g0 = g0;
         c->reps[k].G = want[k];
+        c->reps[k].res = res[k] != 0;
         for (int q = 0; q < want[k]; ++q) map[g0 + q] = k;
         g0 += want[k];
       }
@@ -216,14 +244,17 @@ vcsgc_status assign_workgroups(vcsgc_ctx *c) {
                             hipMemcpyHostToDevice),
                "copy");
       c->grid_total = (int)total;
-      c->trials_per_group = tpg;
+      if (c->strategy < 2) c->trials_per_group = tpg;
+      c->persist_lds = lds;
+      c->persist_ndraw = ndraw;
       if (c->graph_exec) {
         (void)hipGraphExecDestroy(c->graph_exec);
         c->graph_exec = nullptr;
       }
       return VCSGC_OK;
     }
-    tpg *= 2;
+    if (tpg >= (1 << 20))
+      return fail(c, VCSGC_E_INVALID_ARG, "persistent grid does not fit");
   }
 }
 
@@ -613,9 +644,9 @@ vcsgc_status create_impl(const vcsgc_system *sys, int R, const int64_t *rep_atom
   };
   vcsgc_status st = assign_workgroups(c);
   if (st) return bail(st);
-  // trial-kernel partial sums: the larger of the two strategies' needs
+  // trial-kernel partial sums
   const int64_t npart_stage = (r0.ncpc * 16 + vc::BLOCK - 1) / vc::BLOCK + 1;
-  c->npart = std::max<int64_t>(npart_stage, c->grid_total);
+  c->npart = npart_stage;
   if ((e = dalloc(&c->part, vc::NPART * c->npart)) != hipSuccess)
     return bail(dev_fail(c, e, "allocation"));
   if ((e = hipMemsetAsync(c->ds, 0, sizeof(vc::DevState), c->stream)) != hipSuccess)
@@ -814,13 +845,6 @@ vcsgc_status vcsgc_set_tuning(vcsgc_ctx *c, int32_t strategy, int32_t trials_per
     c->trials_per_group = trials_per_group;
     st = assign_workgroups(c);
     if (st) return st;
-    if (c->grid_total > c->npart) {
-      vc::free_stage_graph(c);  // its nodes hold the old buffer
-      (void)hipFree(c->part);
-      c->part = nullptr;
-      c->npart = c->grid_total;
-      VC_CHECK(c, dalloc(&c->part, vc::NPART * c->npart), "allocation");
-    }
   }
   return VCSGC_OK;
 }

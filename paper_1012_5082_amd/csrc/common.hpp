@@ -267,7 +267,8 @@ __device__ __forceinline__ double pot_dphi(const PotD &p, int a, int b, double r
 template <int F = -1>
 __device__ __forceinline__ double embed(const PotD &p, int s, double rho) {
   if (pot_tab<F>(p)) return spline_at(tab_embed(p, s), p.nrho, rho, p.inv_drho, nullptr);
-  return -p.A[s] * sqrt(rho > 0.0 ? rho : 0.0);
+  // (a density is 0 or far from the ends of sqrt_md's range)
+  return -p.A[s] * (rho > 0x1p-700 && rho < 0x1p1000 ? sqrt_md(rho) : sqrt(rho > 0.0 ? rho : 0.0));
 }
 
 template <int F = -1>
@@ -320,8 +321,10 @@ __device__ __forceinline__ double flip_own_term(const PotD &p, int s, double ri)
 
 // The in-order sums of the (pair, embedding) terms of entries 0 .. m-1 held
 // in LDS slots (written by the lanes of one wave, whose LDS accesses are
-// performed in order): eight slots are read per round, so the reads do not
-// wait on the additions.
+// performed in order; the slots from m to KMAX hold +0.0): eight slots are
+// read per round, so the reads do not wait on the additions.  The unused
+// slots of a round are added too: a sum that starts at +0.0 is never -0.0,
+// so adding +0.0 changes nothing, and the additions need no selects.
 __device__ __forceinline__ void sum_flip_terms(const double2 *grp, int m, double &pair,
                                                double &emb) {
   pair = 0.0;
@@ -332,11 +335,10 @@ __device__ __forceinline__ void sum_flip_terms(const double2 *grp, int m, double
 #pragma unroll
     for (int u = 0; u < 8; ++u) q[u] = grp[k0 + u];
 #pragma unroll
-    for (int u = 0; u < 8; ++u)
-      if (k0 + u < m) {
-        pair += q[u].x;
-        emb += q[u].y;
-      }
+    for (int u = 0; u < 8; ++u) {
+      pair += q[u].x;
+      emb += q[u].y;
+    }
   }
 }
 
@@ -421,6 +423,7 @@ struct RepHost {
   int nb[3] = {0, 0, 0};     // search bins per dimension
   int64_t nbins = 0, boff = 0;
   int g0 = 0, G = 1;         // workgroups of the persistent sweep
+  bool res = false;          // one workgroup with the replica's state in LDS
 };
 
 struct vcsgc_ctx {
@@ -571,7 +574,9 @@ struct vcsgc_ctx {
   void *d_rs = nullptr;       // per-replica chain state and counters
   int32_t *d_wg_rep = nullptr;  // workgroup -> replica
   int grid_total = 0;
-  int trials_per_group = 1;   // tiling: active cells per trial group and stage
+  size_t persist_lds = 0;   // dynamic LDS of the persistent sweep's workgroups
+  int persist_ndraw = 0;    // trials a workgroup draws ahead
+  int trials_per_group = 1;   // tiling: trial groups per active cell (see assign_workgroups)
   int strategy = 0;           // 0: persistent (graph), 1: persistent (direct), 2: per-stage
   unsigned int spin_limit = 1u << 24;
   hipEvent_t stage_ev = nullptr;
@@ -657,11 +662,11 @@ hipError_t launch_sqrt(const double *in, double *out, int64_t n, hipStream_t s);
 hipError_t launch_md_math(const double *a, const double *b, double *sq, double *q, int64_t n,
                           hipStream_t s);
 // persistent sweep (persist.hip)
-int persist_block();
 int persist_groups();
+size_t persist_lds_need(int64_t chunk, int64_t nres, int *ndraw);
 size_t repd_size();
 size_t repstate_size();
-hipError_t persist_max_blocks(int *per_cu, bool tab);
+hipError_t persist_max_blocks(int *per_cu, bool tab, size_t lds, size_t lds_max);
 hipError_t persist_stage_params(vcsgc_ctx *c, const double *dmu0, const double *kappa,
                                 const double *cbar, const double *T, int64_t n_sweeps,
                                 uint64_t seed);

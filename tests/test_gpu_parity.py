@@ -818,3 +818,38 @@ def test_colours27_after_md_and_replicas(torch_cuda, oracle_mod):
         assert s1[k]["flips"] == sok["flips"] and s1[k]["n_final"] == sok["n_final"], k
         assert np.array_equal(b.replica_species(k), stk.species), k
     b.close()
+
+
+@pytest.mark.parametrize("nx,colours,kappa,tpg", [
+    ((6, 6, 6), 8, 0.0, 1),        # state in LDS, one cell per stage, accepted stages
+    ((10, 10, 10), 27, 1.0, 1),    # resident, 8 cells per stage
+    ((17, 18, 19), 8, 1.0, 1),     # the last sizes that stay resident
+    ((18, 18, 19), 8, 0.0, 1),     # the first that do not: several workgroups, commits at every stage
+    ((23, 31, 17), 27, 10.0, 4),   # uneven shares of the cells
+    ((33, 26, 29), 8, 1000.0, 16),  # more cells per workgroup than trial groups
+])
+def test_persistent_batches(torch_cuda, oracle_mod, nx, colours, kappa, tpg):
+    """The persistent sweep tries batches of stages: on both sides of its
+    choices (state in LDS or in memory, one or several workgroups, one or
+    several passes over the cells) three calls give the oracle's chain bit for
+    bit, with the statistics of decided stages only."""
+    O = oracle_mod
+    from paper_1012_5082_amd.binding import VCSGC
+    pot = I.params("FS-P1")
+    x, y, z, box = I.bcc(*nx)
+    x, y, z = I.thermalize(x, y, z, box, 0.04, 5)
+    sp = I.initial_species(x.size, 0.1, 6)
+    g = VCSGC(x, y, z, box, sp, pot, colours=colours)
+    g.set_tuning("graph", 2)
+    g.set_tuning("graph", tpg)
+    st = O.SweepState(x, y, z, box, sp, pot)
+    for n_sw in (1, 2, 1):
+        a = g.sweep(-0.2, kappa, 0.1, 600.0, n_sw, 31)
+        b, _, _ = O.sweep(st, -0.2, kappa, 0.1, 600.0, n_sw, 31,
+                          colour_period=3 if colours == 27 else 2)
+        for k in ("trials", "local_accepts", "stages", "stage_accepts", "flips", "n_final",
+                  "sum_n", "sum_n2"):
+            assert a[k] == b[k], (k, a[k], b[k])
+    assert np.array_equal(g.species.cpu().numpy(), st.species)
+    assert np.array_equal(g.rho().cpu().numpy(), st.rho)
+    g.close()
