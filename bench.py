@@ -59,7 +59,7 @@ def algorithmic_bytes(kind, n, pairs_md, pairs_mc, trials, fused=0.0):
     kick_drift: x,y,z,v,F,species,reference positions read (105), x,y,z,v and the
                 packed positions written (80)
     kick      : v, F, species read (49), v written (24)
-    trial     : per trial, own species/rho/row length (10) + per r < rc pair the
+    trial, persist: per trial, own species/rho/row length (10) + per r < rc pair the
                 index, (rc-r)^2, c0+c1 r (20) and the neighbour's species and rho
                 (9) + cell start/atom (8+4) + record (4)
     stage     : the trial bytes above with the site and ln u read from the site
@@ -74,7 +74,7 @@ def algorithmic_bytes(kind, n, pairs_md, pairs_mc, trials, fused=0.0):
         return 185 * n
     if kind == "kick":
         return 73 * n
-    if kind == "trial":
+    if kind in ("trial", "persist"):
         k = pairs_mc / n
         return trials * (26 + 21 * k)
     if kind == "stage":
@@ -84,7 +84,7 @@ def algorithmic_bytes(kind, n, pairs_md, pairs_mc, trials, fused=0.0):
     return None
 
 
-HAS_BYTES = ("forces", "density", "kick_drift", "kick", "trial", "stage")
+HAS_BYTES = ("forces", "density", "kick_drift", "kick", "trial", "stage", "persist")
 SAMPLE = 8  # sweep-kernel launches per timed launch
 
 # kernel class -> (kernel symbol, source file, profile summary holding its
@@ -94,6 +94,7 @@ TRAFFIC = {
     "density": ("k_density_md", "paper_1012_5082_amd/csrc/md.hip",
                 "profiles/k_density_md_c3_traffic.md"),
     "stage": ("k_stage", "paper_1012_5082_amd/csrc/sweep.hip", "profiles/k_stage_c3_traffic.md"),
+    "persist": ("k_sweep_persistent", "paper_1012_5082_amd/csrc/persist.hip", ""),
     "batch": ("k_stage_spec", "paper_1012_5082_amd/csrc/sweep.hip",
               "profiles/k_stage_spec_c3_traffic.md"),
 }
@@ -515,7 +516,7 @@ def main():
     # pairs at every launch would add host and stream work; the pipelines
     # time the span of each graph replay); the dominant class is the one with
     # the largest time over the timed cycles.
-    g.kernel_timing(["trial", "commit", "stage", "density", "forces", "kick_drift", "kick",
+    g.kernel_timing(["trial", "commit", "density", "forces", "kick_drift", "kick",
                      "build", "persist"], every=SAMPLE)
     ev = [(torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True),
            torch.cuda.Event(enable_timing=True)) for _ in range(args.steps)]
@@ -542,7 +543,7 @@ def main():
     breakdown = {k: (v[0] / v[1] * v[2] / args.steps, v[2] / args.steps) for k, v in kt.items()}
     top = max(breakdown, key=lambda k: breakdown[k][0])
     dominant = max((k for k in breakdown if k in HAS_BYTES), key=lambda k: breakdown[k][0])
-    sweep_cls = "stage" if "stage" in breakdown else ("trial" if "trial" in breakdown else None)
+    sweep_cls = next((k for k in ("persist", "stage", "trial") if k in breakdown), None)
     log("breakdown (ms per cycle, launches per cycle): " + ", ".join(
         f"{k}={v[0]:.3f}/{v[1]:.0f}" for k, v in sorted(breakdown.items(), key=lambda t: -t[1][0])))
     info2 = g.info()
@@ -560,6 +561,8 @@ def main():
         avg_s = tot_ms / launches / 1e3
         per_launch = 0
         if cls == "trial":
+            per_launch = trials / max(1, all_launches)
+        elif cls == "persist":  # one launch per call: its trials' bytes
             per_launch = trials / max(1, all_launches)
         elif cls == "stage":
             per_launch = (trials / max(1, all_launches), stages * ncpc / max(1, all_launches))

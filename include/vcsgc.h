@@ -235,7 +235,11 @@ vcsgc_status vcsgc_sweep_batch(vcsgc_ctx *ctx, const double *dmu0, const double 
  *               stage, after which the trials are made again (single system
  *               only; trials_per_group in [1, 16], capped at half the stages
  *               of a sweep; with trial or stage logs on, or fewer than two
- *               stages per sweep, it runs as strategy 2);
+ *               stages per sweep, it runs as strategy 2).
+ *            Strategies 2 and 3 run plain sweeps that are neither logged nor
+ *            timed per stage kernel through the persistent launch where its
+ *            workgroups cover the active cells (about 4M sites): it tries
+ *            batches of stages too, and faster;
  *   trials_per_group: strategies 0 and 1: divides the number of workgroups
  *            of a replica in the persistent kernel, and with it the stages
  *            tried per batch (a replica that fits one compute unit's LDS

@@ -190,10 +190,11 @@ vcsgc_status assign_workgroups(vcsgc_ctx *c) {
                                     c->device),
            "device query");
   const int R = (int)c->reps.size();
-  int tpg = c->trials_per_group < 1 ? 1 : c->trials_per_group;
+  // (the pipeline strategies' parameter is the stages of their kernels' batch)
+  int tpg = c->strategy >= 2 || c->trials_per_group < 1 ? 1 : c->trials_per_group;
   for (;; tpg *= 2) {
-    for (int step = 0; step < 16; ++step) {
-      const int split = 1 + step / 4, spec = PERSIST_SPEC >> (step % 4);
+    for (int step = 0; step < 4 * 8; ++step) {
+      const int split = 1 + step / 8, spec = PERSIST_SPEC - step % 8;
       // LDS of a workgroup with the static part and some slack left out
       const size_t room = split <= 3 ? (size_t)lds_cu / split - 1024 : 0;
       std::vector<int> want(R);
@@ -219,7 +220,7 @@ vcsgc_status assign_workgroups(vcsgc_ctx *c) {
       VC_CHECK(c, vc::persist_max_blocks(&per_cu, c->pot.tab != 0, lds, (size_t)lds_cu - 1024), "occupancy query");
       const int64_t cap = (int64_t)dev_cu * per_cu;
       if (total > cap) {
-        if (R > cap && step == 15)
+        if (R > cap && step == 4 * 8 - 1)
           return fail(c, VCSGC_E_INVALID_ARG, "more replicas than co-resident workgroups");
         continue;
       }
@@ -747,9 +748,24 @@ vcsgc_status sweep_impl(vcsgc_ctx *c, const double *dmu0, const double *kappa, c
   if (c->local_steps > 1 && (c->da_mode || c->smp_cap > 0))
     return fail(c, VCSGC_E_INVALID_ARG,
                 "delayed acceptance and the sample log need one trial per cell per stage");
-  // delayed acceptance, the training-sample log and local chains run with
-  // per-stage launches
-  if ((c->strategy >= 2 || c->da_mode || c->smp_cap > 0 || c->local_steps > 1) && R == 1) {
+  // Delayed acceptance, the training-sample log, local chains and grown
+  // domains run with kernels per stage or batch of stages, and so do the
+  // pipeline strategies where their stages are logged or timed, or where a
+  // workgroup of the persistent sweep would hold more active cells than
+  // trial groups.  Below that (about 4M sites) the persistent sweep is the
+  // faster form of the same chain: a batch of stages costs it one device
+  // barrier and one round of gathers (6 - 12 us) instead of a kernel with its
+  // launch, site table and row reads one after the other (10 - 12 us), and it
+  // fits the length of its batches to the acceptance.  Per stage, persistent
+  // against the best of 3, 8 and 16 stages per kernel: 250,000 sites at 28%
+  // accepted stages 2.6 / 4.5 us, 0.5M at 24% 2.9 / 4.6, 2M at 23% 4.8 / 7.5,
+  // 1M at 0% 1.2 / 1.2, 4M at 0% 3.7 / 3.5, 8M at 0% 7.2 / 6.3.
+  const bool logged = c->tlog || c->slog || c->dalog;
+  const bool per_stage =
+      c->da_mode || c->smp_cap > 0 || c->local_steps > 1 || c->grown ||
+      (c->strategy >= 2 && (logged || (c->tmask & (1u << VCSGC_KT_STAGE)) ||
+                            c->reps[0].ncpc > (int64_t)c->reps[0].G * vc::persist_groups()));
+  if (per_stage && R == 1) {
     // one trial kernel and one commit kernel per stage
     VC_CHECK(c, vc::persist_sync_nb_to_stage(c), "sweep");
     c->h_state_final = false;
@@ -779,7 +795,7 @@ vcsgc_status sweep_impl(vcsgc_ctx *c, const double *dmu0, const double *kappa, c
   VC_CHECK(c, vc::persist_stage_params(c, dmu0, kappa, cbar, T, n_sweeps, seed), "sweep");
   if (n_sweeps > 0) {
     int h = vc::tstart(c, VCSGC_KT_PERSIST);
-    VC_CHECK(c, vc::launch_persistent(c, c->strategy == 0), "persistent sweep");
+    VC_CHECK(c, vc::launch_persistent(c, c->strategy != 1), "persistent sweep");
     vc::tstop(c, h);
   }
   c->w += (uint64_t)n_sweeps;
@@ -840,9 +856,10 @@ vcsgc_status vcsgc_set_tuning(vcsgc_ctx *c, int32_t strategy, int32_t trials_per
   if (strategy < 2 && c->grown)
     return fail(c, VCSGC_E_INVALID_ARG, "grown domains run on the pipeline strategies (2, 3)");
   VC_CHECK(c, hipStreamSynchronize(c->stream), "sync");
+  const bool same = trials_per_group == c->trials_per_group && strategy / 2 == c->strategy / 2;
   c->strategy = strategy;
-  if (trials_per_group != c->trials_per_group) {
-    c->trials_per_group = trials_per_group;
+  c->trials_per_group = trials_per_group;
+  if (!same) {
     st = assign_workgroups(c);
     if (st) return st;
   }

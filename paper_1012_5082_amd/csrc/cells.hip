@@ -626,15 +626,6 @@ __global__ void __launch_bounds__(BLOCK)
   md_row_stats(c < KMAX ? c : KMAX, c < KMAX ? c : KMAX, c > KMAX, ds);
 }
 
-// Block barrier for LDS traffic only: the fences are restricted to LDS, so
-// the barrier waits for this wave's LDS accesses but not for its global
-// loads and stores.
-__device__ __forceinline__ void block_sync_lds() {
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
-  __builtin_amdgcn_s_barrier();
-  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
-}
-
 // Exclusive scans over the block of two per-thread values (one value per
 // thread; BLOCK / 64 waves); returns the block totals.  Contains barriers:
 // every thread of the block calls it.

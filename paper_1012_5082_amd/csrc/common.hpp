@@ -223,6 +223,19 @@ __device__ __forceinline__ const double *tab_embed(const PotD &p, int s) {
   return p.tc + 4 * (5 * (int64_t)(p.nr - 1) + (int64_t)s * (p.nrho - 1));
 }
 
+// Per-species and per-pair parameters by selects: an array of a kernel's
+// arguments indexed by a lane's value is a vector load from the argument
+// segment, which sat in the dependent chain of every trial (three in the
+// energy change: 0.9 us of the persistent sweep's batch).
+__device__ __forceinline__ double by_species(const double (&v)[2], int s) {
+  const double a = v[0], b = v[1];
+  return s ? b : a;
+}
+__device__ __forceinline__ double by_pair(const double (&v)[3], int k) {
+  const double a = v[0], b = v[1], c = v[2];
+  return k == 0 ? a : (k == 1 ? b : c);
+}
+
 // The potential's form for the helpers below: F = 0 analytic, 1 tabulated
 // (fixed at compile time), -1 (the default) read from p.tab.
 template <int F>
@@ -236,7 +249,7 @@ __device__ __forceinline__ bool pot_tab(const PotD &p) {
 template <int F = -1>
 __device__ __forceinline__ double pot_f(const PotD &p, int s, double r) {
   if (pot_tab<F>(p)) return spline_at(tab_radial(p, s), p.nr, r, p.inv_dr, nullptr);
-  return p.t[s] * pair_dd(p, r);
+  return by_species(p.t, s) * pair_dd(p, r);
 }
 template <int F = -1>
 __device__ __forceinline__ double pot_df(const PotD &p, int s, double r) {
@@ -245,12 +258,12 @@ __device__ __forceinline__ double pot_df(const PotD &p, int s, double r) {
     spline_at(tab_radial(p, s), p.nr, r, p.inv_dr, &g);
     return g;
   }
-  return -2.0 * p.t[s] * (p.rc - r);
+  return -2.0 * by_species(p.t, s) * (p.rc - r);
 }
 template <int F = -1>
 __device__ __forceinline__ double pot_phi(const PotD &p, int a, int b, double r) {
   if (pot_tab<F>(p)) return spline_at(tab_radial(p, 2 + a + b), p.nr, r, p.inv_dr, nullptr);
-  return p.eps[a + b] * pair_dd(p, r) * pair_g(p, r);
+  return by_pair(p.eps, a + b) * pair_dd(p, r) * pair_g(p, r);
 }
 template <int F = -1>
 __device__ __forceinline__ double pot_dphi(const PotD &p, int a, int b, double r) {
@@ -260,7 +273,7 @@ __device__ __forceinline__ double pot_dphi(const PotD &p, int a, int b, double r
     return g;
   }
   const double d = p.rc - r;
-  return p.eps[a + b] * (-2.0 * d * (p.c0 + p.c1 * r) + p.c1 * (d * d));
+  return by_pair(p.eps, a + b) * (-2.0 * d * (p.c0 + p.c1 * r) + p.c1 * (d * d));
 }
 
 // F_X(rho) = -A_X sqrt(max(rho, 0)) and F'_X(rho) (0 at rho <= 0), or the tables
@@ -268,7 +281,7 @@ template <int F = -1>
 __device__ __forceinline__ double embed(const PotD &p, int s, double rho) {
   if (pot_tab<F>(p)) return spline_at(tab_embed(p, s), p.nrho, rho, p.inv_drho, nullptr);
   // (a density is 0 or far from the ends of sqrt_md's range)
-  return -p.A[s] * (rho > 0x1p-700 && rho < 0x1p1000 ? sqrt_md(rho) : sqrt(rho > 0.0 ? rho : 0.0));
+  return -by_species(p.A, s) * (rho > 0x1p-700 && rho < 0x1p1000 ? sqrt_md(rho) : sqrt(rho > 0.0 ? rho : 0.0));
 }
 
 template <int F = -1>
@@ -278,7 +291,7 @@ __device__ __forceinline__ double dembed(const PotD &p, int s, double rho) {
     spline_at(tab_embed(p, s), p.nrho, rho, p.inv_drho, &g);
     return g;
   }
-  return rho > 0.0 ? -p.A[s] / (2.0 * sqrt(rho)) : 0.0;
+  return rho > 0.0 ? -by_species(p.A, s) / (2.0 * sqrt(rho)) : 0.0;
 }
 
 // What flipping a site from species s to 1 - s changes, in the order every
@@ -294,11 +307,11 @@ __device__ __forceinline__ double dembed(const PotD &p, int s, double rho) {
 // t_{1-s} dd - t_s dd and the pair change (eps_{1-s,sj} dd) g - (eps_{s,sj} dd) g.)
 // the Finnis-Sinclair forms from dd and g formed beforehand
 __device__ __forceinline__ double flip_rho_shift_fs(const PotD &p, int s, double dd) {
-  return p.t[1 - s] * dd - p.t[s] * dd;
+  return by_species(p.t, 1 - s) * dd - by_species(p.t, s) * dd;
 }
 __device__ __forceinline__ double flip_pair_term_fs(const PotD &p, int s, int sj, double dd,
                                                     double g) {
-  return p.eps[1 - s + sj] * dd * g - p.eps[s + sj] * dd * g;
+  return by_pair(p.eps, 1 - s + sj) * dd * g - by_pair(p.eps, s + sj) * dd * g;
 }
 template <int F = -1>
 __device__ __forceinline__ double flip_rho_shift(const PotD &p, int s, double r) {
@@ -370,6 +383,15 @@ __device__ __forceinline__ int64_t xcd_block() {
   const int64_t nb = gridDim.x, b = blockIdx.x;
   const int64_t q = nb >> 3, r = nb & 7, x = b & 7, k = b >> 3;
   return x < r ? x * (q + 1) + k : r * (q + 1) + (x - r) * q + k;
+}
+
+// Block barrier for LDS traffic only: the fences are restricted to LDS, so
+// the barrier waits for this wave's LDS accesses but not for its global
+// loads and stores.
+__device__ __forceinline__ void block_sync_lds() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+  __builtin_amdgcn_s_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
 }
 
 constexpr int SCAN_CHUNK = 1024;  // values per block of the cell-count scan

@@ -127,7 +127,7 @@ __device__ __forceinline__ void kick_drift_clear(const KickDrift &k, int64_t i, 
 __device__ __forceinline__ void kick_drift_atom(const KickDrift &k, int64_t i, int s, double x0,
                                                 double y0, double z0, double fxi, double fyi,
                                                 double fzi, const Box &b, const PotD &p) {
-  const double cm = p.cm[s];
+  const double cm = by_species(p.cm, s);
   const double hdt = 0.5 * k.dt;
   const double ax = fxi * cm, ay = fyi * cm, az = fzi * cm;
   double ux = k.vx[i], uy = k.vy[i], uz = k.vz[i];
@@ -178,7 +178,8 @@ __device__ __forceinline__ void force_row(int64_t n, int64_t i, int m, int si, c
                                           const PotD &p, double &ax, double &ay, double &az,
                                           double *wv = nullptr) {
   const double fpi = qi.w;
-  const double e0 = p.eps[si], e1 = p.eps[si + 1], t0 = p.t[0], t1 = p.t[1], ti = p.t[si];
+  const double e0 = by_pair(p.eps, si), e1 = by_pair(p.eps, si + 1);
+  const double t0 = p.t[0], t1 = p.t[1], ti = by_species(p.t, si);
   for (int k0 = 0; k0 < m; k0 += IB) {
     int32_t jb[IB];
 #pragma unroll
@@ -384,7 +385,7 @@ __global__ void k_kick(int64_t n, double *vx, double *vy, double *vz, const doub
                        const uint8_t *__restrict__ sp, PotD p, double dt) {
   int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (i >= n) return;
-  const double cm = p.cm[sp[i]];
+  const double cm = by_species(p.cm, sp[i]);
   const double hdt = 0.5 * dt;
   vx[i] = vx[i] + hdt * (fx[i] * cm);
   vy[i] = vy[i] + hdt * (fy[i] * cm);
@@ -430,7 +431,7 @@ __global__ void __launch_bounds__(BLOCK)
     const int s = sp[i];
     double ux = vx[i], uy = vy[i], uz = vz[i];
     if (KICK) {
-      const double cm = p.cm[s];
+      const double cm = by_species(p.cm, s);
       const double hdt = 0.5 * dt;
       ux = ux + hdt * (fx[i] * cm);
       uy = uy + hdt * (fy[i] * cm);
@@ -439,7 +440,7 @@ __global__ void __launch_bounds__(BLOCK)
       vy[i] = uy;
       vz[i] = uz;
     }
-    t = p.mass[s] * ((ux * ux + uy * uy) + uz * uz);
+    t = by_species(p.mass, s) * ((ux * ux + uy * uy) + uz * uz);
   }
   a[threadIdx.x] = t;
   __syncthreads();
@@ -707,7 +708,7 @@ __global__ void __launch_bounds__(BLOCK)
   bool far = false;
   if (i < n) {
     const int s = sp[i];
-    const double cm = p.cm[s];
+    const double cm = by_species(p.cm, s);
     double ux = vx[i], uy = vy[i], uz = vz[i];
     ux = ux * f1;
     uy = uy * f1;
@@ -759,7 +760,7 @@ __global__ void __launch_bounds__(BLOCK)
     const int s = sp[i];
     double ux = vx[i], uy = vy[i], uz = vz[i];
     if (KICK) {
-      const double cm = p.cm[s];
+      const double cm = by_species(p.cm, s);
       ux = ux * c;
       uy = uy * c;
       uz = uz * c;
@@ -773,7 +774,7 @@ __global__ void __launch_bounds__(BLOCK)
       vy[i] = uy;
       vz[i] = uz;
     }
-    a = p.mass[s] * ((ux * ux + uy * uy) + uz * uz);
+    a = by_species(p.mass, s) * ((ux * ux + uy * uy) + uz * uz);
     q = w[i];
   }
   s0[t] = a;

@@ -4,9 +4,9 @@
 //
 // Replica r owns workgroups [g0, g0 + G) of the grid, each a contiguous share
 // of the replica's active cells.  A stage whose global test fails changes
-// nothing, so a batch of up to D consecutive stages of a sweep is tried at
-// once on the state as it is, one group of PTL lanes per trial:
-//   1. every group makes its trial (the arithmetic of the per-stage kernels):
+// nothing, so a batch of consecutive stages of a sweep is tried at once on the
+// state as it is, one group of PTL lanes per trial:
+//   1. every group makes its trials (the arithmetic of the per-stage kernels):
 //      local factor of Eq. trans_vcsgc_par1; the workgroup's counts per stage
 //      (accepts with dn = +1 and -1) are summed in LDS;
 //   2. replicas of several workgroups: each adds its counts, packed with an
@@ -20,18 +20,25 @@
 //      makes it visible before the next batch.
 // The chain is the one-stage-at-a-time chain, stage for stage.
 //
-// What bounds it: the latency of a batch, not bytes or arithmetic.  So the
-// sites and ln u of many stages ahead are drawn at once into LDS (off the
-// path of a stage: two Philox blocks, a logarithm and two dependent loads),
-// the neighbour rows of the next batch are read before the decision of the
-// current one, and a replica whose densities and species fit the LDS runs in
-// one workgroup that keeps them there (RES) and needs no device barrier.
+// What bounds it: the latency of a batch (6 - 12 us), not bytes or
+// arithmetic: about a third the trials' dependent chain, a third waiting for
+// the slowest workgroup, the rest decisions and loop code.  Therefore:
+//   - sites, ln u and ln u_g are drawn ahead into LDS rings by waves that
+//     would otherwise wait (two Philox blocks, a logarithm and two dependent
+//     loads per trial);
+//   - the rows of the next batch are read before the decision of this one;
+//   - a batch holds as many stages as the groups try in one pass, and twice
+//     as many after each rejected batch: with few accepted stages the batch's
+//     fixed cost is shared by more of them, with many none is tried in vain;
+//   - a replica whose densities and species fit the LDS runs in one workgroup
+//     that keeps them there (RES) and needs no device barrier;
+//   - 8 lanes per trial, two entries' chains side by side in a lane (16 lanes
+//     per trial doubled the instructions a SIMD issues per batch).
 // Measured (calls included; before: one stage per two release/acquire
-// barriers of the device scope, one row per 16 lanes, every draw on the
-// path): a sweep of 2,000 rigid sites 11.2 -> 0.27 ms; of 128,000 thermal
-// sites 4.3 -> 1.8 ms near equilibrium (0.6 ms from a random start, where few
-// stages are accepted); two sweeps of 64 replicas of 2,000 to 250,000 sites
-// 22.3 -> 6.9 ms.
+// barriers of the device scope, every draw on the path): a sweep of 2,000
+// rigid sites 11.2 -> 0.22 ms; of 128,000 thermal sites 4.3 -> 1.3 ms near
+// equilibrium (0.47 ms from a random start, where few stages are accepted);
+// two sweeps of 64 replicas of 2,000 to 250,000 sites 21.8 -> 5.5 ms.
 //
 // The densities and species of replicas of several workgroups are read and
 // written with relaxed device-scope atomics, which bypass the caches that are
@@ -41,6 +48,7 @@
 // exceeds the spin limit sets the replica's error flag and the workgroup
 // leaves the kernel, so the launch always drains.
 #include <algorithm>
+#include <mutex>
 
 #include "common.hpp"
 
@@ -51,10 +59,10 @@ constexpr int PH = KMAX / PTL;        // row entries per lane
 constexpr int PBLOCK = 512;           // threads of a workgroup
 constexpr int PGROUPS = PBLOCK / PTL; // trials per workgroup pass
 constexpr int PDMAX = 32;             // stages per batch, at most
-constexpr int PDG = 8;                // the same with several workgroups
-constexpr int PWIN = 256;             // stages drawn ahead, at most
-constexpr int PDRAW = 1024;           // trials drawn ahead (at least the workgroup's cells)
-static_assert(8 * PDG == 64 && 2 * PDMAX <= PBLOCK && PDMAX <= 64, "one wave per batch of words");
+constexpr int PDG = 16;               // the same with several workgroups
+constexpr int PWIN = 256;             // stages whose counters are drawn ahead (a power of two)
+constexpr int PDRAW = 1024;           // trials drawn ahead (twice that without a resident replica)
+static_assert(8 * PDG == 128 && 2 * PDMAX <= PBLOCK && PDMAX <= 64, "a wave holds a batch's words");
 
 struct RepD {
   int64_t n, aoff;
@@ -77,12 +85,15 @@ struct alignas(128) RepState {
   // words of the batches' stages, a ring of four batches: the words of batch
   // b + 2 are cleared by a workgroup that has seen all of them arrive at
   // batch b - 1 (so none still polls b - 2) and before it arrives at b.
-  // Workgroup q adds to row q mod 8, a 64-byte line: the adds to one line are
+  // Workgroup q adds to row q mod 8, a 128-byte line: the adds to one line are
   // served one after the other (216 workgroups on one line took 8 us a batch)
   unsigned long long word[4][8][PDG];
-  // commit barrier: 64-bit arrival counter (it grows by G per accepted stage
-  // and is zeroed only once per call)
-  alignas(128) unsigned long long bar;
+  // commit barrier: 64-bit arrival counters, one line per row of workgroups
+  // (they grow by the row's workgroups per accepted stage and are zeroed only
+  // once per call)
+  struct alignas(128) Bar {
+    unsigned long long n;
+  } bar[8];
   alignas(128) long long n_b;  // n_B at the start of the call
   unsigned long long trials, local_acc, stages, stage_acc, flips, near_ties;
   double sum_n, sum_n2;
@@ -114,18 +125,19 @@ struct PersistArgs {
 // counts, and the state of a resident replica of nres atoms
 struct PLds {
   double2 *terms;           // [PGROUPS][KMAX]
-  double *lnu, *lnug;       // [ndraw], [PWIN]
+  double *lnu, *lnug;       // [ndraw], [PWIN]: ln u of trials, ln u_g of stages
   unsigned long long *cw;   // [3][PDMAX][2]: packed accepts; trials | ties << 32
   unsigned long long *tot;  // [PDMAX]
   double *rho;              // [nres]
   int32_t *site, *rec;      // [ndraw] each
+  uint8_t *col;             // [PWIN] colours of stages
   uint8_t *sp;              // [nres]
 };
 
 static size_t persist_lds_bytes(int64_t ndraw, int64_t nres) {
   return sizeof(double2) * PGROUPS * KMAX + sizeof(double) * (ndraw + PWIN) +
          sizeof(unsigned long long) * 7 * PDMAX + sizeof(double) * nres +
-         2 * sizeof(int32_t) * ndraw + nres;
+         2 * sizeof(int32_t) * ndraw + PWIN + nres;
 }
 
 __device__ __forceinline__ PLds persist_lds(unsigned char *base, int ndraw, int64_t nres) {
@@ -138,7 +150,8 @@ __device__ __forceinline__ PLds persist_lds(unsigned char *base, int ndraw, int6
   l.rho = (double *)(l.tot + PDMAX);
   l.site = (int32_t *)(l.rho + nres);
   l.rec = l.site + ndraw;
-  l.sp = (uint8_t *)(l.rec + ndraw);
+  l.col = (uint8_t *)(l.rec + ndraw);
+  l.sp = l.col + PWIN;
   return l;
 }
 
@@ -156,10 +169,11 @@ __device__ __forceinline__ int64_t p_colour_cell(const RepD &r, int colour, uint
 __device__ __forceinline__ void wait_stores() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
 
 // What a lane holds of a site's row: entries lane + h PTL (inside the
-// KMAX-entry row; entries beyond the row length are not dereferenced).
+// KMAX-entry row; entries beyond the row length are not dereferenced), and
+// the densities the trial read for them.
 struct PRow {
   int32_t j[PH];
-  double r[PH];
+  double r[PH], rj[PH];
   int m;
 };
 
@@ -202,56 +216,98 @@ struct PState {
   }
 };
 
+// F_X(rho) of the trial without a branch for the densities that sqrt_md
+// serves; `slow` is raised for others (0 among them)
+template <int F>
+__device__ __forceinline__ double p_embed(const PotD &p, int s, double rho, bool &slow) {
+  if (F == 1) return embed<1>(p, s, rho);
+  const bool in = rho > 0x1p-700 && rho < 0x1p1000;
+  slow = slow || !in;
+  return -by_species(p.A, s) * sqrt_md(in ? rho : 1.0);
+}
+
 // transmutation energy change by the PTL lanes of a group (in-order sums of
 // the terms the lanes leave in the group's LDS slots; a group is 8 lanes of
-// one wave, whose LDS accesses are performed in order); s: the site's species
+// one wave, whose LDS accesses are performed in order); s: the site's species.
+// One wave per SIMD works on a stage here, so the chains of a lane's entries
+// are laid side by side: two entries at a time without a branch (unused ones
+// read the site itself and leave +0.0), the second two only where some row of
+// the wave has more than 16 entries.
 template <int F, bool RES>
-__device__ __forceinline__ double p_delta_u(const PState<RES> &st, int64_t i, int lane,
-                                            const PRow &v, double2 *grp, int &s) {
+__device__ __forceinline__ double p_delta_u(const PState<RES> &st, int64_t i, int lane, PRow &v,
+                                            double2 *grp, int &s) {
   const PotD &p = st.a.p;
   s = st.sp(i);
   const double ri = st.rho(i);
+  const bool more = __any(v.m > 2 * PTL);
   int sj[PH];
-  double rj[PH];
 #pragma unroll
-  for (int h = 0; h < PH; ++h)
-    if (lane + h * PTL < v.m) {  // sj and rj are used under the same condition only
-      sj[h] = st.sp(v.j[h]);
-      rj[h] = st.rho(v.j[h]);
+  for (int h0 = 0; h0 < PH; h0 += 2) {
+    if (h0 && !more) break;
+#pragma unroll
+    for (int h = h0; h < h0 + 2; ++h) {
+      const int64_t j = lane + h * PTL < v.m ? (int64_t)v.j[h] : i;
+      sj[h] = st.sp(j);
+      v.rj[h] = st.rho(j);
+    }
+  }
+  bool slow = false;
+  const double own_new = p_embed<F>(p, 1 - s, ri, slow), own_old = p_embed<F>(p, s, ri, slow);
+#pragma unroll
+  for (int h0 = 0; h0 < PH; h0 += 2) {
+    if (h0 && !more) {
+      grp[lane + h0 * PTL] = grp[lane + (h0 + 1) * PTL] = make_double2(0.0, 0.0);
+      continue;
+    }
+    double tp[2], te[2];
+    bool odd = false;
+#pragma unroll
+    for (int q = 0; q < 2; ++q) {
+      const int h = h0 + q;
+      const bool in = lane + h * PTL < v.m;
+      const double r = in ? v.r[h] : p.rc;
+      bool sl = false;
+      const double shift = flip_rho_shift<F>(p, s, r);
+      const double a = flip_pair_term<F>(p, s, sj[h], r);
+      const double b = p_embed<F>(p, sj[h], v.rj[h] + shift, sl) -
+                       p_embed<F>(p, sj[h], v.rj[h], sl);
+      tp[q] = in ? a : 0.0;
+      te[q] = in ? b : 0.0;
+      odd = odd || (in && sl);
+    }
+    if (F == 0 && odd) {  // a density outside sqrt_md's range: the general form
+#pragma unroll
+      for (int q = 0; q < 2; ++q)
+        if (lane + (h0 + q) * PTL < v.m)
+          te[q] = flip_embed_term<0>(p, sj[h0 + q], v.rj[h0 + q],
+                                     flip_rho_shift<0>(p, s, v.r[h0 + q]));
     }
 #pragma unroll
-  for (int h = 0; h < PH; ++h) {
-    double tp = 0.0, te = 0.0;
-    if (lane + h * PTL < v.m) {
-      tp = flip_pair_term<F>(p, s, sj[h], v.r[h]);
-      te = flip_embed_term<F>(p, sj[h], rj[h], flip_rho_shift<F>(p, s, v.r[h]));
-    }
-    grp[lane + h * PTL] = make_double2(tp, te);
+    for (int q = 0; q < 2; ++q) grp[lane + (h0 + q) * PTL] = make_double2(tp[q], te[q]);
   }
   __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
   double pair, emb;
   sum_flip_terms(grp, v.m, pair, emb);
-  const double own = flip_own_term<F>(p, s, ri);
+  const double own = F == 0 && slow ? flip_own_term<0>(p, s, ri) : own_new - own_old;
   return own + pair + emb;
 }
 
 // the flip of site i (species s0) by its group: densities of the row's
-// neighbours, species, velocity
+// neighbours (rj as the trial read them: nothing was committed since),
+// species, velocity
 template <int F, bool RES>
 __device__ __forceinline__ void p_commit(const PState<RES> &st, int64_t i, int lane, int s0,
                                          const PRow &v) {
   const PersistArgs &a = st.a;
 #pragma unroll
   for (int h = 0; h < PH; ++h)
-    if (lane + h * PTL < v.m) {
-      const double delta = flip_rho_shift<F>(a.p, s0, v.r[h]);
-      st.set_rho(v.j[h], st.rho(v.j[h]) + delta);
-    }
+    if (lane + h * PTL < v.m)
+      st.set_rho(v.j[h], v.rj[h] + flip_rho_shift<F>(a.p, s0, v.r[h]));
   if (lane == 0) {
     st.set_sp(i, 1 - s0);
     if (a.vx) {
-      const double f = sqrt(a.p.mass[s0] / a.p.mass[1 - s0]);
+      const double f = sqrt(by_species(a.p.mass, s0) / by_species(a.p.mass, 1 - s0));
       a.vx[i] = a.vx[i] * f;
       a.vy[i] = a.vy[i] * f;
       a.vz[i] = a.vz[i] * f;
@@ -259,8 +315,45 @@ __device__ __forceinline__ void p_commit(const PState<RES> &st, int64_t i, int l
   }
 }
 
+// Draws ahead of the trials.  Stage counters: the colour and ln u_g of stages
+// [s_lo, s_hi) into the ring of PWIN slots; trials: the site drawn from each
+// own cell and ln u of its local test for stages [s_lo, s_hi) (counters drawn
+// before) into the ring of `win` rows of `chunk` entries.  By threads t of nt.
+__device__ __forceinline__ void p_draw_stages(const RepD &r, const PLds &l, uint64_t w,
+                                              uint32_t s_lo, uint32_t s_hi, int t, int nt) {
+  for (uint32_t s = s_lo + t; s < s_hi; s += nt) {
+    const U4 g = philox(r.seed, r.key1, w, (uint64_t)s, 0, 0);
+    l.col[s & (PWIN - 1)] = (uint8_t)stage_colour(g.v[0], r.ncol);
+    l.lnug[s & (PWIN - 1)] = log(unit_open(g.v[1]));
+  }
+}
+
+__device__ __forceinline__ void p_draw_trials(const RepD &r, const PLds &l, const int32_t *cstart,
+                                              const int32_t *catoms, uint64_t w, uint32_t s_lo,
+                                              uint32_t s_hi, int64_t t_lo, int own, int chunk,
+                                              int win, int t, int nt) {
+  const unsigned n = (s_hi - s_lo) * (unsigned)own;
+  for (unsigned e = (unsigned)t; e < n; e += (unsigned)nt) {
+    const unsigned k = e / (unsigned)own, c = e - k * (unsigned)own;
+    const uint32_t s = s_lo + k;
+    const int64_t cell = p_colour_cell(r, l.col[s & (PWIN - 1)], (uint32_t)(t_lo + c));
+    const int32_t c0 = cstart[cell];
+    const uint32_t m = (uint32_t)(cstart[cell + 1] - c0);
+    int32_t site = -1;
+    double lnu = 0.0;
+    if (m > 0) {
+      const U4 rr = philox(r.seed, r.key1, w, (uint64_t)s, (uint64_t)cell, 1);
+      site = catoms[c0 + draw_index(rr.v[0], m)];
+      lnu = log(unit_open(rr.v[1]));
+    }
+    const int slot = (int)(s % (uint32_t)win) * chunk + (int)c;
+    l.site[slot] = site;
+    l.lnu[slot] = lnu;
+  }
+}
+
 // the sweeps of one replica by one of its workgroups
-template <int F, bool RES>
+template <int F, bool RES, bool LOG>
 __device__ __forceinline__ void sweep_replica(const PersistArgs &a, const RepD &r, RepState *st,
                                               const PLds &l, int *flag) {
   const int tid = threadIdx.x, lane = tid % PTL, grp = tid / PTL, wl = tid & 63;
@@ -276,13 +369,17 @@ __device__ __forceinline__ void sweep_replica(const PersistArgs &a, const RepD &
   const int32_t *cstart = a.cstart + r.cso;
   const int32_t *catoms = a.catoms + r.aoff;
   const PState<RES> state{a, l, r.aoff};
-  // one pass per batch when the groups cover the cells: as many stages as
-  // they can try at once (one with logs on: dropped trials would be logged)
-  const int fit = PGROUPS / chunk;
-  const int dmax = RES || r.G == 1 ? PDMAX : PDG;
-  const int D = a.tlog || a.slog || fit < 1 ? 1 : (fit < dmax ? fit : dmax);
-  const bool one_pass = chunk <= PGROUPS;
-  const int win = a.ndraw / chunk < PWIN ? a.ndraw / chunk : PWIN;  // stages drawn ahead
+  const int win = a.ndraw / chunk < PWIN ? a.ndraw / chunk : PWIN;  // stages of drawn trials
+  const int wave = tid >> 6;
+  // Stages per batch: as many as the trial groups make in one pass, doubled
+  // (more passes) while whole batches are rejected, so that a batch's fixed
+  // cost is shared by more stages where few are accepted; one with logs on
+  // (dropped trials would be logged).  Twice a batch has to be drawn ahead.
+  const int fit = LOG || chunk > PGROUPS ? 1 : PGROUPS / chunk;
+  const int cap = LOG ? 1 : max(1, min(RES || r.G == 1 ? PDMAX : PDG, win / 4));
+  const int span0 = min(fit, cap);
+  int span = span0;
+  const uint32_t S = (uint32_t)r.S;  // below 2^31 for n < 2^31
   long long nb = st->n_b;
   // per lane k of every wave: counts of the stages k of the batches; replica
   // totals in the first workgroup
@@ -300,49 +397,48 @@ __device__ __forceinline__ void sweep_replica(const PersistArgs &a, const RepD &
 
   for (int64_t sw = 0; sw < r.n_sweeps; ++sw) {
     const uint64_t w = (uint64_t)(r.w0 + sw);
-    int64_t d0 = 0, d1 = 0;  // stages [d0, d1) are drawn
-    int64_t pre_s = -1;      // first stage of the batch whose rows are in `row`
+    uint32_t hs = 0, hd = 0;  // stages whose counters / trials are drawn
+    bool have = false;        // the batch's rows are in `row`
     PRow row;
     row.m = 0;
-    for (int64_t s0 = 0; s0 < r.S; ++batch) {
-      const int len = (int)(r.S - s0 < D ? r.S - s0 : D);
+    for (uint32_t s0 = 0; s0 < S; ++batch) {
+      const int len = S - s0 < (uint32_t)span ? (int)(S - s0) : span;
+      const bool one_pass = len * own <= PGROUPS;
       unsigned long long *cw = l.cw + 2 * PDMAX * (batch % 3);
-      if (s0 + len > d1) {  // draw the sites, ln u and ln u_g of the next stages
-        __syncthreads();    // the last batch's readers of ln u_g are done
-        d0 = s0;
-        d1 = s0 + win < r.S ? s0 + win : r.S;
-        const int ns = (int)(d1 - d0);
-        for (int k = tid; k < ns; k += PBLOCK)
-          l.lnug[k] = log(unit_open(philox(r.seed, r.key1, w, (uint64_t)(d0 + k), 0, 0).v[1]));
-        for (int e = tid; e < ns * own; e += PBLOCK) {
-          const int k = e / own, c = e - k * own;
-          const uint64_t s = (uint64_t)(d0 + k);
-          const int colour = stage_colour(philox(r.seed, r.key1, w, s, 0, 0).v[0], r.ncol);
-          const int64_t cell = p_colour_cell(r, colour, (uint32_t)(t_lo + c));
-          const int32_t c0 = cstart[cell];
-          const uint32_t m = (uint32_t)(cstart[cell + 1] - c0);
-          int32_t site = -1;
-          double lnu = 0.0;
-          if (m > 0) {
-            const U4 rr = philox(r.seed, r.key1, w, s, (uint64_t)cell, 1);
-            site = catoms[c0 + draw_index(rr.v[0], m)];
-            lnu = log(unit_open(rr.v[1]));
-          }
-          l.site[e] = site;
-          l.lnu[e] = lnu;
+      if (s0 + len > hd) {  // the trials of this batch (and a few more) are due now
+        block_sync_lds();   // the last batch's readers of the rings are done
+        const uint32_t ts = min(s0 + 4 * len, S);
+        if (hs < ts) {
+          p_draw_stages(r, l, w, hs, ts, tid, PBLOCK);
+          hs = ts;
         }
-        __syncthreads();
+        block_sync_lds();
+        const uint32_t to = min(min(s0 + 3 * len, s0 + win), S);
+        p_draw_trials(r, l, cstart, catoms, w, hd, to, t_lo, own, chunk, win, tid, PBLOCK);
+        hd = to;
+        block_sync_lds();
       }
+      // what the waves draw while the others work or wait: about a batch of
+      // trials and of stage counters, kept clear of the slots of the last batch
+      const uint32_t td = max(hd, min(hd + 2 * len, min(s0 + win - cap, hs)));
+      const uint32_t ts = max(hs, min(hs + 4 * len, min(s0 + PWIN - 2 * PDMAX, S)));
+      auto draw_ahead = [&](int first) {
+        if (wave == PBLOCK / 64 - 1)
+          p_draw_stages(r, l, w, hs, ts, wl, 64);
+        else if (wave >= first)
+          p_draw_trials(r, l, cstart, catoms, w, hd, td, t_lo, own, chunk, win, tid - 64 * first,
+                        PBLOCK - 64 - 64 * first);
+      };
       // ---- trials: p = k own + c, stage s0 + k and cell t_lo + c
       int my_s = 0;         // one pass: the species of an accepted trial's site
       int32_t my_i = -1;    // and the site
       for (int p = grp; p < len * own; p += PGROUPS) {
         const int k = p / own;
-        const int e = (int)(s0 - d0) * own + p;
+        const int e = (int)((s0 + k) % (uint32_t)win) * chunk + (p - k * own);
         const int32_t i = l.site[e];
         int32_t rec = -1;
         if (i >= 0) {
-          if (pre_s != s0) p_row(a, i, lane, row);
+          if (!have || p != grp) p_row(a, i, lane, row);
           int s;
           const double du = p_delta_u<F, RES>(state, i, lane, row, l.terms + grp * KMAX, s);
           const double lnu = l.lnu[e];
@@ -353,7 +449,7 @@ __device__ __forceinline__ void sweep_replica(const PersistArgs &a, const RepD &
           if (lane == 0) {
             if (ok) atomicAdd(&cw[2 * k], dn > 0 ? 1ull : 1ull << PK_BITS);
             atomicAdd(&cw[2 * k + 1], 1ull | (fabs(margin) < TIE ? 1ull << 32 : 0ull));
-            if (a.tlog) {
+            if (LOG && a.tlog) {
               const unsigned long long idx = atomicAdd(&a.log_n[0], 1ull);
               if ((int64_t)idx < a.tcap) {
                 const U4 g = philox(r.seed, r.key1, w, (uint64_t)s0, 0, 0);
@@ -377,23 +473,21 @@ __device__ __forceinline__ void sweep_replica(const PersistArgs &a, const RepD &
         }
         if (!one_pass && lane == 0) l.rec[p] = rec;
       }
-      // the rows of the next batch, if this one is rejected as a whole (its
-      // stages are in the drawn window): their reads overlap the barrier
+      // the row of this group's first trial in the next batch, if this one is
+      // rejected as a whole and the site is drawn: its reads overlap the barrier
       PRow ahead;
       ahead.m = 0;
-      int64_t ahead_s = -1;
-      if (one_pass && s0 + len < r.S) {
-        const int64_t s1 = s0 + len;
-        const int len1 = (int)(r.S - s1 < D ? r.S - s1 : D);
-        if (s1 + len1 <= d1) {
-          ahead_s = s1;
-          if (grp < len1 * own) {
-            const int32_t i = l.site[(int)(s1 - d0) * own + grp];
-            if (i >= 0) p_row(a, i, lane, ahead);
-          }
+      bool have_ahead = false;
+      if (own > 0) {
+        const uint32_t k = (uint32_t)grp / (uint32_t)own, s1 = s0 + len + k;
+        if (s1 < hd && (int)k < min(2 * span, cap)) {
+          have_ahead = true;
+          const int32_t i = l.site[(int)(s1 % (uint32_t)win) * chunk + (grp - (int)k * own)];
+          if (i >= 0) p_row(a, i, lane, ahead);
         }
       }
-      __syncthreads();
+      if (RES || r.G == 1) draw_ahead(PBLOCK / 128);  // by the waves with the fewest trials
+      block_sync_lds();
       // the counts of the batch after next, last read before this barrier
       if (tid >= PBLOCK - 2 * PDMAX)
         l.cw[2 * PDMAX * ((batch + 2) % 3) + tid - (PBLOCK - 2 * PDMAX)] = 0;
@@ -404,24 +498,31 @@ __device__ __forceinline__ void sweep_replica(const PersistArgs &a, const RepD &
         if (tid < 64) {
           unsigned long long *word = &st->word[batch & 3][0][0];
           if (q == 0) {
-            __hip_atomic_store(&st->word[(batch + 2) & 3][0][0] + wl, 0ull, __ATOMIC_RELAXED,
-                               __HIP_MEMORY_SCOPE_AGENT);
+            unsigned long long *next = &st->word[(batch + 2) & 3][0][0];
+            __hip_atomic_store(next + wl, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            __hip_atomic_store(next + 64 + wl, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             wait_stores();
           }
           if (wl < len)
             __hip_atomic_fetch_add(&word[(q & 7) * PDG + wl],
                                    cw[2 * wl] + (1ull << (2 * PK_BITS)), __ATOMIC_RELAXED,
                                    __HIP_MEMORY_SCOPE_AGENT);
-          // lane 8 x + k polls stage k's word of row x
+          // lane 16 x + k polls stage k's words of rows x and x + 4
           const int sub = wl / PDG, sk = wl % PDG;
-          const unsigned long long due =
-              sk < len && sub < r.G ? (unsigned long long)((r.G - sub + 7) / 8) : 0ull;
+          auto due_of = [&](int x) {
+            return sk < len && x < r.G ? (unsigned long long)((r.G - x + 7) / 8) : 0ull;
+          };
+          const unsigned long long due0 = due_of(sub), due1 = due_of(sub + 4);
           unsigned int it = 0;
           int late = 0;
           for (;;) {
-            unsigned long long v = 0;
-            if (due) v = __hip_atomic_load(&word[wl], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            if (__all((v >> (2 * PK_BITS)) == due)) {
+            unsigned long long v = 0, u = 0;
+            if (due0)
+              v = __hip_atomic_load(&word[wl], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            if (due1)
+              u = __hip_atomic_load(&word[64 + wl], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            if (__all((v >> (2 * PK_BITS)) == due0 && (u >> (2 * PK_BITS)) == due1)) {
+              v += u;
 #pragma unroll
               for (int o = PDG; o < 64; o <<= 1) v += __shfl_xor(v, o);
               if (wl < len) l.tot[wl] = v;
@@ -438,8 +539,10 @@ __device__ __forceinline__ void sweep_replica(const PersistArgs &a, const RepD &
               __hip_atomic_fetch_or(&st->err, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             *flag = late;
           }
+        } else {
+          draw_ahead(1);
         }
-        __syncthreads();
+        block_sync_lds();
         if (*flag) return;
         tot = l.tot;
         tst = 1;
@@ -459,7 +562,7 @@ __device__ __forceinline__ void sweep_replica(const PersistArgs &a, const RepD &
           const double tt = (double)nb - r.ncbar;
           const double dnd = (double)dn_tot;
           xg = r.beta * r.kN * dnd * (dnd + 2.0 * tt);
-          const double lnug = l.lnug[(int)(s0 - d0) + wl];
+          const double lnug = l.lnug[(s0 + wl) & (PWIN - 1)];
           mg = lnug + xg;
           gacc = lnug < -xg ? 1 : 0;
         }
@@ -483,11 +586,11 @@ __device__ __forceinline__ void sweep_replica(const PersistArgs &a, const RepD &
             }
           }
         }
-        if (q == 0 && s0 + done == r.S && wl == 0) {
+        if (q == 0 && s0 + done == S && wl == 0) {
           sum_n += (double)nb;
           sum_n2 += (double)nb * (double)nb;
         }
-        if (a.slog && q == 0 && wl == 0) {
+        if (LOG && a.slog && q == 0 && wl == 0) {
           const unsigned long long idx = atomicAdd(&a.log_n[1], 1ull);
           if ((int64_t)idx < a.scap) {
             const U4 g = philox(r.seed, r.key1, w, (uint64_t)s0, 0, 0);
@@ -509,49 +612,59 @@ __device__ __forceinline__ void sweep_replica(const PersistArgs &a, const RepD &
           if (grp < len * own && grp / own == ka && my_i >= 0)
             p_commit<F, RES>(state, my_i, lane, my_s, row);
         } else {
-          for (int p = grp; p < own; p += PGROUPS) {
+          for (int p = grp; p < len * own; p += PGROUPS) {
+            if (p / own != ka) continue;
             const int32_t i = l.rec[p];
             if (i >= 0) {
               PRow v;
               p_row(a, i, lane, v);
+#pragma unroll
+              for (int h = 0; h < PH; ++h)
+                v.rj[h] = lane + h * PTL < v.m ? state.rho(v.j[h]) : 0.0;
               p_commit<F, RES>(state, i, lane, state.sp(i), v);
             }
           }
         }
         if (!RES && r.G > 1) {
           wait_stores();
-          __syncthreads();
+          block_sync_lds();
           ++ncom;
-          if (tid == 0) {
-            const unsigned long long target = ncom * (unsigned long long)r.G;
-            __hip_atomic_fetch_add(&st->bar, 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+          if (tid < 64) {
+            // row q mod 8 counts its workgroups; lane x < 8 polls row x
+            if (wl == 0)
+              __hip_atomic_fetch_add(&st->bar[q & 7].n, 1ull, __ATOMIC_RELAXED,
+                                     __HIP_MEMORY_SCOPE_AGENT);
+            const unsigned long long due =
+                wl < 8 && wl < r.G ? ncom * (unsigned long long)((r.G - wl + 7) / 8) : 0ull;
             unsigned int it = 0;
             int late = 0;
-            while (__hip_atomic_load(&st->bar, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) <
-                   target) {
+            while (!__all(due == 0 || __hip_atomic_load(&st->bar[wl & 7].n, __ATOMIC_RELAXED,
+                                                        __HIP_MEMORY_SCOPE_AGENT) >= due)) {
               __builtin_amdgcn_s_sleep(1);
               if (++it > a.spin_limit) {
-                __hip_atomic_fetch_or(&st->err, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
                 late = 1;
                 break;
               }
             }
-            *flag = late;
+            if (wl == 0) {
+              if (late)
+                __hip_atomic_fetch_or(&st->err, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+              *flag = late;
+            }
           }
-          __syncthreads();
+          block_sync_lds();
           if (*flag) return;
         } else {
-          if (!RES) wait_stores();
-          __syncthreads();  // the next batch's trials see the commit
+          if (!RES || a.vx) wait_stores();
+          block_sync_lds();  // the next batch's trials see the commit
         }
       }
       s0 += done;
-      if (ka < 0) {
-        row = ahead;
-        pre_s = ahead_s;
-      } else {
-        pre_s = -1;
-      }
+      hd = td;
+      hs = ts;
+      span = ka < 0 ? min(2 * span, cap) : span0;
+      if (ka < 0) row = ahead;
+      have = ka < 0 && have_ahead;
     }
   }
   if (RES)
@@ -580,18 +693,38 @@ __device__ __forceinline__ void sweep_replica(const PersistArgs &a, const RepD &
 
 // TAB: the potential's form (analytic or tabulated) fixed at compile time,
 // so each variant keeps only its own arithmetic and registers.
-template <bool TAB>
+// LOG: trial or stage logs are written (one stage per batch).
+// The replica's constants of the arithmetic go to vector registers: with
+// everything uniform in scalar ones the loop spilled them a thousand times
+// into vector lanes.
+__device__ __forceinline__ void in_vgpr(double &x) { asm volatile("" : "+v"(x)); }
+
+template <bool TAB, bool LOG>
 __global__ void __launch_bounds__(PBLOCK) k_sweep_persistent(PersistArgs a) {
   constexpr int F = TAB ? 1 : 0;
   extern __shared__ __align__(16) unsigned char lds[];
   __shared__ int flag;
   const int rix = a.wg_rep[blockIdx.x];
-  const RepD r = a.reps[rix];
+  RepD r = a.reps[rix];
+  in_vgpr(r.beta);
+  in_vgpr(r.dmu0);
+  in_vgpr(r.kN);
+  in_vgpr(r.ncbar);
+  in_vgpr(a.p.rc);
+  if (!TAB) {
+    in_vgpr(a.p.c0);
+    in_vgpr(a.p.c1);
+    for (int k = 0; k < 3; ++k) in_vgpr(a.p.eps[k]);
+    for (int k = 0; k < 2; ++k) {
+      in_vgpr(a.p.t[k]);
+      in_vgpr(a.p.A[k]);
+    }
+  }
   const PLds l = persist_lds(lds, a.ndraw, r.res ? r.n : 0);
   if (r.res)
-    sweep_replica<F, true>(a, r, a.rs + rix, l, &flag);
+    sweep_replica<F, true, LOG>(a, r, a.rs + rix, l, &flag);
   else
-    sweep_replica<F, false>(a, r, a.rs + rix, l, &flag);
+    sweep_replica<F, false, LOG>(a, r, a.rs + rix, l, &flag);
 }
 
 // zero the barrier counters, the timeout flag and the per-call counters;
@@ -605,7 +738,7 @@ __global__ void k_persist_reset(RepState *rs, int R) {
   s.trials = s.local_acc = s.stages = s.stage_acc = s.flips = s.near_ties = 0;
   s.sum_n = 0.0;
   s.sum_n2 = 0.0;
-  s.bar = 0;
+  for (int q = 0; q < 8; ++q) s.bar[q].n = 0;
   s.err = 0;
 }
 
@@ -620,26 +753,35 @@ int persist_groups() { return PGROUPS; }
 // dynamic LDS of a grid whose largest share of cells is `chunk` and whose
 // largest resident replica has nres atoms, and its drawn trials
 size_t persist_lds_need(int64_t chunk, int64_t nres, int *ndraw) {
-  const int64_t nd = std::max<int64_t>(PDRAW, chunk);
+  const int64_t nd = std::max<int64_t>(nres > 0 ? PDRAW : 2 * PDRAW, chunk);
   if (ndraw) *ndraw = (int)nd;
   return persist_lds_bytes(nd, nres);
 }
 size_t repd_size() { return sizeof(RepD); }
 size_t repstate_size() { return sizeof(RepState); }
 
-static const void *persist_kernel(bool tab) {
-  return tab ? (const void *)k_sweep_persistent<true> : (const void *)k_sweep_persistent<false>;
+static const void *persist_kernel(bool tab, bool log) {
+  if (tab)
+    return log ? (const void *)k_sweep_persistent<true, true>
+               : (const void *)k_sweep_persistent<true, false>;
+  return log ? (const void *)k_sweep_persistent<false, true>
+             : (const void *)k_sweep_persistent<false, false>;
 }
 
-// lds_max: the bound asked for once and for all (more than 64 KB has to be)
+// co-resident workgroups per CU of the potential form's kernels (with and
+// without logs); lds_max: the LDS bound asked for once and for all (more
+// than 64 KB has to be)
 hipError_t persist_max_blocks(int *per_cu, bool tab, size_t lds, size_t lds_max) {
-  hipError_t e = hipFuncSetAttribute(persist_kernel(tab), hipFuncAttributeMaxDynamicSharedMemorySize,
-                                     (int)lds_max);
-  if (e != hipSuccess) return e;
-  return tab ? hipOccupancyMaxActiveBlocksPerMultiprocessor(per_cu, k_sweep_persistent<true>,
-                                                             PBLOCK, lds)
-             : hipOccupancyMaxActiveBlocksPerMultiprocessor(per_cu, k_sweep_persistent<false>,
-                                                             PBLOCK, lds);
+  *per_cu = 0;
+  for (int log = 0; log < 2; ++log) {
+    const void *f = persist_kernel(tab, log != 0);
+    hipError_t e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_max);
+    int n = 0;
+    if (e == hipSuccess) e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, f, PBLOCK, lds);
+    if (e != hipSuccess) return e;
+    *per_cu = log == 0 ? n : std::min(*per_cu, n);
+  }
+  return hipSuccess;
 }
 
 static PersistArgs make_args(vcsgc_ctx *c) {
@@ -736,7 +878,7 @@ static hipError_t build_graph(vcsgc_ctx *c) {
   *ga = make_args(c);
   void *sargs[] = {ga};
   hipKernelNodeParams sp = {};
-  sp.func = const_cast<void *>(persist_kernel(c->pot.tab != 0));
+  sp.func = const_cast<void *>(persist_kernel(c->pot.tab != 0, c->tlog || c->slog));
   sp.gridDim = dim3((unsigned)c->grid_total);
   sp.blockDim = dim3(PBLOCK);
   sp.sharedMemBytes = (unsigned)c->persist_lds;
@@ -755,7 +897,30 @@ static hipError_t build_graph(vcsgc_ctx *c) {
   return hipSuccess;
 }
 
+// Two grids whose workgroups wait for each other must not share the chip
+// half resident each (the bounded waits would end both calls in an error), so
+// such launches of one process follow each other on the device, whatever
+// streams and threads they come from.
+constexpr int PGATE_DEVICES = 64;
+static std::mutex g_gate_mu;
+static hipEvent_t g_gate[PGATE_DEVICES] = {};
+
+static hipError_t launch_ungated(vcsgc_ctx *c, bool use_graph);
+
 hipError_t launch_persistent(vcsgc_ctx *c, bool use_graph) {
+  bool waits = false;
+  for (const RepHost &r : c->reps) waits = waits || r.G > 1;
+  if (!waits || c->device < 0 || c->device >= PGATE_DEVICES) return launch_ungated(c, use_graph);
+  std::lock_guard<std::mutex> lock(g_gate_mu);
+  hipEvent_t &ev = g_gate[c->device];
+  hipError_t e = ev ? hipStreamWaitEvent(c->stream, ev, 0)
+                    : hipEventCreateWithFlags(&ev, hipEventDisableTiming);
+  if (e == hipSuccess) e = launch_ungated(c, use_graph);
+  if (e == hipSuccess) e = hipEventRecord(ev, c->stream);
+  return e;
+}
+
+static hipError_t launch_ungated(vcsgc_ctx *c, bool use_graph) {
   const int R = (int)c->reps.size();
   if (use_graph) {
     if (!c->graph_exec || c->graph_args_tlog != c->tlog || c->graph_args_slog != c->slog) {
@@ -769,7 +934,7 @@ hipError_t launch_persistent(vcsgc_ctx *c, bool use_graph) {
   if (e != hipSuccess) return e;
   PersistArgs a = make_args(c);
   void *args[] = {&a};
-  return hipLaunchCooperativeKernel(persist_kernel(c->pot.tab != 0), dim3((unsigned)c->grid_total),
+  return hipLaunchCooperativeKernel(persist_kernel(c->pot.tab != 0, c->tlog || c->slog), dim3((unsigned)c->grid_total),
                                     dim3(PBLOCK), args, (unsigned)c->persist_lds, c->stream);
 }
 

@@ -567,7 +567,7 @@ __global__ void __launch_bounds__(BLOCK) k_trial_chain(SweepArgs a, uint64_t w_a
         if (lane == 0) {
           a.sp[i] = (uint8_t)s1;
           if (a.vx) {
-            const double f = sqrt(a.p.mass[s0] / a.p.mass[s1]);
+            const double f = sqrt(by_species(a.p.mass, s0) / by_species(a.p.mass, s1));
             a.u_v[3 * uq + 0] = a.vx[i];
             a.u_v[3 * uq + 1] = a.vy[i];
             a.u_v[3 * uq + 2] = a.vz[i];
@@ -872,7 +872,7 @@ __global__ void __launch_bounds__(BLOCK) k_commit(SweepArgs a, uint64_t w_arg, i
     if (lane == 0) {
       a.sp[i] = (uint8_t)s1;
       if (a.vx) {
-        const double f = sqrt(a.p.mass[s0] / a.p.mass[s1]);
+        const double f = sqrt(by_species(a.p.mass, s0) / by_species(a.p.mass, s1));
         a.vx[i] = a.vx[i] * f;
         a.vy[i] = a.vy[i] * f;
         a.vz[i] = a.vz[i] * f;
@@ -1095,7 +1095,7 @@ __device__ __forceinline__ void pipe_commit(const SweepArgs &a, int32_t i, int l
   if (lane == 0) {
     a.sp[i] = (uint8_t)s1;
     if (a.vx) {
-      const double f = sqrt(a.p.mass[s0] / a.p.mass[s1]);
+      const double f = sqrt(by_species(a.p.mass, s0) / by_species(a.p.mass, s1));
       a.vx[i] = a.vx[i] * f;
       a.vy[i] = a.vy[i] * f;
       a.vz[i] = a.vz[i] * f;
