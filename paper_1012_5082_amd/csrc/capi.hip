@@ -609,8 +609,8 @@ vcsgc_status create_impl(const vcsgc_system *sys, int R, const int64_t *rep_atom
     A(dalloc(&c->xr, n));
     A(dalloc(&c->yr, n));
     A(dalloc(&c->zr, n));
-    A(dalloc(&c->ps4, n));
-    A(dalloc(&c->pf4, n));
+    A(dalloc(&c->ps4, 2 * n));
+    A(dalloc(&c->pf4, 2 * n));
     A(dalloc(&c->rho_f, n));
     A(dalloc(&c->eatom, n));
     A(dalloc(&c->nvt, 8));
@@ -916,7 +916,7 @@ vcsgc_status eam_energy_forces(vcsgc_ctx *c, double *energy_eV, int want_forces)
   }
   VC_CHECK(c, vc::launch_pack(c), "pack");
   VC_CHECK(c, vc::launch_energy(c), "energy");
-  if (want_forces) VC_CHECK(c, vc::launch_forces(c), "forces");
+  if (want_forces) VC_CHECK(c, vc::launch_forces_only(c), "forces");
   c->rho_f_fresh = true;
   if (energy_eV) {
     VC_CHECK(c, vc::launch_reduce_sum(c, c->eatom, c->n, c->red + (c->n + vc::BLOCK - 1) / vc::BLOCK + 1),
@@ -1100,7 +1100,7 @@ vcsgc_status cg_eval(vcsgc_ctx *c, bool check_list, double *e) {
     }
   }
   VC_CHECK(c, vc::launch_energy(c), "energy");
-  VC_CHECK(c, vc::launch_forces(c), "forces");
+  VC_CHECK(c, vc::launch_forces_only(c), "forces");
   double *out = c->red + (c->n + vc::BLOCK - 1) / vc::BLOCK + 1;
   VC_CHECK(c, vc::launch_reduce_sum(c, c->eatom, c->n, out), "reduce");
   VC_CHECK(c, hipMemcpyAsync(e, out, sizeof(double), hipMemcpyDeviceToHost, c->stream), "copy");

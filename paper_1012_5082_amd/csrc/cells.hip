@@ -970,7 +970,7 @@ __global__ void k_density_mc(int64_t n, const int32_t *__restrict__ nj,
 constexpr int MFM_G = 8;  // measured per sweep: 16 lanes 1% and 4 lanes 12% slower
 
 __global__ void __launch_bounds__(BLOCK)
-    k_mc_from_md(int64_t n, const double4 *__restrict__ ps4, Grid g, const int32_t *__restrict__ mdj,
+    k_mc_from_md(int64_t n, const double2 *__restrict__ ps4, Grid g, const int32_t *__restrict__ mdj,
                  const uint8_t *__restrict__ mdcnt, PotD p, int32_t *nj, double *nr,
                  uint8_t *cnt) {
   const int64_t gid = xcd_block() * BLOCK + threadIdx.x;
@@ -978,7 +978,7 @@ __global__ void __launch_bounds__(BLOCK)
   const int l = (int)(gid % MFM_G);
   if (i >= n) return;  // whole groups leave together
   const int wl = threadIdx.x & 63, gb = wl & ~(MFM_G - 1);
-  const double4 qi = ps4[i];
+  const double4 qi = packed_load(ps4, i);
   const int m = mdcnt[i];
   int base = 0;
   for (int k0 = 0; k0 < m; k0 += MFM_G) {
@@ -988,7 +988,7 @@ __global__ void __launch_bounds__(BLOCK)
     double r = 0.0;
     if (k < m) {
       j = mdj[(int64_t)k * n + i];
-      const double4 qj = ps4[j];
+      const double4 qj = packed_load(ps4, j);
       const double dx = min_image(qj.x - qi.x, g.L0);
       const double dy = min_image(qj.y - qi.y, g.L1);
       const double dz = min_image(qj.z - qi.z, g.L2);

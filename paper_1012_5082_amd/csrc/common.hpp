@@ -355,6 +355,17 @@ __device__ __forceinline__ void sum_flip_terms(const double2 *grp, int m, double
   }
 }
 
+// Packed per-atom quadruples (x, y), (z, w) for the gathers of the MD passes.
+__device__ __forceinline__ double4 packed_load(const double2 *__restrict__ p, int64_t i) {
+  const double2 u = p[2 * i], v = p[2 * i + 1];
+  return make_double4(u.x, u.y, v.x, v.y);
+}
+__device__ __forceinline__ void packed_store(double2 *p, int64_t i, double x, double y, double z,
+                                             double w) {
+  p[2 * i] = make_double2(x, y);
+  p[2 * i + 1] = make_double2(z, w);
+}
+
 __device__ __forceinline__ double min_image(double d, double L) {
   const double h = 0.5 * L;
   if (d > h) return d - L;
@@ -534,8 +545,8 @@ struct vcsgc_ctx {
   uint8_t *md_cnt = nullptr;
   double *xr = nullptr, *yr = nullptr, *zr = nullptr;
 
-  double4 *ps4 = nullptr;  // MD: (x, y, z, species) packed for neighbour gathers
-  double4 *pf4 = nullptr;  // MD: (x, y, z, F') written by the density pass
+  double2 *ps4 = nullptr;  // MD: (x, y, z, species) packed for neighbour gathers [2 n]
+  double2 *pf4 = nullptr;  // MD: (x, y, z, F') written by the density pass [2 n]
   double *rho = nullptr;                        // density cache of the sweep
   double *rho_f = nullptr;  // fresh density (energy, MD)
   double *eatom = nullptr, *red = nullptr;
@@ -649,6 +660,7 @@ void free_stage_graph(vcsgc_ctx *c);
 void free_pipe_graph(vcsgc_ctx *c);
 hipError_t launch_energy(vcsgc_ctx *c);  // fresh rho (MD list) + per-atom energies
 hipError_t launch_forces(vcsgc_ctx *c);  // fresh rho, F', forces (MD list)
+hipError_t launch_forces_only(vcsgc_ctx *c);  // forces after launch_energy
 hipError_t launch_validate(vcsgc_ctx *c, const RepHost &r);
 hipError_t launch_reduce_sum(vcsgc_ctx *c, const double *v, int64_t n, double *out_dev);
 hipError_t launch_sweeps(vcsgc_ctx *c, double dmu0, double kappa, double cbar, double T,

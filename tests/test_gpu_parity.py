@@ -616,6 +616,31 @@ def test_md_parity_build_paths(torch_cuda, oracle_mod, n, skin):
     g.close()
 
 
+@pytest.mark.parametrize("dims,pot", [
+    ((29, 29, 29), "FS-P1"),  # 48,778 atoms: the largest cube with four lanes per atom
+    ((30, 28, 30), "FS-P1"),  # 50,400: one lane
+    ((30, 28, 30), "TAB-X"),  # two lanes
+    ((6, 7, 9), "TAB-X"),     # four lanes, a row is one to two rounds, every wave wraps
+])
+def test_md_lanes_per_atom(torch_cuda, oracle_mod, dims, pot):
+    """Energies, forces and three steps on both sides of the sizes at which the
+    MD passes change their lanes per atom, bit for bit."""
+    O = oracle_mod
+    pot = I.params(pot) if pot == "FS-P1" else I.table(pot)
+    x, y, z, box = I.bcc(*dims)
+    x, y, z = I.thermalize(x, y, z, box, 0.08, 21)
+    sp = I.initial_species(x.size, 0.2, 22)
+    vx, vy, vz = I.mb_velocities(sp, 900.0, 23)
+    d = dict(x=x, y=y, z=z, box=box, species=sp, vx=vx, vy=vy, vz=vz)
+    _eam_parity(O, d, pot)
+    g = gpu_context(d, pot, velocities=True)
+    g.md(2.0, 3)
+    out = O.md(x, y, z, vx, vy, vz, sp, box, pot, 2.0, 3)
+    for nm, want in zip(("x", "y", "z", "vx", "vy", "vz", "fx", "fy", "fz"), out[:9]):
+        assert np.array_equal(getattr(g, nm).cpu().numpy(), want), nm
+    g.close()
+
+
 @pytest.mark.parametrize("path", ["pipeline", "da_perfect", "chain3", "persistent", "batch",
                                   "da_batch"])
 def test_sweep_paths_after_md(torch_cuda, oracle_mod, path):
