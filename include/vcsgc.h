@@ -524,7 +524,9 @@ vcsgc_status vcsgc_sample_count(vcsgc_ctx *ctx, int64_t *n_logged);
  * surrogate (dE = exact dU; equals the plain chain), 3 zero surrogate.  Mode 1
  * needs VCSGC_FLAG_DESCRIPTOR and r_dep >= 4.41 + rc (the descriptor reads
  * densities that depend on species up to that distance).  The network must
- * outlive its use.  Delayed acceptance runs with per-stage launches. */
+ * outlive its use.  The network's sweeps run persistently (one launch per call)
+ * unless they are logged, timed per stage or the grid does not fit; the other
+ * modes with per-stage launches.  All give the same chain. */
 vcsgc_status vcsgc_set_surrogate(vcsgc_ctx *ctx, const vcsgc_mlp *m, int32_t mode);
 /* While enabled, every delayed-acceptance trial appends (w, s, cell, dE_f,
  * dE_r or NaN) to a caller device buffer of cap rows. */

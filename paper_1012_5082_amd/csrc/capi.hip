@@ -748,8 +748,12 @@ vcsgc_status sweep_impl(vcsgc_ctx *c, const double *dmu0, const double *kappa, c
   if (c->local_steps > 1 && (c->da_mode || c->smp_cap > 0))
     return fail(c, VCSGC_E_INVALID_ARG,
                 "delayed acceptance and the sample log need one trial per cell per stage");
-  // Delayed acceptance, the training-sample log, local chains and grown
-  // domains run with kernels per stage or batch of stages, and so do the
+  // The training-sample log, local chains, grown domains and delayed
+  // acceptance other than with the network run with kernels per stage or batch
+  // of stages, and so do the network's where its stages are logged or timed,
+  // where the dU row is not part of the descriptor list (rc > 4.41 A), or
+  // beyond about 6M sites (8.2M sites: 11.9 ms either way; 4.2M 3.1 ms
+  // persistent, 6.3 ms with 16 stages per kernel); and so do the
   // pipeline strategies where their stages are logged or timed, or where a
   // workgroup of the persistent sweep would hold more active cells than
   // trial groups.  Below that (about 4M sites) the persistent sweep is the
@@ -761,9 +765,18 @@ vcsgc_status sweep_impl(vcsgc_ctx *c, const double *dmu0, const double *kappa, c
   // accepted stages 2.6 / 4.5 us, 0.5M at 24% 2.9 / 4.6, 2M at 23% 4.8 / 7.5,
   // 1M at 0% 1.2 / 1.2, 4M at 0% 3.7 / 3.5, 8M at 0% 7.2 / 6.3.
   const bool logged = c->tlog || c->slog || c->dalog;
+  const unsigned stage_timers =
+      1u << VCSGC_KT_STAGE | 1u << VCSGC_KT_TRIAL | 1u << VCSGC_KT_COMMIT;
+  // (the network's dU row is the r < rc part of the descriptor list)
+  bool da = n_sweeps > 0 && c->da_mode == 1 && c->smp_cap == 0 && !c->grown && !logged &&
+            !(c->tmask & stage_timers) && c->pot.rc <= vc::DESC_CUT;
+  if (da) {
+    VC_CHECK(c, vc::persist_da_grid(c), "occupancy query");
+    da = c->da_wg > 0;
+  }
   const bool per_stage =
-      c->da_mode || c->smp_cap > 0 || c->local_steps > 1 || c->grown ||
-      (c->strategy >= 2 && (logged || (c->tmask & (1u << VCSGC_KT_STAGE)) ||
+      (c->da_mode && !da) || c->smp_cap > 0 || c->local_steps > 1 || c->grown ||
+      (!da && c->strategy >= 2 && (n_sweeps == 0 || logged || (c->tmask & (1u << VCSGC_KT_STAGE)) ||
                             c->reps[0].ncpc > (int64_t)c->reps[0].G * vc::persist_groups()));
   if (per_stage && R == 1) {
     // one trial kernel and one commit kernel per stage
@@ -792,17 +805,20 @@ vcsgc_status sweep_impl(vcsgc_ctx *c, const double *dmu0, const double *kappa, c
     }
     return VCSGC_OK;
   }
-  VC_CHECK(c, vc::persist_stage_params(c, dmu0, kappa, cbar, T, n_sweeps, seed), "sweep");
+  VC_CHECK(c, vc::persist_stage_params(c, dmu0, kappa, cbar, T, n_sweeps, seed, da), "sweep");
   if (n_sweeps > 0) {
     int h = vc::tstart(c, VCSGC_KT_PERSIST);
-    VC_CHECK(c, vc::launch_persistent(c, c->strategy != 1), "persistent sweep");
+    if (da)
+      VC_CHECK(c, vc::launch_persistent_da(c), "persistent sweep");
+    else
+      VC_CHECK(c, vc::launch_persistent(c, c->strategy != 1), "persistent sweep");
     vc::tstop(c, h);
   }
   c->w += (uint64_t)n_sweeps;
   // the timeout flags are read after every call, with or without statistics:
   // a workgroup that left a timed-out wait may have committed part of a stage
   int err = 0;
-  VC_CHECK(c, vc::persist_read_stats(c, out, &err), "sweep");
+  VC_CHECK(c, vc::persist_read_stats(c, out, &err, da), "sweep");
   if (err) {
     c->sticky = true;
     return fail(c, VCSGC_E_BARRIER_TIMEOUT, "persistent sweep: a barrier wait exceeded its limit");

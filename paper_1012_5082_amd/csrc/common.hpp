@@ -609,6 +609,8 @@ struct vcsgc_ctx {
   int grid_total = 0;
   size_t persist_lds = 0;   // dynamic LDS of the persistent sweep's workgroups
   int persist_ndraw = 0;    // trials a workgroup draws ahead
+  int da_wg = 0, da_ndraw = 0;  // the same sweep with the network: workgroups (0: not yet
+                                // sized, -1: does not fit), trials drawn ahead
   int trials_per_group = 1;   // tiling: trial groups per active cell (see assign_workgroups)
   int strategy = 0;           // 0: persistent (graph), 1: persistent (direct), 2: per-stage
   unsigned int spin_limit = 1u << 24;
@@ -703,9 +705,11 @@ size_t repstate_size();
 hipError_t persist_max_blocks(int *per_cu, bool tab, size_t lds, size_t lds_max);
 hipError_t persist_stage_params(vcsgc_ctx *c, const double *dmu0, const double *kappa,
                                 const double *cbar, const double *T, int64_t n_sweeps,
-                                uint64_t seed);
+                                uint64_t seed, bool da = false);
 hipError_t launch_persistent(vcsgc_ctx *c, bool use_graph);
-hipError_t persist_read_stats(vcsgc_ctx *c, vcsgc_stats *out, int *err);
+hipError_t persist_da_grid(vcsgc_ctx *c);
+hipError_t launch_persistent_da(vcsgc_ctx *c);
+hipError_t persist_read_stats(vcsgc_ctx *c, vcsgc_stats *out, int *err, bool da = false);
 hipError_t persist_count(vcsgc_ctx *c);
 hipError_t persist_sync_nb_to_stage(vcsgc_ctx *c);
 hipError_t persist_sync_nb_from_stage(vcsgc_ctx *c);

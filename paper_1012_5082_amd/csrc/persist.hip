@@ -49,8 +49,10 @@
 // leaves the kernel, so the launch always drains.
 #include <algorithm>
 #include <mutex>
+#include <type_traits>
 
 #include "common.hpp"
+#include "mlp_device.hpp"
 
 namespace vc {
 
@@ -80,6 +82,11 @@ struct RepD {
 // (21-41), arrivals (42-63); the host keeps cells and workgroups below 2^21.
 constexpr int PK_BITS = 21;
 constexpr unsigned long long PK_MASK = (1ull << PK_BITS) - 1;
+// A workgroup's counts of a stage with delayed acceptance: trials, trials that
+// pass the network, near ties (a workgroup's share of cells is its LDS ring's
+// at most, far below 2^21)
+constexpr int DA_BITS = 21;
+constexpr unsigned long long DA_MASK = (1ull << DA_BITS) - 1;
 
 struct alignas(128) RepState {
   // words of the batches' stages, a ring of four batches: the words of batch
@@ -95,7 +102,7 @@ struct alignas(128) RepState {
     unsigned long long n;
   } bar[8];
   alignas(128) long long n_b;  // n_B at the start of the call
-  unsigned long long trials, local_acc, stages, stage_acc, flips, near_ties;
+  unsigned long long trials, stage1, local_acc, stages, stage_acc, flips, near_ties;
   double sum_n, sum_n2;
   int err;
   long long n_final;
@@ -121,6 +128,15 @@ struct PersistArgs {
   int ndraw;  // trials drawn ahead (LDS entries)
 };
 
+// delayed acceptance with the network: its parameters and the r < 4.41 A list
+// (sorted rows, of which the r < rc entries are the dU row)
+struct PersistArgsDa : PersistArgs {
+  MlpDev md;
+  const int32_t *dj;
+  const double *dr;
+  const uint8_t *dcnt;
+};
+
 // dynamic LDS of a workgroup: the groups' terms, the drawn trials and ln u_g,
 // counts, and the state of a resident replica of nres atoms
 struct PLds {
@@ -132,6 +148,8 @@ struct PLds {
   int32_t *site, *rec;      // [ndraw] each
   uint8_t *col;             // [PWIN] colours of stages
   uint8_t *sp;              // [nres]
+  double *lnu2;             // [ndraw]: ln u of the second stage (delayed acceptance)
+  struct DaLds *da;
 };
 
 static size_t persist_lds_bytes(int64_t ndraw, int64_t nres) {
@@ -177,13 +195,14 @@ struct PRow {
   int m;
 };
 
-__device__ __forceinline__ void p_row(const PersistArgs &a, int64_t i, int lane, PRow &v) {
-  v.m = a.cnt[i];
+__device__ __forceinline__ void p_row(const int32_t *nj, const double *nr, const uint8_t *cnt,
+                                      int64_t i, int lane, PRow &v) {
+  v.m = cnt[i];
 #pragma unroll
   for (int h = 0; h < PH; ++h) {
     const int64_t e = i * KMAX + lane + h * PTL;
-    v.j[h] = a.nj[e];
-    v.r[h] = a.nr[e];
+    v.j[h] = nj[e];
+    v.r[h] = nr[e];
   }
 }
 
@@ -294,15 +313,15 @@ __device__ __forceinline__ double p_delta_u(const PState<RES> &st, int64_t i, in
 }
 
 // the flip of site i (species s0) by its group: densities of the row's
-// neighbours (rj as the trial read them: nothing was committed since),
-// species, velocity
-template <int F, bool RES>
+// neighbours (rj as the trial read them: nothing was committed since; DA: the
+// row reaches beyond rc), species, velocity
+template <int F, bool RES, bool DA>
 __device__ __forceinline__ void p_commit(const PState<RES> &st, int64_t i, int lane, int s0,
                                          const PRow &v) {
   const PersistArgs &a = st.a;
 #pragma unroll
   for (int h = 0; h < PH; ++h)
-    if (lane + h * PTL < v.m)
+    if (lane + h * PTL < v.m && (!DA || v.r[h] < a.p.rc))
       st.set_rho(v.j[h], v.rj[h] + flip_rho_shift<F>(a.p, s0, v.r[h]));
   if (lane == 0) {
     st.set_sp(i, 1 - s0);
@@ -313,6 +332,225 @@ __device__ __forceinline__ void p_commit(const PState<RES> &st, int64_t i, int l
       a.vz[i] = a.vz[i] * f;
     }
   }
+}
+
+// ---- delayed acceptance: the trials of a wave's eight groups ----------------
+// The two-stage test of the per-stage kernels, in the batches of this sweep:
+// a kernel per batch took 14.5 us, and two of them per accepted stage.  128,000
+// sites: 2.3 ms at 4 and 1.4 ms at 16 stages per kernel, now 0.69 ms (9%
+// accepted stages); 5.3 -> 3.2 ms (62%); 2,000 sites 6.7 -> 0.69, 1.02M sites
+// 2.0 -> 0.97, 4.2M 6.3 -> 3.1 ms.
+// The 16 descriptor rows (current and flipped environment of eight sites) are
+// the rows of one MFMA tile, so a wave evaluates its own trials from the
+// weights in LDS, without meeting the workgroup's other waves.
+constexpr int DKP = MLP_KP + 8, DHP = MLP_H + 8;  // padded rows: no 16-way bank conflicts
+constexpr int PWAVES = PBLOCK / 64;
+struct DaWave {
+  // an entry's densities before and after the flip, its pair and embedding
+  // terms (zeros outside rc), and per entry 1 + shell (0: none)
+  double q[64 / PTL][KMAX][4];
+  uint8_t code[64 / PTL][KMAX];
+};
+struct DaHidden {  // in the place of the terms, once they are summed
+  __bf16 h1[16 * DHP], h2[16 * DHP];
+};
+static_assert(sizeof(DaHidden) <= sizeof(DaWave), "hidden layers in the terms' place");
+struct DaLds {
+  DaWave wave[PWAVES];
+  __bf16 zs[PWAVES][16 * DKP];
+  __bf16 w1[MLP_H * DKP], w2[MLP_H * DHP];
+  float b1[MLP_H], b2[MLP_H], w3[MLP_H];
+  float mu[MLP_IN], sd[MLP_IN];
+};
+
+// dynamic LDS with delayed acceptance
+static size_t persist_lds_bytes_da(int64_t ndraw) {
+  return sizeof(DaLds) + sizeof(double) * (2 * ndraw + PWIN) +
+         sizeof(unsigned long long) * 7 * PDMAX + 2 * sizeof(int32_t) * ndraw + PWIN;
+}
+__device__ __forceinline__ PLds persist_lds_da(unsigned char *base, int ndraw) {
+  PLds l;
+  l.da = (DaLds *)base;
+  l.lnu = (double *)(base + sizeof(DaLds));
+  l.lnu2 = l.lnu + ndraw;
+  l.lnug = l.lnu2 + ndraw;
+  l.cw = (unsigned long long *)(l.lnug + PWIN);
+  l.tot = l.cw + 6 * PDMAX;
+  l.site = (int32_t *)(l.tot + PDMAX);
+  l.rec = l.site + ndraw;
+  l.col = (uint8_t *)(l.rec + ndraw);
+  l.terms = nullptr;
+  l.rho = nullptr;
+  l.sp = nullptr;
+  return l;
+}
+
+__device__ __forceinline__ void da_weights(const MlpDev &m, DaLds &d, int tid) {
+  for (int e = tid; e < MLP_H * MLP_KP; e += PBLOCK)
+    d.w1[(e / MLP_KP) * DKP + e % MLP_KP] = m.w1[e];
+  for (int e = tid; e < MLP_H * MLP_H; e += PBLOCK) d.w2[(e / MLP_H) * DHP + e % MLP_H] = m.w2[e];
+  for (int e = tid; e < MLP_H; e += PBLOCK) {
+    d.b1[e] = m.b1[e];
+    d.b2[e] = m.b2[e];
+    d.w3[e] = m.w3[e];
+  }
+  for (int e = tid; e < MLP_IN; e += PBLOCK) {
+    d.mu[e] = m.mu[e];
+    d.sd[e] = m.sd[e];
+  }
+}
+
+__device__ __forceinline__ void wave_lds() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+__device__ __forceinline__ bf16x8 da_frag(const __bf16 *p) { return *(const bf16x8 *)p; }
+
+// Network values of the wave's 16 rows of z: lane L < 16 returns row L's
+// normalized output (the products and sums of mlp_block16f).
+__device__ __forceinline__ float da_network(const MlpDev &m, const DaLds &d, const __bf16 *z,
+                                            DaHidden &h) {
+  const int wl = threadIdx.x & 63, r = wl & 15, kb = (wl >> 4) * 8;
+  {
+    const bf16x8 a = da_frag(z + r * DKP + kb);
+#pragma unroll
+    for (int t = 0; t < MLP_H / 16; ++t) {
+      const int n = 16 * t + r;
+      floatx4 c = {0.f, 0.f, 0.f, 0.f};
+      c = mfma16(a, da_frag(d.w1 + n * DKP + kb), c);
+      const float b = d.b1[n];
+#pragma unroll
+      for (int q = 0; q < 4; ++q) h.h1[((wl >> 4) * 4 + q) * DHP + n] = to_bf16(silu(c[q] + b));
+    }
+  }
+  wave_lds();
+  {
+    const bf16x8 a0 = da_frag(h.h1 + r * DHP + kb), a1 = da_frag(h.h1 + r * DHP + 32 + kb);
+#pragma unroll
+    for (int t = 0; t < MLP_H / 16; ++t) {
+      const int n = 16 * t + r;
+      floatx4 c = {0.f, 0.f, 0.f, 0.f};
+      c = mfma16(a0, da_frag(d.w2 + n * DHP + kb), c);
+      c = mfma16(a1, da_frag(d.w2 + n * DHP + 32 + kb), c);
+      const float b = d.b2[n];
+#pragma unroll
+      for (int q = 0; q < 4; ++q) h.h2[((wl >> 4) * 4 + q) * DHP + n] = to_bf16(silu(c[q] + b));
+    }
+  }
+  wave_lds();
+  float y = 0.0f;
+  if (wl < 16) {
+    y = m.b3[0];
+    for (int k = 0; k < MLP_H; k += 8) {
+      const bf16x8 v = da_frag(h.h2 + wl * DHP + k);
+#pragma unroll
+      for (int u = 0; u < 8; ++u) y += d.w3[k + u] * (float)v[u];
+    }
+  }
+  wave_lds();
+  return y;
+}
+
+// Exact dU of site i and the network's forward and reverse values, by all
+// lanes of a wave (groups without a site: has = false, i any atom).  Lane c of
+// a group sums one column of its entries in order (c < 3: densities of shell
+// c, c < 6: the densities after the flip, 6: pair terms, 7: embedding terms);
+// an entry of another shell adds +0.0 (the sums are never -0.0).
+template <int F>
+__device__ __forceinline__ double da_trial(const PState<false> &st, const PersistArgsDa &a,
+                                           DaLds &d, bool has, int64_t i, int lane, PRow &v,
+                                           int &s, double &ef, double &er) {
+  const PotD &p = st.a.p;
+  const int wl = threadIdx.x & 63, g = wl / PTL;
+  DaWave &w = d.wave[threadIdx.x >> 6];
+  __bf16 *z = d.zs[threadIdx.x >> 6];
+  s = st.sp(i);
+  const double ri = st.rho(i);
+  const int m = has ? v.m : 0;
+  int sj[PH];
+#pragma unroll
+  for (int h = 0; h < PH; ++h) {
+    const int64_t j = lane + h * PTL < m ? (int64_t)v.j[h] : i;
+    sj[h] = st.sp(j);
+    v.rj[h] = st.rho(j);
+  }
+  // numbers of neighbours per shell (8 bits each) and of B among them
+  unsigned int cnt = 0, cb = 0;
+#pragma unroll
+  for (int h = 0; h < PH; ++h) {
+    const int k = lane + h * PTL;
+    double rj = 0.0, rjf = 0.0, tp = 0.0, te = 0.0;
+    int code = 0;
+    if (k < m) {
+      const double r = v.r[h];
+      code = r < 2.68 ? 1 : (r < 3.46 ? 2 : (r < DESC_CUT ? 3 : 0));
+      rj = v.rj[h];
+      rjf = rj;
+      if (r < p.rc) {
+        const double delta = flip_rho_shift<F>(p, s, r);
+        rjf = rj + delta;
+        tp = flip_pair_term<F>(p, s, sj[h], r);
+        te = flip_embed_term<F>(p, sj[h], rj, delta);
+      }
+      const unsigned int one = code ? 1u << (8 * (code - 1)) : 0u;
+      cnt += one;
+      cb += sj[h] ? one : 0u;
+    }
+    w.code[g][k] = (uint8_t)code;
+    *(double4 *)w.q[g][k] = make_double4(rj, rjf, tp, te);
+  }
+  const double own = flip_own_term<F>(p, s, ri);
+#pragma unroll
+  for (int o = 1; o < PTL; o <<= 1) {
+    cnt += __shfl_xor(cnt, o);
+    cb += __shfl_xor(cb, o);
+  }
+  wave_lds();
+  const int col = lane < 6 ? lane / 3 : lane - 4, shell = lane % 3;
+  const int want = lane < 6 ? shell + 1 : -1;
+  double sum = 0.0;
+#pragma unroll
+  for (int k0 = 0; k0 < KMAX; k0 += 8) {
+    if (!__any(k0 < m)) break;
+    const unsigned long long cd = *(const unsigned long long *)&w.code[g][k0];
+    double t[8];
+#pragma unroll
+    for (int u = 0; u < 8; ++u) t[u] = w.q[g][k0 + u][col];
+#pragma unroll
+    for (int u = 0; u < 8; ++u) {
+      const int ck = (int)((cd >> (8 * u)) & 255u);
+      sum += want < 0 || ck == want ? t[u] : 0.0;
+    }
+  }
+  const double pair = __shfl(sum, 6, PTL), emb = __shfl(sum, 7, PTL);
+  // descriptors: species, B per shell, neighbours per shell, mean densities
+  {
+    const int cs = (int)((cnt >> (8 * shell)) & 255u), bs = (int)((cb >> (8 * shell)) & 255u);
+    const double mean = cs > 0 ? sum / (double)cs : 0.0;
+    auto input = [&](int k, double x) {
+      return to_bf16((float)((x - (double)d.mu[k]) / (double)d.sd[k]));
+    };
+    __bf16 *zf = z + g * DKP, *zr = z + (8 + g) * DKP;
+    // lanes 0-5: a count for both rows, and the mean of one of them
+    const int kc = lane < 6 ? 1 + lane : 0;
+    const double xc = lane < 3 ? (double)bs : lane < 6 ? (double)cs
+                                                       : (double)(lane == 6 ? s : 1 - s);
+    const __bf16 vc = input(kc, xc);
+    if (lane != 7) zf[kc] = vc;
+    if (lane != 6) zr[kc] = vc;
+    if (lane < 6) (lane < 3 ? zf : zr)[7 + shell] = input(7 + shell, mean);
+    for (int k = MLP_IN / 2 + lane; k < MLP_KP / 2; k += PTL) {
+      ((unsigned int *)zf)[k] = 0u;
+      ((unsigned int *)zr)[k] = 0u;
+    }
+  }
+  wave_lds();
+  const float y = da_network(a.md, d, z, *(DaHidden *)&w);
+  ef = (double)(__shfl(y, g) * a.md.out_sd + a.md.out_mu);
+  er = (double)(__shfl(y, 8 + g) * a.md.out_sd + a.md.out_mu);
+  return own + pair + emb;
 }
 
 // Draws ahead of the trials.  Stage counters: the colour and ln u_g of stages
@@ -328,6 +566,7 @@ __device__ __forceinline__ void p_draw_stages(const RepD &r, const PLds &l, uint
   }
 }
 
+template <bool DA>
 __device__ __forceinline__ void p_draw_trials(const RepD &r, const PLds &l, const int32_t *cstart,
                                               const int32_t *catoms, uint64_t w, uint32_t s_lo,
                                               uint32_t s_hi, int64_t t_lo, int own, int chunk,
@@ -340,22 +579,32 @@ __device__ __forceinline__ void p_draw_trials(const RepD &r, const PLds &l, cons
     const int32_t c0 = cstart[cell];
     const uint32_t m = (uint32_t)(cstart[cell + 1] - c0);
     int32_t site = -1;
-    double lnu = 0.0;
+    double lnu = 0.0, lnu2 = 0.0;
     if (m > 0) {
       const U4 rr = philox(r.seed, r.key1, w, (uint64_t)s, (uint64_t)cell, 1);
       site = catoms[c0 + draw_index(rr.v[0], m)];
       lnu = log(unit_open(rr.v[1]));
+      if (DA) lnu2 = log(unit_open(rr.v[2]));
     }
     const int slot = (int)(s % (uint32_t)win) * chunk + (int)c;
     l.site[slot] = site;
     l.lnu[slot] = lnu;
+    if (DA) l.lnu2[slot] = lnu2;
   }
 }
 
 // the sweeps of one replica by one of its workgroups
-template <int F, bool RES, bool LOG>
-__device__ __forceinline__ void sweep_replica(const PersistArgs &a, const RepD &r, RepState *st,
-                                              const PLds &l, int *flag) {
+template <int F, bool RES, bool LOG, bool DA>
+__device__ __forceinline__ void sweep_replica(
+    const typename std::conditional<DA, PersistArgsDa, PersistArgs>::type &a, const RepD &r,
+    RepState *st, const PLds &l, int *flag) {
+  static_assert(!DA || (!RES && !LOG), "delayed acceptance");
+  auto row_of = [&](int64_t i, PRow &v) {
+    if constexpr (DA)
+      p_row(a.dj, a.dr, a.dcnt, i, threadIdx.x % PTL, v);
+    else
+      p_row(a.nj, a.nr, a.cnt, i, threadIdx.x % PTL, v);
+  };
   const int tid = threadIdx.x, lane = tid % PTL, grp = tid / PTL, wl = tid & 63;
   const int q = (int)blockIdx.x - r.g0;  // rank inside the replica
   // contiguous share of the active cells; consecutive shares on one XCD
@@ -384,6 +633,7 @@ __device__ __forceinline__ void sweep_replica(const PersistArgs &a, const RepD &
   // per lane k of every wave: counts of the stages k of the batches; replica
   // totals in the first workgroup
   unsigned long long n_trial = 0, n_tie = 0, n_acc = 0, n_stage = 0, n_sacc = 0, n_flip = 0;
+  unsigned long long n_pass = 0;  // trials that pass the network's stage
   double sum_n = 0.0, sum_n2 = 0.0;
   unsigned long long ncom = 0;
   unsigned int batch = 0;
@@ -393,6 +643,7 @@ __device__ __forceinline__ void sweep_replica(const PersistArgs &a, const RepD &
       l.sp[i] = a.sp[r.aoff + i];
     }
   for (int e = tid; e < 6 * PDMAX; e += PBLOCK) l.cw[e] = 0;
+  if constexpr (DA) da_weights(a.md, *l.da, tid);
   __syncthreads();
 
   for (int64_t sw = 0; sw < r.n_sweeps; ++sw) {
@@ -414,7 +665,7 @@ __device__ __forceinline__ void sweep_replica(const PersistArgs &a, const RepD &
         }
         block_sync_lds();
         const uint32_t to = min(min(s0 + 3 * len, s0 + win), S);
-        p_draw_trials(r, l, cstart, catoms, w, hd, to, t_lo, own, chunk, win, tid, PBLOCK);
+        p_draw_trials<DA>(r, l, cstart, catoms, w, hd, to, t_lo, own, chunk, win, tid, PBLOCK);
         hd = to;
         block_sync_lds();
       }
@@ -426,19 +677,63 @@ __device__ __forceinline__ void sweep_replica(const PersistArgs &a, const RepD &
         if (wave == PBLOCK / 64 - 1)
           p_draw_stages(r, l, w, hs, ts, wl, 64);
         else if (wave >= first)
-          p_draw_trials(r, l, cstart, catoms, w, hd, td, t_lo, own, chunk, win, tid - 64 * first,
+          p_draw_trials<DA>(r, l, cstart, catoms, w, hd, td, t_lo, own, chunk, win, tid - 64 * first,
                         PBLOCK - 64 - 64 * first);
       };
       // ---- trials: p = k own + c, stage s0 + k and cell t_lo + c
       int my_s = 0;         // one pass: the species of an accepted trial's site
       int32_t my_i = -1;    // and the site
+      if constexpr (DA) {
+        // whole waves: the lanes of one network evaluation
+        for (int pw = grp & ~(64 / PTL - 1); pw < len * own; pw += PGROUPS) {
+          const int p = pw + grp % (64 / PTL), k = p < len * own ? p / own : 0;
+          const int e = (int)((s0 + k) % (uint32_t)win) * chunk + (p - k * own);
+          const int32_t i = p < len * own ? l.site[e] : -1;
+          int32_t rec = -1;
+          const bool has = i >= 0;
+          if (__any(has)) {
+            if (has && (!have || p != grp)) row_of(i, row);
+            int s;
+            double ef, er;
+            const double du = da_trial<F>(state, a, *l.da, has, has ? (int64_t)i : r.aoff, lane,
+                                          row, s, ef, er);
+            if (has) {
+              const int dn = 1 - 2 * s;
+              const double lnu1 = l.lnu[e], lnu2 = l.lnu2[e];
+              const double x1 = r.beta * (ef + r.dmu0 * (double)dn);
+              const bool pass1 = lnu1 < -x1;
+              bool ok = false;
+              double margin = lnu1 + x1;
+              if (pass1) {
+                const double sr = er - r.dmu0 * (double)dn;
+                const double xl = r.beta * (du + r.dmu0 * (double)dn);
+                const double xr = -(r.beta * sr);
+                const double l2 = (-xl + (xr < 0.0 ? xr : 0.0)) - (-x1 < 0.0 ? -x1 : 0.0);
+                ok = lnu2 < l2;
+                margin = lnu2 - l2;
+              }
+              if (lane == 0) {
+                if (ok) atomicAdd(&cw[2 * k], dn > 0 ? 1ull : 1ull << PK_BITS);
+                atomicAdd(&cw[2 * k + 1], 1ull | (pass1 ? 1ull << DA_BITS : 0ull) |
+                                              (fabs(margin) < TIE ? 1ull << (2 * DA_BITS) : 0ull));
+              }
+              if (ok) {
+                rec = i;
+                my_i = i;
+                my_s = s;
+              }
+            }
+          }
+          if (!one_pass && lane == 0 && p < len * own) l.rec[p] = rec;
+        }
+      } else
       for (int p = grp; p < len * own; p += PGROUPS) {
         const int k = p / own;
         const int e = (int)((s0 + k) % (uint32_t)win) * chunk + (p - k * own);
         const int32_t i = l.site[e];
         int32_t rec = -1;
         if (i >= 0) {
-          if (!have || p != grp) p_row(a, i, lane, row);
+          if (!have || p != grp) row_of(i, row);
           int s;
           const double du = p_delta_u<F, RES>(state, i, lane, row, l.terms + grp * KMAX, s);
           const double lnu = l.lnu[e];
@@ -483,7 +778,7 @@ __device__ __forceinline__ void sweep_replica(const PersistArgs &a, const RepD &
         if (s1 < hd && (int)k < min(2 * span, cap)) {
           have_ahead = true;
           const int32_t i = l.site[(int)(s1 % (uint32_t)win) * chunk + (grp - (int)k * own)];
-          if (i >= 0) p_row(a, i, lane, ahead);
+          if (i >= 0) row_of(i, ahead);
         }
       }
       if (RES || r.G == 1) draw_ahead(PBLOCK / 128);  // by the waves with the fewest trials
@@ -574,8 +869,14 @@ __device__ __forceinline__ void sweep_replica(const PersistArgs &a, const RepD &
       if (tid < 64) {
         if (wl < done) {
           const unsigned long long c = cw[2 * wl + 1];
-          n_trial += c & 0xffffffffull;
-          n_tie += c >> 32;
+          if (DA) {
+            n_trial += c & DA_MASK;
+            n_pass += (c >> DA_BITS) & DA_MASK;
+            n_tie += c >> (2 * DA_BITS);
+          } else {
+            n_trial += c & 0xffffffffull;
+            n_tie += c >> 32;
+          }
           if (q == 0) {
             n_acc += nrec;
             n_stage += 1;
@@ -610,18 +911,18 @@ __device__ __forceinline__ void sweep_replica(const PersistArgs &a, const RepD &
       if (ka >= 0) {
         if (one_pass) {
           if (grp < len * own && grp / own == ka && my_i >= 0)
-            p_commit<F, RES>(state, my_i, lane, my_s, row);
+            p_commit<F, RES, DA>(state, my_i, lane, my_s, row);
         } else {
           for (int p = grp; p < len * own; p += PGROUPS) {
             if (p / own != ka) continue;
             const int32_t i = l.rec[p];
             if (i >= 0) {
               PRow v;
-              p_row(a, i, lane, v);
+              row_of(i, v);
 #pragma unroll
               for (int h = 0; h < PH; ++h)
                 v.rj[h] = lane + h * PTL < v.m ? state.rho(v.j[h]) : 0.0;
-              p_commit<F, RES>(state, i, lane, state.sp(i), v);
+              p_commit<F, RES, DA>(state, i, lane, state.sp(i), v);
             }
           }
         }
@@ -675,6 +976,7 @@ __device__ __forceinline__ void sweep_replica(const PersistArgs &a, const RepD &
   if (tid < 64) {
     if (wl < PDMAX) {
       atomicAdd(&st->trials, n_trial);
+      if (DA) atomicAdd(&st->stage1, n_pass);
       atomicAdd(&st->near_ties, n_tie);
       if (q == 0) {
         atomicAdd(&st->local_acc, n_acc);
@@ -722,9 +1024,24 @@ __global__ void __launch_bounds__(PBLOCK) k_sweep_persistent(PersistArgs a) {
   }
   const PLds l = persist_lds(lds, a.ndraw, r.res ? r.n : 0);
   if (r.res)
-    sweep_replica<F, true, LOG>(a, r, a.rs + rix, l, &flag);
+    sweep_replica<F, true, LOG, false>(a, r, a.rs + rix, l, &flag);
   else
-    sweep_replica<F, false, LOG>(a, r, a.rs + rix, l, &flag);
+    sweep_replica<F, false, LOG, false>(a, r, a.rs + rix, l, &flag);
+}
+
+// delayed acceptance with the network, one system, state in memory
+template <bool TAB>
+__global__ void __launch_bounds__(PBLOCK) k_sweep_persistent_da(PersistArgsDa a) {
+  constexpr int F = TAB ? 1 : 0;
+  extern __shared__ __align__(16) unsigned char lds[];
+  __shared__ int flag;
+  RepD r = a.reps[0];
+  in_vgpr(r.beta);
+  in_vgpr(r.dmu0);
+  in_vgpr(r.kN);
+  in_vgpr(r.ncbar);
+  const PLds l = persist_lds_da(lds, a.ndraw);
+  sweep_replica<F, false, false, true>(a, r, a.rs, l, &flag);
 }
 
 // zero the barrier counters, the timeout flag and the per-call counters;
@@ -735,7 +1052,7 @@ __global__ void k_persist_reset(RepState *rs, int R) {
   RepState &s = rs[k];
   s.n_b = s.n_final;
   for (int q = 0; q < 4 * 8 * PDG; ++q) (&s.word[0][0][0])[q] = 0;
-  s.trials = s.local_acc = s.stages = s.stage_acc = s.flips = s.near_ties = 0;
+  s.trials = s.stage1 = s.local_acc = s.stages = s.stage_acc = s.flips = s.near_ties = 0;
   s.sum_n = 0.0;
   s.sum_n2 = 0.0;
   for (int q = 0; q < 8; ++q) s.bar[q].n = 0;
@@ -785,7 +1102,7 @@ hipError_t persist_max_blocks(int *per_cu, bool tab, size_t lds, size_t lds_max)
 }
 
 static PersistArgs make_args(vcsgc_ctx *c) {
-  PersistArgs a;
+  PersistArgs a = {};
   a.reps = (const RepD *)c->d_reps;
   a.rs = (RepState *)c->d_rs;
   a.wg_rep = c->d_wg_rep;
@@ -815,7 +1132,7 @@ static PersistArgs make_args(vcsgc_ctx *c) {
 // staging buffer is rewritten.
 hipError_t persist_stage_params(vcsgc_ctx *c, const double *dmu0, const double *kappa,
                                 const double *cbar, const double *T, int64_t n_sweeps,
-                                uint64_t seed) {
+                                uint64_t seed, bool da) {
   hipError_t e = hipEventSynchronize(c->stage_ev);
   if (e != hipSuccess) return e;
   RepD *h = (RepD *)c->h_reps;
@@ -831,7 +1148,7 @@ hipError_t persist_stage_params(vcsgc_ctx *c, const double *dmu0, const double *
     d.n2 = r.nc[2];
     d.cso = r.cso;
     d.ncpc = r.ncpc;
-    d.res = r.res ? 1 : 0;
+    d.res = r.res && !da ? 1 : 0;
     d.S = r.S;
     d.beta = 1.0 / (KB * T[k]);
     d.dmu0 = dmu0[k];
@@ -839,8 +1156,8 @@ hipError_t persist_stage_params(vcsgc_ctx *c, const double *dmu0, const double *
     d.ncbar = (double)r.n * cbar[k];
     d.seed = seed;
     d.key1 = (uint64_t)k;
-    d.g0 = r.g0;
-    d.G = r.G;
+    d.g0 = da ? 0 : r.g0;
+    d.G = da ? c->da_wg : r.G;
     d.n_sweeps = n_sweeps;
     d.w0 = (int64_t)c->w;
   }
@@ -905,19 +1222,25 @@ constexpr int PGATE_DEVICES = 64;
 static std::mutex g_gate_mu;
 static hipEvent_t g_gate[PGATE_DEVICES] = {};
 
+template <class L>
+static hipError_t gated(vcsgc_ctx *c, L launch) {
+  if (c->device < 0 || c->device >= PGATE_DEVICES) return launch();
+  std::lock_guard<std::mutex> lock(g_gate_mu);
+  hipEvent_t &ev = g_gate[c->device];
+  hipError_t e = ev ? hipStreamWaitEvent(c->stream, ev, 0)
+                    : hipEventCreateWithFlags(&ev, hipEventDisableTiming);
+  if (e == hipSuccess) e = launch();
+  if (e == hipSuccess) e = hipEventRecord(ev, c->stream);
+  return e;
+}
+
 static hipError_t launch_ungated(vcsgc_ctx *c, bool use_graph);
 
 hipError_t launch_persistent(vcsgc_ctx *c, bool use_graph) {
   bool waits = false;
   for (const RepHost &r : c->reps) waits = waits || r.G > 1;
-  if (!waits || c->device < 0 || c->device >= PGATE_DEVICES) return launch_ungated(c, use_graph);
-  std::lock_guard<std::mutex> lock(g_gate_mu);
-  hipEvent_t &ev = g_gate[c->device];
-  hipError_t e = ev ? hipStreamWaitEvent(c->stream, ev, 0)
-                    : hipEventCreateWithFlags(&ev, hipEventDisableTiming);
-  if (e == hipSuccess) e = launch_ungated(c, use_graph);
-  if (e == hipSuccess) e = hipEventRecord(ev, c->stream);
-  return e;
+  auto launch = [&]() { return launch_ungated(c, use_graph); };
+  return waits ? gated(c, launch) : launch();
 }
 
 static hipError_t launch_ungated(vcsgc_ctx *c, bool use_graph) {
@@ -938,8 +1261,68 @@ static hipError_t launch_ungated(vcsgc_ctx *c, bool use_graph) {
                                     dim3(PBLOCK), args, (unsigned)c->persist_lds, c->stream);
 }
 
+// ---- delayed acceptance with the network (one system) ----
+static const void *persist_da_kernel(bool tab) {
+  return tab ? (const void *)k_sweep_persistent_da<true> : (const void *)k_sweep_persistent_da<false>;
+}
+
+// Trial groups per active cell.  A trial is longer than a plain one, so a
+// second pass over the groups costs more than a barrier of more workgroups:
+// 128,000 sites at 9% accepted stages 1.02 ms with 8, 0.74 with 16, 0.69 with
+// 32; 16,000 sites 1.76, 1.37, 1.20; 1.02M sites 0.96, 0.95, 0.98.
+constexpr int PERSIST_SPEC_DA = 32;
+
+// The grid of the delayed-acceptance sweep into c->da_wg (-1: its shares of the
+// cells do not fit a workgroup's groups) and c->da_ndraw, once per context.
+hipError_t persist_da_grid(vcsgc_ctx *c) {
+  if (c->da_wg) return hipSuccess;
+  const RepHost &r = c->reps[0];
+  int cu = 0, lds_cu = 0, per_cu = 0;
+  hipError_t e = hipDeviceGetAttribute(&cu, hipDeviceAttributeMultiprocessorCount, c->device);
+  if (e == hipSuccess)
+    e = hipDeviceGetAttribute(&lds_cu, hipDeviceAttributeMaxSharedMemoryPerMultiprocessor,
+                              c->device);
+  if (e != hipSuccess) return e;
+  const size_t room = (size_t)lds_cu - 1024;
+  c->da_wg = -1;
+  const int nd = 2 * PDRAW;
+  const size_t lds = persist_lds_bytes_da(nd);
+  if (lds > room) return hipSuccess;
+  const void *f = persist_da_kernel(c->pot.tab != 0);
+  e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, (int)room);
+  if (e == hipSuccess) e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, f, PBLOCK, lds);
+  if (e != hipSuccess) return e;
+  int64_t g = (PERSIST_SPEC_DA * r.ncpc + PGROUPS - 1) / PGROUPS;
+  if (g >= 8) g = (g + 7) / 8 * 8;
+  g = std::min<int64_t>(g, (int64_t)cu * per_cu);
+  if (g < 1 || r.ncpc > g * PGROUPS) return hipSuccess;
+  c->da_wg = (int)g;
+  c->da_ndraw = nd;
+  return hipSuccess;
+}
+
+hipError_t launch_persistent_da(vcsgc_ctx *c) {
+  PersistArgsDa a;
+  static_cast<PersistArgs &>(a) = make_args(c);
+  a.ndraw = c->da_ndraw;
+  a.md = mlp_dev(c->mlp);
+  a.dj = c->d_j;
+  a.dr = c->d_r;
+  a.dcnt = c->d_cnt;
+  auto launch = [&]() {
+    k_persist_reset<<<1, BLOCK, 0, c->stream>>>((RepState *)c->d_rs, 1);
+    hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+    void *args[] = {&a};
+    return hipLaunchCooperativeKernel(persist_da_kernel(c->pot.tab != 0), dim3((unsigned)c->da_wg),
+                                      dim3(PBLOCK), args,
+                                      (unsigned)persist_lds_bytes_da(c->da_ndraw), c->stream);
+  };
+  return c->da_wg > 1 ? gated(c, launch) : launch();
+}
+
 // per-replica statistics after the call (synchronizes)
-hipError_t persist_read_stats(vcsgc_ctx *c, vcsgc_stats *out, int *err) {
+hipError_t persist_read_stats(vcsgc_ctx *c, vcsgc_stats *out, int *err, bool da) {
   const int R = (int)c->reps.size();
   std::vector<RepState> h(R);
   hipError_t e = hipMemcpyAsync(h.data(), c->d_rs, sizeof(RepState) * R, hipMemcpyDeviceToHost,
@@ -959,7 +1342,7 @@ hipError_t persist_read_stats(vcsgc_ctx *c, vcsgc_stats *out, int *err) {
     out[k].n_final = h[k].n_final;
     out[k].sum_n = h[k].sum_n;
     out[k].sum_n2 = h[k].sum_n2;
-    out[k].stage1_pass = (int64_t)h[k].trials;
+    out[k].stage1_pass = (int64_t)(da ? h[k].stage1 : h[k].trials);
   }
   return hipSuccess;
 }

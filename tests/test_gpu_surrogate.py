@@ -243,6 +243,44 @@ def test_da_network_graph_replay_matches_direct(torch_cuda, oracle_mod, batch):
     net.close()
 
 
+@pytest.mark.parametrize("dims,colours,pot,kappa", [
+    ((6, 6, 6), 8, "FS-P1", 0.0),       # one workgroup, one cell per stage
+    ((17, 13, 19), 8, "TAB-X", 1.0),    # tables, several workgroups
+    ((23, 31, 17), 27, "FS-P1", 10.0),  # 27 colours, uneven shares of the cells
+    ((62, 60, 64), 8, "FS-P1", 1000.0),  # more than one pass of the trial groups
+])
+def test_da_network_persistent_matches_stages(torch_cuda, dims, colours, pot, kappa):
+    """The network's delayed acceptance in the persistent sweep against the
+    kernels per stage (the surrogate log takes that path): the same chain and
+    statistics bit for bit."""
+    from paper_1012_5082_amd.binding import VCSGC
+    pot = I.params(pot) if pot == "FS-P1" else I.table(pot)
+    x, y, z, box = I.bcc(*dims)
+    x, y, z = I.thermalize(x, y, z, box, 0.04, 5)
+    sp = I.initial_species(x.size, 0.1, 6)
+    m = _params(7)
+    m.out_mu, m.out_sd = float(np.float32(0.45)), float(np.float32(0.2))
+    net = _gpu_mlp(m)
+    runs = []
+    for logged in (True, False):
+        g = VCSGC(x, y, z, box, sp, pot, descriptor=True, r_dep=8.01, colours=colours)
+        g.set_surrogate("mlp", net)
+        if logged:
+            g.enable_surrogate_log(10 ** 6)
+        out = []
+        for n_sw in (1, 2):
+            s = g.sweep(-0.2, kappa, 0.1, 600.0, n_sw, 31)
+            out.append({k: s[k] for k in ("trials", "stage1_pass", "local_accepts", "stages",
+                                           "stage_accepts", "flips", "n_final", "sum_n", "sum_n2")})
+        runs.append((out, g.species.cpu().numpy().copy(), g.rho().cpu().numpy().copy()))
+        g.close()
+    net.close()
+    assert runs[0][0] == runs[1][0]
+    assert 0 < runs[0][0][0]["stage1_pass"] < runs[0][0][0]["trials"]
+    assert np.array_equal(runs[0][1], runs[1][1])
+    assert np.array_equal(runs[0][2], runs[1][2])
+
+
 def test_sample_log_and_training(torch_cuda, oracle_mod):
     torch = torch_cuda
     pot = I.params("FS-P1")
