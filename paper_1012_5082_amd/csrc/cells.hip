@@ -32,18 +32,6 @@ hipError_t launch_validate(vcsgc_ctx *c, const RepHost &r) {
 // ----------------------------------------------------------------------------
 // binning: count, exclusive scan, scatter, then sort each cell ascending
 // ----------------------------------------------------------------------------
-struct Grid {
-  double L0, L1, L2;
-  int n0, n1, n2;
-};
-
-__device__ __forceinline__ int cell_of(const Grid &g, double a, double b, double c) {
-  const int cx = cell_coord(a, g.L0, g.n0);
-  const int cy = cell_coord(b, g.L1, g.n1);
-  const int cz = cell_coord(c, g.L2, g.n2);
-  return cx + g.n0 * (cy + g.n1 * cz);
-}
-
 // atomicAdd(&counter[key], 1) for every active lane, with one atomic per
 // distinct key in the wave (neighbouring atoms mostly share a cell); returns
 // the lane's old value plus its rank among the lanes with the same key.  The
@@ -565,6 +553,26 @@ __device__ __forceinline__ void sort_row(int32_t (&v)[KMAX]) {
   }
 }
 
+// the row v of atom i (INT32_MAX after the last entry) sorted into the
+// column-major list, its length and the position of this build
+__device__ __forceinline__ void md_store_row(int32_t (&v)[KMAX], int64_t n, int64_t i, int32_t *nj,
+                                             uint8_t *cnt, const double *__restrict__ x,
+                                             const double *__restrict__ y,
+                                             const double *__restrict__ z, double *xr, double *yr,
+                                             double *zr) {
+  sort_row(v);
+  int m = 0;
+#pragma unroll
+  for (int k = 0; k < KMAX; ++k) {
+    if (v[k] != INT32_MAX) nj[(int64_t)k * n + i] = v[k];
+    m += v[k] != INT32_MAX ? 1 : 0;
+  }
+  cnt[i] = (uint8_t)m;
+  xr[i] = x[i];
+  yr[i] = y[i];
+  zr[i] = z[i];
+}
+
 // r < rc + skin list, one lane per atom (used when some axis has fewer than
 // four search bins): the lane walks the surrounding search bins through the
 // packed (x, y, z, index) slots and appends hits to its row; INT32_MAX fills
@@ -679,11 +687,21 @@ __device__ __forceinline__ int2 block_scan2(int &a, int &b, int2 *wtot) {
 constexpr int RG_X = 4, RG_Y = 4;  // own bins of a region along x and y
 constexpr int RG_GRID = 2048;      // blocks of a region launch (at most)
 
-template <int BMAX, int RZ, int CAP>
+// FIN: the kernel also does k_md_finish's work (fin), one launch less per step,
+// for systems small enough that its scattered stores stay in the L2s.
+struct MdFinish {
+  int64_t n;
+  const double *x, *y, *z;
+  int32_t *nj;
+  uint8_t *cnt;
+  double *xr, *yr, *zr;
+};
+
+template <int BMAX, int RZ, int CAP, bool FIN>
 __global__ void __launch_bounds__(BLOCK)
     k_md_search(Grid g, int nrx, int nry, int64_t nreg, const int32_t *__restrict__ bcount,
-                const double4 *__restrict__ bpos, float cut2f, int32_t *rows, DevState *ds,
-                const int *cond) {
+                const double4 *__restrict__ bpos, float cut2f, int32_t *rows, MdFinish fin,
+                DevState *ds, const int *cond) {
   constexpr int SX = RG_X + 2, SY = RG_Y + 2, SZ = RZ + 2, NST = SX * SY * SZ;
   constexpr int OWN_CAP = RG_X * RG_Y * RZ * BMAX;
   static_assert(NST <= BLOCK && NST <= 256, "one thread per staged bin, bin ids in a byte");
@@ -726,7 +744,9 @@ __global__ void __launch_bounds__(BLOCK)
       if (gy < 0) { gy += g.n1; hy = -1; } else if (gy >= g.n1) { gy -= g.n1; hy = 1; }
       if (gz < 0) { gz += g.n2; hz = -1; } else if (gz >= g.n2) { gz -= g.n2; hz = 1; }
       const int b = gx + g.n0 * (gy + g.n1 * gz);
-      cn = min(bcount[b], BMAX);
+      const int occ = bcount[b];
+      cn = min(occ, BMAX);
+      if (FIN && occ > BMAX) atomicOr(&ds->bin_overflow, 1);  // the drift's binning raises nothing
       ocn = own ? cn : 0;
       gbin[tid] = b;
       shc[tid] = make_char4(hx, hy, hz, 0);
@@ -818,23 +838,30 @@ __global__ void __launch_bounds__(BLOCK)
       // one lies beyond the entries read)
       const int nb = c - 1, cc = nb < KMAX ? nb : KMAX;
       const int last = hit[min(c - 1, KMAX + 1)][tid];
+      int32_t w[FIN ? KMAX : 4];
 #pragma unroll
       for (int u = 0; u < KMAX; u += 4) {
-        int32_t w[4];
+        int32_t *v = w + (FIN ? u : 0);
 #pragma unroll
         for (int k = 0; k < 4; ++k) {
           int sk = hit[u + k][tid];
           sk = sk == si ? last : sk;
-          w[k] = u + k < cc ? __float_as_int(cand[min(sk, CAP - 1)].w) : INT32_MAX;
+          v[k] = u + k < cc ? __float_as_int(cand[min(sk, CAP - 1)].w) : INT32_MAX;
         }
-        *(int4 *)(rows + (int64_t)i * KMAX + u) = make_int4(w[0], w[1], w[2], w[3]);
+        if (!FIN) *(int4 *)(rows + (int64_t)i * KMAX + u) = make_int4(v[0], v[1], v[2], v[3]);
       }
+      if constexpr (FIN) md_store_row(w, fin.n, i, fin.nj, fin.cnt, fin.x, fin.y, fin.z, fin.xr,
+                                      fin.yr, fin.zr);
       pairs += cc;
       kmx = nb > kmx ? nb : kmx;
       ovf = ovf || nb > KMAX;
     }
   }
-  md_row_stats(pairs, kmx < KMAX ? kmx : KMAX, ovf, ds);
+  if (FIN)
+    block_row_stats(pairs, kmx < KMAX ? kmx : KMAX, ovf, &ds->pairs_new, &ds->kmax_new,
+                    &ds->overflow);
+  else
+    md_row_stats(pairs, kmx < KMAX ? kmx : KMAX, ovf, ds);
 }
 
 // The rows written by the search (row-major [i * KMAX + k], unsorted,
@@ -863,27 +890,23 @@ __global__ void __launch_bounds__(BLOCK)
       v[u + 2] = q.z;
       v[u + 3] = q.w;
     }
-    sort_row(v);
-    int m = 0;
-#pragma unroll
-    for (int k = 0; k < KMAX; ++k) {
-      if (v[k] != INT32_MAX) nj[(int64_t)k * n + i] = v[k];
-      m += v[k] != INT32_MAX ? 1 : 0;
-    }
-    cnt[i] = (uint8_t)m;
-    xr[i] = x[i];
-    yr[i] = y[i];
-    zr[i] = z[i];
+    md_store_row(v, n, i, nj, cnt, x, y, z, xr, yr, zr);
   }
+}
+
+static bool md_regions(const vcsgc_ctx *c) {
+  const int *nb = c->reps[0].nb;
+  return nb[0] >= 4 && nb[1] >= 4 && nb[2] >= 4 && (c->bmax == 16 || c->bmax == 32);
 }
 
 // the list build from filled search bins (regions when every axis has at
 // least four bins and a bin holds at most 32 atoms, else one lane per atom),
-// then the column-major rows, their lengths and the positions of the build
-hipError_t launch_md_build_chain(vcsgc_ctx *c, const Grid &g, const int *cond) {
+// then the column-major rows, their lengths and the positions of the build;
+// fin: search and finish in one kernel
+static hipError_t launch_md_build_chain(vcsgc_ctx *c, const Grid &g, const int *cond, bool fin) {
   const RepHost &r = c->reps[0];
   const double cut = c->pot.rc + c->skin;
-  if (g.n0 >= 4 && g.n1 >= 4 && g.n2 >= 4 && (c->bmax == 16 || c->bmax == 32)) {
+  if (md_regions(c)) {
     const float cf = (float)(cut + 1e-3);
     const int nrx = (g.n0 + RG_X - 1) / RG_X, nry = (g.n1 + RG_Y - 1) / RG_Y;
     const int rz = c->bmax == 16 ? 2 : 1;
@@ -892,12 +915,17 @@ hipError_t launch_md_build_chain(vcsgc_ctx *c, const Grid &g, const int *cond) {
     const unsigned G = (unsigned)std::min<int64_t>((nreg + 7) / 8 * 8, RG_GRID);
     // 16-slot bins: up to eight staged atoms per bin on average (a denser
     // region has the bins grown); 32-slot bins: every slot
+    const MdFinish f = {r.n, c->x, c->y, c->z, c->md_j, c->md_cnt, c->xr, c->yr, c->zr};
+    auto search = [&](auto kernel) {
+      kernel<<<G, BLOCK, 0, c->stream>>>(g, nrx, nry, nreg, c->bin_count, c->bin_pos, cf * cf,
+                                         c->md_rows, f, c->ds, cond);
+    };
     if (c->bmax == 16)
-      k_md_search<16, 2, 6 * 6 * 4 * 8><<<G, BLOCK, 0, c->stream>>>(
-          g, nrx, nry, nreg, c->bin_count, c->bin_pos, cf * cf, c->md_rows, c->ds, cond);
+      search(fin ? k_md_search<16, 2, 6 * 6 * 4 * 8, true> : k_md_search<16, 2, 6 * 6 * 4 * 8, false>);
     else
-      k_md_search<32, 1, 6 * 6 * 3 * 32><<<G, BLOCK, 0, c->stream>>>(
-          g, nrx, nry, nreg, c->bin_count, c->bin_pos, cf * cf, c->md_rows, c->ds, cond);
+      search(fin ? k_md_search<32, 1, 6 * 6 * 3 * 32, true>
+                 : k_md_search<32, 1, 6 * 6 * 3 * 32, false>);
+    if (fin) return hipGetLastError();
   } else {
     k_build_md<<<grid_for(r.n), BLOCK, 0, c->stream>>>(r.n, c->x, c->y, c->z, g, c->bin_count,
                                                        c->bin_pos, c->bmax, cut * cut,
@@ -917,7 +945,7 @@ hipError_t launch_build_md_list(vcsgc_ctx *c) {
   if (e == hipSuccess) e = hipMemsetAsync(&c->ds->kmax_md, 0, sizeof(int), c->stream);
   if (e != hipSuccess) return e;
   int h = tstart(c, VCSGC_KT_BUILD);
-  e = launch_md_build_chain(c, g, nullptr);
+  e = launch_md_build_chain(c, g, nullptr, false);
   tstop(c, h);
   return e;
 }
@@ -933,11 +961,23 @@ hipError_t launch_md_rebuild_cond(vcsgc_ctx *c, int par) {
   Grid g{r.box[0], r.box[1], r.box[2], r.nb[0], r.nb[1], r.nb[2]};
   const int *cond = &c->ds->rebuild[par];
   int h = tstart(c, VCSGC_KT_BUILD);
-  k_bin_search<<<std::min(grid_for(r.n), BIN_GRID), BLOCK, 0, c->stream>>>(
-      r.n, c->x, c->y, c->z, g, c->bmax, c->bin_count, c->bin_atoms, c->bin_pos, c->ds, cond);
-  hipError_t e = launch_md_build_chain(c, g, cond);
+  const bool fused = md_binned_drift(c);
+  if (!fused)
+    k_bin_search<<<std::min(grid_for(r.n), BIN_GRID), BLOCK, 0, c->stream>>>(
+        r.n, c->x, c->y, c->z, g, c->bmax, c->bin_count, c->bin_atoms, c->bin_pos, c->ds, cond);
+  hipError_t e = launch_md_build_chain(c, g, cond, fused);
   tstop(c, h);
   return e;
+}
+
+// Small systems: the drift bins its atoms at every step (the density pass
+// before it has cleared the counts) and one kernel searches and finishes, so a
+// step without a rebuild has one idle launch instead of three (about 4.5 us
+// each).  20 NVE steps at 2,000 atoms 474 -> 390 us, at 31,250 522 -> 453; at
+// 94,054 the binning costs what the launches did (1,225 and 1,240 us), and
+// from there on the scattered stores lose (1.02M atoms 3.5 and 4.9 ms).
+bool md_binned_drift(const vcsgc_ctx *c) {
+  return c->bin_pos && c->n <= 48 * 1024 && md_regions(c);
 }
 
 bool md_rebuild_on_device(const vcsgc_ctx *c) { return c->bin_pos != nullptr; }

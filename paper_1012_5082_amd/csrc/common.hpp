@@ -92,6 +92,10 @@ struct DevState {
   unsigned long long stage1_pass;         // trials passing the surrogate stage
   unsigned long long smp_n, dalog_n;      // sample-log and surrogate-log records written
   unsigned long long md_rebuilds;         // MD list rebuilds taken on the device
+  // entries and longest row of a list built by the kernel that also finishes it
+  // (its blocks add to them; the next density pass moves them to pairs_md, kmax_md)
+  unsigned long long pairs_new;
+  int kmax_new;
   unsigned long long wcur;                // sweep counter of a graph-replayed sweep
   StageProgress pipe;                     // fused stage pipeline of the current call
 };
@@ -385,6 +389,19 @@ __device__ __forceinline__ int cell_coord(double u, double L, int nc) {
   return c < 0 ? 0 : (c >= nc ? nc - 1 : c);
 }
 
+// cells (or search bins) of a periodic box
+struct Grid {
+  double L0, L1, L2;
+  int n0, n1, n2;
+};
+
+__device__ __forceinline__ int cell_of(const Grid &g, double a, double b, double c) {
+  const int cx = cell_coord(a, g.L0, g.n0);
+  const int cy = cell_coord(b, g.L1, g.n1);
+  const int cz = cell_coord(c, g.L2, g.n2);
+  return cx + g.n0 * (cy + g.n1 * cz);
+}
+
 // Workgroups are dispatched to the eight XCDs round robin (workgroup b runs on
 // XCD b mod 8), and each XCD has its own L2.  For gather kernels whose
 // neighbouring atoms have neighbouring indices, this maps the launch so that
@@ -652,6 +669,7 @@ hipError_t launch_build_mc_list(vcsgc_ctx *c, const RepHost &r);
 hipError_t launch_build_md_list(vcsgc_ctx *c);
 hipError_t launch_md_rebuild_cond(vcsgc_ctx *c, int par);
 bool md_rebuild_on_device(const vcsgc_ctx *c);
+bool md_binned_drift(const vcsgc_ctx *c);
 hipError_t launch_mc_row_stats(vcsgc_ctx *c);
 hipError_t launch_build_desc_list(vcsgc_ctx *c, const RepHost &r);
 hipError_t launch_descriptors(vcsgc_ctx *c, const int32_t *sites, int64_t n, int flip,

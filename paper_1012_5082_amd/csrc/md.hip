@@ -228,12 +228,31 @@ __device__ __forceinline__ void density_store(int64_t i, const double4 &qi, cons
   if (EN) e[i] = embed<TAB ? 1 : 0>(p, si, s.rho) + 0.5 * s.phi;
 }
 
+// What a density pass does for the next drift's binning: clear the bin counts
+// (their readers, the last step's list build, have finished), and take over
+// that build's statistics.
+struct BinClear {
+  int32_t *count;  // NULL: nothing
+  int64_t nbins;
+  DevState *ds;
+};
+__device__ __forceinline__ void bin_clear(const BinClear &c, int64_t i, int64_t threads) {
+  for (int64_t q = i; q < c.nbins; q += threads) c.count[q] = 0;
+  if (i == 0 && c.ds->pairs_new) {
+    c.ds->pairs_md = c.ds->pairs_new;
+    c.ds->kmax_md = c.ds->kmax_new;
+    c.ds->pairs_new = 0ull;
+    c.ds->kmax_new = 0;
+  }
+}
+
 template <int LPA, bool TAB, bool EN>
 __global__ void __launch_bounds__(BLOCK)
     k_density_md(int64_t n, const double2 *__restrict__ ps4, const int32_t *__restrict__ nj,
                  const uint8_t *__restrict__ cnt, Box b, double reach, PotD p, double *rho,
-                 double2 *pf4, double *e) {
+                 double2 *pf4, double *e, BinClear bc) {
   const int64_t gid = xcd_block() * blockDim.x + threadIdx.x;
+  if (bc.count) bin_clear(bc, gid, (int64_t)gridDim.x * blockDim.x);
   const int64_t i = gid / LPA;
   const int lane = (int)(gid % LPA);
   if (i >= n) return;  // whole groups leave together
@@ -266,12 +285,15 @@ struct KickDrift {
   int32_t *bcount;
   int64_t nbins;
   DevState *ds;
+  double4 *bpos;  // not NULL: the drifted atom goes to its search bin (bcount, bmax slots each)
+  Grid g;
+  int bmax;
   const double *nvt;  // Nose-Hoover: v = (v s1) s2 before the kick (nvt[3], nvt[4]); NULL: none
 };
 
 // The step's clearing work, by thread i of a grid of `threads`.
 __device__ __forceinline__ void kick_drift_clear(const KickDrift &k, int64_t i, int64_t threads) {
-  if (k.bcount)
+  if (k.bcount && !k.bpos)
     for (int64_t q = i; q < k.nbins; q += threads) k.bcount[q] = 0;
   if (i == 0) k.ds->rebuild[k.par ^ 1] = 0;
 }
@@ -319,6 +341,11 @@ __device__ __forceinline__ void kick_drift_atom(const KickDrift &k, const KickIn
   k.y[i] = ny;
   k.z[i] = nz;
   packed_store(k.ps4, i, nx, ny, nz, (double)s);
+  if (k.bpos) {  // a bin with more atoms than slots is the list build's to report
+    const int bin = cell_of(k.g, nx, ny, nz);
+    const int slot = atomicAdd(&k.bcount[bin], 1);
+    if (slot < k.bmax) k.bpos[(int64_t)bin * k.bmax + slot] = make_double4(nx, ny, nz, (double)i);
+  }
   const double ex = min_image(nx - in.xr, b.L0);
   const double ey = min_image(ny - in.yr, b.L1);
   const double ez = min_image(nz - in.zr, b.L2);
@@ -517,12 +544,13 @@ static int lanes_per_atom(const vcsgc_ctx *c, bool steps) {
 template <int LPA, bool EN>
 static void density_md_on(vcsgc_ctx *c, const Box &b) {
   const double reach = list_reach(c);
+  const BinClear bc = {!EN && md_binned_drift(c) ? c->bin_count : nullptr, c->reps[0].nbins, c->ds};
   if (c->pot.tab)
     k_density_md<LPA, true, EN><<<grid_for(c->n * LPA), BLOCK, 0, c->stream>>>(
-        c->n, c->ps4, c->md_j, c->md_cnt, b, reach, c->pot, c->rho_f, c->pf4, c->eatom);
+        c->n, c->ps4, c->md_j, c->md_cnt, b, reach, c->pot, c->rho_f, c->pf4, c->eatom, bc);
   else
     k_density_md<LPA, false, EN><<<grid_for(c->n * LPA), BLOCK, 0, c->stream>>>(
-        c->n, c->ps4, c->md_j, c->md_cnt, b, reach, c->pot, c->rho_f, c->pf4, c->eatom);
+        c->n, c->ps4, c->md_j, c->md_cnt, b, reach, c->pot, c->rho_f, c->pf4, c->eatom, bc);
 }
 
 template <bool EN>
@@ -588,6 +616,12 @@ static KickDrift kick_drift_args(vcsgc_ctx *c, double dt, bool kick_first, int p
   k.par = par;
   k.bcount = c->bin_count;
   k.nbins = c->reps[0].nbins;
+  if (md_binned_drift(c)) {
+    const int *nb = c->reps[0].nb;
+    k.bpos = c->bin_pos;
+    k.g = Grid{c->box[0], c->box[1], c->box[2], nb[0], nb[1], nb[2]};
+    k.bmax = c->bmax;
+  }
   k.ds = c->ds;
   return k;
 }

@@ -641,6 +641,41 @@ def test_md_lanes_per_atom(torch_cuda, oracle_mod, dims, pot):
     g.close()
 
 
+@pytest.mark.parametrize("dims", [(6, 8, 11), (29, 29, 29), (30, 28, 30)])
+def test_md_list_statistics_after_rebuild(torch_cuda, oracle_mod, dims):
+    """The list the steps rebuild, with the drift's own binning (up to 48k
+    atoms) and without: after the step that rebuilds it holds every pair
+    within rc + skin and none beyond the float margin of the search; the
+    trajectory is the oracle's."""
+    O = oracle_mod
+    pot = I.params("FS-P1")
+    skin = 0.3
+    x, y, z, box = I.bcc(*dims)
+    x, y, z = I.thermalize(x, y, z, box, 0.05, 41)
+    sp = I.initial_species(x.size, 0.1, 42)
+    vx, vy, vz = I.mb_velocities(sp, 1500.0, 43)
+    d = dict(x=x, y=y, z=z, box=box, species=sp, vx=vx, vy=vy, vz=vz)
+    g = gpu_context(d, pot, velocities=True, skin=skin)
+    g.md(1.0, 1)
+    base, steps = g.info()["md_rebuilds"], 1
+    while g.info()["md_rebuilds"] == base:
+        g.md(1.0, 1)
+        steps += 1
+        assert steps < 60
+    pos = [v.cpu().numpy() for v in (g.x, g.y, g.z)]
+    lo = O.neighbors(*pos, box, pot.rc + skin, vectors=False).j.size
+    hi = O.neighbors(*pos, box, pot.rc + skin + 2e-3, vectors=False).j.size
+    assert lo <= g.info()["md_pairs"] <= hi
+    g.close()
+    g = gpu_context(d, pot, velocities=True, skin=skin)
+    g.md(1.0, steps + 2)
+    assert g.info()["md_rebuilds"] > base
+    out = O.md(x, y, z, vx, vy, vz, sp, box, pot, 1.0, steps + 2)
+    for nm, want in zip(("x", "y", "z", "vx", "vy", "vz", "fx", "fy", "fz"), out[:9]):
+        assert np.array_equal(getattr(g, nm).cpu().numpy(), want), nm
+    g.close()
+
+
 @pytest.mark.parametrize("path", ["pipeline", "da_perfect", "chain3", "persistent", "batch",
                                   "da_batch"])
 def test_sweep_paths_after_md(torch_cuda, oracle_mod, path):
