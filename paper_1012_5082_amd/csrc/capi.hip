@@ -37,7 +37,9 @@ void free_all(vcsgc_ctx *c) {
   for (void *p : ptrs)
     if (p) (void)hipFree(p);
   if (c->h_reps) (void)hipHostFree(c->h_reps);
+  if (c->h_rs) (void)hipHostFree(c->h_rs);
   if (c->h_state) (void)hipHostFree(c->h_state);
+  if (c->h_tot) (void)hipHostFree(c->h_tot);
   if (c->graph_exec) (void)hipGraphExecDestroy(c->graph_exec);
   if (c->graph) (void)hipGraphDestroy(c->graph);
   if (c->stage_ev) (void)hipEventDestroy(c->stage_ev);
@@ -628,6 +630,8 @@ vcsgc_status create_impl(const vcsgc_system *sys, int R, const int64_t *rep_atom
   A(dalloc((unsigned char **)&c->d_reps, vc::repd_size() * R));
   A(dalloc((unsigned char **)&c->d_rs, vc::repstate_size() * R));
   if (e == hipSuccess) e = hipHostMalloc(&c->h_reps, vc::repd_size() * R, hipHostMallocDefault);
+  if (e == hipSuccess) e = hipHostMalloc(&c->h_rs, vc::repstate_size() * R, hipHostMallocDefault);
+  if (e == hipSuccess) e = hipHostMalloc((void **)&c->h_tot, 8 * sizeof(double), hipHostMallocDefault);
   if (e == hipSuccess) e = hipEventCreateWithFlags(&c->stage_ev, hipEventDisableTiming);
   if (e != hipSuccess) {
     free_all(c);
@@ -935,14 +939,9 @@ vcsgc_status eam_energy_forces(vcsgc_ctx *c, double *energy_eV, int want_forces)
   if (want_forces) VC_CHECK(c, vc::launch_forces_only(c), "forces");
   c->rho_f_fresh = true;
   if (energy_eV) {
-    VC_CHECK(c, vc::launch_reduce_sum(c, c->eatom, c->n, c->red + (c->n + vc::BLOCK - 1) / vc::BLOCK + 1),
-             "reduce");
-    double h = 0.0;
-    VC_CHECK(c, hipMemcpyAsync(&h, c->red + (c->n + vc::BLOCK - 1) / vc::BLOCK + 1, sizeof(double),
-                               hipMemcpyDeviceToHost, c->stream),
-             "copy");
+    VC_CHECK(c, vc::launch_reduce_sum(c, c->eatom, c->n, c->h_tot), "reduce");
     VC_CHECK(c, hipStreamSynchronize(c->stream), "sync");
-    *energy_eV = h;
+    *energy_eV = c->h_tot[0];
   }
   return VCSGC_OK;
 }
@@ -995,7 +994,7 @@ vcsgc_status md_steps_device(vcsgc_ctx *c, double dt_fs, int64_t n_steps) {
   // the last force pass stores the forces for the closing half kick
   VC_CHECK(c, vc::launch_forces_kick_drift(c, dt_fs, false, 0), "forces");
   for (int64_t k = 0; k < n_steps; ++k) {
-    VC_CHECK(c, vc::launch_md_rebuild_cond(c, (int)(k & 1)), "neighbour list (MD)");
+    VC_CHECK(c, vc::launch_md_rebuild_cond(c, (int)(k & 1), vc::md_binned_drift(c)), "neighbour list (MD)");
     if (k + 1 < n_steps)
       VC_CHECK(c, vc::launch_forces_kick_drift(c, dt_fs, true, (int)((k + 1) & 1)), "forces");
     else
@@ -1056,7 +1055,7 @@ vcsgc_status md_nvt_steps(vcsgc_ctx *c, double dt_fs, int64_t n_steps, bool dev)
     const int par = dev ? (int)(k & 1) : 0;
     VC_CHECK(c, vc::launch_nvt_kick_drift(c, dt_fs, par), "kick-drift");
     if (dev) {
-      VC_CHECK(c, vc::launch_md_rebuild_cond(c, par), "neighbour list (MD)");
+      VC_CHECK(c, vc::launch_md_rebuild_cond(c, par, vc::md_binned_drift(c)), "neighbour list (MD)");
     } else {
       int flag = 0;
       VC_CHECK(c, hipMemcpyAsync(&flag, &c->ds->rebuild[0], sizeof(int), hipMemcpyDeviceToHost,
@@ -1100,48 +1099,77 @@ vcsgc_status md_nvt_steps(vcsgc_ctx *c, double dt_fs, int64_t n_steps, bool dev)
   return md_nvt_steps(c, dt_fs, n_steps, false);
 }
 
-// Energy (fixed-shape total into *e) and forces at the current positions:
-// the MD list is rebuilt first when the last move raised ds->rebuild[0].
-vcsgc_status cg_eval(vcsgc_ctx *c, bool check_list, double *e) {
-  if (check_list) {
-    int flag = 0;
-    VC_CHECK(c, hipMemcpyAsync(&flag, &c->ds->rebuild[0], sizeof(int), hipMemcpyDeviceToHost,
-                               c->stream),
-             "copy");
-    VC_CHECK(c, hipStreamSynchronize(c->stream), "sync");
-    if (flag) {
-      VC_CHECK(c, hipMemsetAsync(&c->ds->rebuild[0], 0, sizeof(int), c->stream), "reset");
-      vcsgc_status st = refresh_md(c);
-      if (st) return st;
-    }
+// After a device-decided rebuild that overflowed (code of k_totals): the bins
+// grow if it was a bin, and the list is rebuilt on the host's decisions.
+vcsgc_status rebuild_after_overflow(vcsgc_ctx *c, int code) {
+  const int zero[2] = {0, 0};
+  VC_CHECK(c, hipMemcpyAsync(&c->ds->overflow, zero, 2 * sizeof(int), hipMemcpyHostToDevice,
+                             c->stream),
+           "reset");
+  if (code & 1) {
+    vcsgc_status st = grow_bins(c);
+    if (st) return st;
   }
-  VC_CHECK(c, vc::launch_energy(c), "energy");
-  VC_CHECK(c, vc::launch_forces_only(c), "forces");
-  double *out = c->red + (c->n + vc::BLOCK - 1) / vc::BLOCK + 1;
-  VC_CHECK(c, vc::launch_reduce_sum(c, c->eatom, c->n, out), "reduce");
-  VC_CHECK(c, hipMemcpyAsync(e, out, sizeof(double), hipMemcpyDeviceToHost, c->stream), "copy");
-  VC_CHECK(c, hipStreamSynchronize(c->stream), "sync");
-  return VCSGC_OK;
+  return refresh_md(c);
 }
 
-// the two totals of mode 0 or 1 (launch_cg_totals) on the host
-vcsgc_status cg_totals(vcsgc_ctx *c, int mode, const double *u, double out[2]) {
-  const int64_t nch = (c->n + vc::BLOCK - 1) / vc::BLOCK;
-  double *part = c->cg + 9 * c->n, *dev_out = part + 2 * nch;
-  VC_CHECK(c, vc::launch_cg_totals(c, mode, u, part, dev_out), "relaxation");
-  VC_CHECK(c, hipMemcpyAsync(out, dev_out, 2 * sizeof(double), hipMemcpyDeviceToHost, c->stream),
+// the host's part of a list rebuild decision: the flag of the last move
+vcsgc_status rebuild_if_due(vcsgc_ctx *c) {
+  int flag = 0;
+  VC_CHECK(c, hipMemcpyAsync(&flag, &c->ds->rebuild[0], sizeof(int), hipMemcpyDeviceToHost,
+                             c->stream),
            "copy");
   VC_CHECK(c, hipStreamSynchronize(c->stream), "sync");
-  return VCSGC_OK;
+  if (!flag) return VCSGC_OK;
+  VC_CHECK(c, hipMemsetAsync(&c->ds->rebuild[0], 0, sizeof(int), c->stream), "reset");
+  return refresh_md(c);
 }
 
-// three device vectors of n doubles into one of 3 n
-vcsgc_status cg_gather3(vcsgc_ctx *c, double *dst, double *a, double *b, double *d) {
-  const size_t nb = sizeof(double) * (size_t)c->n;
-  double *src[3] = {a, b, d};
-  for (int k = 0; k < 3; ++k)
-    VC_CHECK(c, hipMemcpyAsync(dst + k * c->n, src[k], nb, hipMemcpyDeviceToDevice, c->stream),
-             "copy");
+// a device-decided rebuild has been taken: the list is of the current box
+void rebuilt_on_device(vcsgc_ctx *c) {
+  c->md_rebuilds += 1;
+  for (int d = 0; d < 3; ++d) c->box_build[d] = c->box[d];
+}
+
+// Energy, forces, F . F and F . f0 (fixed-shape totals into t[0..2]) at the
+// current positions; after a move the MD list is rebuilt first when it raised
+// ds->rebuild[0].  One host round trip (a relaxation's iteration took four,
+// with the decision, the energy and the totals each in one).
+vcsgc_status cg_eval(vcsgc_ctx *c, bool after_move, const double *f0, double t[3]) {
+  double *part = c->cg + 9 * c->n;
+  const double *h = c->h_tot;
+  const bool dev = after_move && vc::md_rebuild_on_device(c);
+  if (after_move && !dev) {
+    vcsgc_status st = rebuild_if_due(c);
+    if (st) return st;
+  }
+  if (dev)
+    VC_CHECK(c, vc::launch_md_rebuild_cond(c, 0, vc::md_binned_drift(c)), "neighbour list (MD)");
+  for (;;) {
+    VC_CHECK(c, vc::launch_energy(c), "energy");
+    VC_CHECK(c, vc::launch_forces_only(c), "forces");
+    VC_CHECK(c, vc::launch_cg_eval(c, f0, part, c->h_tot), "relaxation");
+    VC_CHECK(c, hipStreamSynchronize(c->stream), "sync");
+    for (int k = 0; k < 3; ++k) t[k] = h[k];
+    if (dev && h[3] != 0.0) {
+      vcsgc_status st = rebuild_after_overflow(c, (int)h[3]);
+      if (st) return st;
+      continue;
+    }
+    if (dev && h[4] != 0.0) rebuilt_on_device(c);
+    return VCSGC_OK;
+  }
+}
+
+// A line search's start (launch_cg_start): F . d and max |d_i|^2 into t.
+vcsgc_status cg_start(vcsgc_ctx *c, double b, bool copy, double t[2]) {
+  const int64_t n = c->n;
+  VC_CHECK(c, vc::launch_cg_start(c, c->cg, c->cg + 3 * n, c->cg + 6 * n, b, copy, c->cg + 9 * n,
+                                  c->h_tot),
+           "relaxation");
+  VC_CHECK(c, hipStreamSynchronize(c->stream), "sync");
+  t[0] = c->h_tot[0];
+  t[1] = c->h_tot[1];
   return VCSGC_OK;
 }
 
@@ -1180,23 +1208,33 @@ double npt_thermo(double h, double g1kT, double Q, double W, double &K, double &
 
 // Forces with the virial terms at the current positions, the closing kick
 // (if kick), and the totals: *K (eV) and *vir (eV).
-vcsgc_status npt_forces_sums(vcsgc_ctx *c, bool kick, double cv, double h, double *K,
-                             double *vir) {
-  const int64_t nch = (c->n + vc::BLOCK - 1) / vc::BLOCK;
-  double *out = c->npt_part + 2 * nch;
-  VC_CHECK(c, vc::launch_forces_virial(c, c->eatom), "forces");
-  VC_CHECK(c, vc::launch_npt_sums(c, kick, cv, h, c->eatom, c->npt_part, out), "barostat");
-  double t[2];
-  VC_CHECK(c, hipMemcpyAsync(t, out, sizeof(t), hipMemcpyDeviceToHost, c->stream), "copy");
-  VC_CHECK(c, hipStreamSynchronize(c->stream), "sync");
-  *K = 0.5 * t[0] / vc::ACC;
-  *vir = -0.5 * t[1];
-  return VCSGC_OK;
+// dev: a device-decided rebuild comes first (binned: of atoms the drift has
+// binned).
+vcsgc_status npt_forces_sums(vcsgc_ctx *c, bool kick, bool dev, bool binned, double cv, double h,
+                             double *K, double *vir) {
+  const double *t = c->h_tot;
+  if (dev) VC_CHECK(c, vc::launch_md_rebuild_cond(c, 0, binned), "neighbour list (MD)");
+  for (;;) {
+    VC_CHECK(c, vc::launch_forces_virial(c, c->eatom), "forces");
+    VC_CHECK(c, vc::launch_npt_sums(c, kick, cv, h, c->eatom, c->npt_part, c->h_tot), "barostat");
+    VC_CHECK(c, hipStreamSynchronize(c->stream), "sync");
+    if (dev && t[2] != 0.0) {  // nothing was kicked
+      vcsgc_status st = rebuild_after_overflow(c, (int)t[2]);
+      if (st) return st;
+      continue;
+    }
+    if (dev && t[3] != 0.0) rebuilt_on_device(c);
+    *K = 0.5 * t[0] / vc::ACC;
+    *vir = -0.5 * t[1];
+    return VCSGC_OK;
+  }
 }
 
 // Nose-Hoover NPT steps, driven from the host (the box changes every step;
-// its edges are kernel arguments).  The MD list is rebuilt on the host's
-// decision; c->eatom holds the per-atom virial terms.
+// its edges are kernel arguments), one round trip per step: the MD list is
+// rebuilt on the device's decision (on the host's where the search bins do
+// not allow it), and the flags come with the totals.  c->eatom holds the
+// per-atom virial terms.
 vcsgc_status md_npt_steps(vcsgc_ctx *c, double dt, int64_t n_steps) {
   const int64_t n = c->n;
   if (!c->npt_part)
@@ -1215,7 +1253,7 @@ vcsgc_status md_npt_steps(vcsgc_ctx *c, double dt, int64_t n_steps) {
   VC_CHECK(c, hipMemsetAsync(&c->ds->rebuild[0], 0, sizeof(int), c->stream), "reset");
   VC_CHECK(c, vc::launch_pack(c), "pack");
   double K = 0.0, vir = 0.0;
-  vcsgc_status st = npt_forces_sums(c, false, 1.0, h, &K, &vir);
+  vcsgc_status st = npt_forces_sums(c, false, false, false, 1.0, h, &K, &vir);
   if (st) return st;
   double s_pend = 1.0;
   // writes the thermostat and barostat state back (the velocities take the
@@ -1250,17 +1288,12 @@ vcsgc_status md_npt_steps(vcsgc_ctx *c, double dt, int64_t n_steps) {
       lmin = std::min(lmin, lam[d]);
     }
     const double thr = 0.5 * (lmin * reach - rc);
-    VC_CHECK(c, vc::launch_npt_kick_drift(c, s_pend, s, cv, h, dt, q, lam, thr), "kick-drift");
-    int flag = 0;
-    VC_CHECK(c, hipMemcpyAsync(&flag, &c->ds->rebuild[0], sizeof(int), hipMemcpyDeviceToHost,
-                               c->stream),
-             "copy");
-    VC_CHECK(c, hipStreamSynchronize(c->stream), "sync");
-    if (flag) {
-      VC_CHECK(c, hipMemsetAsync(&c->ds->rebuild[0], 0, sizeof(int), c->stream), "reset");
-      if ((st = refresh_md(c))) return st;
-    }
-    if ((st = npt_forces_sums(c, true, cv, h, &K, &vir))) return st;
+    // (the grid of search bins may have changed with the box)
+    const bool dev = vc::md_rebuild_on_device(c), binned = c->bins_clear && vc::md_binned_drift(c);
+    VC_CHECK(c, vc::launch_npt_kick_drift(c, s_pend, s, cv, h, dt, q, lam, thr, binned),
+             "kick-drift");
+    if (!dev && (st = rebuild_if_due(c))) return st;
+    if ((st = npt_forces_sums(c, true, dev, binned, cv, h, &K, &vir))) return st;
     V = c->box[0] * c->box[1] * c->box[2];
     P = (2.0 * K + vir) / (3.0 * V);
     pe = pe + h * (3.0 * V * (P - c->npt_p) + (3.0 / g) * (2.0 * K));
@@ -1336,7 +1369,7 @@ vcsgc_status vcsgc_minimize(vcsgc_ctx *c, const vcsgc_cg_params *prm, vcsgc_cg_r
     return fail(c, VCSGC_E_INVALID_ARG,
                 "need max_iter, max_eval >= 0, finite etol, ftol >= 0, 0 < dmax < L/2");
   const int64_t n = c->n;
-  if (!c->cg) VC_CHECK(c, dalloc(&c->cg, 9 * (size_t)n + 2 * (size_t)((n + vc::BLOCK - 1) / vc::BLOCK) + 8),
+  if (!c->cg) VC_CHECK(c, dalloc(&c->cg, 9 * (size_t)n + 3 * (size_t)((n + vc::BLOCK - 1) / vc::BLOCK) + 8),
                        "allocation");
   double *d = c->cg, *x0 = c->cg + 3 * n, *f0 = c->cg + 6 * n;
   c->rho_f_fresh = false;
@@ -1346,14 +1379,10 @@ vcsgc_status vcsgc_minimize(vcsgc_ctx *c, const vcsgc_cg_params *prm, vcsgc_cg_r
   }
   VC_CHECK(c, hipMemsetAsync(&c->ds->rebuild[0], 0, sizeof(int), c->stream), "reset");
   VC_CHECK(c, vc::launch_pack(c), "pack");
-  double E = 0.0;
-  st = cg_eval(c, false, &E);
+  double e[3], t[2];
+  st = cg_eval(c, false, f0, e);  // (F . f0 means nothing yet)
   if (st) return st;
-  VC_CHECK(c, vc::launch_cg_dir(c, d, 0.0, true), "relaxation");
-  double t[2];
-  st = cg_totals(c, 1, d, t);
-  if (st) return st;
-  double gg = t[0], dE_prev = 0.0;
+  double E = e[0], gg = e[1], b = 0.0, dE_prev = 0.0;
   int64_t it = 0, ev = 0;
   int32_t reason = 0;
   bool moved = false;
@@ -1370,11 +1399,11 @@ vcsgc_status vcsgc_minimize(vcsgc_ctx *c, const vcsgc_cg_params *prm, vcsgc_cg_r
       reason = VCSGC_CG_EVAL;
       break;
     }
-    if ((st = cg_totals(c, 0, d, t))) return st;
+    // d = F, or F + b d
+    if ((st = cg_start(c, b, it == 0, t))) return st;
     double sl = t[0], dm2 = t[1];
     if (!(sl > 0.0)) {  // not a descent direction: restart along the force
-      VC_CHECK(c, vc::launch_cg_dir(c, d, 0.0, true), "relaxation");
-      if ((st = cg_totals(c, 0, d, t))) return st;
+      if ((st = cg_start(c, 0.0, true, t))) return st;
       sl = t[0];
       dm2 = t[1];
     }
@@ -1383,14 +1412,13 @@ vcsgc_status vcsgc_minimize(vcsgc_ctx *c, const vcsgc_cg_params *prm, vcsgc_cg_r
       const double a1 = 2.0 * dE_prev / sl;
       if (a1 < a) a = a1;
     }
-    if ((st = cg_gather3(c, x0, c->x, c->y, c->z))) return st;
-    if ((st = cg_gather3(c, f0, c->fx, c->fy, c->fz))) return st;
     double Et = 0.0;
     bool accepted = false;
     for (int k = 0; k < VCSGC_CG_TRIALS; ++k) {
       VC_CHECK(c, vc::launch_cg_move(c, x0, d, a), "relaxation");
       moved = true;
-      if ((st = cg_eval(c, true, &Et))) return st;
+      if ((st = cg_eval(c, true, f0, e))) return st;
+      Et = e[0];
       ev += 1;
       if (Et <= E - VCSGC_CG_C1 * a * sl && Et < E) {
         accepted = true;
@@ -1400,16 +1428,13 @@ vcsgc_status vcsgc_minimize(vcsgc_ctx *c, const vcsgc_cg_params *prm, vcsgc_cg_r
     }
     if (!accepted) {  // back to the line search's start (forces recomputed there)
       VC_CHECK(c, vc::launch_cg_move(c, x0, d, 0.0), "relaxation");
-      double e_back = 0.0;
-      if ((st = cg_eval(c, true, &e_back))) return st;
+      if ((st = cg_eval(c, true, f0, e))) return st;
       reason = VCSGC_CG_LINESEARCH;
       break;
     }
-    if ((st = cg_totals(c, 1, f0, t))) return st;
-    const double g_new = t[0], g_mix = t[1];
-    double b = (g_new - g_mix) / gg;
+    const double g_new = e[1], g_mix = e[2];
+    b = (g_new - g_mix) / gg;
     if (!(b > 0.0)) b = 0.0;
-    VC_CHECK(c, vc::launch_cg_dir(c, d, b, false), "relaxation");
     const double dE = E - Et;
     dE_prev = dE;
     E = Et;

@@ -336,6 +336,7 @@ __global__ void k_bin_search(int64_t n, const double *__restrict__ x, const doub
 
 // search bins of one replica (local atom indices)
 hipError_t launch_bin_search(vcsgc_ctx *c, const RepHost &r) {
+  c->bins_clear = false;
   Grid g{r.box[0], r.box[1], r.box[2], r.nb[0], r.nb[1], r.nb[2]};
   int32_t *count = c->bin_count + r.boff, *atoms = c->bin_atoms + r.boff * c->bmax;
   hipError_t e = hipMemsetAsync(count, 0, sizeof(int32_t) * r.nbins, c->stream);
@@ -951,21 +952,20 @@ hipError_t launch_build_md_list(vcsgc_ctx *c) {
 }
 
 // MD list rebuild decided on the device, for step parity par: every kernel
-// returns at once unless the last drift raised ds->rebuild[par].  The bin
-// counts were cleared by that drift.  Overflows are flagged as in the
+// returns at once unless the last drift raised ds->rebuild[par].  binned: that
+// drift has binned its atoms (md_binned_drift), else it cleared the counts.  Overflows are flagged as in the
 // host-decided path; the caller checks them once at the end of its steps.
 constexpr int BIN_GRID = 2048;  // blocks of a device-decided binning (at most)
 
-hipError_t launch_md_rebuild_cond(vcsgc_ctx *c, int par) {
+hipError_t launch_md_rebuild_cond(vcsgc_ctx *c, int par, bool binned) {
   const RepHost &r = c->reps[0];
   Grid g{r.box[0], r.box[1], r.box[2], r.nb[0], r.nb[1], r.nb[2]};
   const int *cond = &c->ds->rebuild[par];
   int h = tstart(c, VCSGC_KT_BUILD);
-  const bool fused = md_binned_drift(c);
-  if (!fused)
+  if (!binned)
     k_bin_search<<<std::min(grid_for(r.n), BIN_GRID), BLOCK, 0, c->stream>>>(
         r.n, c->x, c->y, c->z, g, c->bmax, c->bin_count, c->bin_atoms, c->bin_pos, c->ds, cond);
-  hipError_t e = launch_md_build_chain(c, g, cond, fused);
+  hipError_t e = launch_md_build_chain(c, g, cond, binned);
   tstop(c, h);
   return e;
 }

@@ -581,6 +581,10 @@ struct vcsgc_ctx {
   // pinned copy of the device state, read by the pipeline's progress checks;
   // h_state_final: the last check saw the call's end (statistics included)
   vc::DevState *h_state = nullptr;
+  // totals a kernel leaves for the host (pinned; 8 doubles)
+  double *h_tot = nullptr;
+  // the bin counts are zero: cleared by the last density pass, no binning since
+  bool bins_clear = false;
   bool h_state_final = false;
   double m_acc_rate = 0.05;             // accepted stages per stage, last call
   double m_spec_rate = 0.0;             // batched pipeline: kernels per stage, last call
@@ -621,6 +625,7 @@ struct vcsgc_ctx {
   // persistent batched sweep
   void *d_reps = nullptr;     // per-replica parameters (device)
   void *h_reps = nullptr;     // pinned staging buffer for them
+  void *h_rs = nullptr;       // pinned copy of the replicas' states
   void *d_rs = nullptr;       // per-replica chain state and counters
   int32_t *d_wg_rep = nullptr;  // workgroup -> replica
   int grid_total = 0;
@@ -667,7 +672,7 @@ hipError_t launch_bin_cells(vcsgc_ctx *c, const RepHost &r);
 hipError_t launch_bin_search(vcsgc_ctx *c, const RepHost &r);
 hipError_t launch_build_mc_list(vcsgc_ctx *c, const RepHost &r);
 hipError_t launch_build_md_list(vcsgc_ctx *c);
-hipError_t launch_md_rebuild_cond(vcsgc_ctx *c, int par);
+hipError_t launch_md_rebuild_cond(vcsgc_ctx *c, int par, bool binned);
 bool md_rebuild_on_device(const vcsgc_ctx *c);
 bool md_binned_drift(const vcsgc_ctx *c);
 hipError_t launch_mc_row_stats(vcsgc_ctx *c);
@@ -700,15 +705,16 @@ hipError_t launch_nvt_scale(vcsgc_ctx *c);
 // totals (mode 0: F . u and max |u_i|^2; mode 1: F . F and F . u) into
 // out[0..1] through part [2 ceil(n / BLOCK)]; d = F or d = F + b d
 hipError_t launch_cg_move(vcsgc_ctx *c, const double *x0, const double *d, double a);
-hipError_t launch_cg_totals(vcsgc_ctx *c, int mode, const double *u, double *part, double *out);
-hipError_t launch_cg_dir(vcsgc_ctx *c, double *d, double b, bool copy);
+hipError_t launch_cg_start(vcsgc_ctx *c, double *d, double *x0, double *f0, double b, bool copy,
+                           double *part, double *out);
+hipError_t launch_cg_eval(vcsgc_ctx *c, const double *f0, double *part, double *out);
 // NPT: forces with the per-atom virial terms w; the step's scalings, kick
 // and drift (launch_npt_kick_drift); the closing kick (if kick) with the
 // totals of m v^2 and w into out[0..1] through part [2 ceil(n / BLOCK)];
 // v *= s
 hipError_t launch_forces_virial(vcsgc_ctx *c, double *w);
 hipError_t launch_npt_kick_drift(vcsgc_ctx *c, double f1, double f2, double cv, double h,
-                                 double dt, double q, const double lam[3], double thr);
+                                 double dt, double q, const double lam[3], double thr, bool binned);
 hipError_t launch_npt_sums(vcsgc_ctx *c, bool kick, double cv, double h, const double *w,
                            double *part, double *out);
 hipError_t launch_scale_v(vcsgc_ctx *c, double s);

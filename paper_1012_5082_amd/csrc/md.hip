@@ -270,31 +270,49 @@ __global__ void __launch_bounds__(BLOCK)
   if (lane == 0) density_store<TAB, EN>(i, qi, s, p, rho, pf4, e);
 }
 
+// The part of a drift that readies the next device-decided rebuild: with pos
+// the moved atom goes to its search bin (count, bmax slots each; a bin with
+// more atoms than slots is the list build's to report), else the counts are
+// cleared for the binning kernel.
+struct BinDrift {
+  int32_t *count;
+  int64_t nbins;
+  double4 *pos;
+  Grid g;
+  int bmax;
+};
+__device__ __forceinline__ void bin_drift_clear(const BinDrift &d, int64_t i, int64_t threads) {
+  if (!d.pos)
+    for (int64_t q = i; q < d.nbins; q += threads) d.count[q] = 0;
+}
+__device__ __forceinline__ void bin_drift_add(const BinDrift &d, int64_t i, double x, double y,
+                                              double z) {
+  if (!d.pos) return;
+  const int bin = cell_of(d.g, x, y, z);
+  const int slot = atomicAdd(&d.count[bin], 1);
+  if (slot < d.bmax) d.pos[(int64_t)bin * d.bmax + slot] = make_double4(x, y, z, (double)i);
+}
+
 // [v += (dt/2)(F cm) (closing the previous step) ;] v += (dt/2)(F cm);
 // x = wrap(x + dt v); raise ds->rebuild[par] when an atom has moved more than
 // skin/2 from its position at the last build.  Also readies the next
 // device-decided rebuild: the flag of the other parity (read by the previous
 // step's rebuild kernels, which have finished) is cleared, and so are the
-// search-bin counts (bcount may be NULL).
+// search bins.
 struct KickDrift {
   double *x, *y, *z, *vx, *vy, *vz;
   const double *xr, *yr, *zr;  // positions at the last MD-list build
   double2 *ps4;
   double dt, half_skin2;
   int kick_first, par;
-  int32_t *bcount;
-  int64_t nbins;
+  BinDrift bins;
   DevState *ds;
-  double4 *bpos;  // not NULL: the drifted atom goes to its search bin (bcount, bmax slots each)
-  Grid g;
-  int bmax;
   const double *nvt;  // Nose-Hoover: v = (v s1) s2 before the kick (nvt[3], nvt[4]); NULL: none
 };
 
 // The step's clearing work, by thread i of a grid of `threads`.
 __device__ __forceinline__ void kick_drift_clear(const KickDrift &k, int64_t i, int64_t threads) {
-  if (k.bcount && !k.bpos)
-    for (int64_t q = i; q < k.nbins; q += threads) k.bcount[q] = 0;
+  bin_drift_clear(k.bins, i, threads);
   if (i == 0) k.ds->rebuild[k.par ^ 1] = 0;
 }
 
@@ -341,11 +359,7 @@ __device__ __forceinline__ void kick_drift_atom(const KickDrift &k, const KickIn
   k.y[i] = ny;
   k.z[i] = nz;
   packed_store(k.ps4, i, nx, ny, nz, (double)s);
-  if (k.bpos) {  // a bin with more atoms than slots is the list build's to report
-    const int bin = cell_of(k.g, nx, ny, nz);
-    const int slot = atomicAdd(&k.bcount[bin], 1);
-    if (slot < k.bmax) k.bpos[(int64_t)bin * k.bmax + slot] = make_double4(nx, ny, nz, (double)i);
-  }
+  bin_drift_add(k.bins, i, nx, ny, nz);
   const double ex = min_image(nx - in.xr, b.L0);
   const double ey = min_image(ny - in.yr, b.L1);
   const double ez = min_image(nz - in.zr, b.L2);
@@ -544,7 +558,8 @@ static int lanes_per_atom(const vcsgc_ctx *c, bool steps) {
 template <int LPA, bool EN>
 static void density_md_on(vcsgc_ctx *c, const Box &b) {
   const double reach = list_reach(c);
-  const BinClear bc = {!EN && md_binned_drift(c) ? c->bin_count : nullptr, c->reps[0].nbins, c->ds};
+  const BinClear bc = {md_binned_drift(c) ? c->bin_count : nullptr, c->nbins_total, c->ds};
+  c->bins_clear = bc.count != nullptr;
   if (c->pot.tab)
     k_density_md<LPA, true, EN><<<grid_for(c->n * LPA), BLOCK, 0, c->stream>>>(
         c->n, c->ps4, c->md_j, c->md_cnt, b, reach, c->pot, c->rho_f, c->pf4, c->eatom, bc);
@@ -597,6 +612,13 @@ hipError_t launch_forces(vcsgc_ctx *c) {
   return launch_forces_only(c);
 }
 
+static BinDrift bin_drift_args(vcsgc_ctx *c, bool binned) {
+  c->bins_clear = false;
+  const int *nb = c->reps[0].nb;
+  return BinDrift{c->bin_count, c->reps[0].nbins, binned ? c->bin_pos : nullptr,
+                  Grid{c->box[0], c->box[1], c->box[2], nb[0], nb[1], nb[2]}, c->bmax};
+}
+
 static KickDrift kick_drift_args(vcsgc_ctx *c, double dt, bool kick_first, int par) {
   const double hs = 0.5 * c->skin;
   KickDrift k{};
@@ -614,14 +636,7 @@ static KickDrift kick_drift_args(vcsgc_ctx *c, double dt, bool kick_first, int p
   k.half_skin2 = hs * hs;
   k.kick_first = kick_first ? 1 : 0;
   k.par = par;
-  k.bcount = c->bin_count;
-  k.nbins = c->reps[0].nbins;
-  if (md_binned_drift(c)) {
-    const int *nb = c->reps[0].nb;
-    k.bpos = c->bin_pos;
-    k.g = Grid{c->box[0], c->box[1], c->box[2], nb[0], nb[1], nb[2]};
-    k.bmax = c->bmax;
-  }
+  k.bins = bin_drift_args(c, md_binned_drift(c));
   k.ds = c->ds;
   return k;
 }
@@ -839,8 +854,10 @@ __global__ void __launch_bounds__(BLOCK)
     k_cg_move(int64_t n, const double *__restrict__ x0, const double *__restrict__ d, double a,
               double *x, double *y, double *z, const uint8_t *__restrict__ sp, double2 *ps4,
               const double *__restrict__ xr, const double *__restrict__ yr,
-              const double *__restrict__ zr, Box b, double half_skin2, DevState *ds) {
+              const double *__restrict__ zr, Box b, double half_skin2, BinDrift bins,
+              DevState *ds) {
   const int64_t i = (int64_t)blockIdx.x * BLOCK + threadIdx.x;
+  bin_drift_clear(bins, i, (int64_t)gridDim.x * BLOCK);
   bool far = false;
   if (i < n) {
     const double nx = wrap_box(x0[i] + a * d[i], b.L0);
@@ -850,6 +867,7 @@ __global__ void __launch_bounds__(BLOCK)
     y[i] = ny;
     z[i] = nz;
     packed_store(ps4, i, nx, ny, nz, (double)sp[i]);
+    bin_drift_add(bins, i, nx, ny, nz);
     const double ex = min_image(nx - xr[i], b.L0);
     const double ey = min_image(ny - yr[i], b.L1);
     const double ez = min_image(nz - zr[i], b.L2);
@@ -859,86 +877,117 @@ __global__ void __launch_bounds__(BLOCK)
   if (moved && __lane_id() == __ffsll((long long)moved) - 1) atomicOr(&ds->rebuild[0], 1);
 }
 
-// Chunk values of two totals, per-atom dot terms (a_x b_x + a_y b_y) + a_z b_z:
-// MODE 0: F . u and max_i |u_i|^2;  MODE 1: F . F and F . u.
-// part[c] and part[nch + c] for chunk c.
-template <int MODE>
-__global__ void __launch_bounds__(BLOCK)
-    k_cg_part(int64_t n, const double *__restrict__ fx, const double *__restrict__ fy,
-              const double *__restrict__ fz, const double *__restrict__ u, double *part) {
-  __shared__ double s0[BLOCK], s1[BLOCK];
+// K values per thread into the block's chunk values (halving strides; the
+// last by maximum if MAX), value k of chunk c into part[k nch + c].
+template <int K, bool MAX>
+__device__ __forceinline__ void chunk_values(const double (&v)[K], double *part) {
+  __shared__ double s[K][BLOCK];
   const int t = threadIdx.x;
-  const int64_t i = (int64_t)blockIdx.x * BLOCK + t;
-  double a = 0.0, q = 0.0;
+#pragma unroll
+  for (int k = 0; k < K; ++k) s[k][t] = v[k];
+  __syncthreads();
+  for (int h = BLOCK / 2; h > 0; h >>= 1) {
+    if (t < h)
+#pragma unroll
+      for (int k = 0; k < K; ++k)
+        s[k][t] = MAX && k == K - 1 ? fmax(s[k][t], s[k][t + h]) : s[k][t] + s[k][t + h];
+    __syncthreads();
+  }
+  if (t == 0)
+#pragma unroll
+    for (int k = 0; k < K; ++k) part[(int64_t)k * gridDim.x + blockIdx.x] = s[k][0];
+}
+
+// The start of a line search: the direction d = F (copy) or d = F + b d, the
+// positions and forces kept for it (x0, f0), and the chunk values of F . d and
+// max_i |d_i|^2; per-atom dot terms (a_x b_x + a_y b_y) + a_z b_z.
+__global__ void __launch_bounds__(BLOCK)
+    k_cg_start(int64_t n, const double *__restrict__ x, const double *__restrict__ y,
+               const double *__restrict__ z, const double *__restrict__ fx,
+               const double *__restrict__ fy, const double *__restrict__ fz, double *d, double *x0,
+               double *f0, double b, int copy, double *part) {
+  const int64_t i = (int64_t)blockIdx.x * BLOCK + threadIdx.x;
+  double v[2] = {0.0, 0.0};
   if (i < n) {
     const double gx = fx[i], gy = fy[i], gz = fz[i];
-    const double ux = u[i], uy = u[n + i], uz = u[2 * n + i];
-    if (MODE == 0) {
-      a = (gx * ux + gy * uy) + gz * uz;
-      q = (ux * ux + uy * uy) + uz * uz;
-    } else {
-      a = (gx * gx + gy * gy) + gz * gz;
-      q = (gx * ux + gy * uy) + gz * uz;
+    double ux = gx, uy = gy, uz = gz;
+    if (!copy) {
+      ux = gx + b * d[i];
+      uy = gy + b * d[n + i];
+      uz = gz + b * d[2 * n + i];
     }
+    d[i] = ux;
+    d[n + i] = uy;
+    d[2 * n + i] = uz;
+    x0[i] = x[i];
+    x0[n + i] = y[i];
+    x0[2 * n + i] = z[i];
+    f0[i] = gx;
+    f0[n + i] = gy;
+    f0[2 * n + i] = gz;
+    v[0] = (gx * ux + gy * uy) + gz * uz;
+    v[1] = (ux * ux + uy * uy) + uz * uz;
   }
-  s0[t] = a;
-  s1[t] = q;
-  __syncthreads();
-  for (int h = BLOCK / 2; h > 0; h >>= 1) {
-    if (t < h) {
-      s0[t] = s0[t] + s0[t + h];
-      s1[t] = MODE == 0 ? fmax(s1[t], s1[t + h]) : s1[t] + s1[t + h];
-    }
-    __syncthreads();
-  }
-  if (t == 0) {
-    const int64_t nch = gridDim.x;
-    part[blockIdx.x] = s0[0];
-    part[nch + blockIdx.x] = s1[0];
-  }
+  chunk_values<2, true>(v, part);
 }
 
-// the two totals from the chunk values (one block): out[0], out[1]
-template <int MODE>
+// Chunk values of an evaluation: E, F . F and F . f0.
 __global__ void __launch_bounds__(BLOCK)
-    k_cg_total(int64_t nch, const double *__restrict__ part, double *out) {
-  __shared__ double s0[BLOCK], s1[BLOCK];
-  const int t = threadIdx.x;
-  double a = 0.0, q = 0.0;
-  for (int64_t c = t; c < nch; c += BLOCK) {
-    a = a + part[c];
-    q = MODE == 0 ? fmax(q, part[nch + c]) : q + part[nch + c];
-  }
-  s0[t] = a;
-  s1[t] = q;
-  __syncthreads();
-  for (int h = BLOCK / 2; h > 0; h >>= 1) {
-    if (t < h) {
-      s0[t] = s0[t] + s0[t + h];
-      s1[t] = MODE == 0 ? fmax(s1[t], s1[t + h]) : s1[t] + s1[t + h];
-    }
-    __syncthreads();
-  }
-  if (t == 0) {
-    out[0] = s0[0];
-    out[1] = s1[0];
-  }
-}
-
-// d = F (copy) or d = F + b d
-__global__ void __launch_bounds__(BLOCK)
-    k_cg_dir(int64_t n, const double *__restrict__ fx, const double *__restrict__ fy,
-             const double *__restrict__ fz, double *d, double b, int copy) {
+    k_cg_eval(int64_t n, const double *__restrict__ e, const double *__restrict__ fx,
+              const double *__restrict__ fy, const double *__restrict__ fz,
+              const double *__restrict__ f0, double *part) {
   const int64_t i = (int64_t)blockIdx.x * BLOCK + threadIdx.x;
-  if (i >= n) return;
-  if (copy) {
-    d[i] = fx[i];
-    d[n + i] = fy[i];
-    d[2 * n + i] = fz[i];
-  } else {
-    d[i] = fx[i] + b * d[i];
-    d[n + i] = fy[i] + b * d[n + i];
-    d[2 * n + i] = fz[i] + b * d[2 * n + i];
+  double v[3] = {0.0, 0.0, 0.0};
+  if (i < n) {
+    const double gx = fx[i], gy = fy[i], gz = fz[i];
+    v[0] = e[i];
+    v[1] = (gx * gx + gy * gy) + gz * gz;
+    v[2] = (gx * f0[i] + gy * f0[n + i]) + gz * f0[2 * n + i];
+  }
+  chunk_values<3, false>(v, part);
+}
+
+// The K totals from the chunk values (one block) into out[0..K); with ds also
+// out[K]: what a device-decided rebuild overflowed (1: a bin, 2: a row), and
+// out[K + 1]: whether one was due, the flag being lowered.  out is pinned host
+// memory: one synchronization tells the host all it has to know about a move
+// and the evaluation after it (a copy to pageable memory costs about 15 us
+// more, and there were four per line search and two per NPT step: ten line
+// searches at 128,000 atoms 2.2 -> 1.3 ms, 20 NPT steps at 2,000 atoms 1.55 ->
+// 0.85 ms, at 0.5M 4.1 -> 3.6 ms).
+template <int K, bool MAX>
+__global__ void __launch_bounds__(BLOCK)
+    k_totals(int64_t nch, const double *__restrict__ part, double *out, DevState *ds) {
+  __shared__ double s[K][BLOCK];
+  const int t = threadIdx.x;
+  double v[K];
+#pragma unroll
+  for (int k = 0; k < K; ++k) v[k] = 0.0;
+  for (int64_t c = t; c < nch; c += BLOCK) {
+#pragma unroll
+    for (int k = 0; k < K; ++k) {
+      const double p = part[k * nch + c];
+      v[k] = MAX && k == K - 1 ? fmax(v[k], p) : v[k] + p;
+    }
+  }
+#pragma unroll
+  for (int k = 0; k < K; ++k) s[k][t] = v[k];
+  __syncthreads();
+  for (int h = BLOCK / 2; h > 0; h >>= 1) {
+    if (t < h)
+#pragma unroll
+      for (int k = 0; k < K; ++k)
+        s[k][t] = MAX && k == K - 1 ? fmax(s[k][t], s[k][t + h]) : s[k][t] + s[k][t + h];
+    __syncthreads();
+  }
+  if (t == 0) {
+#pragma unroll
+    for (int k = 0; k < K; ++k) out[k] = s[k][0];
+    if (ds) {
+      out[K] = (ds->bin_overflow ? 1.0 : 0.0) + (ds->overflow ? 2.0 : 0.0);
+      out[K + 1] = ds->rebuild[0] ? 1.0 : 0.0;
+      ds->rebuild[0] = 0;
+    }
   }
 }
 
@@ -947,19 +996,23 @@ hipError_t launch_cg_move(vcsgc_ctx *c, const double *x0, const double *d, doubl
   const double hs = 0.5 * c->skin;
   k_cg_move<<<grid_for(c->n), BLOCK, 0, c->stream>>>(c->n, x0, d, a, c->x, c->y, c->z, c->sp,
                                                      c->ps4, c->xr, c->yr, c->zr, b, hs * hs,
-                                                     c->ds);
+                                                     bin_drift_args(c, md_binned_drift(c)), c->ds);
   return hipGetLastError();
 }
 
-hipError_t launch_cg_totals(vcsgc_ctx *c, int mode, const double *u, double *part, double *out) {
+hipError_t launch_cg_start(vcsgc_ctx *c, double *d, double *x0, double *f0, double b, bool copy,
+                           double *part, double *out) {
   const int nch = grid_for(c->n);
-  if (mode == 0) {
-    k_cg_part<0><<<nch, BLOCK, 0, c->stream>>>(c->n, c->fx, c->fy, c->fz, u, part);
-    k_cg_total<0><<<1, BLOCK, 0, c->stream>>>(nch, part, out);
-  } else {
-    k_cg_part<1><<<nch, BLOCK, 0, c->stream>>>(c->n, c->fx, c->fy, c->fz, u, part);
-    k_cg_total<1><<<1, BLOCK, 0, c->stream>>>(nch, part, out);
-  }
+  k_cg_start<<<nch, BLOCK, 0, c->stream>>>(c->n, c->x, c->y, c->z, c->fx, c->fy, c->fz, d, x0, f0,
+                                           b, copy ? 1 : 0, part);
+  k_totals<2, true><<<1, BLOCK, 0, c->stream>>>(nch, part, out, nullptr);
+  return hipGetLastError();
+}
+
+hipError_t launch_cg_eval(vcsgc_ctx *c, const double *f0, double *part, double *out) {
+  const int nch = grid_for(c->n);
+  k_cg_eval<<<nch, BLOCK, 0, c->stream>>>(c->n, c->eatom, c->fx, c->fy, c->fz, f0, part);
+  k_totals<3, false><<<1, BLOCK, 0, c->stream>>>(nch, part, out, c->ds);
   return hipGetLastError();
 }
 
@@ -981,8 +1034,9 @@ __global__ void __launch_bounds__(BLOCK)
                      double f1, double f2, double c, double h, double dt, double q, Box b,
                      double lx, double ly, double lz, double thr,
                      const double *__restrict__ xr, const double *__restrict__ yr,
-                     const double *__restrict__ zr, double2 *ps4, DevState *ds) {
+                     const double *__restrict__ zr, double2 *ps4, BinDrift bins, DevState *ds) {
   const int64_t i = (int64_t)blockIdx.x * BLOCK + threadIdx.x;
+  bin_drift_clear(bins, i, (int64_t)gridDim.x * BLOCK);
   bool far = false;
   if (i < n) {
     const int s = sp[i];
@@ -1013,6 +1067,7 @@ __global__ void __launch_bounds__(BLOCK)
     y[i] = ny;
     z[i] = nz;
     packed_store(ps4, i, nx, ny, nz, (double)s);
+    bin_drift_add(bins, i, nx, ny, nz);
     const double ex = min_image(nx - lx * xr[i], b.L0);
     const double ey = min_image(ny - ly * yr[i], b.L1);
     const double ez = min_image(nz - lz * zr[i], b.L2);
@@ -1022,18 +1077,19 @@ __global__ void __launch_bounds__(BLOCK)
   if (moved && __lane_id() == __ffsll((long long)moved) - 1) atomicOr(&ds->rebuild[0], 1);
 }
 
-// [v = v c; v += h a; v = v c;] chunk values of m ((vx^2 + vy^2) + vz^2)
-// into part[c] and of w into part[nch + c]
+// [v = v c; v += h a; v = v c;] chunk values of m ((vx^2 + vy^2) + vz^2) and
+// of w.  After a rebuild that overflowed nothing is kicked: the host rebuilds
+// and repeats the evaluation.
 template <bool KICK>
 __global__ void __launch_bounds__(BLOCK)
     k_npt_kick_sums(int64_t n, double *vx, double *vy, double *vz,
                     const double *__restrict__ fx, const double *__restrict__ fy,
                     const double *__restrict__ fz, const uint8_t *__restrict__ sp, PotD p,
-                    double c, double h, const double *__restrict__ w, double *part) {
-  __shared__ double s0[BLOCK], s1[BLOCK];
-  const int t = threadIdx.x;
-  const int64_t i = (int64_t)blockIdx.x * BLOCK + t;
-  double a = 0.0, q = 0.0;
+                    double c, double h, const double *__restrict__ w, double *part,
+                    const DevState *ds) {
+  const int64_t i = (int64_t)blockIdx.x * BLOCK + threadIdx.x;
+  if (KICK && (ds->bin_overflow || ds->overflow)) return;
+  double v[2] = {0.0, 0.0};
   if (i < n) {
     const int s = sp[i];
     double ux = vx[i], uy = vy[i], uz = vz[i];
@@ -1052,24 +1108,10 @@ __global__ void __launch_bounds__(BLOCK)
       vy[i] = uy;
       vz[i] = uz;
     }
-    a = by_species(p.mass, s) * ((ux * ux + uy * uy) + uz * uz);
-    q = w[i];
+    v[0] = by_species(p.mass, s) * ((ux * ux + uy * uy) + uz * uz);
+    v[1] = w[i];
   }
-  s0[t] = a;
-  s1[t] = q;
-  __syncthreads();
-  for (int hh = BLOCK / 2; hh > 0; hh >>= 1) {
-    if (t < hh) {
-      s0[t] = s0[t] + s0[t + hh];
-      s1[t] = s1[t] + s1[t + hh];
-    }
-    __syncthreads();
-  }
-  if (t == 0) {
-    const int64_t nch = gridDim.x;
-    part[blockIdx.x] = s0[0];
-    part[nch + blockIdx.x] = s1[0];
-  }
+  chunk_values<2, false>(v, part);
 }
 
 // v *= s
@@ -1105,12 +1147,14 @@ hipError_t launch_forces_virial(vcsgc_ctx *c, double *w) {
 }
 
 hipError_t launch_npt_kick_drift(vcsgc_ctx *c, double f1, double f2, double cv, double h,
-                                 double dt, double q, const double lam[3], double thr) {
+                                 double dt, double q, const double lam[3], double thr,
+                                 bool binned) {
   Box b{c->box[0], c->box[1], c->box[2]};
   int t = tstart(c, VCSGC_KT_KICKDRIFT);
   k_npt_kick_drift<<<grid_for(c->n), BLOCK, 0, c->stream>>>(
       c->n, c->x, c->y, c->z, c->vx, c->vy, c->vz, c->fx, c->fy, c->fz, c->sp, c->pot, f1, f2,
-      cv, h, dt, q, b, lam[0], lam[1], lam[2], thr, c->xr, c->yr, c->zr, c->ps4, c->ds);
+      cv, h, dt, q, b, lam[0], lam[1], lam[2], thr, c->xr, c->yr, c->zr, c->ps4,
+      bin_drift_args(c, binned), c->ds);
   tstop(c, t);
   return hipGetLastError();
 }
@@ -1121,24 +1165,18 @@ hipError_t launch_npt_sums(vcsgc_ctx *c, bool kick, double cv, double h, const d
   int t = tstart(c, VCSGC_KT_KICK);
   if (kick)
     k_npt_kick_sums<true><<<nch, BLOCK, 0, c->stream>>>(c->n, c->vx, c->vy, c->vz, c->fx, c->fy,
-                                                        c->fz, c->sp, c->pot, cv, h, w, part);
+                                                        c->fz, c->sp, c->pot, cv, h, w, part, c->ds);
   else
     k_npt_kick_sums<false><<<nch, BLOCK, 0, c->stream>>>(c->n, c->vx, c->vy, c->vz, c->fx,
                                                          c->fy, c->fz, c->sp, c->pot, cv, h, w,
-                                                         part);
-  k_cg_total<1><<<1, BLOCK, 0, c->stream>>>(nch, part, out);
+                                                         part, c->ds);
+  k_totals<2, false><<<1, BLOCK, 0, c->stream>>>(nch, part, out, c->ds);
   tstop(c, t);
   return hipGetLastError();
 }
 
 hipError_t launch_scale_v(vcsgc_ctx *c, double s) {
   k_scale_v<<<grid_for(c->n), BLOCK, 0, c->stream>>>(c->n, c->vx, c->vy, c->vz, s);
-  return hipGetLastError();
-}
-
-hipError_t launch_cg_dir(vcsgc_ctx *c, double *d, double b, bool copy) {
-  k_cg_dir<<<grid_for(c->n), BLOCK, 0, c->stream>>>(c->n, c->fx, c->fy, c->fz, d, b,
-                                                    copy ? 1 : 0);
   return hipGetLastError();
 }
 

@@ -48,6 +48,7 @@
 // exceeds the spin limit sets the replica's error flag and the workgroup
 // leaves the kernel, so the launch always drains.
 #include <algorithm>
+#include <cstddef>
 #include <mutex>
 #include <type_traits>
 
@@ -1324,9 +1325,11 @@ hipError_t launch_persistent_da(vcsgc_ctx *c) {
 // per-replica statistics after the call (synchronizes)
 hipError_t persist_read_stats(vcsgc_ctx *c, vcsgc_stats *out, int *err, bool da) {
   const int R = (int)c->reps.size();
-  std::vector<RepState> h(R);
-  hipError_t e = hipMemcpyAsync(h.data(), c->d_rs, sizeof(RepState) * R, hipMemcpyDeviceToHost,
-                                c->stream);
+  // (a pageable target would be staged); one replica: without the barrier words
+  RepState *h = (RepState *)c->h_rs;
+  const size_t off = R == 1 ? offsetof(RepState, n_b) : 0;
+  hipError_t e = hipMemcpyAsync((char *)h + off, (const char *)c->d_rs + off,
+                                sizeof(RepState) * R - off, hipMemcpyDeviceToHost, c->stream);
   if (e == hipSuccess) e = hipStreamSynchronize(c->stream);
   if (e != hipSuccess) return e;
   *err = 0;

@@ -76,6 +76,20 @@ def test_cg_parity_every_trial_rebuilds(torch_cuda, oracle_mod):
     g.close()
 
 
+@pytest.mark.parametrize("dims", [(29, 29, 29), (30, 28, 30)])
+def test_cg_parity_both_list_builds(torch_cuda, oracle_mod, dims):
+    """A relaxation that rebuilds its list on both sides of the size up to
+    which the moves bin their atoms themselves (the lattice is displaced by
+    more than half the skin, which it loses on the way)."""
+    x, y, z, box = I.bcc(*dims)
+    x, y, z = I.thermalize(x, y, z, box, 0.12, 3)
+    d = dict(x=x, y=y, z=z, box=box, species=I.initial_species(x.size, 0.2, 4))
+    g, ro, _ = _compare(oracle_mod, d, I.params("FS-P1"), max_iter=12, ftol=1e-6, dmax=0.2)
+    assert ro["iterations"] == 12
+    assert g.info()["md_rebuilds"] > 1
+    g.close()
+
+
 def test_cg_limits_and_line_search_end(torch_cuda, oracle_mod):
     O = oracle_mod
     pot = I.params("FS-P1")

@@ -67,6 +67,19 @@ def test_npt_parity_compressed_tabulated(torch_cuda, oracle_mod):
     g.close()
 
 
+@pytest.mark.parametrize("n,steps", [(15, 60), (30, 12)])
+def test_npt_parity_search_grid_changes(torch_cuda, oracle_mod, n, steps):
+    """Under pressure, with the drift's own binning (6,750 atoms: the box
+    shrinks from 11 to 10 search bins per axis) and without (54,000)."""
+    d = _system(n=n, seed=43)
+    g, _, box, _ = _run_both(oracle_mod, d, I.params("FS-P1"), 2.5, steps, 700.0, 100.0, 0.15,
+                             120.0, skin=0.3)
+    if n == 15:
+        assert d["box"][0] > 11 * 3.9 > box[0]
+    assert g.info()["md_rebuilds"] > 1
+    g.close()
+
+
 def test_npt_parity_thin_skin(torch_cuda, oracle_mod):
     """MD-list skin 0.05 A: rebuilds nearly every step."""
     d = _system(n=8, seed=51)
