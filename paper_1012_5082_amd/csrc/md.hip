@@ -11,21 +11,29 @@ struct Box {
   double L0, L1, L2;
 };
 
-// The density and force passes of large systems are bound by the address and
-// data path of their gathers: with one lane per atom, whose two 16-byte loads
-// per entry go to lines of their own (the k-th neighbours of adjacent atoms
-// are rarely adjacent: 46 line accesses per load of a wave), it is busy for
-// 80 - 85% of the density pass, and neither fewer instructions (without the
-// periodic images: half of them) nor (x, y) and (z, w) in arrays of their own
-// changed the times.  So LPA lanes share an atom, in pairs that read the two
-// halves of one entry's quadruple in the same load (one line access per entry
-// instead of two) and exchange what the other needs; lane l of a group takes
-// entries l, l + LPA, ... of the row, and the group's first lane adds the
-// terms in entry order.  At 1.95M atoms (polycrystal, 15.6 entries) density
-// 116 -> 109 us, forces with kick and drift 169 -> 158.
-// rounds whose indices are loaded together; their gathers go two by two
+// The density and force passes of large systems are bound by the loads they
+// have in flight.  Their gathers hit L1 and L2 (at 1.95M atoms the memory is
+// read at a third of its rate), each going to lines of its own (the k-th
+// neighbours of adjacent atoms are rarely adjacent: 46 line accesses per load
+// of a wave with one lane per atom); fewer instructions (without the periodic
+// images half of them, or a fifth by another split of the pair's work) and
+// (x, y) and (z, w) in arrays of their own changed nothing, registers did.  So
+// LPA lanes share an atom, in pairs that read the two halves of one entry's
+// quadruple in the same load (one line access per entry instead of two) and
+// exchange what the other needs; lane l of a group takes entries l, l + LPA, ...
+// of the row, and the group's first lane adds the terms in entry order.  At
+// 1.95M atoms (polycrystal, 15.6 entries) density 116 -> 111 us, forces with
+// kick and drift 169 -> 156 with two lanes.
+// Rounds whose indices are loaded together, and rounds whose gathers are in
+// flight together: more of them cost registers and so waves.  (The loads are
+// named: an array of them had the compiler move the next ones up, 91 registers
+// instead of 74 with two lanes.)  Rounds in flight 1, 2, 4: 1.02M atoms (one
+// lane, 20 steps) 4.09, 3.54, 3.35 ms; 1.95M (two lanes) 7.31, 6.87, 7.09;
+// 2,000 (four lanes) 0.37, 0.39, 0.40.
 template <int LPA>
-constexpr int NRF = LPA >= 8 ? 2 : LPA == 4 ? 4 : 8 / LPA;
+constexpr int NRF = LPA == 4 ? 4 : 8 / LPA;
+template <int LPA>
+constexpr int NRG = 4 / LPA;
 
 // A row's first indices, loaded beside its length (what lies beyond the length
 // is not used); the rest of a longer row is loaded as the rounds reach it.
@@ -199,12 +207,16 @@ __device__ __forceinline__ DensityTerm density_row(int64_t n, int64_t i, int m, 
       }
     }
 #pragma unroll
-    for (int g = 0; g < NRF<LPA>; g += 2) {
+    for (int g = 0; g < NRF<LPA>; g += NRG<LPA>) {
       if (k0 + g * LPA >= m) break;
-      const PairLoad l0 = pair_load<LPA>(ps4, jb[g], odd), l1 = pair_load<LPA>(ps4, jb[g + 1], odd);
+      PairLoad l0, l1, l2, l3;
+      l0 = pair_load<LPA>(ps4, jb[g], odd);
+      if constexpr (NRG<LPA> > 1) l1 = pair_load<LPA>(ps4, jb[g + 1], odd);
+      if constexpr (NRG<LPA> > 2) l2 = pair_load<LPA>(ps4, jb[g + 2], odd);
+      if constexpr (NRG<LPA> > 2) l3 = pair_load<LPA>(ps4, jb[g + 3], odd);
 #pragma unroll
-      for (int u = 0; u < 2; ++u) {
-        const double4 q = pair_quad<LPA>(u ? l1 : l0, odd);
+      for (int u = 0; u < NRG<LPA>; ++u) {
+        const double4 q = pair_quad<LPA>(u == 0 ? l0 : u == 1 ? l1 : u == 2 ? l2 : l3, odd);
         const bool in = k0 + (g + u) * LPA + lane < m;
         const DensityTerm t = density_term<TAB, EN, W>(q, qi, si, in, b, p);
         add_group<LPA>(s.rho, t.rho);
@@ -454,12 +466,16 @@ __device__ __forceinline__ double4 force_row(int64_t n, int64_t i, int m, int la
       }
     }
 #pragma unroll
-    for (int g = 0; g < NRF<LPA>; g += 2) {
+    for (int g = 0; g < NRF<LPA>; g += NRG<LPA>) {
       if (k0 + g * LPA >= m) break;
-      const PairLoad l0 = pair_load<LPA>(pf4, jb[g], odd), l1 = pair_load<LPA>(pf4, jb[g + 1], odd);
+      PairLoad l0, l1, l2, l3;
+      l0 = pair_load<LPA>(pf4, jb[g], odd);
+      if constexpr (NRG<LPA> > 1) l1 = pair_load<LPA>(pf4, jb[g + 1], odd);
+      if constexpr (NRG<LPA> > 2) l2 = pair_load<LPA>(pf4, jb[g + 2], odd);
+      if constexpr (NRG<LPA> > 2) l3 = pair_load<LPA>(pf4, jb[g + 3], odd);
 #pragma unroll
-      for (int u = 0; u < 2; ++u) {
-        const double4 q = pair_quad<LPA>(u ? l1 : l0, odd);
+      for (int u = 0; u < NRG<LPA>; ++u) {
+        const double4 q = pair_quad<LPA>(u == 0 ? l0 : u == 1 ? l1 : u == 2 ? l2 : l3, odd);
         const bool in = k0 + (g + u) * LPA + lane < m;
         const double4 t = force_term<TAB, VIR, W>(q, o, in, b, p);
         add_group<LPA>(f.x, t.x);
