@@ -688,8 +688,7 @@ __device__ __forceinline__ int2 block_scan2(int &a, int &b, int2 *wtot) {
 constexpr int RG_X = 4, RG_Y = 4;  // own bins of a region along x and y
 constexpr int RG_GRID = 2048;      // blocks of a region launch (at most)
 
-// FIN: the kernel also does k_md_finish's work (fin), one launch less per step,
-// for systems small enough that its scattered stores stay in the L2s.
+// FIN: the kernel also does k_md_finish's work (fin).
 struct MdFinish {
   int64_t n;
   const double *x, *y, *z;
@@ -965,19 +964,24 @@ hipError_t launch_md_rebuild_cond(vcsgc_ctx *c, int par, bool binned) {
   if (!binned)
     k_bin_search<<<std::min(grid_for(r.n), BIN_GRID), BLOCK, 0, c->stream>>>(
         r.n, c->x, c->y, c->z, g, c->bmax, c->bin_count, c->bin_atoms, c->bin_pos, c->ds, cond);
-  hipError_t e = launch_md_build_chain(c, g, cond, binned);
+  hipError_t e = launch_md_build_chain(c, g, cond, md_one_kernel_build(c));
   tstop(c, h);
   return e;
 }
 
-// Small systems: the drift bins its atoms at every step (the density pass
-// before it has cleared the counts) and one kernel searches and finishes, so a
-// step without a rebuild has one idle launch instead of three (about 4.5 us
-// each).  20 NVE steps at 2,000 atoms 474 -> 390 us, at 31,250 522 -> 453; at
-// 94,054 the binning costs what the launches did (1,225 and 1,240 us), and
-// from there on the scattered stores lose (1.02M atoms 3.5 and 4.9 ms).
+// Device-decided rebuilds search and finish in one kernel up to about 1M atoms:
+// an idle launch less per step (4.5 us).  20 steps at 128,000 atoms 797 -> 752
+// us, at 0.25M 1,216 -> 1,167, at 1.02M 3,360 -> 3,280 (NPT at 0.5M 3,420 ->
+// 3,220); at 1.95M atoms the scattered stores lose (6,810 and 6,940 us).
+bool md_one_kernel_build(const vcsgc_ctx *c) { return c->n <= 1280 * 1024 && md_regions(c); }
+
+// Small systems: the drift also bins its atoms at every step (the density pass
+// before it has cleared the counts), so a step without a rebuild has one idle
+// launch.  20 NVE steps at 2,000 atoms 474 -> 390 us, at 31,250 522 -> 453
+// (with the one-kernel build); at 94,054 the binning costs more than the
+// launch.
 bool md_binned_drift(const vcsgc_ctx *c) {
-  return c->bin_pos && c->n <= 48 * 1024 && md_regions(c);
+  return c->bin_pos && c->n <= 48 * 1024 && md_one_kernel_build(c);
 }
 
 bool md_rebuild_on_device(const vcsgc_ctx *c) { return c->bin_pos != nullptr; }

@@ -674,6 +674,7 @@ hipError_t launch_build_mc_list(vcsgc_ctx *c, const RepHost &r);
 hipError_t launch_build_md_list(vcsgc_ctx *c);
 hipError_t launch_md_rebuild_cond(vcsgc_ctx *c, int par, bool binned);
 bool md_rebuild_on_device(const vcsgc_ctx *c);
+bool md_one_kernel_build(const vcsgc_ctx *c);
 bool md_binned_drift(const vcsgc_ctx *c);
 hipError_t launch_mc_row_stats(vcsgc_ctx *c);
 hipError_t launch_build_desc_list(vcsgc_ctx *c, const RepHost &r);

@@ -240,16 +240,17 @@ __device__ __forceinline__ void density_store(int64_t i, const double4 &qi, cons
   if (EN) e[i] = embed<TAB ? 1 : 0>(p, si, s.rho) + 0.5 * s.phi;
 }
 
-// What a density pass does for the next drift's binning: clear the bin counts
-// (their readers, the last step's list build, have finished), and take over
-// that build's statistics.
+// What a density pass does for the list rebuilds: take over the statistics of
+// a one-kernel build, and before a drift that bins its atoms clear the bin
+// counts (their readers, the last step's list build, have finished).
 struct BinClear {
-  int32_t *count;  // NULL: nothing
+  int32_t *count;  // NULL: not cleared
   int64_t nbins;
-  DevState *ds;
+  DevState *ds;  // NULL: nothing to do
 };
 __device__ __forceinline__ void bin_clear(const BinClear &c, int64_t i, int64_t threads) {
-  for (int64_t q = i; q < c.nbins; q += threads) c.count[q] = 0;
+  if (c.count)
+    for (int64_t q = i; q < c.nbins; q += threads) c.count[q] = 0;
   if (i == 0 && c.ds->pairs_new) {
     c.ds->pairs_md = c.ds->pairs_new;
     c.ds->kmax_md = c.ds->kmax_new;
@@ -264,7 +265,7 @@ __global__ void __launch_bounds__(BLOCK)
                  const uint8_t *__restrict__ cnt, Box b, double reach, PotD p, double *rho,
                  double2 *pf4, double *e, BinClear bc) {
   const int64_t gid = xcd_block() * blockDim.x + threadIdx.x;
-  if (bc.count) bin_clear(bc, gid, (int64_t)gridDim.x * blockDim.x);
+  if (bc.ds) bin_clear(bc, gid, (int64_t)gridDim.x * blockDim.x);
   const int64_t i = gid / LPA;
   const int lane = (int)(gid % LPA);
   if (i >= n) return;  // whole groups leave together
@@ -574,7 +575,8 @@ static int lanes_per_atom(const vcsgc_ctx *c, bool steps) {
 template <int LPA, bool EN>
 static void density_md_on(vcsgc_ctx *c, const Box &b) {
   const double reach = list_reach(c);
-  const BinClear bc = {md_binned_drift(c) ? c->bin_count : nullptr, c->nbins_total, c->ds};
+  const BinClear bc = {md_binned_drift(c) ? c->bin_count : nullptr, c->nbins_total,
+                       md_one_kernel_build(c) ? c->ds : nullptr};
   c->bins_clear = bc.count != nullptr;
   if (c->pot.tab)
     k_density_md<LPA, true, EN><<<grid_for(c->n * LPA), BLOCK, 0, c->stream>>>(
