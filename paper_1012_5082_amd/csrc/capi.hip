@@ -768,6 +768,18 @@ vcsgc_status sweep_impl(vcsgc_ctx *c, const double *dmu0, const double *kappa, c
   // against the best of 3, 8 and 16 stages per kernel: 250,000 sites at 28%
   // accepted stages 2.6 / 4.5 us, 0.5M at 24% 2.9 / 4.6, 2M at 23% 4.8 / 7.5,
   // 1M at 0% 1.2 / 1.2, 4M at 0% 3.7 / 3.5, 8M at 0% 7.2 / 6.3.
+  // Tabulated potentials: where the last call accepted next to nothing, the
+  // stages are bound by the tables' gathers, for which the pipeline has more
+  // waves; it is the faster one with long batches, or where the persistent
+  // sweep's workgroups hold most of their groups in one stage.  At 0%, 16
+  // stages per kernel against persistent: 128,000 sites 335 / 383 us a sweep,
+  // 0.25M 266 / 340, 1.02M 477 / 589, with 27 colours 153 / 174, 195 / 212,
+  // 450 / 823 (4 stages 594); but with 8 per kernel 438 / 383, 378 / 340,
+  // 596 / 589, and at 10% accepted 838 / 770 (54,000 sites).
+  const bool quiet = c->strategy == 3 && c->pot.tab && c->m_stage_acc >= 0.0 &&
+                     c->m_stage_acc < 0.02 &&
+                     (c->trials_per_group > 8 ||
+                      2 * c->reps[0].ncpc > (int64_t)c->reps[0].G * vc::persist_groups());
   const bool logged = c->tlog || c->slog || c->dalog;
   const unsigned stage_timers =
       1u << VCSGC_KT_STAGE | 1u << VCSGC_KT_TRIAL | 1u << VCSGC_KT_COMMIT;
@@ -780,7 +792,7 @@ vcsgc_status sweep_impl(vcsgc_ctx *c, const double *dmu0, const double *kappa, c
   }
   const bool per_stage =
       (c->da_mode && !da) || c->smp_cap > 0 || c->local_steps > 1 || c->grown ||
-      (!da && c->strategy >= 2 && (n_sweeps == 0 || logged || (c->tmask & (1u << VCSGC_KT_STAGE)) ||
+      (!da && c->strategy >= 2 && (n_sweeps == 0 || quiet || logged || (c->tmask & (1u << VCSGC_KT_STAGE)) ||
                             c->reps[0].ncpc > (int64_t)c->reps[0].G * vc::persist_groups()));
   if (per_stage && R == 1) {
     // one trial kernel and one commit kernel per stage
@@ -792,6 +804,8 @@ vcsgc_status sweep_impl(vcsgc_ctx *c, const double *dmu0, const double *kappa, c
     c->h_state_final = false;
     if (!have) VC_CHECK(c, vc::persist_sync_nb_from_stage(c), "sweep");
     c->w += (uint64_t)n_sweeps;
+    if (have && c->h_state->stages)
+      c->m_stage_acc = (double)c->h_state->stage_acc / (double)c->h_state->stages;
     if (out) {
       hipError_t e = hipSuccess;
       vc::DevState h = have ? *c->h_state : read_state(c, &e);
@@ -822,7 +836,11 @@ vcsgc_status sweep_impl(vcsgc_ctx *c, const double *dmu0, const double *kappa, c
   // the timeout flags are read after every call, with or without statistics:
   // a workgroup that left a timed-out wait may have committed part of a stage
   int err = 0;
-  VC_CHECK(c, vc::persist_read_stats(c, out, &err, da), "sweep");
+  vcsgc_stats one;
+  vcsgc_stats *const got = out ? out : R == 1 ? &one : nullptr;
+  VC_CHECK(c, vc::persist_read_stats(c, got, &err, da), "sweep");
+  if (R == 1 && got->stages)
+    c->m_stage_acc = (double)got->stage_accepts / (double)got->stages;
   if (err) {
     c->sticky = true;
     return fail(c, VCSGC_E_BARRIER_TIMEOUT, "persistent sweep: a barrier wait exceeded its limit");

@@ -588,6 +588,7 @@ struct vcsgc_ctx {
   bool h_state_final = false;
   double m_acc_rate = 0.05;             // accepted stages per stage, last call
   double m_spec_rate = 0.0;             // batched pipeline: kernels per stage, last call
+  double m_stage_acc = -1.0;  // stages accepted per stage in the last sweep call (-1: none yet)
   void *pipe_graph = nullptr;           // graphs of pipeline kernels
   long long *part = nullptr;  // per trial block: trials, local accepts, sum dn, near ties
   int64_t npart = 0;

@@ -75,6 +75,36 @@ def test_table_sweep_parity(torch_cuda, oracle_mod, path):
     g.close()
 
 
+@pytest.mark.parametrize("dims,colours,batch", [((14, 15, 13), 8, 16), ((20, 16, 18), 27, 9),
+                                                ((14, 15, 13), 8, 8)])
+def test_table_sweep_parity_quiet_calls(torch_cuda, oracle_mod, dims, colours, batch):
+    """Calls after one that accepted next to nothing (kappa = 10^6 at cbar = 0,
+    all sites A) take the pipeline for batches of more than 8 stages, and the
+    persistent sweep again after one that accepts (kappa = 0): the oracle's
+    chain through all of them."""
+    from paper_1012_5082_amd.binding import VCSGC
+    O = oracle_mod
+    tab = I.table("TAB-X")
+    x, y, z, box = I.bcc(*dims)
+    x, y, z = I.thermalize(x, y, z, box, 0.04, 15)
+    sp = np.zeros(x.size, np.uint8)
+    g = VCSGC(x, y, z, box, sp, tab, colours=colours)
+    g.set_tuning("batch", batch)
+    st = O.SweepState(x, y, z, box, sp, tab)
+    quiet = 0
+    for kappa in (1e6, 1e6, 1e6, 0.0, 0.0, 1e6):
+        a = g.sweep(-5.0, kappa, 0.0, 600.0, 1, 33)
+        b, _, _ = O.sweep(st, -5.0, kappa, 0.0, 600.0, 1, 33,
+                          colour_period=3 if colours == 27 else 2)
+        for k in ("trials", "local_accepts", "stages", "stage_accepts", "flips", "n_final"):
+            assert a[k] == b[k], (k, a[k], b[k])
+        quiet += a["stage_accepts"] < 0.02 * a["stages"]
+    assert 3 <= quiet < 6
+    assert np.array_equal(g.species.cpu().numpy(), st.species)
+    assert np.array_equal(g.rho().cpu().numpy(), st.rho)
+    g.close()
+
+
 def test_table_md_and_hybrid_cycle(torch_cuda, oracle_mod):
     """40 MD steps (with list rebuilds), then [sweep on the batched pipeline;
     20 MD steps] x 2 with TAB-X: positions, velocities, forces, species and
