@@ -94,7 +94,8 @@ TRAFFIC = {
     "density": ("k_density_md", "paper_1012_5082_amd/csrc/md.hip",
                 "profiles/k_density_md_c3_traffic.md"),
     "stage": ("k_stage", "paper_1012_5082_amd/csrc/sweep.hip", "profiles/k_stage_c3_traffic.md"),
-    "persist": ("k_sweep_persistent", "paper_1012_5082_amd/csrc/persist.hip", ""),
+    "persist": ("k_sweep_persistent", "paper_1012_5082_amd/csrc/persist.hip",
+                "profiles/k_sweep_persistent_c3_traffic.md"),
     "batch": ("k_stage_spec", "paper_1012_5082_amd/csrc/sweep.hip",
               "profiles/k_stage_spec_c3_traffic.md"),
 }

@@ -557,15 +557,16 @@ __global__ void __launch_bounds__(BLOCK)
 // the density pass (EN: with the atoms' energies) and the force pass for the
 // context's potential form
 // Lanes per atom.  Few atoms leave the chip idle and their time is latency: 4
-// (20 NVE steps at 2,000 atoms 588 us with 1, 517 with 2, 485 with 4, 464 with
-// 8; at 31,250 atoms 600, 535, 525, 558; at 94,054 tabulated 1,380, 1,250,
-// 1,285).  The tables' evaluations are worth a second lane at any size.  From
-// there to about 1M atoms one lane: the quadruples fit the L2s and the
-// exchange costs more than the saved line accesses (0.25M atoms 1,215 us with
-// 1, 1,265 with 2; 1.02M atoms equal); beyond, two for the steps (1.95M atoms
-// 7,940 us with 1, 6,850 with 2), one for single passes over a lattice in its
-// own order, whose neighbours do share lines (1.02M atoms, energy and forces:
-// 153 us with 1, 168 with 2; 1.95M atoms in grains equal).
+// (20 NVE steps at 2,000 atoms 502 us with 1, 425 with 2, 375 with 4, 8 within
+// 3% of 4 there and slower from 8,000 on; at 31,250 atoms 550, 460, 440; at
+// 94,054 tabulated 1,370, 1,230, 1,285).  The tables' evaluations are worth a
+// second lane at any size.  From there to about 1M atoms one lane: the
+// quadruples fit the L2s and the exchange costs more than the saved line
+// accesses (0.25M atoms 1,225 us with 1, 1,280 with 2; 1.02M 3,360 and 3,560);
+// beyond, two for the steps (1.95M atoms 7,440 us with 1, 6,860 with 2), one
+// for single passes over a lattice in its own order, whose neighbours do share
+// lines (1.02M atoms, energy and forces: 141 us with 1, 162 with 2; 1.95M
+// atoms in grains 272 and 298).
 static int lanes_per_atom(const vcsgc_ctx *c, bool steps) {
   if (c->n <= 48 * 1024) return 4;
   if (c->pot.tab || (steps && c->n > 1024 * 1024)) return 2;
