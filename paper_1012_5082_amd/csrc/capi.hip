@@ -26,7 +26,7 @@ void free_all(vcsgc_ctx *c) {
                   c->mc_cnt,     c->md_j,       c->md_cnt,    c->xr,   c->yr,
                   c->zr,         c->rho,        c->rho_f,      c->eatom, c->red,
                   c->rec,        c->ds,         c->ps4,        c->pf4,       c->part,
-                  c->d_reps,     c->d_rs,       c->d_wg_rep,   c->d_j,        c->d_r,
+                  c->d_rs,       c->d_wg_rep,   c->d_j,        c->d_r,
                   c->d_cnt,      c->scan_tmp,   c->snap,       c->bin_pos,
                   c->md_rows,    c->sites,      c->site_lnu,
                   c->u_site,     c->u_j,        c->u_rho,      c->u_v,
@@ -42,7 +42,6 @@ void free_all(vcsgc_ctx *c) {
   if (c->h_tot) (void)hipHostFree(c->h_tot);
   if (c->graph_exec) (void)hipGraphExecDestroy(c->graph_exec);
   if (c->graph) (void)hipGraphDestroy(c->graph);
-  if (c->stage_ev) (void)hipEventDestroy(c->stage_ev);
   vc::free_stage_graph(c);
   vc::free_pipe_graph(c);
 }
@@ -627,12 +626,10 @@ vcsgc_status create_impl(const vcsgc_system *sys, int R, const int64_t *rep_atom
   A(dalloc(&c->red, (n + vc::BLOCK - 1) / vc::BLOCK + 8));
   A(dalloc(&c->rec, roff));
   A(dalloc(&c->ds, 1));
-  A(dalloc((unsigned char **)&c->d_reps, vc::repd_size() * R));
   A(dalloc((unsigned char **)&c->d_rs, vc::repstate_size() * R));
   if (e == hipSuccess) e = hipHostMalloc(&c->h_reps, vc::repd_size() * R, hipHostMallocDefault);
   if (e == hipSuccess) e = hipHostMalloc(&c->h_rs, vc::repstate_size() * R, hipHostMallocDefault);
   if (e == hipSuccess) e = hipHostMalloc((void **)&c->h_tot, 8 * sizeof(double), hipHostMallocDefault);
-  if (e == hipSuccess) e = hipEventCreateWithFlags(&c->stage_ev, hipEventDisableTiming);
   if (e != hipSuccess) {
     free_all(c);
     delete c;
@@ -823,7 +820,7 @@ vcsgc_status sweep_impl(vcsgc_ctx *c, const double *dmu0, const double *kappa, c
     }
     return VCSGC_OK;
   }
-  VC_CHECK(c, vc::persist_stage_params(c, dmu0, kappa, cbar, T, n_sweeps, seed, da), "sweep");
+  vc::persist_stage_params(c, dmu0, kappa, cbar, T, n_sweeps, seed, da);
   if (n_sweeps > 0) {
     int h = vc::tstart(c, VCSGC_KT_PERSIST);
     if (da)
@@ -838,7 +835,7 @@ vcsgc_status sweep_impl(vcsgc_ctx *c, const double *dmu0, const double *kappa, c
   int err = 0;
   vcsgc_stats one;
   vcsgc_stats *const got = out ? out : R == 1 ? &one : nullptr;
-  VC_CHECK(c, vc::persist_read_stats(c, got, &err, da), "sweep");
+  VC_CHECK(c, vc::persist_read_stats(c, got, &err, n_sweeps > 0, da), "sweep");
   if (R == 1 && got->stages)
     c->m_stage_acc = (double)got->stage_accepts / (double)got->stages;
   if (err) {
@@ -1537,7 +1534,7 @@ vcsgc_status vcsgc_get_state(vcsgc_ctx *c, vcsgc_state *out) {
   if (!out) return fail(c, VCSGC_E_INVALID_ARG, "null output");
   vcsgc_stats s;
   int err = 0;
-  VC_CHECK(c, vc::persist_read_stats(c, &s, &err), "state");  // n_final of replica 0
+  VC_CHECK(c, vc::persist_read_stats(c, &s, &err, false, false), "state");  // n_final of replica 0
   out->sweeps_done = c->w;
   out->n_b = s.n_final;
   out->seed = c->last_seed;

@@ -624,9 +624,8 @@ struct vcsgc_ctx {
   int64_t kt_n[VCSGC_KT_CLASSES] = {};
 
   // persistent batched sweep
-  void *d_reps = nullptr;     // per-replica parameters (device)
-  void *h_reps = nullptr;     // pinned staging buffer for them
-  void *h_rs = nullptr;       // pinned copy of the replicas' states
+  void *h_reps = nullptr;     // per-replica parameters (pinned, read by the kernel)
+  void *h_rs = nullptr;       // pinned: the replicas' statistics of the last call
   void *d_rs = nullptr;       // per-replica chain state and counters
   int32_t *d_wg_rep = nullptr;  // workgroup -> replica
   int grid_total = 0;
@@ -637,7 +636,6 @@ struct vcsgc_ctx {
   int trials_per_group = 1;   // tiling: trial groups per active cell (see assign_workgroups)
   int strategy = 0;           // 0: persistent (graph), 1: persistent (direct), 2: per-stage
   unsigned int spin_limit = 1u << 24;
-  hipEvent_t stage_ev = nullptr;
   hipGraph_t graph = nullptr;
   hipGraphExec_t graph_exec = nullptr;
   bool graph_coop = false;
@@ -729,13 +727,13 @@ size_t persist_lds_need(int64_t chunk, int64_t nres, int *ndraw);
 size_t repd_size();
 size_t repstate_size();
 hipError_t persist_max_blocks(int *per_cu, bool tab, size_t lds, size_t lds_max);
-hipError_t persist_stage_params(vcsgc_ctx *c, const double *dmu0, const double *kappa,
+void persist_stage_params(vcsgc_ctx *c, const double *dmu0, const double *kappa,
                                 const double *cbar, const double *T, int64_t n_sweeps,
                                 uint64_t seed, bool da = false);
 hipError_t launch_persistent(vcsgc_ctx *c, bool use_graph);
 hipError_t persist_da_grid(vcsgc_ctx *c);
 hipError_t launch_persistent_da(vcsgc_ctx *c);
-hipError_t persist_read_stats(vcsgc_ctx *c, vcsgc_stats *out, int *err, bool da = false);
+hipError_t persist_read_stats(vcsgc_ctx *c, vcsgc_stats *out, int *err, bool launched, bool da);
 hipError_t persist_count(vcsgc_ctx *c);
 hipError_t persist_sync_nb_to_stage(vcsgc_ctx *c);
 hipError_t persist_sync_nb_from_stage(vcsgc_ctx *c);
