@@ -581,6 +581,7 @@ struct vcsgc_ctx {
   // pinned copy of the device state, read by the pipeline's progress checks;
   // h_state_final: the last check saw the call's end (statistics included)
   vc::DevState *h_state = nullptr;
+  unsigned char *h_pin = nullptr;  // the pinned host memory that the h_ pointers share
   // totals a kernel leaves for the host (pinned; 8 doubles)
   double *h_tot = nullptr;
   // the bin counts are zero: cleared by the last density pass, no binning since
