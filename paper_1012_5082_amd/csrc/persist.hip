@@ -36,8 +36,8 @@
 //     per trial doubled the instructions a SIMD issues per batch).
 // Measured (calls included; before: one stage per two release/acquire
 // barriers of the device scope, every draw on the path): a sweep of 2,000
-// rigid sites 11.2 -> 0.22 ms; of 128,000 thermal sites 4.3 -> 1.3 ms near
-// equilibrium (0.47 ms from a random start, where few stages are accepted);
+// rigid sites 11.2 -> 0.20 ms; of 128,000 thermal sites 4.3 -> 1.35 ms near
+// equilibrium (0.42 ms from a random start, where few stages are accepted);
 // two sweeps of 64 replicas of 2,000 to 250,000 sites 21.8 -> 5.5 ms.
 //
 // The densities and species of replicas of several workgroups are read and
