@@ -138,7 +138,8 @@ typedef struct {
 
 typedef struct {
   uint64_t sweeps_done; /* cumulative sweep counter w (Philox counter word 0) */
-  int64_t n_b;          /* current number of B atoms (get only; set recounts it) */
+  int64_t n_b;          /* current number of B atoms (get only; set recounts it);
+                           of the first replica on a batch context */
   uint64_t seed;        /* Philox key word 0 of the last sweep call (0 before any) */
   double *rho_dev;      /* caller DEVICE buffer of N doubles or NULL: get copies the
                            density cache into it, set restores the cache from it */

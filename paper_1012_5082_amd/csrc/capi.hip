@@ -1538,11 +1538,10 @@ vcsgc_status vcsgc_get_state(vcsgc_ctx *c, vcsgc_state *out) {
   vcsgc_status st = check_ctx(c);
   if (st) return st;
   if (!out) return fail(c, VCSGC_E_INVALID_ARG, "null output");
-  vcsgc_stats s;
-  int err = 0;
-  VC_CHECK(c, vc::persist_read_stats(c, &s, &err, false, false), "state");  // n_final of replica 0
+  int64_t n_b = 0;
+  VC_CHECK(c, vc::persist_read_nb(c, &n_b), "state");
   out->sweeps_done = c->w;
-  out->n_b = s.n_final;
+  out->n_b = n_b;
   out->seed = c->last_seed;
   if (out->rho_dev) {
     st = ensure_mc(c);

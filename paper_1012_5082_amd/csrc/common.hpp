@@ -735,6 +735,7 @@ hipError_t launch_persistent(vcsgc_ctx *c, bool use_graph);
 hipError_t persist_da_grid(vcsgc_ctx *c);
 hipError_t launch_persistent_da(vcsgc_ctx *c);
 hipError_t persist_read_stats(vcsgc_ctx *c, vcsgc_stats *out, int *err, bool launched, bool da);
+hipError_t persist_read_nb(vcsgc_ctx *c, int64_t *n_b);
 hipError_t persist_count(vcsgc_ctx *c);
 hipError_t persist_sync_nb_to_stage(vcsgc_ctx *c);
 hipError_t persist_sync_nb_from_stage(vcsgc_ctx *c);

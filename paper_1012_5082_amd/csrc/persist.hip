@@ -1360,6 +1360,16 @@ hipError_t persist_read_stats(vcsgc_ctx *c, vcsgc_stats *out, int *err, bool lau
   return hipSuccess;
 }
 
+// n_B of the system, or of the first replica of a batch (synchronizes)
+hipError_t persist_read_nb(vcsgc_ctx *c, int64_t *n_b) {
+  RepState *h = (RepState *)c->h_rs;
+  hipError_t e = hipMemcpyAsync(&h->n_final, &((RepState *)c->d_rs)->n_final, sizeof(long long),
+                                hipMemcpyDeviceToHost, c->stream);
+  if (e == hipSuccess) e = hipStreamSynchronize(c->stream);
+  if (e == hipSuccess) *n_b = h->n_final;
+  return e;
+}
+
 // n_final of replica k (used to seed the per-stage path's counter)
 __global__ void k_set_nfinal(RepState *rs, int k, const long long *src) {
   if (threadIdx.x == 0 && blockIdx.x == 0) rs[k].n_b = rs[k].n_final = *src;

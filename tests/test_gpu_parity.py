@@ -389,6 +389,30 @@ def test_batch_replicas_match_oracle(torch_cuda, oracle_mod):
     b.close()
 
 
+def test_batch_get_state(torch_cuda):
+    """get_state on a batch of replicas: the sweep counter, the seed, n_B of the
+    first replica and the density cache, and nothing beyond the state it was
+    given is written."""
+    import ctypes as C
+    from paper_1012_5082_amd import binding as B
+    reps = _replica_set()
+    b = B.VCSGCBatch(reps, I.params("FS-P1"))
+    args = [np.array([r[k] for r in reps]) for k in ("dmu0", "kappa", "cbar", "T")]
+    b.sweep_batch(*args, 2, 777)
+    states = (B.State * 3)()
+    C.memset(C.byref(states), 0x5A, C.sizeof(states))
+    guard = bytes(states[0]), bytes(states[2])
+    states[1].rho_dev = None
+    b._check(B.lib().vcsgc_get_state(b._h, C.byref(states[1])), "get_state")
+    assert (states[1].sweeps_done, states[1].seed) == (2, 777)
+    assert states[1].n_b == int(b.replica_species(0).sum())
+    assert (bytes(states[0]), bytes(states[2])) == guard
+    st = b.get_state(with_rho=True)
+    assert st["n_b"] == states[1].n_b
+    assert np.array_equal(st["rho"].cpu().numpy(), b.rho().cpu().numpy())
+    b.close()
+
+
 def test_sweep_chunking_and_determinism(torch_cuda, oracle_mod):
     d = W.c2(cbar=0.05)
     pot = I.params("FS-P1")
