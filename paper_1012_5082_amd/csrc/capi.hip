@@ -167,6 +167,12 @@ vcsgc_status refresh_md(vcsgc_ctx *c) {
   }
 }
 
+// The persistent sweep's graph is built again by the next call.
+void drop_graph(vcsgc_ctx *c) {
+  if (c->graph_exec) (void)hipGraphExecDestroy(c->graph_exec);
+  c->graph_exec = nullptr;
+}
+
 // Workgroups of the persistent sweep.  A replica whose densities and species
 // (nine bytes per atom) fit the LDS of one workgroup runs in one: its stages
 // then need no device barrier.  The others get trial groups for
@@ -246,10 +252,7 @@ vcsgc_status assign_workgroups(vcsgc_ctx *c) {
       if (c->strategy < 2) c->trials_per_group = tpg;
       c->persist_lds = lds;
       c->persist_ndraw = ndraw;
-      if (c->graph_exec) {
-        (void)hipGraphExecDestroy(c->graph_exec);
-        c->graph_exec = nullptr;
-      }
+      drop_graph(c);
       return VCSGC_OK;
     }
     if (tpg >= (1 << 20))
@@ -878,10 +881,7 @@ vcsgc_status vcsgc_set_wait_limit(vcsgc_ctx *c, uint32_t polls) {
   if (polls < 1) return fail(c, VCSGC_E_INVALID_ARG, "polls must be >= 1");
   VC_CHECK(c, hipStreamSynchronize(c->stream), "sync");
   c->spin_limit = polls;
-  if (c->graph_exec) {  // its kernel node holds the old limit
-    (void)hipGraphExecDestroy(c->graph_exec);
-    c->graph_exec = nullptr;
-  }
+  drop_graph(c);  // its kernel node holds the old limit
   return VCSGC_OK;
 }
 
@@ -1520,6 +1520,7 @@ vcsgc_status vcsgc_set_log(vcsgc_ctx *c, double *tlog, int64_t tcap, double *slo
                              hipMemcpyHostToDevice, c->stream),
            "log reset");
   VC_CHECK(c, hipStreamSynchronize(c->stream), "sync");
+  drop_graph(c);  // its kernel node holds the old buffers and capacities
   return VCSGC_OK;
 }
 

@@ -640,7 +640,6 @@ struct vcsgc_ctx {
   hipGraph_t graph = nullptr;
   hipGraphExec_t graph_exec = nullptr;
   bool graph_coop = false;
-  double *graph_args_tlog = nullptr, *graph_args_slog = nullptr;
   alignas(16) unsigned char graph_args_storage[512];  // kernel arguments of the graph node
 
   std::string err;

@@ -1214,11 +1214,7 @@ static hipError_t build_graph(vcsgc_ctx *c) {
   dp.kernelParams = dargs;
   e = hipGraphAddKernelNode(&n_done, c->graph, &n_sweep, 1, &dp);
   if (e != hipSuccess) return e;
-  e = hipGraphInstantiate(&c->graph_exec, c->graph, nullptr, nullptr, 0);
-  if (e != hipSuccess) return e;
-  c->graph_args_tlog = c->tlog;
-  c->graph_args_slog = c->slog;
-  return hipSuccess;
+  return hipGraphInstantiate(&c->graph_exec, c->graph, nullptr, nullptr, 0);
 }
 
 // Two grids whose workgroups wait for each other must not share the chip
@@ -1259,7 +1255,7 @@ hipError_t launch_persistent(vcsgc_ctx *c, bool use_graph) {
 static hipError_t launch_ungated(vcsgc_ctx *c, bool use_graph) {
   const int R = (int)c->reps.size();
   if (use_graph) {
-    if (!c->graph_exec || c->graph_args_tlog != c->tlog || c->graph_args_slog != c->slog) {
+    if (!c->graph_exec) {
       hipError_t e = build_graph(c);
       if (e != hipSuccess) return e;
     }

@@ -389,6 +389,30 @@ def test_batch_replicas_match_oracle(torch_cuda, oracle_mod):
     b.close()
 
 
+def test_log_capacity_of_the_last_set_log(torch_cuda):
+    """A log set again on the same buffers with smaller capacities: the sweep
+    (graph-captured, as built for the first ones) writes no row beyond them."""
+    torch = torch_cuda
+    import ctypes as C
+    from paper_1012_5082_amd import binding as B
+    d = W.c1()
+    g = gpu_context(d, I.params("FS-P1"))
+    t = torch.zeros((4000, 8), dtype=torch.float64, device="cuda")
+    s = torch.zeros((4000, 8), dtype=torch.float64, device="cuda")
+    P = C.c_void_p
+    for cap in (4000, 7):
+        t.fill_(-1.0)
+        s.fill_(-1.0)
+        g._check(B.lib().vcsgc_set_log(g._h, P(t.data_ptr()), cap, P(s.data_ptr()), cap), "set_log")
+        n = g.sweep(d["dmu0"], 10.0, d["cbar"], d["T"], 1, d["seed"])["trials"]
+        assert n == 2000
+        torch.cuda.synchronize()
+        written = min(cap, n)
+        for a in (t, s):
+            assert bool((a[:written, 0] >= 0.0).all()) and bool((a[written:] == -1.0).all()), cap
+    g.close()
+
+
 def test_batch_get_state(torch_cuda):
     """get_state on a batch of replicas: the sweep counter, the seed, n_B of the
     first replica and the density cache, and nothing beyond the state it was
