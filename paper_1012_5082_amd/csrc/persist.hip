@@ -65,6 +65,12 @@ constexpr int PDMAX = 32;             // stages per batch, at most
 constexpr int PDG = 16;               // the same with several workgroups
 constexpr int PWIN = 256;             // stages whose counters are drawn ahead (a power of two)
 constexpr int PDRAW = 1024;           // trials drawn ahead (twice that without a resident replica)
+// Rings over the batches of a call: the counts in LDS and the words in memory.
+// The batch number runs modulo a multiple of both (a 32-bit counter left the
+// LDS ring's order when it wrapped: 2^32 mod 3 = 1, so after 2^32 batches of one
+// call a batch added to counts that had not been cleared).
+constexpr int PCW = 3, PWORDS = 4, PRINGS = 12;
+static_assert(PRINGS % PCW == 0 && PRINGS % PWORDS == 0, "batch rings");
 static_assert(8 * PDG == 128 && 2 * PDMAX <= PBLOCK && PDMAX <= 64, "a wave holds a batch's words");
 
 struct RepD {
@@ -95,7 +101,7 @@ struct alignas(128) RepState {
   // batch b - 1 (so none still polls b - 2) and before it arrives at b.
   // Workgroup q adds to row q mod 8, a 128-byte line: the adds to one line are
   // served one after the other (216 workgroups on one line took 8 us a batch)
-  unsigned long long word[4][8][PDG];
+  unsigned long long word[PWORDS][8][PDG];
   // commit barrier: 64-bit arrival counters, one line per row of workgroups
   // (they grow by the row's workgroups per accepted stage and are zeroed only
   // once per call)
@@ -143,7 +149,7 @@ struct PersistArgsDa : PersistArgs {
 struct PLds {
   double2 *terms;           // [PGROUPS][KMAX]
   double *lnu, *lnug;       // [ndraw], [PWIN]: ln u of trials, ln u_g of stages
-  unsigned long long *cw;   // [3][PDMAX][2]: packed accepts; trials | ties << 32
+  unsigned long long *cw;   // [PCW][PDMAX][2]: packed accepts; trials | ties << 32
   unsigned long long *tot;  // [PDMAX]
   double *rho;              // [nres]
   int32_t *site, *rec;      // [ndraw] each
@@ -155,7 +161,7 @@ struct PLds {
 
 static size_t persist_lds_bytes(int64_t ndraw, int64_t nres) {
   return sizeof(double2) * PGROUPS * KMAX + sizeof(double) * (ndraw + PWIN) +
-         sizeof(unsigned long long) * 7 * PDMAX + sizeof(double) * nres +
+         sizeof(unsigned long long) * (2 * PCW + 1) * PDMAX + sizeof(double) * nres +
          2 * sizeof(int32_t) * ndraw + PWIN + nres;
 }
 
@@ -165,7 +171,7 @@ __device__ __forceinline__ PLds persist_lds(unsigned char *base, int ndraw, int6
   l.lnu = (double *)(l.terms + PGROUPS * KMAX);
   l.lnug = l.lnu + ndraw;
   l.cw = (unsigned long long *)(l.lnug + PWIN);
-  l.tot = l.cw + 6 * PDMAX;
+  l.tot = l.cw + 2 * PCW * PDMAX;
   l.rho = (double *)(l.tot + PDMAX);
   l.site = (int32_t *)(l.rho + nres);
   l.rec = l.site + ndraw;
@@ -367,7 +373,7 @@ struct DaLds {
 // dynamic LDS with delayed acceptance
 static size_t persist_lds_bytes_da(int64_t ndraw) {
   return sizeof(DaLds) + sizeof(double) * (2 * ndraw + PWIN) +
-         sizeof(unsigned long long) * 7 * PDMAX + 2 * sizeof(int32_t) * ndraw + PWIN;
+         sizeof(unsigned long long) * (2 * PCW + 1) * PDMAX + 2 * sizeof(int32_t) * ndraw + PWIN;
 }
 __device__ __forceinline__ PLds persist_lds_da(unsigned char *base, int ndraw) {
   PLds l;
@@ -376,7 +382,7 @@ __device__ __forceinline__ PLds persist_lds_da(unsigned char *base, int ndraw) {
   l.lnu2 = l.lnu + ndraw;
   l.lnug = l.lnu2 + ndraw;
   l.cw = (unsigned long long *)(l.lnug + PWIN);
-  l.tot = l.cw + 6 * PDMAX;
+  l.tot = l.cw + 2 * PCW * PDMAX;
   l.site = (int32_t *)(l.tot + PDMAX);
   l.rec = l.site + ndraw;
   l.col = (uint8_t *)(l.rec + ndraw);
@@ -643,7 +649,7 @@ __device__ __forceinline__ void sweep_replica(
       l.rho[i] = a.rho[r.aoff + i];
       l.sp[i] = a.sp[r.aoff + i];
     }
-  for (int e = tid; e < 6 * PDMAX; e += PBLOCK) l.cw[e] = 0;
+  for (int e = tid; e < 2 * PCW * PDMAX; e += PBLOCK) l.cw[e] = 0;
   if constexpr (DA) da_weights(a.md, *l.da, tid);
   __syncthreads();
 
@@ -653,10 +659,10 @@ __device__ __forceinline__ void sweep_replica(
     bool have = false;        // the batch's rows are in `row`
     PRow row;
     row.m = 0;
-    for (uint32_t s0 = 0; s0 < S; ++batch) {
+    for (uint32_t s0 = 0; s0 < S; batch = batch + 1 == PRINGS ? 0 : batch + 1) {
       const int len = S - s0 < (uint32_t)span ? (int)(S - s0) : span;
       const bool one_pass = len * own <= PGROUPS;
-      unsigned long long *cw = l.cw + 2 * PDMAX * (batch % 3);
+      unsigned long long *cw = l.cw + 2 * PDMAX * (batch % PCW);
       if (s0 + len > hd) {  // the trials of this batch (and a few more) are due now
         block_sync_lds();   // the last batch's readers of the rings are done
         const uint32_t ts = min(s0 + 4 * len, S);
@@ -786,15 +792,15 @@ __device__ __forceinline__ void sweep_replica(
       block_sync_lds();
       // the counts of the batch after next, last read before this barrier
       if (tid >= PBLOCK - 2 * PDMAX)
-        l.cw[2 * PDMAX * ((batch + 2) % 3) + tid - (PBLOCK - 2 * PDMAX)] = 0;
+        l.cw[2 * PDMAX * ((batch + 2) % PCW) + tid - (PBLOCK - 2 * PDMAX)] = 0;
       const unsigned long long *tot = cw;
       int tst = 2;
       if (!RES && r.G > 1) {
         // ---- counts and barrier in one word per stage
         if (tid < 64) {
-          unsigned long long *word = &st->word[batch & 3][0][0];
+          unsigned long long *word = &st->word[batch % PWORDS][0][0];
           if (q == 0) {
-            unsigned long long *next = &st->word[(batch + 2) & 3][0][0];
+            unsigned long long *next = &st->word[(batch + 2) % PWORDS][0][0];
             __hip_atomic_store(next + wl, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             __hip_atomic_store(next + 64 + wl, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             wait_stores();
@@ -1070,7 +1076,7 @@ __global__ void __launch_bounds__(BLOCK) k_persist_done(RepState *rs, RepState *
     s.sum_n2 = 0.0;
     s.err = 0;
   }
-  for (int q = threadIdx.x; q < 4 * 8 * PDG; q += BLOCK) (&s.word[0][0][0])[q] = 0;
+  for (int q = threadIdx.x; q < PWORDS * 8 * PDG; q += BLOCK) (&s.word[0][0][0])[q] = 0;
   if (threadIdx.x < 8) s.bar[threadIdx.x].n = 0;
 }
 
