@@ -210,7 +210,9 @@ vcsgc_status vcsgc_set_local_steps(vcsgc_ctx *ctx, int32_t k);
  * rep_box[3 r .. 3 r + 2] gives replica r's box.  Each replica gets its own
  * cells, stage count and Philox key (seed, r).  MC only: md_verlet_step,
  * eam_energy_forces and vcsgc_atom_energies reject batch contexts.
- * rep_atoms and rep_box are host arrays of n_rep and 3 n_rep entries. */
+ * rep_atoms and rep_box are host arrays of n_rep and 3 n_rep entries; n_rep is
+ * at most four per compute unit of the device (1,024 on MI355X), with a
+ * tabulated potential three (768), else VCSGC_E_INVALID_ARG. */
 vcsgc_status vcsgc_create_batch(const vcsgc_system *sys, int32_t n_rep, const int64_t *rep_atoms,
                                 const double *rep_box, hipStream_t stream, vcsgc_ctx **out);
 

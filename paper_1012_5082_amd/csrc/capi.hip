@@ -178,82 +178,95 @@ void drop_graph(vcsgc_ctx *c) {
 // then need no device barrier.  The others get trial groups for
 // PERSIST_SPEC / trials_per_group stages of their active cells per batch (at
 // least one workgroup, a multiple of 8 starting at a multiple of 8 from 8 on,
-// so that their shares can be laid out XCD by XCD).  The grid must fit the
-// co-resident capacity, which the LDS of the largest resident replica
-// lowers: first fewer stages are tried per batch, then the LDS bound of
-// residence is lowered (one, two, three workgroups per CU, none resident),
-// then trials_per_group doubles.
+// so that their shares can be laid out XCD by XCD).  Workgroups that wait for
+// each other must all be resident (one per CU: eight waves of more than 128
+// registers): first fewer stages are tried per batch, then trials_per_group
+// doubles.  Where the LDS of the largest resident replica and of the largest
+// share of cells do not go together, the bound of residence is lowered.
+// More replicas than CUs get one workgroup each: none of them waits, so the
+// grid may be any size and the rest follows as workgroups end.
 constexpr int PERSIST_SPEC = 8;
 constexpr int64_t PERSIST_MAX = 1 << 20;  // active cells and workgroups of a replica, at most
+// replicas of a batch, per CU (vcsgc_create_batch states the limit)
+constexpr int REPLICAS_PER_CU = 4, REPLICAS_PER_CU_TAB = 3;
 
 vcsgc_status assign_workgroups(vcsgc_ctx *c) {
-  int dev_cu = 0, lds_cu = 0;
+  int dev_cu = 0, lds_cu = 0, per_cu = 0;
   VC_CHECK(c, hipDeviceGetAttribute(&dev_cu, hipDeviceAttributeMultiprocessorCount, c->device),
            "device query");
   VC_CHECK(c, hipDeviceGetAttribute(&lds_cu, hipDeviceAttributeMaxSharedMemoryPerMultiprocessor,
                                     c->device),
            "device query");
   const int R = (int)c->reps.size();
+  const bool tab = c->pot.tab != 0;
+  if (R > dev_cu * (tab ? REPLICAS_PER_CU_TAB : REPLICAS_PER_CU))
+    return fail(c, VCSGC_E_INVALID_ARG, "more replicas than co-resident workgroups");
+  for (const RepHost &r : c->reps)
+    if (r.ncpc > PERSIST_MAX)
+      return fail(c, VCSGC_E_INVALID_ARG, "too many cells for the persistent sweep");
+  // LDS of a workgroup with the static part and some slack left out
+  const size_t room = (size_t)lds_cu - 1024;
+  VC_CHECK(c, vc::persist_max_blocks(&per_cu, tab, vc::persist_lds_need(1, 0, nullptr), room),
+           "occupancy query");
+  const int64_t cap0 = (int64_t)dev_cu * per_cu;  // workgroups of the least LDS
+  const bool single = R > cap0;                   // one workgroup per replica
   // (the pipeline strategies' parameter is the stages of their kernels' batch)
   int tpg = c->strategy >= 2 || c->trials_per_group < 1 ? 1 : c->trials_per_group;
+  std::vector<int> want(R), order(R);
+  std::vector<char> res(R);
+  const size_t bounds[] = {room, (size_t)lds_cu / 2 - 1024, 0};
   for (;; tpg *= 2) {
-    for (int step = 0; step < 4 * 8; ++step) {
-      const int split = 1 + step / 8, spec = PERSIST_SPEC - step % 8;
-      // LDS of a workgroup with the static part and some slack left out
-      const size_t room = split <= 3 ? (size_t)lds_cu / split - 1024 : 0;
-      std::vector<int> want(R);
-      std::vector<char> res(R);
-      int64_t total = 0, chunk = 1, nres = 0;
-      for (int k = 0; k < R; ++k) {
-        const RepHost &r = c->reps[k];
-        if (r.ncpc > PERSIST_MAX)
-          return fail(c, VCSGC_E_INVALID_ARG, "too many cells for the persistent sweep");
-        res[k] = vc::persist_lds_need(r.ncpc, r.n, nullptr) <= room;
-        const int64_t per = (int64_t)vc::persist_groups() * tpg;
-        int64_t g = res[k] ? 1 : (spec * r.ncpc + per - 1) / per;
-        if (g < 1) g = 1;
-        if (g >= 8) g = (g + 7) / 8 * 8;
-        want[k] = (int)g;
-        total += g;
-        chunk = std::max<int64_t>(chunk, (r.ncpc + g - 1) / g);
-        if (res[k]) nres = std::max<int64_t>(nres, r.n);
+    for (int spec = PERSIST_SPEC; spec >= 1; --spec) {
+      for (const size_t bound : bounds) {
+        int64_t total = 0, chunk = 1, nres = 0;
+        for (int k = 0; k < R; ++k) {
+          const RepHost &r = c->reps[k];
+          res[k] = vc::persist_lds_need(r.ncpc, r.n, nullptr) <= bound;
+          const int64_t per = (int64_t)vc::persist_groups() * tpg;
+          int64_t g = res[k] || single ? 1 : (spec * r.ncpc + per - 1) / per;
+          if (g < 1) g = 1;
+          if (g >= 8) g = (g + 7) / 8 * 8;
+          want[k] = (int)g;
+          total += g;
+          chunk = std::max<int64_t>(chunk, (r.ncpc + g - 1) / g);
+          if (res[k]) nres = std::max<int64_t>(nres, r.n);
+        }
+        const bool waits = total > R;
+        if (waits && total > cap0) break;  // a lower bound only adds workgroups
+        int ndraw = 0;
+        const size_t lds = vc::persist_lds_need(chunk, nres, &ndraw);
+        if (lds > room) continue;
+        VC_CHECK(c, vc::persist_max_blocks(&per_cu, tab, lds, room), "occupancy query");
+        if (waits && total > (int64_t)dev_cu * per_cu) break;
+        // large replicas first (aligned; of one workgroup each, by atoms, so
+        // that none of the long ones starts last), then the single-digit ones
+        for (int k = 0; k < R; ++k) order[k] = k;
+        std::stable_sort(order.begin(), order.end(), [&](int a, int b) {
+          return single ? c->reps[a].n > c->reps[b].n : (want[a] >= 8) > (want[b] >= 8);
+        });
+        std::vector<int32_t> map((size_t)total);
+        int g0 = 0;
+        for (int k : order) {
+          c->reps[k].g0 = g0;
+          c->reps[k].G = want[k];
+          c->reps[k].res = res[k] != 0;
+          for (int q = 0; q < want[k]; ++q) map[g0 + q] = k;
+          g0 += want[k];
+        }
+        if (c->d_wg_rep) (void)hipFree(c->d_wg_rep);
+        c->d_wg_rep = nullptr;
+        VC_CHECK(c, dalloc(&c->d_wg_rep, (size_t)total), "allocation");
+        VC_CHECK(c, hipMemcpy(c->d_wg_rep, map.data(), sizeof(int32_t) * total,
+                              hipMemcpyHostToDevice),
+                 "copy");
+        c->grid_total = (int)total;
+        if (c->strategy < 2) c->trials_per_group = tpg;
+        c->persist_lds = lds;
+        c->persist_ndraw = ndraw;
+        c->persist_waits = waits;
+        drop_graph(c);
+        return VCSGC_OK;
       }
-      int ndraw = 0, per_cu = 0;
-      const size_t lds = vc::persist_lds_need(chunk, nres, &ndraw);
-      if (lds > (size_t)lds_cu - 1024) continue;
-      VC_CHECK(c, vc::persist_max_blocks(&per_cu, c->pot.tab != 0, lds, (size_t)lds_cu - 1024), "occupancy query");
-      const int64_t cap = (int64_t)dev_cu * per_cu;
-      if (total > cap) {
-        if (R > cap && step == 4 * 8 - 1)
-          return fail(c, VCSGC_E_INVALID_ARG, "more replicas than co-resident workgroups");
-        continue;
-      }
-      // large replicas first (aligned), then the single-digit ones
-      std::vector<int> order(R);
-      for (int k = 0; k < R; ++k) order[k] = k;
-      std::stable_sort(order.begin(), order.end(),
-                       [&](int a, int b) { return (want[a] >= 8) > (want[b] >= 8); });
-      std::vector<int32_t> map((size_t)total);
-      int g0 = 0;
-      for (int k : order) {
-        c->reps[k].g0 = g0;
-        c->reps[k].G = want[k];
-        c->reps[k].res = res[k] != 0;
-        for (int q = 0; q < want[k]; ++q) map[g0 + q] = k;
-        g0 += want[k];
-      }
-      if (c->d_wg_rep) (void)hipFree(c->d_wg_rep);
-      c->d_wg_rep = nullptr;
-      VC_CHECK(c, dalloc(&c->d_wg_rep, (size_t)total), "allocation");
-      VC_CHECK(c, hipMemcpy(c->d_wg_rep, map.data(), sizeof(int32_t) * total,
-                            hipMemcpyHostToDevice),
-               "copy");
-      c->grid_total = (int)total;
-      if (c->strategy < 2) c->trials_per_group = tpg;
-      c->persist_lds = lds;
-      c->persist_ndraw = ndraw;
-      drop_graph(c);
-      return VCSGC_OK;
     }
     if (tpg >= (1 << 20))
       return fail(c, VCSGC_E_INVALID_ARG, "persistent grid does not fit");

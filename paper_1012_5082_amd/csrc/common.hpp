@@ -630,6 +630,7 @@ struct vcsgc_ctx {
   void *d_rs = nullptr;       // per-replica chain state and counters
   int32_t *d_wg_rep = nullptr;  // workgroup -> replica
   int grid_total = 0;
+  bool persist_waits = false;  // some replica has several workgroups, which wait for each other
   size_t persist_lds = 0;   // dynamic LDS of the persistent sweep's workgroups
   int persist_ndraw = 0;    // trials a workgroup draws ahead
   int da_wg = 0, da_ndraw = 0;  // the same sweep with the network: workgroups (0: not yet
@@ -639,7 +640,6 @@ struct vcsgc_ctx {
   unsigned int spin_limit = 1u << 24;
   hipGraph_t graph = nullptr;
   hipGraphExec_t graph_exec = nullptr;
-  bool graph_coop = false;
   alignas(16) unsigned char graph_args_storage[512];  // kernel arguments of the graph node
 
   std::string err;

@@ -1206,11 +1206,12 @@ static hipError_t build_graph(vcsgc_ctx *c) {
   sp.kernelParams = sargs;
   e = hipGraphAddKernelNode(&n_sweep, c->graph, nullptr, 0, &sp);
   if (e != hipSuccess) return e;
-  hipLaunchAttributeValue v = {};
-  v.cooperative = 1;
-  c->graph_coop = hipGraphKernelNodeSetAttribute(n_sweep, hipLaunchAttributeCooperative, &v) ==
-                  hipSuccess;
-  (void)hipGetLastError();
+  if (c->persist_waits) {
+    hipLaunchAttributeValue v = {};
+    v.cooperative = 1;
+    (void)hipGraphKernelNodeSetAttribute(n_sweep, hipLaunchAttributeCooperative, &v);
+    (void)hipGetLastError();
+  }
   RepState *rs = (RepState *)c->d_rs, *host = (RepState *)c->h_rs;
   void *dargs[] = {&rs, &host};
   hipKernelNodeParams dp = {};
@@ -1252,10 +1253,8 @@ static hipError_t launch_done(vcsgc_ctx *c) {
 static hipError_t launch_ungated(vcsgc_ctx *c, bool use_graph);
 
 hipError_t launch_persistent(vcsgc_ctx *c, bool use_graph) {
-  bool waits = false;
-  for (const RepHost &r : c->reps) waits = waits || r.G > 1;
   auto launch = [&]() { return launch_ungated(c, use_graph); };
-  return waits ? gated(c, launch) : launch();
+  return c->persist_waits ? gated(c, launch) : launch();
 }
 
 static hipError_t launch_ungated(vcsgc_ctx *c, bool use_graph) {
@@ -1269,8 +1268,12 @@ static hipError_t launch_ungated(vcsgc_ctx *c, bool use_graph) {
   }
   PersistArgs a = make_args(c);
   void *args[] = {&a};
-  hipError_t e = hipLaunchCooperativeKernel(persist_kernel(c->pot.tab != 0, c->tlog || c->slog), dim3((unsigned)c->grid_total),
-                                    dim3(PBLOCK), args, (unsigned)c->persist_lds, c->stream);
+  const void *f = persist_kernel(c->pot.tab != 0, c->tlog || c->slog);
+  const dim3 grid((unsigned)c->grid_total), block(PBLOCK);
+  const unsigned lds = (unsigned)c->persist_lds;
+  const hipError_t e = c->persist_waits
+                           ? hipLaunchCooperativeKernel(f, grid, block, args, lds, c->stream)
+                           : hipLaunchKernel(f, grid, block, args, lds, c->stream);
   return e == hipSuccess ? launch_done(c) : e;
 }
 

@@ -413,6 +413,51 @@ def test_log_capacity_of_the_last_set_log(torch_cuda):
     g.close()
 
 
+@pytest.mark.parametrize("pot,n_rep,strategy", [
+    ("FS-P1", 257, "graph"),        # one more than compute units
+    ("FS-P1", 1024, "persistent"),  # the most
+    ("TAB-X", 768, "graph"),
+])
+def test_batch_of_more_replicas_than_compute_units(torch_cuda, oracle_mod, pot, n_rep, strategy):
+    """Small replicas with some among them whose state does not fit the LDS, one
+    workgroup each: the chains of the first, the last and every 37th replica
+    are the oracle's; one replica more than the most is refused."""
+    O = oracle_mod
+    from paper_1012_5082_amd.binding import VCSGCBatch, VcsgcError
+    print(f"[batch] {pot} {n_rep} {strategy}", flush=True)
+    limit = {"FS-P1": 1024, "TAB-X": 768}[pot]
+    p = I.params(pot) if pot == "FS-P1" else I.table(pot)
+    small, large = I.bcc(6, 6, 7), I.bcc(19, 18, 19)
+    reps = []
+    for k in range(n_rep):
+        x, y, z, box = large if k in (3, n_rep - 2) else small
+        reps.append(dict(x=x, y=y, z=z, box=box,
+                         species=I.initial_species(x.size, 0.05 + 0.1 * (k % 3), 900 + k),
+                         T=500.0 + k, kappa=1.0 + k % 2, cbar=0.1, dmu0=-0.2 + 0.01 * (k % 5)))
+    b = VCSGCBatch(reps, p)
+    b.set_tuning(strategy, 1)
+    assert b.tuning()["workgroups"] == n_rep
+    args = [np.array([r[k] for r in reps]) for k in ("dmu0", "kappa", "cbar", "T")]
+    s1 = b.sweep_batch(*args, 1, 12)
+    s2 = b.sweep_batch(*args, 2, 12)
+    species, rho = b.species.cpu().numpy(), b.rho().cpu().numpy()
+    for k in sorted({0, 3, n_rep - 2, n_rep - 1, *range(0, n_rep, 37)}):
+        r = reps[k]
+        st = O.SweepState(r["x"], r["y"], r["z"], r["box"], r["species"], p)
+        so, _, _ = O.sweep(st, r["dmu0"], r["kappa"], r["cbar"], r["T"], 3, 12, replica=k)
+        for key in ("trials", "stages", "stage_accepts", "flips"):
+            assert s1[k][key] + s2[k][key] == so[key], (k, key)
+        assert s2[k]["n_final"] == so["n_final"], k
+        own = slice(b.offsets[k], b.offsets[k + 1])
+        assert np.array_equal(species[own], st.species), k
+        assert np.array_equal(rho[own], st.rho), k
+    b.close()
+    if n_rep == limit:
+        with pytest.raises(VcsgcError) as e:
+            VCSGCBatch(reps + reps[:1], p)
+        assert e.value.code == -1
+
+
 def test_batch_get_state(torch_cuda):
     """get_state on a batch of replicas: the sweep counter, the seed, n_B of the
     first replica and the density cache, and nothing beyond the state it was
