@@ -33,7 +33,7 @@ void free_all(vcsgc_ctx *c) {
                   c->stage_lnug, c->m_sites,   c->m_lnu,      c->m_lnu2,     c->m_lnug,   c->m_rec,
                   c->m_part,     c->s_rec,      c->s_part,     c->nvt,        c->nvt_part,
                   c->tab_coef,   c->cg,         c->npt_part,   c->g_start,    c->g_list,
-                  c->g_cum,      c->g_cnt};
+                  c->g_cum,      c->g_cnt,      c->big_lnu,    c->big_site};
   for (void *p : ptrs)
     if (p) (void)hipFree(p);
   if (c->h_pin) (void)hipHostFree(c->h_pin);
@@ -184,9 +184,12 @@ void drop_graph(vcsgc_ctx *c) {
 // doubles.  Where the LDS of the largest resident replica and of the largest
 // share of cells do not go together, the bound of residence is lowered.
 // More replicas than CUs get one workgroup each: none of them waits, so the
-// grid may be any size and the rest follows as workgroups end.
+// grid may be any size and the rest follows as workgroups end.  A share of
+// cells whose draws of one stage the LDS does not hold (some 7,900 cells, two
+// million active cells on 256 workgroups) has them in memory.
 constexpr int PERSIST_SPEC = 8;
-constexpr int64_t PERSIST_MAX = 1 << 20;  // active cells and workgroups of a replica, at most
+constexpr int64_t PERSIST_MAX = ((int64_t)1 << 28) - 1;  // active cells, by the packed counts
+constexpr int64_t PERSIST_WG = 8 * 255;                  // and workgroups of a replica, at most
 // replicas of a batch, per CU (vcsgc_create_batch states the limit)
 constexpr int REPLICAS_PER_CU = 4, REPLICAS_PER_CU_TAB = 3;
 
@@ -215,7 +218,7 @@ vcsgc_status assign_workgroups(vcsgc_ctx *c) {
   std::vector<int> want(R), order(R);
   std::vector<char> res(R);
   const size_t bounds[] = {room, (size_t)lds_cu / 2 - 1024, 0};
-  for (;; tpg *= 2) {
+  for (;; tpg *= 2) {  // (one workgroup per replica fits in the end)
     for (int spec = PERSIST_SPEC; spec >= 1; --spec) {
       for (const size_t bound : bounds) {
         int64_t total = 0, chunk = 1, nres = 0;
@@ -225,7 +228,7 @@ vcsgc_status assign_workgroups(vcsgc_ctx *c) {
           const int64_t per = (int64_t)vc::persist_groups() * tpg;
           int64_t g = res[k] || single ? 1 : (spec * r.ncpc + per - 1) / per;
           if (g < 1) g = 1;
-          if (g >= 8) g = (g + 7) / 8 * 8;
+          if (g >= 8) g = std::min<int64_t>((g + 7) / 8 * 8, PERSIST_WG);
           want[k] = (int)g;
           total += g;
           chunk = std::max<int64_t>(chunk, (r.ncpc + g - 1) / g);
@@ -234,7 +237,9 @@ vcsgc_status assign_workgroups(vcsgc_ctx *c) {
         const bool waits = total > R;
         if (waits && total > cap0) break;  // a lower bound only adds workgroups
         int ndraw = 0;
-        const size_t lds = vc::persist_lds_need(chunk, nres, &ndraw);
+        size_t lds = vc::persist_lds_need(chunk, nres, &ndraw);
+        const bool big = vc::persist_lds_need(chunk, 0, nullptr) > room;
+        if (big) lds = vc::persist_lds_need(0, nres, &ndraw);
         if (lds > room) continue;
         VC_CHECK(c, vc::persist_max_blocks(&per_cu, tab, lds, room), "occupancy query");
         if (waits && total > (int64_t)dev_cu * per_cu) break;
@@ -265,11 +270,18 @@ vcsgc_status assign_workgroups(vcsgc_ctx *c) {
         c->persist_ndraw = ndraw;
         c->persist_waits = waits;
         drop_graph(c);
+        if (c->big_lnu) (void)hipFree(c->big_lnu);
+        if (c->big_site) (void)hipFree(c->big_site);
+        c->big_lnu = nullptr;
+        c->big_site = nullptr;
+        if (big) {
+          const RepHost &z = c->reps.back();
+          VC_CHECK(c, dalloc(&c->big_lnu, (size_t)(z.roff + z.ncpc)), "allocation");
+          VC_CHECK(c, dalloc(&c->big_site, (size_t)(z.roff + z.ncpc)), "allocation");
+        }
         return VCSGC_OK;
       }
     }
-    if (tpg >= (1 << 20))
-      return fail(c, VCSGC_E_INVALID_ARG, "persistent grid does not fit");
   }
 }
 

@@ -631,6 +631,10 @@ struct vcsgc_ctx {
   int32_t *d_wg_rep = nullptr;  // workgroup -> replica
   int grid_total = 0;
   bool persist_waits = false;  // some replica has several workgroups, which wait for each other
+  // a stage's drawn sites and ln u per active cell, where a workgroup's share of
+  // the cells is more than its LDS holds (else NULL)
+  double *big_lnu = nullptr;
+  int32_t *big_site = nullptr;
   size_t persist_lds = 0;   // dynamic LDS of the persistent sweep's workgroups
   int persist_ndraw = 0;    // trials a workgroup draws ahead
   int da_wg = 0, da_ndraw = 0;  // the same sweep with the network: workgroups (0: not yet

@@ -77,7 +77,7 @@ struct RepD {
   int64_t n, aoff;
   int n0, n1, n2;
   int per, ncol;  // colour period per axis, colours
-  int64_t cso, ncpc, S;
+  int64_t cso, ncpc, roff, S;
   double beta, dmu0, kN, ncbar;
   uint64_t seed, key1;
   int g0, G;
@@ -85,9 +85,11 @@ struct RepD {
   int64_t n_sweeps, w0;
 };
 
-// Packed counts of a stage: accepts with dn = +1 (bits 0-20), with dn = -1
-// (21-41), arrivals (42-63); the host keeps cells and workgroups below 2^21.
-constexpr int PK_BITS = 21;
+// Packed counts of a stage: accepts with dn = +1 (bits 0-27), with dn = -1
+// (28-55), arrivals at one row of words (56-63).  A replica has fewer than 2^31
+// cells, so fewer than 2^28 are active, and at most 8 * 255 workgroups (the
+// arrivals are read per row; the sum of the rows may carry out at the top).
+constexpr int PK_BITS = 28;
 constexpr unsigned long long PK_MASK = (1ull << PK_BITS) - 1;
 // A workgroup's counts of a stage with delayed acceptance: trials, trials that
 // pass the network, near ties (a workgroup's share of cells is its LDS ring's
@@ -133,6 +135,9 @@ struct PersistArgs {
   unsigned long long *log_n;  // [2]: trial and stage records written
   unsigned int spin_limit;
   int ndraw;  // trials drawn ahead (LDS entries)
+  // BIG: the drawn trials and records of one stage, per active cell of the replicas
+  double *big_lnu;
+  int32_t *big_site, *big_rec;
 };
 
 // delayed acceptance with the network: its parameters and the r < 4.41 A list
@@ -600,12 +605,21 @@ __device__ __forceinline__ void p_draw_trials(const RepD &r, const PLds &l, cons
   }
 }
 
-// the sweeps of one replica by one of its workgroups
-template <int F, bool RES, bool LOG, bool DA>
+// the sweeps of one replica by one of its workgroups; BIG: the share of cells is
+// more than the LDS can draw a stage of (one stage per batch, LOG), the draws are
+// in memory, and the block's barriers order memory too
+template <int F, bool RES, bool LOG, bool DA, bool BIG>
 __device__ __forceinline__ void sweep_replica(
     const typename std::conditional<DA, PersistArgsDa, PersistArgs>::type &a, const RepD &r,
-    RepState *st, const PLds &l, int *flag) {
+    RepState *st, const PLds &lds, int *flag) {
   static_assert(!DA || (!RES && !LOG), "delayed acceptance");
+  static_assert(!BIG || LOG, "one stage per batch");
+  auto sync = [] {
+    if constexpr (BIG)
+      __syncthreads();
+    else
+      block_sync_lds();
+  };
   auto row_of = [&](int64_t i, PRow &v) {
     if constexpr (DA)
       p_row(a.dj, a.dr, a.dcnt, i, threadIdx.x % PTL, v);
@@ -624,8 +638,15 @@ __device__ __forceinline__ void sweep_replica(
   const int own = t_hi > t_lo ? (int)(t_hi - t_lo) : 0;
   const int32_t *cstart = a.cstart + r.cso;
   const int32_t *catoms = a.catoms + r.aoff;
+  PLds l = lds;
+  if constexpr (BIG) {
+    l.lnu = a.big_lnu + r.roff + t_lo;
+    l.site = a.big_site + r.roff + t_lo;
+    l.rec = a.big_rec + r.roff + t_lo;
+  }
   const PState<RES> state{a, l, r.aoff};
-  const int win = a.ndraw / chunk < PWIN ? a.ndraw / chunk : PWIN;  // stages of drawn trials
+  // stages of drawn trials
+  const int win = BIG ? 1 : a.ndraw / chunk < PWIN ? a.ndraw / chunk : PWIN;
   const int wave = tid >> 6;
   // Stages per batch: as many as the trial groups make in one pass, doubled
   // (more passes) while whole batches are rejected, so that a batch's fixed
@@ -664,17 +685,17 @@ __device__ __forceinline__ void sweep_replica(
       const bool one_pass = len * own <= PGROUPS;
       unsigned long long *cw = l.cw + 2 * PDMAX * (batch % PCW);
       if (s0 + len > hd) {  // the trials of this batch (and a few more) are due now
-        block_sync_lds();   // the last batch's readers of the rings are done
+        sync();   // the last batch's readers of the rings are done
         const uint32_t ts = min(s0 + 4 * len, S);
         if (hs < ts) {
           p_draw_stages(r, l, w, hs, ts, tid, PBLOCK);
           hs = ts;
         }
-        block_sync_lds();
+        sync();
         const uint32_t to = min(min(s0 + 3 * len, s0 + win), S);
         p_draw_trials<DA>(r, l, cstart, catoms, w, hd, to, t_lo, own, chunk, win, tid, PBLOCK);
         hd = to;
-        block_sync_lds();
+        sync();
       }
       // what the waves draw while the others work or wait: about a batch of
       // trials and of stage counters, kept clear of the slots of the last batch
@@ -789,7 +810,7 @@ __device__ __forceinline__ void sweep_replica(
         }
       }
       if (RES || r.G == 1) draw_ahead(PBLOCK / 128);  // by the waves with the fewest trials
-      block_sync_lds();
+      sync();
       // the counts of the batch after next, last read before this barrier
       if (tid >= PBLOCK - 2 * PDMAX)
         l.cw[2 * PDMAX * ((batch + 2) % PCW) + tid - (PBLOCK - 2 * PDMAX)] = 0;
@@ -844,7 +865,7 @@ __device__ __forceinline__ void sweep_replica(
         } else {
           draw_ahead(1);
         }
-        block_sync_lds();
+        sync();
         if (*flag) return;
         tot = l.tot;
         tst = 1;
@@ -935,7 +956,7 @@ __device__ __forceinline__ void sweep_replica(
         }
         if (!RES && r.G > 1) {
           wait_stores();
-          block_sync_lds();
+          sync();
           ++ncom;
           if (tid < 64) {
             // row q mod 8 counts its workgroups; lane x < 8 polls row x
@@ -960,11 +981,11 @@ __device__ __forceinline__ void sweep_replica(
               *flag = late;
             }
           }
-          block_sync_lds();
+          sync();
           if (*flag) return;
         } else {
           if (!RES || a.vx) wait_stores();
-          block_sync_lds();  // the next batch's trials see the commit
+          sync();  // the next batch's trials see the commit
         }
       }
       s0 += done;
@@ -1002,13 +1023,13 @@ __device__ __forceinline__ void sweep_replica(
 
 // TAB: the potential's form (analytic or tabulated) fixed at compile time,
 // so each variant keeps only its own arithmetic and registers.
-// LOG: trial or stage logs are written (one stage per batch).
+// LOG: trial or stage logs are written (one stage per batch), or BIG.
 // The replica's constants of the arithmetic go to vector registers: with
 // everything uniform in scalar ones the loop spilled them a thousand times
 // into vector lanes.
 __device__ __forceinline__ void in_vgpr(double &x) { asm volatile("" : "+v"(x)); }
 
-template <bool TAB, bool LOG>
+template <bool TAB, bool LOG, bool BIG>
 __global__ void __launch_bounds__(PBLOCK) k_sweep_persistent(PersistArgs a) {
   constexpr int F = TAB ? 1 : 0;
   extern __shared__ __align__(16) unsigned char lds[];
@@ -1031,9 +1052,9 @@ __global__ void __launch_bounds__(PBLOCK) k_sweep_persistent(PersistArgs a) {
   }
   const PLds l = persist_lds(lds, a.ndraw, r.res ? r.n : 0);
   if (r.res)
-    sweep_replica<F, true, LOG, false>(a, r, a.rs + rix, l, &flag);
+    sweep_replica<F, true, LOG, false, BIG>(a, r, a.rs + rix, l, &flag);
   else
-    sweep_replica<F, false, LOG, false>(a, r, a.rs + rix, l, &flag);
+    sweep_replica<F, false, LOG, false, BIG>(a, r, a.rs + rix, l, &flag);
 }
 
 // delayed acceptance with the network, one system, state in memory
@@ -1048,7 +1069,7 @@ __global__ void __launch_bounds__(PBLOCK) k_sweep_persistent_da(PersistArgsDa a)
   in_vgpr(r.kN);
   in_vgpr(r.ncbar);
   const PLds l = persist_lds_da(lds, a.ndraw);
-  sweep_replica<F, false, false, true>(a, r, a.rs, l, &flag);
+  sweep_replica<F, false, false, true, false>(a, r, a.rs, l, &flag);
 }
 
 // The end of a call, one block per replica: its statistics to the host's pinned
@@ -1089,35 +1110,38 @@ namespace vc {
 
 int persist_groups() { return PGROUPS; }
 // dynamic LDS of a grid whose largest share of cells is `chunk` and whose
-// largest resident replica has nres atoms, and its drawn trials
+// largest resident replica has nres atoms, and its drawn trials (chunk 0: the
+// draws are in memory)
 size_t persist_lds_need(int64_t chunk, int64_t nres, int *ndraw) {
-  const int64_t nd = std::max<int64_t>(nres > 0 ? PDRAW : 2 * PDRAW, chunk);
+  const int64_t nd = chunk ? std::max<int64_t>(nres > 0 ? PDRAW : 2 * PDRAW, chunk) : 0;
   if (ndraw) *ndraw = (int)nd;
   return persist_lds_bytes(nd, nres);
 }
 size_t repd_size() { return sizeof(RepD); }
 size_t repstate_size() { return sizeof(RepState); }
 
-static const void *persist_kernel(bool tab, bool log) {
+static const void *persist_kernel(bool tab, bool log, bool big) {
   if (tab)
-    return log ? (const void *)k_sweep_persistent<true, true>
-               : (const void *)k_sweep_persistent<true, false>;
-  return log ? (const void *)k_sweep_persistent<false, true>
-             : (const void *)k_sweep_persistent<false, false>;
+    return big   ? (const void *)k_sweep_persistent<true, true, true>
+           : log ? (const void *)k_sweep_persistent<true, true, false>
+                 : (const void *)k_sweep_persistent<true, false, false>;
+  return big   ? (const void *)k_sweep_persistent<false, true, true>
+         : log ? (const void *)k_sweep_persistent<false, true, false>
+               : (const void *)k_sweep_persistent<false, false, false>;
 }
 
 // co-resident workgroups per CU of the potential form's kernels (with and
-// without logs); lds_max: the LDS bound asked for once and for all (more
+// without logs, and with the draws in memory); lds_max: the LDS bound asked for once and for all (more
 // than 64 KB has to be)
 hipError_t persist_max_blocks(int *per_cu, bool tab, size_t lds, size_t lds_max) {
   *per_cu = 0;
-  for (int log = 0; log < 2; ++log) {
-    const void *f = persist_kernel(tab, log != 0);
+  for (int v = 0; v < 3; ++v) {
+    const void *f = persist_kernel(tab, v == 1, v == 2);
     hipError_t e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_max);
     int n = 0;
     if (e == hipSuccess) e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, f, PBLOCK, lds);
     if (e != hipSuccess) return e;
-    *per_cu = log == 0 ? n : std::min(*per_cu, n);
+    *per_cu = v == 0 ? n : std::min(*per_cu, n);
   }
   return hipSuccess;
 }
@@ -1145,6 +1169,9 @@ static PersistArgs make_args(vcsgc_ctx *c) {
   a.log_n = &c->ds->tlog_n;
   a.spin_limit = c->spin_limit;
   a.ndraw = c->persist_ndraw;
+  a.big_lnu = c->big_lnu;
+  a.big_site = c->big_site;
+  a.big_rec = c->rec;
   return a;
 }
 
@@ -1166,6 +1193,7 @@ void persist_stage_params(vcsgc_ctx *c, const double *dmu0, const double *kappa,
     d.n2 = r.nc[2];
     d.cso = r.cso;
     d.ncpc = r.ncpc;
+    d.roff = r.roff;
     d.res = r.res && !da ? 1 : 0;
     d.S = r.S;
     d.beta = 1.0 / (KB * T[k]);
@@ -1199,7 +1227,7 @@ static hipError_t build_graph(vcsgc_ctx *c) {
   *ga = make_args(c);
   void *sargs[] = {ga};
   hipKernelNodeParams sp = {};
-  sp.func = const_cast<void *>(persist_kernel(c->pot.tab != 0, c->tlog || c->slog));
+  sp.func = const_cast<void *>(persist_kernel(c->pot.tab != 0, c->tlog || c->slog, c->big_lnu != nullptr));
   sp.gridDim = dim3((unsigned)c->grid_total);
   sp.blockDim = dim3(PBLOCK);
   sp.sharedMemBytes = (unsigned)c->persist_lds;
@@ -1268,7 +1296,7 @@ static hipError_t launch_ungated(vcsgc_ctx *c, bool use_graph) {
   }
   PersistArgs a = make_args(c);
   void *args[] = {&a};
-  const void *f = persist_kernel(c->pot.tab != 0, c->tlog || c->slog);
+  const void *f = persist_kernel(c->pot.tab != 0, c->tlog || c->slog, c->big_lnu != nullptr);
   const dim3 grid((unsigned)c->grid_total), block(PBLOCK);
   const unsigned lds = (unsigned)c->persist_lds;
   const hipError_t e = c->persist_waits

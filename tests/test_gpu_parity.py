@@ -389,6 +389,78 @@ def test_batch_replicas_match_oracle(torch_cuda, oracle_mod):
     b.close()
 
 
+def _sparse_system(cells, pot):
+    """A 12^3 bcc block and 20,000 scattered atoms in a box of cells^3 link
+    cells, most of them empty."""
+    rng = np.random.default_rng(5)
+    box = np.full(3, cells * 2.0 * pot.rc + 1.0)
+    x, y, z, _ = I.bcc(12, 12, 12)
+    p = rng.uniform(0.0, 1.0, (20000, 3)) * box
+    p = p[~np.all(p < 45.0, axis=1)]
+    x, y, z = (np.concatenate([a + 5.0, p[:, k]]) for k, a in enumerate((x, y, z)))
+    return dict(x=x, y=y, z=z, box=box, species=I.initial_species(x.size, 0.5, 6))
+
+
+@pytest.mark.parametrize("cells,strategy", [
+    (204, "graph"),       # 1,061,208 active cells: more than 2^20
+    (204, "batch"),
+    (254, "persistent"),  # 2,048,383: more per workgroup than the LDS draws at once
+    (254, "graph"),
+])
+def test_many_active_cells(torch_cuda, oracle_mod, cells, strategy):
+    """Boxes of over a million active cells per stage: created, and every
+    strategy gives the oracle's chain (logs included where they are kept)."""
+    O = oracle_mod
+    pot = I.params("FS-P1")
+    d = _sparse_system(cells, pot)
+    print(f"[cells] {cells} {strategy}", flush=True)
+    g = gpu_context(d, pot, skin=3.6)
+    g.set_tuning(strategy, 1)
+    log = (cells, strategy) == (254, "graph")
+    if log:
+        g.enable_log(100000, 100)
+    a = [g.sweep(0.0, 3e-3, 0.5, 600.0, k, 31) for k in (1, 2)]
+    st = O.SweepState(d["x"], d["y"], d["z"], d["box"], d["species"], pot)
+    so, tl_o, sl_o = O.sweep(st, 0.0, 3e-3, 0.5, 600.0, 3, 31, log_trials=100000 if log else 0,
+                             log_stages=100 if log else 0)
+    for k in ("trials", "local_accepts", "stages", "stage_accepts", "flips"):
+        assert a[0][k] + a[1][k] == so[k], k
+    assert a[1]["n_final"] == so["n_final"]
+    if log:
+        tl_g, sl_g, _, _ = g.logs()
+        compare_logs(tl_g, sl_g, tl_o, sl_o)
+        g.disable_log()
+    assert so["stage_accepts"] == so["stages"]  # then a stiffer reservoir, with rejected stages
+    a = g.sweep(0.0, 30.0, 0.5, 600.0, 2, 31)
+    so, _, _ = O.sweep(st, 0.0, 30.0, 0.5, 600.0, 2, 31)
+    assert so["stage_accepts"] < so["stages"]
+    for k in ("trials", "local_accepts", "stages", "stage_accepts", "flips", "n_final"):
+        assert a[k] == so[k], k
+    assert np.array_equal(g.species.cpu().numpy(), st.species)
+    assert np.array_equal(g.rho().cpu().numpy(), st.rho)
+    g.close()
+
+
+def test_batch_with_many_active_cells(torch_cuda, oracle_mod):
+    """The same box in a batch with a replica that fits the LDS."""
+    O = oracle_mod
+    from paper_1012_5082_amd.binding import VCSGCBatch
+    pot = I.params("FS-P1")
+    reps = [_sparse_system(254, pot), dict(zip(("x", "y", "z", "box"), I.bcc(6, 6, 6)))]
+    reps[1]["species"] = I.initial_species(reps[1]["x"].size, 0.5, 8)
+    print("[cells] batch", flush=True)
+    b = VCSGCBatch(reps, pot)
+    s = b.sweep_batch(0.0, 3e-3, 0.5, 600.0, 2, 31)
+    for k, r in enumerate(reps):
+        st = O.SweepState(r["x"], r["y"], r["z"], r["box"], r["species"], pot)
+        so, _, _ = O.sweep(st, 0.0, 3e-3, 0.5, 600.0, 2, 31, replica=k)
+        for key in ("trials", "local_accepts", "stages", "stage_accepts", "flips", "n_final"):
+            assert s[k][key] == so[key], (k, key)
+        assert np.array_equal(b.replica_species(k), st.species), k
+        assert np.array_equal(b.replica_rho(k), st.rho), k
+    b.close()
+
+
 def test_log_capacity_of_the_last_set_log(torch_cuda):
     """A log set again on the same buffers with smaller capacities: the sweep
     (graph-captured, as built for the first ones) writes no row beyond them."""
