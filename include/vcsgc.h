@@ -254,12 +254,18 @@ vcsgc_status vcsgc_set_tuning(vcsgc_ctx *ctx, int32_t strategy, int32_t trials_p
 vcsgc_status vcsgc_get_tuning(vcsgc_ctx *ctx, int32_t *strategy, int32_t *trials_per_group,
                               int32_t *workgroups);
 
-/* Bound on the waits of the persistent sweep (strategies 0 and 1): a
- * workgroup that polls a per-replica barrier `polls` times without seeing
- * every workgroup of its replica arrive abandons the call; vcsgc_sweep and
+/* Bound on the waits of the persistent sweep: a workgroup that polls a
+ * per-replica barrier `polls` times without seeing every workgroup of its
+ * replica arrive abandons the call; vcsgc_sweep (strategies 0 and 1) and
  * vcsgc_sweep_batch then return VCSGC_E_BARRIER_TIMEOUT and the context is
  * left in the error state (part of a stage may have been committed).
  * polls >= 1; the default, 2^24 polls with a short sleep each, is seconds.
+ * Nothing is committed before all workgroups of a replica have started.
+ * Where they have not within 2^14 polls (or the limit, if lower: another
+ * process's grid may hold their places) the launch ends without effect and is
+ * made again until the limit is reached; with strategies 2 and 3 and with the
+ * network's delayed acceptance the call runs with kernels per stage instead
+ * and does not end in this error.
  * For failure-handling tests and diagnostics. */
 vcsgc_status vcsgc_set_wait_limit(vcsgc_ctx *ctx, uint32_t polls);
 

@@ -209,8 +209,7 @@ vcsgc_status assign_workgroups(vcsgc_ctx *c) {
       return fail(c, VCSGC_E_INVALID_ARG, "too many cells for the persistent sweep");
   // LDS of a workgroup with the static part and some slack left out
   const size_t room = (size_t)lds_cu - 1024;
-  VC_CHECK(c, vc::persist_max_blocks(&per_cu, tab, vc::persist_lds_need(1, 0, nullptr), room),
-           "occupancy query");
+  VC_CHECK(c, vc::persist_max_blocks(&per_cu, tab, false, room), "occupancy query");
   const int64_t cap0 = (int64_t)dev_cu * per_cu;  // workgroups of the least LDS
   const bool single = R > cap0;                   // one workgroup per replica
   // (the pipeline strategies' parameter is the stages of their kernels' batch)
@@ -241,8 +240,11 @@ vcsgc_status assign_workgroups(vcsgc_ctx *c) {
         const bool big = vc::persist_lds_need(chunk, 0, nullptr) > room;
         if (big) lds = vc::persist_lds_need(0, nres, &ndraw);
         if (lds > room) continue;
-        VC_CHECK(c, vc::persist_max_blocks(&per_cu, tab, lds, room), "occupancy query");
-        if (waits && total > (int64_t)dev_cu * per_cu) break;
+        int by_regs = per_cu;
+        if (big)
+          VC_CHECK(c, vc::persist_max_blocks(&by_regs, tab, true, room), "occupancy query");
+        const int by_lds = std::max(1, (int)(lds_cu / (lds + 2048)));
+        if (waits && total > (int64_t)dev_cu * std::min(by_regs, by_lds)) break;
         // large replicas first (aligned; of one workgroup each, by atoms, so
         // that none of the long ones starts last), then the single-digit ones
         for (int k = 0; k < R; ++k) order[k] = k;
@@ -759,6 +761,37 @@ bool valid_params(double dmu0, double kappa, double cbar, double T) {
          cbar <= 1.0 && is_fin(T) && T > 0.0;
 }
 
+// Sweeps of a single system with kernels per stage or batch of stages.
+vcsgc_status sweep_stages(vcsgc_ctx *c, double dmu0, double kappa, double cbar, double T,
+                          int64_t n_sweeps, uint64_t seed, vcsgc_stats *out) {
+  VC_CHECK(c, vc::persist_sync_nb_to_stage(c), "sweep");
+  c->h_state_final = false;
+  VC_CHECK(c, vc::launch_sweeps(c, dmu0, kappa, cbar, T, n_sweeps, seed), "sweep");
+  // the pipelines end with the device state read and n_B synchronized
+  const bool have = c->h_state_final;
+  c->h_state_final = false;
+  if (!have) VC_CHECK(c, vc::persist_sync_nb_from_stage(c), "sweep");
+  c->w += (uint64_t)n_sweeps;
+  if (have && c->h_state->stages)
+    c->m_stage_acc = (double)c->h_state->stage_acc / (double)c->h_state->stages;
+  if (out) {
+    hipError_t e = hipSuccess;
+    vc::DevState h = have ? *c->h_state : read_state(c, &e);
+    if (e != hipSuccess) return dev_fail(c, e, "sweep");
+    out->trials = (int64_t)h.trials;
+    out->local_accepts = (int64_t)h.local_acc;
+    out->stages = (int64_t)h.stages;
+    out->stage_accepts = (int64_t)h.stage_acc;
+    out->flips = (int64_t)h.flips;
+    out->near_ties = (int64_t)h.near_ties;
+    out->n_final = h.n_b_cur;
+    out->sum_n = h.sum_n;
+    out->sum_n2 = h.sum_n2;
+    out->stage1_pass = (int64_t)h.stage1_pass;
+  }
+  return VCSGC_OK;
+}
+
 // Sweeps of every replica with per-replica parameters; stats may be NULL.
 vcsgc_status sweep_impl(vcsgc_ctx *c, const double *dmu0, const double *kappa, const double *cbar,
                         const double *T, int64_t n_sweeps, uint64_t seed, vcsgc_stats *out) {
@@ -825,52 +858,36 @@ vcsgc_status sweep_impl(vcsgc_ctx *c, const double *dmu0, const double *kappa, c
       (c->da_mode && !da) || c->smp_cap > 0 || c->local_steps > 1 || c->grown ||
       (!da && c->strategy >= 2 && (n_sweeps == 0 || quiet || logged || (c->tmask & (1u << VCSGC_KT_STAGE)) ||
                             c->reps[0].ncpc > (int64_t)c->reps[0].G * vc::persist_groups()));
-  if (per_stage && R == 1) {
-    // one trial kernel and one commit kernel per stage
-    VC_CHECK(c, vc::persist_sync_nb_to_stage(c), "sweep");
-    c->h_state_final = false;
-    VC_CHECK(c, vc::launch_sweeps(c, dmu0[0], kappa[0], cbar[0], T[0], n_sweeps, seed), "sweep");
-    // the pipelines end with the device state read and n_B synchronized
-    const bool have = c->h_state_final;
-    c->h_state_final = false;
-    if (!have) VC_CHECK(c, vc::persist_sync_nb_from_stage(c), "sweep");
-    c->w += (uint64_t)n_sweeps;
-    if (have && c->h_state->stages)
-      c->m_stage_acc = (double)c->h_state->stage_acc / (double)c->h_state->stages;
-    if (out) {
-      hipError_t e = hipSuccess;
-      vc::DevState h = have ? *c->h_state : read_state(c, &e);
-      if (e != hipSuccess) return dev_fail(c, e, "sweep");
-      out->trials = (int64_t)h.trials;
-      out->local_accepts = (int64_t)h.local_acc;
-      out->stages = (int64_t)h.stages;
-      out->stage_accepts = (int64_t)h.stage_acc;
-      out->flips = (int64_t)h.flips;
-      out->near_ties = (int64_t)h.near_ties;
-      out->n_final = h.n_b_cur;
-      out->sum_n = h.sum_n;
-      out->sum_n2 = h.sum_n2;
-      out->stage1_pass = (int64_t)h.stage1_pass;
-    }
-    return VCSGC_OK;
-  }
-  vc::persist_stage_params(c, dmu0, kappa, cbar, T, n_sweeps, seed, da);
-  if (n_sweeps > 0) {
-    int h = vc::tstart(c, VCSGC_KT_PERSIST);
-    if (da)
-      VC_CHECK(c, vc::launch_persistent_da(c), "persistent sweep");
-    else
-      VC_CHECK(c, vc::launch_persistent(c, c->strategy != 1), "persistent sweep");
-    vc::tstop(c, h);
-  }
-  c->w += (uint64_t)n_sweeps;
-  // the timeout flags are read after every call, with or without statistics:
-  // a workgroup that left a timed-out wait may have committed part of a stage
+  if (per_stage && R == 1)
+    return sweep_stages(c, dmu0[0], kappa[0], cbar[0], T[0], n_sweeps, seed, out);
+  // A replica whose workgroups did not all start has not changed: it is tried
+  // again, or, where the call need not be persistent, run with kernels per
+  // stage.
   int err = 0;
   vcsgc_stats one;
   vcsgc_stats *const got = out ? out : R == 1 ? &one : nullptr;
-  VC_CHECK(c, vc::persist_read_stats(c, got, &err, n_sweeps > 0, da), "sweep");
-  if (R == 1 && got->stages)
+  std::vector<char> todo((size_t)R, 1);
+  for (uint64_t polls = 0;;) {
+    vc::persist_stage_params(c, dmu0, kappa, cbar, T, n_sweeps, todo.data(), seed, da);
+    if (n_sweeps > 0) {
+      int h = vc::tstart(c, VCSGC_KT_PERSIST);
+      if (da)
+        VC_CHECK(c, vc::launch_persistent_da(c), "persistent sweep");
+      else
+        VC_CHECK(c, vc::launch_persistent(c, c->strategy != 1), "persistent sweep");
+      vc::tstop(c, h);
+    }
+    // the error words are read after every call, with or without statistics:
+    // a workgroup that left a timed-out wait may have committed part of a stage
+    VC_CHECK(c, vc::persist_read_stats(c, got, todo.data(), &err, n_sweeps > 0, da), "sweep");
+    if (!(err & vc::PERSIST_NOT_STARTED)) break;
+    if (R == 1 && (da || c->strategy >= 2))
+      return sweep_stages(c, dmu0[0], kappa[0], cbar[0], T[0], n_sweeps, seed, out);
+    polls += std::min(c->spin_limit, vc::ENTRY_LIMIT);
+    if (polls >= c->spin_limit || (err & vc::PERSIST_TIMEOUT)) break;
+  }
+  c->w += (uint64_t)n_sweeps;
+  if (R == 1 && got->stages && !err)
     c->m_stage_acc = (double)got->stage_accepts / (double)got->stages;
   if (err) {
     c->sticky = true;

@@ -641,7 +641,7 @@ struct vcsgc_ctx {
                                 // sized, -1: does not fit), trials drawn ahead
   int trials_per_group = 1;   // tiling: trial groups per active cell (see assign_workgroups)
   int strategy = 0;           // 0: persistent (graph), 1: persistent (direct), 2: per-stage
-  unsigned int spin_limit = 1u << 24;
+  unsigned int spin_limit = 1u << 24;  // see vcsgc_set_wait_limit
   hipGraph_t graph = nullptr;
   hipGraphExec_t graph_exec = nullptr;
   alignas(16) unsigned char graph_args_storage[512];  // kernel arguments of the graph node
@@ -730,14 +730,22 @@ int persist_groups();
 size_t persist_lds_need(int64_t chunk, int64_t nres, int *ndraw);
 size_t repd_size();
 size_t repstate_size();
-hipError_t persist_max_blocks(int *per_cu, bool tab, size_t lds, size_t lds_max);
+hipError_t persist_max_blocks(int *per_cu, bool tab, bool big, size_t lds_max);
+// bits of a replica's error word: a barrier wait exceeded its limit; its
+// workgroups did not all start, and it has not changed
+constexpr int PERSIST_TIMEOUT = 1, PERSIST_NOT_STARTED = 2;
+// Polls (with a short sleep, about 1 us each) of a barrier by default, and of
+// the entry barrier at most: workgroups start within microseconds of each other
+// unless another process's grid holds their places.
+constexpr unsigned int SPIN_LIMIT = 1u << 24, ENTRY_LIMIT = 1u << 14;
 void persist_stage_params(vcsgc_ctx *c, const double *dmu0, const double *kappa,
-                                const double *cbar, const double *T, int64_t n_sweeps,
-                                uint64_t seed, bool da = false);
+                          const double *cbar, const double *T, int64_t n_sweeps,
+                          const char *todo, uint64_t seed, bool da);
 hipError_t launch_persistent(vcsgc_ctx *c, bool use_graph);
 hipError_t persist_da_grid(vcsgc_ctx *c);
 hipError_t launch_persistent_da(vcsgc_ctx *c);
-hipError_t persist_read_stats(vcsgc_ctx *c, vcsgc_stats *out, int *err, bool launched, bool da);
+hipError_t persist_read_stats(vcsgc_ctx *c, vcsgc_stats *out, char *todo, int *err, bool launched,
+                              bool da);
 hipError_t persist_read_nb(vcsgc_ctx *c, int64_t *n_b);
 hipError_t persist_count(vcsgc_ctx *c);
 hipError_t persist_sync_nb_to_stage(vcsgc_ctx *c);

@@ -110,12 +110,17 @@ struct alignas(128) RepState {
   struct alignas(128) Bar {
     unsigned long long n;
   } bar[8];
+  // entry barrier: workgroups that have started; the top bit: given up
+  struct alignas(128) Entry {
+    unsigned long long n;
+  } entry;
   alignas(128) long long n_b;  // n_B at the start of the next call
   unsigned long long trials, stage1, local_acc, stages, stage_acc, flips, near_ties;
   double sum_n, sum_n2;
-  int err;
+  int err;  // PERSIST_TIMEOUT, PERSIST_NOT_STARTED
   long long n_final;
 };
+constexpr unsigned long long ENTRY_GIVEN_UP = 1ull << 63;
 
 struct PersistArgs {
   const RepD *reps;
@@ -133,7 +138,7 @@ struct PersistArgs {
   double *slog;
   int64_t scap;
   unsigned long long *log_n;  // [2]: trial and stage records written
-  unsigned int spin_limit;
+  unsigned int spin_limit, entry_limit;  // polls of a barrier and of the entry barrier
   int ndraw;  // trials drawn ahead (LDS entries)
   // BIG: the drawn trials and records of one stage, per active cell of the replicas
   double *big_lnu;
@@ -565,6 +570,30 @@ __device__ __forceinline__ double da_trial(const PState<false> &st, const Persis
   return own + pair + emb;
 }
 
+// Whether all G workgroups of the replica have started (lane 0 of a wave).
+// Another process's grid on the same device can keep some of them from it for as
+// long as it waits for workgroups that these keep out.  So a workgroup that
+// has polled `limit` times gives up, unless the last arrival came first: one
+// compare-and-swap decides it for all of them, before anything is committed.
+__device__ __forceinline__ bool p_entered(RepState *st, unsigned long long G, unsigned int limit) {
+  unsigned int it = 0;
+  for (;;) {
+    unsigned long long v =
+        __hip_atomic_load(&st->entry.n, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (v & ENTRY_GIVEN_UP) return false;
+    if (v == G) return true;
+    if (++it <= limit) {
+      __builtin_amdgcn_s_sleep(1);
+    } else if (__hip_atomic_compare_exchange_strong(&st->entry.n, &v, v | ENTRY_GIVEN_UP,
+                                                    __ATOMIC_RELAXED, __ATOMIC_RELAXED,
+                                                    __HIP_MEMORY_SCOPE_AGENT)) {
+      __hip_atomic_fetch_or(&st->err, PERSIST_NOT_STARTED, __ATOMIC_RELAXED,
+                            __HIP_MEMORY_SCOPE_AGENT);
+      return false;
+    }  // (else another one has arrived or given up)
+  }
+}
+
 // Draws ahead of the trials.  Stage counters: the colour and ln u_g of stages
 // [s_lo, s_hi) into the ring of PWIN slots; trials: the site drawn from each
 // own cell and ln u of its local test for stages [s_lo, s_hi) (counters drawn
@@ -665,6 +694,18 @@ __device__ __forceinline__ void sweep_replica(
   double sum_n = 0.0, sum_n2 = 0.0;
   unsigned long long ncom = 0;
   unsigned int batch = 0;
+  bool entered = RES || r.G == 1;
+  if (!entered && tid == 0)
+    __hip_atomic_fetch_add(&st->entry.n, 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  // before the first barrier, or with logs before the first trial
+  auto enter = [&]() {
+    if (tid == 0) *flag = !p_entered(st, (unsigned long long)r.G, a.entry_limit);
+    sync();
+    entered = !*flag;
+    sync();  // (the flag has been read)
+    return entered;
+  };
+  if (LOG && !entered && !enter()) return;
   if (RES)
     for (int64_t i = tid; i < r.n; i += PBLOCK) {
       l.rho[i] = a.rho[r.aoff + i];
@@ -818,6 +859,7 @@ __device__ __forceinline__ void sweep_replica(
       int tst = 2;
       if (!RES && r.G > 1) {
         // ---- counts and barrier in one word per stage
+        if (!LOG && !entered && !enter()) return;
         if (tid < 64) {
           unsigned long long *word = &st->word[batch % PWORDS][0][0];
           if (q == 0) {
@@ -859,7 +901,8 @@ __device__ __forceinline__ void sweep_replica(
           }
           if (wl == 0) {
             if (late)
-              __hip_atomic_fetch_or(&st->err, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+              __hip_atomic_fetch_or(&st->err, PERSIST_TIMEOUT, __ATOMIC_RELAXED,
+                                    __HIP_MEMORY_SCOPE_AGENT);
             *flag = late;
           }
         } else {
@@ -977,7 +1020,8 @@ __device__ __forceinline__ void sweep_replica(
             }
             if (wl == 0) {
               if (late)
-                __hip_atomic_fetch_or(&st->err, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                __hip_atomic_fetch_or(&st->err, PERSIST_TIMEOUT, __ATOMIC_RELAXED,
+                                    __HIP_MEMORY_SCOPE_AGENT);
               *flag = late;
             }
           }
@@ -1099,6 +1143,7 @@ __global__ void __launch_bounds__(BLOCK) k_persist_done(RepState *rs, RepState *
   }
   for (int q = threadIdx.x; q < PWORDS * 8 * PDG; q += BLOCK) (&s.word[0][0][0])[q] = 0;
   if (threadIdx.x < 8) s.bar[threadIdx.x].n = 0;
+  if (threadIdx.x == 0) s.entry.n = 0;
 }
 
 }  // namespace vc
@@ -1130,18 +1175,19 @@ static const void *persist_kernel(bool tab, bool log, bool big) {
                : (const void *)k_sweep_persistent<false, false, false>;
 }
 
-// co-resident workgroups per CU of the potential form's kernels (with and
-// without logs, and with the draws in memory); lds_max: the LDS bound asked for once and for all (more
-// than 64 KB has to be)
-hipError_t persist_max_blocks(int *per_cu, bool tab, size_t lds, size_t lds_max) {
-  *per_cu = 0;
-  for (int v = 0; v < 3; ++v) {
-    const void *f = persist_kernel(tab, v == 1, v == 2);
+// Co-resident workgroups per CU that the registers of the potential form's
+// kernels allow (with and without logs, or with the draws in memory), and the
+// LDS bound asked for once and for all (more than 64 KB has to be).
+hipError_t persist_max_blocks(int *per_cu, bool tab, bool big, size_t lds_max) {
+  *per_cu = 1 << 10;
+  for (int log = big ? 1 : 0; log < 2; ++log) {
+    const void *f = persist_kernel(tab, log != 0, big);
     hipError_t e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_max);
     int n = 0;
-    if (e == hipSuccess) e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, f, PBLOCK, lds);
+    if (e == hipSuccess)
+      e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, f, PBLOCK, persist_lds_bytes(0, 0));
     if (e != hipSuccess) return e;
-    *per_cu = v == 0 ? n : std::min(*per_cu, n);
+    *per_cu = std::min(*per_cu, n);
   }
   return hipSuccess;
 }
@@ -1167,7 +1213,10 @@ static PersistArgs make_args(vcsgc_ctx *c) {
   a.slog = c->slog;
   a.scap = c->scap;
   a.log_n = &c->ds->tlog_n;
-  a.spin_limit = c->spin_limit;
+  // Strategies 0 and 1 end in an error where a wait exceeds the caller's limit;
+  // the others have kernels that wait for nothing to fall back on, at the entry.
+  a.spin_limit = c->strategy >= 2 || c->da_mode ? SPIN_LIMIT : c->spin_limit;
+  a.entry_limit = std::min(c->spin_limit, ENTRY_LIMIT);
   a.ndraw = c->persist_ndraw;
   a.big_lnu = c->big_lnu;
   a.big_site = c->big_site;
@@ -1178,8 +1227,8 @@ static PersistArgs make_args(vcsgc_ctx *c) {
 // The per-call replica parameters, in pinned memory that the kernel reads
 // itself; every call has been waited for before the next one writes them.
 void persist_stage_params(vcsgc_ctx *c, const double *dmu0, const double *kappa,
-                                const double *cbar, const double *T, int64_t n_sweeps,
-                                uint64_t seed, bool da) {
+                          const double *cbar, const double *T, int64_t n_sweeps,
+                          const char *todo, uint64_t seed, bool da) {
   RepD *h = (RepD *)c->h_reps;
   for (size_t k = 0; k < c->reps.size(); ++k) {
     const RepHost &r = c->reps[k];
@@ -1204,7 +1253,7 @@ void persist_stage_params(vcsgc_ctx *c, const double *dmu0, const double *kappa,
     d.key1 = (uint64_t)k;
     d.g0 = da ? 0 : r.g0;
     d.G = da ? c->da_wg : r.G;
-    d.n_sweeps = n_sweeps;
+    d.n_sweeps = todo[k] ? n_sweeps : 0;
     d.w0 = (int64_t)c->w;
   }
 }
@@ -1363,10 +1412,12 @@ hipError_t launch_persistent_da(vcsgc_ctx *c) {
   return c->da_wg > 1 ? gated(c, launch) : launch();
 }
 
-// per-replica statistics of the last call (synchronizes); n_final is the
-// device's where no call has just written it (launched false: other kernels
-// may have moved it)
-hipError_t persist_read_stats(vcsgc_ctx *c, vcsgc_stats *out, int *err, bool launched, bool da) {
+// Statistics of the last launch's replicas in todo (synchronizes), which are
+// then done unless their workgroups did not all start; n_final is the device's
+// where no call has just written it (launched false: other kernels may have
+// moved it).
+hipError_t persist_read_stats(vcsgc_ctx *c, vcsgc_stats *out, char *todo, int *err, bool launched,
+                              bool da) {
   const int R = (int)c->reps.size();
   RepState *h = (RepState *)c->h_rs;
   hipError_t e = hipSuccess;
@@ -1377,8 +1428,10 @@ hipError_t persist_read_stats(vcsgc_ctx *c, vcsgc_stats *out, int *err, bool lau
   if (e != hipSuccess) return e;
   *err = 0;
   for (int k = 0; k < R; ++k) {
-    if (h[k].err) *err = 1;
-    if (!out) continue;
+    if (!todo[k]) continue;
+    *err |= h[k].err;
+    todo[k] = (h[k].err & PERSIST_NOT_STARTED) != 0;
+    if (!out || todo[k]) continue;
     out[k].trials = (int64_t)h[k].trials;
     out[k].local_accepts = (int64_t)h[k].local_acc;
     out[k].stages = (int64_t)h[k].stages;

@@ -389,6 +389,33 @@ def test_batch_replicas_match_oracle(torch_cuda, oracle_mod):
     b.close()
 
 
+@pytest.mark.parametrize("strategy,tpg", [("stage", 1), ("batch", 4)])
+def test_pipeline_strategies_never_time_out(torch_cuda, oracle_mod, strategy, tpg):
+    """With a wait limit of one poll the workgroups of a persistent launch are
+    not all seen to start: the launch ends without effect and the call runs with
+    kernels per stage, then persistently again with the default limit; the chain
+    is the oracle's."""
+    O = oracle_mod
+    pot = I.params("FS-P1")
+    d = W.c2(cbar=0.05)
+    args = (d["dmu0"], 10.0, d["cbar"], d["T"])
+    g = gpu_context(d, pot)
+    g.set_tuning(strategy, tpg)
+    assert g.tuning()["workgroups"] > 1
+    st = oracle_state(O, d, pot)
+    for limit, n_sw in ((1, 1), (1 << 24, 1), (1, 2), (3, 1)):
+        print(f"[limit] {strategy} {limit}", flush=True)
+        g.set_wait_limit(limit)
+        a = g.sweep(*args, n_sw, d["seed"])
+        b, _, _ = O.sweep(st, *args, n_sw, d["seed"])
+        for k in ("trials", "local_accepts", "stages", "stage_accepts", "flips", "n_final",
+                  "sum_n", "sum_n2"):
+            assert a[k] == b[k], (limit, k)
+    assert np.array_equal(g.species.cpu().numpy(), st.species)
+    assert np.array_equal(g.rho().cpu().numpy(), st.rho)
+    g.close()
+
+
 def _sparse_system(cells, pot):
     """A 12^3 bcc block and 20,000 scattered atoms in a box of cells^3 link
     cells, most of them empty."""

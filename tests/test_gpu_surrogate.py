@@ -281,6 +281,52 @@ def test_da_network_persistent_matches_stages(torch_cuda, dims, colours, pot, ka
     assert np.array_equal(runs[0][2], runs[1][2])
 
 
+@pytest.mark.parametrize("strategy,tpg", [("graph", 1), ("batch", 4)])
+def test_da_network_never_times_out(torch_cuda, strategy, tpg):
+    """With a wait limit of one poll the network's persistent sweep ends before
+    it has changed anything and the call runs with kernels per stage: the chain
+    of the default limit, with a network trained on the system's own samples."""
+    from paper_1012_5082_amd.binding import VCSGC, Mlp
+    pot = I.params("FS-P1")
+    x, y, z, box = I.bcc(23, 31, 17)
+    x, y, z = I.thermalize(x, y, z, box, 0.04, 5)
+    sp = I.initial_species(x.size, 0.1, 6)
+    dmu0 = W.dmu_s(600.0, 0.1)
+
+    def context():
+        return VCSGC(x, y, z, box, sp, pot, descriptor=True, r_dep=8.01)
+
+    g = context()
+    g.enable_sample_log(60000, 1)
+    g.sweep(dmu0, 5.0, 0.1, 600.0, 2, 3)
+    desc, dE = g.samples()
+    net = Mlp(seed=1)
+    net.fit_normalization(desc, dE)
+    net.train(desc, dE, epochs=4, batch=4096, lr=2e-3, seed=5)
+    g.close()
+    runs = []
+    for limits in ((1 << 24, 1 << 24, 1 << 24), (1, 1 << 24, 1)):
+        g = context()
+        g.set_surrogate("mlp", net)
+        g.set_tuning(strategy, tpg)
+        out = []
+        for limit in limits:
+            g.set_wait_limit(limit)
+            for kappa in (1000.0, 0.0):
+                print(f"[limit] {strategy} {limit} {kappa}", flush=True)
+                s = g.sweep(dmu0, kappa, 0.1, 600.0, 2, 31)
+                out.append({k: s[k] for k in ("trials", "stage1_pass", "local_accepts", "stages",
+                                               "stage_accepts", "flips", "n_final", "sum_n",
+                                               "sum_n2")})
+        runs.append((out, g.species.cpu().numpy().copy(), g.rho().cpu().numpy().copy()))
+        g.close()
+    net.close()
+    assert runs[0][0] == runs[1][0]
+    assert 0 < runs[0][0][1]["stage_accepts"]
+    assert np.array_equal(runs[0][1], runs[1][1])
+    assert np.array_equal(runs[0][2], runs[1][2])
+
+
 def test_sample_log_and_training(torch_cuda, oracle_mod):
     torch = torch_cuda
     pot = I.params("FS-P1")
