@@ -874,7 +874,7 @@ vcsgc_status sweep_impl(vcsgc_ctx *c, const double *dmu0, const double *kappa, c
       if (da)
         VC_CHECK(c, vc::launch_persistent_da(c), "persistent sweep");
       else
-        VC_CHECK(c, vc::launch_persistent(c, c->strategy != 1), "persistent sweep");
+        VC_CHECK(c, vc::launch_persistent(c, n_sweeps, c->strategy != 1), "persistent sweep");
       vc::tstop(c, h);
     }
     // the error words are read after every call, with or without statistics:

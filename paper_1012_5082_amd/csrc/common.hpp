@@ -741,7 +741,7 @@ constexpr unsigned int SPIN_LIMIT = 1u << 24, ENTRY_LIMIT = 1u << 14;
 void persist_stage_params(vcsgc_ctx *c, const double *dmu0, const double *kappa,
                           const double *cbar, const double *T, int64_t n_sweeps,
                           const char *todo, uint64_t seed, bool da);
-hipError_t launch_persistent(vcsgc_ctx *c, bool use_graph);
+hipError_t launch_persistent(vcsgc_ctx *c, int64_t n_sweeps, bool use_graph);
 hipError_t persist_da_grid(vcsgc_ctx *c);
 hipError_t launch_persistent_da(vcsgc_ctx *c);
 hipError_t persist_read_stats(vcsgc_ctx *c, vcsgc_stats *out, char *todo, int *err, bool launched,

@@ -51,6 +51,7 @@
 #include <cstring>
 #include <mutex>
 #include <type_traits>
+#include <vector>
 
 #include "common.hpp"
 #include "mlp_device.hpp"
@@ -1301,24 +1302,66 @@ static hipError_t build_graph(vcsgc_ctx *c) {
   return hipGraphInstantiate(&c->graph_exec, c->graph, nullptr, nullptr, 0);
 }
 
-// Two grids whose workgroups wait for each other must not share the chip
-// half resident each (the bounded waits would end both calls in an error), so
-// such launches of one process follow each other on the device, whatever
-// streams and threads they come from.
+// Grids whose workgroups wait for each other must not be on the chip half
+// resident each (their waits would not end before the limit).  So a launch
+// of one process waits, on its stream, for the earliest ones under way until
+// the rest and itself have a CU for each workgroup, whatever streams and
+// threads they come from; of any grids running at once the last one launched
+// has counted the others.  (8 contexts of 16,000 sites on 8 threads, a sweep
+// each: 7.7 ms one after the other, 2.0 ms together; 1.0 ms for one alone.)
+// Grids that do not wait hold CUs too: the long ones are counted, a short one
+// has ended before an entry barrier gives up.  An event is used again when its
+// grid has ended, so there are as many per device as grids were under way at
+// once.
+struct Running {
+  hipEvent_t end;
+  int wgs;
+};
+struct Gate {
+  std::vector<Running> running;  // in launch order
+  std::vector<hipEvent_t> idle;
+};
 constexpr int PGATE_DEVICES = 64;
+constexpr int64_t PGATE_STAGES = 1 << 14;  // of a grid that does not wait: 2 ms or more
 static std::mutex g_gate_mu;
-static hipEvent_t g_gate[PGATE_DEVICES] = {};
+static Gate g_gate[PGATE_DEVICES];
 
 template <class L>
-static hipError_t gated(vcsgc_ctx *c, L launch) {
+static hipError_t gated(vcsgc_ctx *c, int wgs, bool waits, L launch) {
   if (c->device < 0 || c->device >= PGATE_DEVICES) return launch();
+  int cu = 0;
+  hipError_t e = hipDeviceGetAttribute(&cu, hipDeviceAttributeMultiprocessorCount, c->device);
+  if (e != hipSuccess) return e;
   std::lock_guard<std::mutex> lock(g_gate_mu);
-  hipEvent_t &ev = g_gate[c->device];
-  hipError_t e = ev ? hipStreamWaitEvent(c->stream, ev, 0)
-                    : hipEventCreateWithFlags(&ev, hipEventDisableTiming);
-  if (e == hipSuccess) e = launch();
-  if (e == hipSuccess) e = hipEventRecord(ev, c->stream);
-  return e;
+  Gate &g = g_gate[c->device];
+  int64_t sum = wgs;
+  size_t kept = 0;
+  for (const Running &r : g.running) {
+    if (hipEventQuery(r.end) == hipSuccess) {
+      g.idle.push_back(r.end);
+    } else {
+      g.running[kept++] = r;
+      sum += r.wgs;
+    }
+  }
+  g.running.resize(kept);
+  (void)hipGetLastError();  // (a query's "not ready")
+  for (size_t k = 0; waits && k < kept && sum > cu; sum -= g.running[k].wgs, ++k)
+    if ((e = hipStreamWaitEvent(c->stream, g.running[k].end, 0)) != hipSuccess) return e;
+  hipEvent_t end = nullptr;
+  if (!g.idle.empty()) {
+    end = g.idle.back();
+    g.idle.pop_back();
+  } else if ((e = hipEventCreateWithFlags(&end, hipEventDisableTiming)) != hipSuccess) {
+    return e;
+  }
+  e = launch();
+  const hipError_t rec = hipEventRecord(end, c->stream);
+  if (rec == hipSuccess)
+    g.running.push_back({end, std::min(wgs, cu)});
+  else
+    g.idle.push_back(end);
+  return e != hipSuccess ? e : rec;
 }
 
 static hipError_t launch_done(vcsgc_ctx *c) {
@@ -1329,9 +1372,12 @@ static hipError_t launch_done(vcsgc_ctx *c) {
 
 static hipError_t launch_ungated(vcsgc_ctx *c, bool use_graph);
 
-hipError_t launch_persistent(vcsgc_ctx *c, bool use_graph) {
+hipError_t launch_persistent(vcsgc_ctx *c, int64_t n_sweeps, bool use_graph) {
+  int64_t S = 0;
+  for (const RepHost &r : c->reps) S = std::max(S, r.S);
   auto launch = [&]() { return launch_ungated(c, use_graph); };
-  return c->persist_waits ? gated(c, launch) : launch();
+  if (!c->persist_waits && n_sweeps * S < PGATE_STAGES) return launch();
+  return gated(c, c->grid_total, c->persist_waits, launch);
 }
 
 static hipError_t launch_ungated(vcsgc_ctx *c, bool use_graph) {
@@ -1409,7 +1455,7 @@ hipError_t launch_persistent_da(vcsgc_ctx *c) {
                                       (unsigned)persist_lds_bytes_da(c->da_ndraw), c->stream);
     return e == hipSuccess ? launch_done(c) : e;
   };
-  return c->da_wg > 1 ? gated(c, launch) : launch();
+  return gated(c, c->da_wg, c->da_wg > 1, launch);
 }
 
 // Statistics of the last launch's replicas in todo (synchronizes), which are

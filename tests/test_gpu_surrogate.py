@@ -327,6 +327,78 @@ def test_da_network_never_times_out(torch_cuda, strategy, tpg):
     assert np.array_equal(runs[0][2], runs[1][2])
 
 
+def test_contexts_on_threads_and_streams(torch_cuda):
+    """Sweeps whose workgroups wait for each other, from six contexts on
+    threads and streams of their own (more workgroups together than compute
+    units; two of them screened by a network, one a batch of replicas), beside
+    a long run of a system in one workgroup: every chain is the one it makes
+    alone."""
+    import threading
+    from paper_1012_5082_amd.binding import VCSGC, VCSGCBatch
+    torch = torch_cuda
+    pot = I.params("FS-P1")
+    m = _params(7)
+    m.out_mu, m.out_sd = float(np.float32(0.45)), float(np.float32(0.2))
+    net = _gpu_mlp(m)
+    torch.cuda.synchronize()
+    sizes = [(20, 20, 20), (40, 40, 40), (23, 31, 17), (40, 38, 42), (62, 60, 64), None,
+             (10, 10, 10)]
+
+    def make(k, stream):
+        if k == 5:
+            reps = []
+            for r in range(6):
+                x, y, z, box = I.bcc(20 + r, 21, 24)
+                reps.append(dict(x=x, y=y, z=z, box=box,
+                                 species=I.initial_species(x.size, 0.1, 80 + r)))
+            return VCSGCBatch(reps, pot, stream=stream)
+        x, y, z, box = I.bcc(*sizes[k])
+        x, y, z = I.thermalize(x, y, z, box, 0.04, 5 + k)
+        g = VCSGC(x, y, z, box, I.initial_species(x.size, 0.1, 60 + k), pot, stream=stream,
+                  descriptor=k in (2, 3), r_dep=8.01 if k in (2, 3) else 0.0)
+        if k in (2, 3):
+            g.set_surrogate("mlp", net)
+        g.set_tuning(*(("batch", 4) if k == 1 else ("graph", 1)))
+        return g
+
+    def chain(k, g, out):
+        stats = []
+        for n_sw in (1, 2, 1, 1) if k < 6 else (200,):
+            for kappa in (1.0, 0.0):
+                stats.append(g.sweep_batch(-0.2, kappa, 0.1, 600.0, n_sw, 31) if k == 5
+                             else g.sweep(-0.2, kappa, 0.1, 600.0, n_sw, 31))
+        out[k] = (stats, g.species.cpu().numpy().copy())
+
+    def contexts():
+        gs = []
+        for k in range(7):
+            s = torch.cuda.Stream()
+            with torch.cuda.stream(s):
+                gs.append(make(k, s))
+        torch.cuda.synchronize()
+        return gs
+
+    alone, together = {}, {}
+    gs = contexts()
+    assert sum(g.tuning()["workgroups"] for g in gs) > 256
+    for k, g in enumerate(gs):
+        print(f"[threads] {k} alone", flush=True)
+        chain(k, g, alone)
+        g.close()
+    gs = contexts()
+    threads = [threading.Thread(target=chain, args=(k, g, together)) for k, g in enumerate(gs)]
+    print("[threads] together", flush=True)
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join()
+    for k, g in enumerate(gs):
+        g.close()
+        assert together[k][0] == alone[k][0], k
+        assert np.array_equal(together[k][1], alone[k][1]), k
+    net.close()
+
+
 def test_sample_log_and_training(torch_cuda, oracle_mod):
     torch = torch_cuda
     pot = I.params("FS-P1")
