@@ -183,6 +183,13 @@ void drop_graph(vcsgc_ctx *c) {
 // registers): first fewer stages are tried per batch, then trials_per_group
 // doubles.  Where the LDS of the largest resident replica and of the largest
 // share of cells do not go together, the bound of residence is lowered.
+// One system whose groups make just one stage at a time has a whole grid, not
+// only the groups of that stage (152 to 248 of 256 workgroups): its batches of
+// several stages are then made in full passes.  At rest 2.45M sites 844 -> 592 us
+// a sweep, 3.46M 973 -> 788, 1.02M with 27 colours 445 -> 322.  Where more than
+// 0.3 of the stages are accepted a batch seldom has a second one and fewer
+// workgroups meet sooner, so the rest of the grid leaves (G_busy; 2.45M at 27%
+// 1,781 us with 152, 1,779 with 256, at 82% 2,407 and 2,783).
 // More replicas than CUs get one workgroup each: none of them waits, so the
 // grid may be any size and the rest follows as workgroups end.  A share of
 // cells whose draws of one stage the LDS does not hold (some 7,900 cells, two
@@ -221,6 +228,7 @@ vcsgc_status assign_workgroups(vcsgc_ctx *c) {
     for (int spec = PERSIST_SPEC; spec >= 1; --spec) {
       for (const size_t bound : bounds) {
         int64_t total = 0, chunk = 1, nres = 0;
+        int busy = 1;
         for (int k = 0; k < R; ++k) {
           const RepHost &r = c->reps[k];
           res[k] = vc::persist_lds_need(r.ncpc, r.n, nullptr) <= bound;
@@ -228,9 +236,12 @@ vcsgc_status assign_workgroups(vcsgc_ctx *c) {
           int64_t g = res[k] || single ? 1 : (spec * r.ncpc + per - 1) / per;
           if (g < 1) g = 1;
           if (g >= 8) g = std::min<int64_t>((g + 7) / 8 * 8, PERSIST_WG);
+          busy = (int)g;  // (of the last replica: used for a single one)
+          if (R == 1 && spec == 1 && tpg == 1 && g >= 8)
+            g = std::max(g, std::min(cap0 / 8 * 8, PERSIST_WG));
           want[k] = (int)g;
           total += g;
-          chunk = std::max<int64_t>(chunk, (r.ncpc + g - 1) / g);
+          chunk = std::max<int64_t>(chunk, (r.ncpc + busy - 1) / busy);
           if (res[k]) nres = std::max<int64_t>(nres, r.n);
         }
         const bool waits = total > R;
@@ -255,11 +266,12 @@ vcsgc_status assign_workgroups(vcsgc_ctx *c) {
         int g0 = 0;
         for (int k : order) {
           c->reps[k].g0 = g0;
-          c->reps[k].G = want[k];
+          c->reps[k].G = c->reps[k].G_busy = want[k];
           c->reps[k].res = res[k] != 0;
           for (int q = 0; q < want[k]; ++q) map[g0 + q] = k;
           g0 += want[k];
         }
+        if (R == 1) c->reps[0].G_busy = busy;
         if (c->d_wg_rep) (void)hipFree(c->d_wg_rep);
         c->d_wg_rep = nullptr;
         VC_CHECK(c, dalloc(&c->d_wg_rep, (size_t)total), "allocation");
@@ -831,7 +843,7 @@ vcsgc_status sweep_impl(vcsgc_ctx *c, const double *dmu0, const double *kappa, c
   // fits the length of its batches to the acceptance.  Per stage, persistent
   // against the best of 3, 8 and 16 stages per kernel: 250,000 sites at 28%
   // accepted stages 2.6 / 4.5 us, 0.5M at 24% 2.9 / 4.6, 2M at 23% 4.8 / 7.5,
-  // 1M at 0% 1.2 / 1.2, 4M at 0% 3.7 / 3.5, 8M at 0% 7.2 / 6.3.
+  // 1M at 0% 1.1 / 1.2, 4M at 0% 3.5 / 3.5, 8M at 0% 7.2 / 6.3.
   // Tabulated potentials: where the last call accepted next to nothing, the
   // stages are bound by the tables' gathers, for which the pipeline has more
   // waves; it is the faster one with long batches, or where the persistent
@@ -840,10 +852,16 @@ vcsgc_status sweep_impl(vcsgc_ctx *c, const double *dmu0, const double *kappa, c
   // 0.25M 266 / 340, 1.02M 477 / 589, with 27 colours 153 / 174, 195 / 212,
   // 450 / 823 (4 stages 594); but with 8 per kernel 438 / 383, 378 / 340,
   // 596 / 589, and at 10% accepted 838 / 770 (54,000 sites).
-  const bool quiet = c->strategy == 3 && c->pot.tab && c->m_stage_acc >= 0.0 &&
-                     c->m_stage_acc < 0.02 &&
-                     (c->trials_per_group > 8 ||
-                      2 * c->reps[0].ncpc > (int64_t)c->reps[0].G * vc::persist_groups());
+  // The analytic form at rest with more than 13/16 of the groups in one stage:
+  // 16 stages per kernel against persistent 3.72M sites 771 / 831 us a sweep, with
+  // 27 colours 1.77M 452 / 489, 4.0M 932 / 934; with fewer cells 3.46M 834 / 788,
+  // 2.45M 641 / 592; with 8 per kernel 3.72M 876, 1.77M 501.
+  const int64_t cells = c->reps[0].ncpc;
+  const int64_t groups = (int64_t)c->reps[0].G * vc::persist_groups();
+  const int batch = c->trials_per_group;
+  const bool quiet = c->strategy == 3 && c->m_stage_acc >= 0.0 &&
+                     (c->pot.tab ? c->m_stage_acc < 0.02 && (batch > 8 || 2 * cells > groups)
+                                 : c->m_stage_acc < 0.01 && batch > 8 && 16 * cells > 13 * groups);
   const bool logged = c->tlog || c->slog || c->dalog;
   const unsigned stage_timers =
       1u << VCSGC_KT_STAGE | 1u << VCSGC_KT_TRIAL | 1u << VCSGC_KT_COMMIT;
@@ -856,8 +874,8 @@ vcsgc_status sweep_impl(vcsgc_ctx *c, const double *dmu0, const double *kappa, c
   }
   const bool per_stage =
       (c->da_mode && !da) || c->smp_cap > 0 || c->local_steps > 1 || c->grown ||
-      (!da && c->strategy >= 2 && (n_sweeps == 0 || quiet || logged || (c->tmask & (1u << VCSGC_KT_STAGE)) ||
-                            c->reps[0].ncpc > (int64_t)c->reps[0].G * vc::persist_groups()));
+      (!da && c->strategy >= 2 &&
+       (n_sweeps == 0 || quiet || logged || (c->tmask & (1u << VCSGC_KT_STAGE)) || cells > groups));
   if (per_stage && R == 1)
     return sweep_stages(c, dmu0[0], kappa[0], cbar[0], T[0], n_sweeps, seed, out);
   // A replica whose workgroups did not all start has not changed: it is tried

@@ -473,6 +473,7 @@ struct RepHost {
   int nb[3] = {0, 0, 0};     // search bins per dimension
   int64_t nbins = 0, boff = 0;
   int g0 = 0, G = 1;         // workgroups of the persistent sweep
+  int G_busy = 1;            // of which take part where many stages are accepted
   bool res = false;          // one workgroup with the replica's state in LDS
 };
 

@@ -658,6 +658,7 @@ __device__ __forceinline__ void sweep_replica(
   };
   const int tid = threadIdx.x, lane = tid % PTL, grp = tid / PTL, wl = tid & 63;
   const int q = (int)blockIdx.x - r.g0;  // rank inside the replica
+  if (q >= r.G) return;                  // (not needed by this call)
   // contiguous share of the active cells; consecutive shares on one XCD
   // (workgroup ids advance round-robin over the 8 XCDs)
   int qc = q;
@@ -1253,7 +1254,7 @@ void persist_stage_params(vcsgc_ctx *c, const double *dmu0, const double *kappa,
     d.seed = seed;
     d.key1 = (uint64_t)k;
     d.g0 = da ? 0 : r.g0;
-    d.G = da ? c->da_wg : r.G;
+    d.G = da ? c->da_wg : c->m_stage_acc > 0.3 ? r.G_busy : r.G;
     d.n_sweeps = todo[k] ? n_sweeps : 0;
     d.w0 = (int64_t)c->w;
   }

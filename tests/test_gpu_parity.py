@@ -389,6 +389,45 @@ def test_batch_replicas_match_oracle(torch_cuda, oracle_mod):
     b.close()
 
 
+@pytest.mark.parametrize("n,batch,persistent", [
+    (76, 8, 3),   # 8,000 active cells: two stages in one pass of 16,000 trial groups
+    (80, 16, 3),  # 9,261: one stage, and the rest of the grid for the next ones
+    (92, 8, 3),   # 13,824
+    (92, 16, 1),  # the pipeline once a call has accepted next to nothing
+])
+def test_sweeps_at_rest_and_with_accepted_stages(torch_cuda, oracle_mod, n, batch, persistent):
+    """27 colours, nothing accepted, on the whole grid: the number of the three
+    calls that run persistently; then every stage accepted, the next calls on
+    fewer workgroups; the chain is the oracle's throughout."""
+    O = oracle_mod
+    from paper_1012_5082_amd.binding import VCSGC
+    pot = I.params("FS-P1")
+    x, y, z, box = I.bcc(n, n, n)
+    sp = I.initial_species(x.size, 0.02, 6)
+    g = VCSGC(x, y, z, box, sp, pot, colours=27)
+    print(f"[rest] {n} {batch} {g.info()['n_cells']}", flush=True)
+    g.set_tuning("batch", batch)
+    assert g.tuning()["workgroups"] >= 248
+    g.kernel_timing(["persist"])
+    args = (3.0, 1000.0, 0.02, 300.0)
+    for _ in range(3):
+        s = g.sweep(*args, 1, 31)
+    assert s["stage_accepts"] == 0
+    assert g.kernel_times()["persist"][2] == persistent
+    st = O.SweepState(x, y, z, box, sp, pot)
+    so, _, _ = O.sweep(st, *args, 3, 31, colour_period=3)
+    assert (s["n_final"], so["flips"]) == (so["n_final"], 0)
+    for kappa in (0.0, 0.0, 0.5):
+        a = g.sweep(-0.2, kappa, 0.02, 600.0, 1, 31)
+        b, _, _ = O.sweep(st, -0.2, kappa, 0.02, 600.0, 1, 31, colour_period=3)
+        for k in ("trials", "local_accepts", "stages", "stage_accepts", "flips", "n_final"):
+            assert a[k] == b[k], (kappa, k)
+        assert kappa or a["stage_accepts"] == a["stages"]
+    assert np.array_equal(g.species.cpu().numpy(), st.species)
+    assert np.array_equal(g.rho().cpu().numpy(), st.rho)
+    g.close()
+
+
 @pytest.mark.parametrize("strategy,tpg", [("stage", 1), ("batch", 4)])
 def test_pipeline_strategies_never_time_out(torch_cuda, oracle_mod, strategy, tpg):
     """With a wait limit of one poll the workgroups of a persistent launch are
