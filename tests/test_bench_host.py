@@ -77,3 +77,16 @@ def test_autotune_cache_key_names_operating_point():
     c = cache_key("gfx950", 1, 1900000, 7000, (-0.21919, 1000.0, 0.03, 700.0))
     assert a != b and a == c
     assert cache_key("gfx950", 1, 1956428, 6859) != a
+
+
+def test_autotune_pick_is_not_noise():
+    """Candidates that run as the same launch differ by noise only: the same one
+    is taken whichever came out fastest; a really faster one wins."""
+    from paper_1012_5082_amd.autotune import BATCH, PREFERENCE, TPG, pick
+    assert len(PREFERENCE) == len(BATCH) + 1 + len(TPG)
+    alike = {c: 1.0 + 0.002 * k for k, c in enumerate(PREFERENCE)}
+    for c in PREFERENCE:
+        assert pick({**alike, c: 0.999}) == "batch:16"
+    assert pick({**alike, "graph:2": 0.9}) == "graph:2"
+    assert pick({**alike, "batch:16": 1.2}) == "batch:8"
+    assert pick({"graph:1": 1.01, "graph:2": 1.0, "graph:4": 2.0, "graph:8": 3.0}) == "graph:1"
