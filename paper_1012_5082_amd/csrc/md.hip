@@ -2,6 +2,7 @@
 // r < rc + skin list (gather only: every atom sums its own row, no atomics),
 // and the velocity-Verlet kick/drift updates.
 #include <algorithm>
+#include <type_traits>
 
 #include "common.hpp"
 
@@ -554,8 +555,6 @@ __global__ void __launch_bounds__(BLOCK)
   w[i] = f.w;
 }
 
-// the density pass (EN: with the atoms' energies) and the force pass for the
-// context's potential form
 // Lanes per atom.  Few atoms leave the chip idle and their time is latency: 4
 // (20 NVE steps at 2,000 atoms 502 us with 1, 425 with 2, 375 with 4, 8 within
 // 3% of 4 there and slower from 8,000 on; at 31,250 atoms 550, 460, 440; at
@@ -563,62 +562,57 @@ __global__ void __launch_bounds__(BLOCK)
 // second lane at any size.  From there to about 1M atoms one lane: the
 // quadruples fit the L2s and the exchange costs more than the saved line
 // accesses (0.25M atoms 1,225 us with 1, 1,280 with 2; 1.02M 3,360 and 3,560);
-// beyond, two for the steps (1.95M atoms 7,440 us with 1, 6,860 with 2), one
-// for single passes over a lattice in its own order, whose neighbours do share
-// lines (1.02M atoms, energy and forces: 141 us with 1, 162 with 2; 1.95M
-// atoms in grains 272 and 298).
-static int lanes_per_atom(const vcsgc_ctx *c, bool steps) {
-  if (c->n <= 48 * 1024) return 4;
-  if (c->pot.tab || (steps && c->n > 1024 * 1024)) return 2;
-  return 1;
+// beyond, two for the passes of NVE and NPT steps (STEPS; 1.95M atoms 7,440 us
+// with 1, 6,860 with 2), one for single passes over a lattice in its own
+// order, whose neighbours do share lines (1.02M atoms, energy and forces: 141 us
+// with 1, 162 with 2; 1.95M atoms in grains 272 and 298), and for the passes that
+// store forces for a kernel of their own (NVT steps, the end of an NVE call).
+// (Not measured between 1.02M and 1.95M atoms.)
+template <bool STEPS, class F>
+static void by_lanes(const vcsgc_ctx *c, F launch) {
+  const std::integral_constant<int, 4> four{};
+  const std::integral_constant<int, 2> two{};
+  const std::integral_constant<int, 1> one{};
+  const bool small = c->n <= 48 * 1024;
+  if (c->pot.tab) {
+    small ? launch(four, std::true_type{}) : launch(two, std::true_type{});
+  } else if (small) {
+    launch(four, std::false_type{});
+  } else {
+    if constexpr (STEPS)
+      if (c->n > 1024 * 1024) return launch(two, std::false_type{});
+    launch(one, std::false_type{});
+  }
 }
 
-template <int LPA, bool EN>
-static void density_md_on(vcsgc_ctx *c, const Box &b) {
+// the density pass (EN: with the atoms' energies) and the force pass for the
+// context's potential form
+template <bool EN, bool STEPS>
+static void density_md_launch(vcsgc_ctx *c, const Box &b) {
   const double reach = list_reach(c);
   const BinClear bc = {md_binned_drift(c) ? c->bin_count : nullptr, c->nbins_total,
                        md_one_kernel_build(c) ? c->ds : nullptr};
   c->bins_clear = bc.count != nullptr;
-  if (c->pot.tab)
-    k_density_md<LPA, true, EN><<<grid_for(c->n * LPA), BLOCK, 0, c->stream>>>(
+  by_lanes<STEPS>(c, [&](auto lpa, auto tab) {
+    k_density_md<lpa.value, tab.value, EN><<<grid_for(c->n * lpa.value), BLOCK, 0, c->stream>>>(
         c->n, c->ps4, c->md_j, c->md_cnt, b, reach, c->pot, c->rho_f, c->pf4, c->eatom, bc);
-  else
-    k_density_md<LPA, false, EN><<<grid_for(c->n * LPA), BLOCK, 0, c->stream>>>(
-        c->n, c->ps4, c->md_j, c->md_cnt, b, reach, c->pot, c->rho_f, c->pf4, c->eatom, bc);
-}
-
-template <bool EN>
-static void density_md_launch(vcsgc_ctx *c, const Box &b, bool steps) {
-  const int l = lanes_per_atom(c, steps);
-  l == 4   ? density_md_on<4, EN>(c, b)
-  : l == 2 ? density_md_on<2, EN>(c, b)
-           : density_md_on<1, EN>(c, b);
-}
-
-template <int LPA, bool KD>
-static void forces_on(vcsgc_ctx *c, const Box &b, const KickDrift &kd) {
-  const double reach = list_reach(c);
-  if (c->pot.tab)
-    k_forces<LPA, KD, true><<<grid_for(c->n * LPA), BLOCK, 0, c->stream>>>(
-        c->n, c->pf4, c->md_j, c->md_cnt, b, reach, c->pot, c->fx, c->fy, c->fz, kd);
-  else
-    k_forces<LPA, KD, false><<<grid_for(c->n * LPA), BLOCK, 0, c->stream>>>(
-        c->n, c->pf4, c->md_j, c->md_cnt, b, reach, c->pot, c->fx, c->fy, c->fz, kd);
+  });
 }
 
 template <bool KD>
-static void forces_launch(vcsgc_ctx *c, const Box &b, const KickDrift &kd, bool steps) {
-  const int l = lanes_per_atom(c, steps);
-  l == 4   ? forces_on<4, KD>(c, b, kd)
-  : l == 2 ? forces_on<2, KD>(c, b, kd)
-           : forces_on<1, KD>(c, b, kd);
+static void forces_launch(vcsgc_ctx *c, const Box &b, const KickDrift &kd) {
+  const double reach = list_reach(c);
+  by_lanes<KD>(c, [&](auto lpa, auto tab) {
+    k_forces<lpa.value, KD, tab.value><<<grid_for(c->n * lpa.value), BLOCK, 0, c->stream>>>(
+        c->n, c->pf4, c->md_j, c->md_cnt, b, reach, c->pot, c->fx, c->fy, c->fz, kd);
+  });
 }
 
 // the force pass alone (after a density pass at the same positions)
 hipError_t launch_forces_only(vcsgc_ctx *c) {
   Box b{c->box[0], c->box[1], c->box[2]};
   const int h = tstart(c, VCSGC_KT_FORCES);
-  forces_launch<false>(c, b, KickDrift{}, false);
+  forces_launch<false>(c, b, KickDrift{});
   tstop(c, h);
   return hipGetLastError();
 }
@@ -626,7 +620,7 @@ hipError_t launch_forces_only(vcsgc_ctx *c) {
 hipError_t launch_forces(vcsgc_ctx *c) {
   Box b{c->box[0], c->box[1], c->box[2]};
   const int h = tstart(c, VCSGC_KT_DENSITY);
-  density_md_launch<false>(c, b, false);
+  density_md_launch<false, false>(c, b);
   tstop(c, h);
   return launch_forces_only(c);
 }
@@ -663,10 +657,10 @@ static KickDrift kick_drift_args(vcsgc_ctx *c, double dt, bool kick_first, int p
 hipError_t launch_forces_kick_drift(vcsgc_ctx *c, double dt, bool kick_first, int par) {
   Box b{c->box[0], c->box[1], c->box[2]};
   int h = tstart(c, VCSGC_KT_DENSITY);
-  density_md_launch<false>(c, b, true);
+  density_md_launch<false, true>(c, b);
   tstop(c, h);
   h = tstart(c, VCSGC_KT_FORCES);
-  forces_launch<true>(c, b, kick_drift_args(c, dt, kick_first, par), true);
+  forces_launch<true>(c, b, kick_drift_args(c, dt, kick_first, par));
   tstop(c, h);
   return hipGetLastError();
 }
@@ -677,7 +671,7 @@ hipError_t launch_forces_kick_drift(vcsgc_ctx *c, double dt, bool kick_first, in
 hipError_t launch_energy(vcsgc_ctx *c) {
   Box b{c->box[0], c->box[1], c->box[2]};
   int h = tstart(c, VCSGC_KT_ENERGY);
-  density_md_launch<true>(c, b, false);
+  density_md_launch<true, false>(c, b);
   tstop(c, h);
   return hipGetLastError();
 }
@@ -1142,25 +1136,17 @@ __global__ void k_scale_v(int64_t n, double *vx, double *vy, double *vz, double 
   vz[i] = vz[i] * s;
 }
 
-template <int LPA>
-static void forces_virial_on(vcsgc_ctx *c, const Box &b, double *w) {
-  const double reach = list_reach(c);
-  if (c->pot.tab)
-    k_forces_vir<LPA, true><<<grid_for(c->n * LPA), BLOCK, 0, c->stream>>>(
-        c->n, c->pf4, c->md_j, c->md_cnt, b, reach, c->pot, c->fx, c->fy, c->fz, w);
-  else
-    k_forces_vir<LPA, false><<<grid_for(c->n * LPA), BLOCK, 0, c->stream>>>(
-        c->n, c->pf4, c->md_j, c->md_cnt, b, reach, c->pot, c->fx, c->fy, c->fz, w);
-}
-
 hipError_t launch_forces_virial(vcsgc_ctx *c, double *w) {
   Box b{c->box[0], c->box[1], c->box[2]};
   int h = tstart(c, VCSGC_KT_DENSITY);
-  density_md_launch<false>(c, b, true);
+  density_md_launch<false, true>(c, b);
   tstop(c, h);
   h = tstart(c, VCSGC_KT_FORCES);
-  const int l = lanes_per_atom(c, true);
-  l == 4 ? forces_virial_on<4>(c, b, w) : l == 2 ? forces_virial_on<2>(c, b, w) : forces_virial_on<1>(c, b, w);
+  const double reach = list_reach(c);
+  by_lanes<true>(c, [&](auto lpa, auto tab) {
+    k_forces_vir<lpa.value, tab.value><<<grid_for(c->n * lpa.value), BLOCK, 0, c->stream>>>(
+        c->n, c->pf4, c->md_j, c->md_cnt, b, reach, c->pot, c->fx, c->fy, c->fz, w);
+  });
   tstop(c, h);
   return hipGetLastError();
 }
