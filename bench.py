@@ -93,11 +93,8 @@ TRAFFIC = {
     "forces": ("k_forces", "paper_1012_5082_amd/csrc/md.hip", "profiles/k_forces_c3_traffic.md"),
     "density": ("k_density_md", "paper_1012_5082_amd/csrc/md.hip",
                 "profiles/k_density_md_c3_traffic.md"),
-    "stage": ("k_stage", "paper_1012_5082_amd/csrc/sweep.hip", "profiles/k_stage_c3_traffic.md"),
     "persist": ("k_sweep_persistent", "paper_1012_5082_amd/csrc/persist.hip",
                 "profiles/k_sweep_persistent_c3_traffic.md"),
-    "batch": ("k_stage_spec", "paper_1012_5082_amd/csrc/sweep.hip",
-              "profiles/k_stage_spec_c3_traffic.md"),
 }
 
 
@@ -517,8 +514,11 @@ def main():
     # pairs at every launch would add host and stream work; the pipelines
     # time the span of each graph replay); the dominant class is the one with
     # the largest time over the timed cycles.
+    # Grown domains run on the pipeline's stage kernels either way; for other
+    # sweeps timing those would choose the route.
     g.kernel_timing(["trial", "commit", "density", "forces", "kick_drift", "kick",
-                     "build", "persist"], every=SAMPLE)
+                     "build", "persist"] + (["stage"] if args.grow_edge > 0.0 else []),
+                    every=SAMPLE)
     ev = [(torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True),
            torch.cuda.Event(enable_timing=True)) for _ in range(args.steps)]
     trials = 0
@@ -574,11 +574,10 @@ def main():
         if not abytes:
             return None
         ach = abytes / avg_s / 1e9
-        tcls = "batch" if cls == "stage" and tuned["choice"][0] == "batch" else cls
-        return {"bound": "hbm", "kernel": TRAFFIC[tcls][0] if tcls in TRAFFIC else cls,
+        return {"bound": "hbm", "kernel": TRAFFIC[cls][0] if cls in TRAFFIC else cls,
                 "achieved": round(ach, 1),
                 "peak": HBM_PEAK_GBS, "unit": "GB/s", "frac": round(ach / HBM_PEAK_GBS, 4),
-                "traffic": measured_traffic(tcls, "%s:%d" % tuple(tuned["choice"])),
+                "traffic": measured_traffic(cls, "%s:%d" % tuple(tuned["choice"])),
                 "bytes_per_launch": int(abytes),
                 "avg_launch_us": round(avg_s * 1e6, 2), "timed_launches": launches,
                 "launches": all_launches}

@@ -242,7 +242,10 @@ vcsgc_status vcsgc_sweep_batch(vcsgc_ctx *ctx, const double *dmu0, const double 
  *            Strategies 2 and 3 run plain sweeps that are neither logged nor
  *            timed per stage kernel through the persistent launch where its
  *            workgroups cover the active cells (about 4M sites): it tries
- *            batches of stages too, and faster;
+ *            batches of stages too, and faster.  Where a call accepted next to
+ *            nothing, long batches of strategy 3 go back to the pipeline if
+ *            that is the faster one (tabulated potentials, and systems near
+ *            that size);
  *   trials_per_group: strategies 0 and 1: divides the number of workgroups
  *            of a replica in the persistent kernel, and with it the stages
  *            tried per batch (a replica that fits one compute unit's LDS

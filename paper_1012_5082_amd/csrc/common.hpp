@@ -504,7 +504,7 @@ struct vcsgc_ctx {
   double *nvt = nullptr, *nvt_part = nullptr;
   double *tab_coef = nullptr;  // tabulated potential's coefficients (PotD::tc)
   // conjugate-gradient relaxation: direction d, start positions x0 and
-  // forces f0 of the line search (3 n each), chunk values, totals
+  // forces f0 of the line search (3 n each), chunk values [3 ceil(n / 256)]
   double *cg = nullptr;
   // grown domains (single system): cells of edge >= max(grow_edge, 2 r_dep),
   // per (cell c, corner k) at q = 8 c + k the domain's atoms g_list and
@@ -583,7 +583,7 @@ struct vcsgc_ctx {
   // h_state_final: the last check saw the call's end (statistics included)
   vc::DevState *h_state = nullptr;
   unsigned char *h_pin = nullptr;  // the pinned host memory that the h_ pointers share
-  // totals a kernel leaves for the host (pinned; 8 doubles)
+  // totals a kernel leaves for the host (pinned; 32 doubles, at most 5 used)
   double *h_tot = nullptr;
   // the bin counts are zero: cleared by the last density pass, no binning since
   bool bins_clear = false;
@@ -640,8 +640,9 @@ struct vcsgc_ctx {
   int persist_ndraw = 0;    // trials a workgroup draws ahead
   int da_wg = 0, da_ndraw = 0;  // the same sweep with the network: workgroups (0: not yet
                                 // sized, -1: does not fit), trials drawn ahead
-  int trials_per_group = 1;   // tiling: trial groups per active cell (see assign_workgroups)
-  int strategy = 0;           // 0: persistent (graph), 1: persistent (direct), 2: per-stage
+  int trials_per_group = 1;   // tiling: divides the trial groups (see assign_workgroups), or
+                              // the stages per batch
+  int strategy = 0;  // 0: persistent (graph), 1: persistent (direct), 2: stages, 3: batches
   unsigned int spin_limit = 1u << 24;  // see vcsgc_set_wait_limit
   hipGraph_t graph = nullptr;
   hipGraphExec_t graph_exec = nullptr;
@@ -706,17 +707,24 @@ hipError_t launch_nvt_ke(vcsgc_ctx *c, double dt, bool closing_kick);
 hipError_t launch_nvt_thermo(vcsgc_ctx *c, double dt, int mode);  // bit 0: end half, 1: start half
 hipError_t launch_nvt_kick_drift(vcsgc_ctx *c, double dt, int par);
 hipError_t launch_nvt_scale(vcsgc_ctx *c);
-// conjugate-gradient relaxation: trial positions x = wrap(x0 + a d); the
-// totals (mode 0: F . u and max |u_i|^2; mode 1: F . F and F . u) into
-// out[0..1] through part [2 ceil(n / BLOCK)]; d = F or d = F + b d
+// conjugate-gradient relaxation, vectors of 3 n doubles: trial positions
+// x = wrap(x0 + a d).  launch_cg_start: d = F (copy) or F + b d, x0 and f0 the
+// positions and forces, F . d and max |d_i|^2 into out[0..1] through part
+// [2 ceil(n / BLOCK)].  launch_cg_eval, after launch_energy and
+// launch_forces_only: E, F . F and F . f0 into out[0..2] through part
+// [3 ceil(n / BLOCK)], what a device-decided rebuild overflowed (1: a bin, 2: a
+// row) into out[3], whether one was due into out[4]; lowers ds->rebuild[0].
+// out is host memory that the device can write.
 hipError_t launch_cg_move(vcsgc_ctx *c, const double *x0, const double *d, double a);
 hipError_t launch_cg_start(vcsgc_ctx *c, double *d, double *x0, double *f0, double b, bool copy,
                            double *part, double *out);
 hipError_t launch_cg_eval(vcsgc_ctx *c, const double *f0, double *part, double *out);
 // NPT: forces with the per-atom virial terms w; the step's scalings, kick
-// and drift (launch_npt_kick_drift); the closing kick (if kick) with the
-// totals of m v^2 and w into out[0..1] through part [2 ceil(n / BLOCK)];
-// v *= s
+// and drift (launch_npt_kick_drift; binned: into bins cleared by the last
+// density pass); the closing kick (if kick, and unless a rebuild overflowed)
+// with the totals of m v^2 and w into out[0..1] through part
+// [2 ceil(n / BLOCK)], the overflow and the rebuild flag into out[2..3] as in
+// launch_cg_eval (ds->rebuild[0] lowered); v *= s
 hipError_t launch_forces_virial(vcsgc_ctx *c, double *w);
 hipError_t launch_npt_kick_drift(vcsgc_ctx *c, double f1, double f2, double cv, double h,
                                  double dt, double q, const double lam[3], double thr, bool binned);

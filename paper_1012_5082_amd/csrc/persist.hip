@@ -28,8 +28,9 @@
 //     loads per trial);
 //   - the rows of the next batch are read before the decision of this one;
 //   - a batch holds as many stages as the groups try in one pass, and twice
-//     as many after each rejected batch: with few accepted stages the batch's
-//     fixed cost is shared by more of them, with many none is tried in vain;
+//     as many after each rejected batch, so that with few accepted stages its
+//     fixed cost is shared by more of them.  (It is never shorter than a pass: with
+//     60% accepted stages 128,000 sites try 8 stages to decide 1.6.)
 //   - a replica whose densities and species fit the LDS runs in one workgroup
 //     that keeps them there (RES) and needs no device barrier;
 //   - 8 lanes per trial, two entries' chains side by side in a lane (16 lanes
@@ -1409,7 +1410,10 @@ static const void *persist_da_kernel(bool tab) {
 // Trial groups per active cell.  A trial is longer than a plain one, so a
 // second pass over the groups costs more than a barrier of more workgroups:
 // 128,000 sites at 9% accepted stages 1.02 ms with 8, 0.74 with 16, 0.69 with
-// 32; 16,000 sites 1.76, 1.37, 1.20; 1.02M sites 0.96, 0.95, 0.98.
+// 32; 16,000 sites 1.76, 1.37, 1.20; 1.02M sites 0.96, 0.95, 0.98.  (A batch has
+// at most PDG = 16 stages, so with 32 half of a workgroup's groups have no trial:
+// what helps is fewer trials per compute unit.  Not measured with many accepted
+// stages.)
 constexpr int PERSIST_SPEC_DA = 32;
 
 // The grid of the delayed-acceptance sweep into c->da_wg (-1: its shares of the
