@@ -21,8 +21,13 @@
 // The chain is the one-stage-at-a-time chain, stage for stage.
 //
 // What bounds it: the latency of a batch (6 - 12 us), not bytes or
-// arithmetic: about a third the trials' dependent chain, a third waiting for
-// the slowest workgroup, the rest decisions and loop code.  Therefore:
+// arithmetic.  Shader cycles of a batch at 128,000 sites with 53% accepted stages,
+// 16,900: the trials' dependent chain 4,000, the barrier of the counts 4,100, the
+// commit 440 and its barrier 4,000, the next rows and the LDS barrier before
+// them 2,250, the draws that are due 1,200, the decision 950.  With few accepted
+// stages the trials of more of them: 6,700 of 17,900 (2.5%; 11 stages per
+// batch); at 1.95M sites 25,000 of 45,500 (2%), with the network 18,700 of 34,800.
+// Therefore:
 //   - sites, ln u and ln u_g are drawn ahead into LDS rings by waves that
 //     would otherwise wait (two Philox blocks, a logarithm and two dependent
 //     loads per trial);
