@@ -264,11 +264,12 @@ vcsgc_status vcsgc_get_tuning(vcsgc_ctx *ctx, int32_t *strategy, int32_t *trials
  * left in the error state (part of a stage may have been committed).
  * polls >= 1; the default, 2^24 polls with a short sleep each, is seconds.
  * Nothing is committed before all workgroups of a replica have started.
- * Where they have not within 2^14 polls (or the limit, if lower: another
- * process's grid may hold their places) the launch ends without effect and is
- * made again until the limit is reached; with strategies 2 and 3 and with the
- * network's delayed acceptance the call runs with kernels per stage instead
- * and does not end in this error.
+ * Where they have not within 2^14 polls (or the limit less one, if lower; a
+ * limit of 1 does not wait at all), because another process's grid holds
+ * their places, the launch ends without effect and is made again until the
+ * limit is reached; with strategies 2 and 3 and with the network's delayed
+ * acceptance the call runs with kernels per stage instead and does not end in
+ * this error.
  * For failure-handling tests and diagnostics. */
 vcsgc_status vcsgc_set_wait_limit(vcsgc_ctx *ctx, uint32_t polls);
 

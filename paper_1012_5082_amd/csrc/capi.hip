@@ -901,7 +901,7 @@ vcsgc_status sweep_impl(vcsgc_ctx *c, const double *dmu0, const double *kappa, c
     if (!(err & vc::PERSIST_NOT_STARTED)) break;
     if (R == 1 && (da || c->strategy >= 2))
       return sweep_stages(c, dmu0[0], kappa[0], cbar[0], T[0], n_sweeps, seed, out);
-    polls += std::min(c->spin_limit, vc::ENTRY_LIMIT);
+    polls += std::min(c->spin_limit, vc::ENTRY_LIMIT);  // (at least one)
     if (polls >= c->spin_limit || (err & vc::PERSIST_TIMEOUT)) break;
   }
   c->w += (uint64_t)n_sweeps;

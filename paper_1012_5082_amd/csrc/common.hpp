@@ -744,8 +744,9 @@ hipError_t persist_max_blocks(int *per_cu, bool tab, bool big, size_t lds_max);
 // workgroups did not all start, and it has not changed
 constexpr int PERSIST_TIMEOUT = 1, PERSIST_NOT_STARTED = 2;
 // Polls (with a short sleep, about 1 us each) of a barrier by default, and of
-// the entry barrier at most: workgroups start within microseconds of each other
-// unless another process's grid holds their places.
+// the count of started workgroups before the rest is given up: they start
+// within microseconds of each other unless another process's grid holds their
+// places.
 constexpr unsigned int SPIN_LIMIT = 1u << 24, ENTRY_LIMIT = 1u << 14;
 void persist_stage_params(vcsgc_ctx *c, const double *dmu0, const double *kappa,
                           const double *cbar, const double *T, int64_t n_sweeps,

@@ -117,7 +117,7 @@ struct alignas(128) RepState {
   struct alignas(128) Bar {
     unsigned long long n;
   } bar[8];
-  // entry barrier: workgroups that have started; the top bit: given up
+  // workgroups that have started; the top bit: given up
   struct alignas(128) Entry {
     unsigned long long n;
   } entry;
@@ -145,7 +145,7 @@ struct PersistArgs {
   double *slog;
   int64_t scap;
   unsigned long long *log_n;  // [2]: trial and stage records written
-  unsigned int spin_limit, entry_limit;  // polls of a barrier and of the entry barrier
+  unsigned int spin_limit, entry_limit;  // polls of a barrier, and for the start
   int ndraw;  // trials drawn ahead (LDS entries)
   // BIG: the drawn trials and records of one stage, per active cell of the replicas
   double *big_lnu;
@@ -577,28 +577,32 @@ __device__ __forceinline__ double da_trial(const PState<false> &st, const Persis
   return own + pair + emb;
 }
 
-// Whether all G workgroups of the replica have started (lane 0 of a wave).
-// Another process's grid on the same device can keep some of them from it for as
-// long as it waits for workgroups that these keep out.  So a workgroup that
-// has polled `limit` times gives up, unless the last arrival came first: one
-// compare-and-swap decides it for all of them, before anything is committed.
+// The start of a replica's workgroups.  Another process's grid on the same
+// device can keep some of them from it for as long as it waits for workgroups that
+// these keep out.  So each counts itself in, and one that has polled `limit`
+// times for the rest gives up unless all have come: one compare-and-swap
+// decides it for all of them, before anything is committed or logged.  (A limit of
+// 0 gives up outright.)
+__device__ __forceinline__ void p_arrive(RepState *st) {
+  __hip_atomic_fetch_add(&st->entry.n, 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
 __device__ __forceinline__ bool p_entered(RepState *st, unsigned long long G, unsigned int limit) {
   unsigned int it = 0;
-  for (;;) {
+  while (limit > 0) {
     unsigned long long v =
         __hip_atomic_load(&st->entry.n, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    if (v & ENTRY_GIVEN_UP) return false;
     if (v == G) return true;
-    if (++it <= limit) {
+    if (v & ENTRY_GIVEN_UP) return false;
+    if (++it <= limit)
       __builtin_amdgcn_s_sleep(1);
-    } else if (__hip_atomic_compare_exchange_strong(&st->entry.n, &v, v | ENTRY_GIVEN_UP,
-                                                    __ATOMIC_RELAXED, __ATOMIC_RELAXED,
-                                                    __HIP_MEMORY_SCOPE_AGENT)) {
-      __hip_atomic_fetch_or(&st->err, PERSIST_NOT_STARTED, __ATOMIC_RELAXED,
-                            __HIP_MEMORY_SCOPE_AGENT);
-      return false;
-    }  // (else another one has arrived or given up)
+    else if (__hip_atomic_compare_exchange_strong(&st->entry.n, &v, v | ENTRY_GIVEN_UP,
+                                                  __ATOMIC_RELAXED, __ATOMIC_RELAXED,
+                                                  __HIP_MEMORY_SCOPE_AGENT))
+      break;  // (else another one has arrived or given up)
   }
+  __hip_atomic_fetch_or(&st->err, PERSIST_NOT_STARTED, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  return false;
 }
 
 // Draws ahead of the trials.  Stage counters: the colour and ln u_g of stages
@@ -703,17 +707,7 @@ __device__ __forceinline__ void sweep_replica(
   unsigned long long ncom = 0;
   unsigned int batch = 0;
   bool entered = RES || r.G == 1;
-  if (!entered && tid == 0)
-    __hip_atomic_fetch_add(&st->entry.n, 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-  // before the first barrier, or with logs before the first trial
-  auto enter = [&]() {
-    if (tid == 0) *flag = !p_entered(st, (unsigned long long)r.G, a.entry_limit);
-    sync();
-    entered = !*flag;
-    sync();  // (the flag has been read)
-    return entered;
-  };
-  if (LOG && !entered && !enter()) return;
+  if (!entered && tid == 0) p_arrive(st);
   if (RES)
     for (int64_t i = tid; i < r.n; i += PBLOCK) {
       l.rho[i] = a.rho[r.aoff + i];
@@ -744,7 +738,14 @@ __device__ __forceinline__ void sweep_replica(
         const uint32_t to = min(min(s0 + 3 * len, s0 + win), S);
         p_draw_trials<DA>(r, l, cstart, catoms, w, hd, to, t_lo, own, chunk, win, tid, PBLOCK);
         hd = to;
+        if (!entered && tid == 0)  // the call's first draws are made
+          *flag = !p_entered(st, (unsigned long long)r.G, a.entry_limit);
         sync();
+        if (!entered) {
+          if (*flag) return;
+          entered = true;
+          sync();  // (the flag has been read)
+        }
       }
       // what the waves draw while the others work or wait: about a batch of
       // trials and of stage counters, kept clear of the slots of the last batch
@@ -867,7 +868,6 @@ __device__ __forceinline__ void sweep_replica(
       int tst = 2;
       if (!RES && r.G > 1) {
         // ---- counts and barrier in one word per stage
-        if (!LOG && !entered && !enter()) return;
         if (tid < 64) {
           unsigned long long *word = &st->word[batch % PWORDS][0][0];
           if (q == 0) {
@@ -1224,7 +1224,7 @@ static PersistArgs make_args(vcsgc_ctx *c) {
   // Strategies 0 and 1 end in an error where a wait exceeds the caller's limit;
   // the others have kernels that wait for nothing to fall back on, at the entry.
   a.spin_limit = c->strategy >= 2 || c->da_mode ? SPIN_LIMIT : c->spin_limit;
-  a.entry_limit = std::min(c->spin_limit, ENTRY_LIMIT);
+  a.entry_limit = std::min(c->spin_limit - 1, ENTRY_LIMIT);
   a.ndraw = c->persist_ndraw;
   a.big_lnu = c->big_lnu;
   a.big_site = c->big_site;

@@ -430,8 +430,8 @@ def test_sweeps_at_rest_and_with_accepted_stages(torch_cuda, oracle_mod, n, batc
 
 @pytest.mark.parametrize("strategy,tpg", [("stage", 1), ("batch", 4)])
 def test_pipeline_strategies_never_time_out(torch_cuda, oracle_mod, strategy, tpg):
-    """With a wait limit of one poll the workgroups of a persistent launch are
-    not all seen to start: the launch ends without effect and the call runs with
+    """With a wait limit of one poll the workgroups of a persistent launch give up
+    before they wait: the launch ends without effect and the call runs with
     kernels per stage, then persistently again with the default limit; the chain
     is the oracle's."""
     O = oracle_mod
