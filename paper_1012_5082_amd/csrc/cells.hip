@@ -708,6 +708,7 @@ __global__ void __launch_bounds__(BLOCK)
   static_assert(CAP <= NST * BMAX && CAP + 3 <= 65536, "staged indices in 16 bits");
   if (cond && *cond == 0) return;
   if (cond && blockIdx.x == 0 && threadIdx.x == 0) ds->md_rebuilds += 1ull;
+  if (FIN && blockIdx.x == 0 && threadIdx.x == 0) atomicOr(&ds->pairs_new, PAIRS_BUILT);
   __shared__ float4 cand[CAP + 3];  // + 3: the search reads up to 3 past a run
   __shared__ int off[NST + 1];
   __shared__ int gbin[NST];

@@ -74,6 +74,7 @@ struct StageProgress {
 };
 
 // Device-resident counters and chain scalars of one context.
+constexpr unsigned long long PAIRS_BUILT = 1ull << 63;
 struct DevState {
   unsigned long long trials, local_acc, stages, stage_acc, flips, near_ties;
   long long n_b[2];             // n_B, ping-pong by stage parity within a call
@@ -93,7 +94,8 @@ struct DevState {
   unsigned long long smp_n, dalog_n;      // sample-log and surrogate-log records written
   unsigned long long md_rebuilds;         // MD list rebuilds taken on the device
   // entries and longest row of a list built by the kernel that also finishes it
-  // (its blocks add to them; the next density pass moves them to pairs_md, kmax_md)
+  // (its blocks add to them; the next density pass moves them to pairs_md, kmax_md);
+  // pairs_new has PAIRS_BUILT set, so that a list without entries is moved, too
   unsigned long long pairs_new;
   int kmax_new;
   unsigned long long wcur;                // sweep counter of a graph-replayed sweep

@@ -253,7 +253,7 @@ __device__ __forceinline__ void bin_clear(const BinClear &c, int64_t i, int64_t 
   if (c.count)
     for (int64_t q = i; q < c.nbins; q += threads) c.count[q] = 0;
   if (i == 0 && c.ds->pairs_new) {
-    c.ds->pairs_md = c.ds->pairs_new;
+    c.ds->pairs_md = c.ds->pairs_new & ~PAIRS_BUILT;
     c.ds->kmax_md = c.ds->kmax_new;
     c.ds->pairs_new = 0ull;
     c.ds->kmax_new = 0;

@@ -907,6 +907,26 @@ def test_md_list_statistics_after_rebuild(torch_cuda, oracle_mod, dims):
     g.close()
 
 
+def test_md_list_statistics_of_an_empty_list(torch_cuda, oracle_mod):
+    """Two atoms that fly apart: the list rebuilt on the way has no entry, and
+    says so."""
+    O = oracle_mod
+    pot = I.params("FS-P1")
+    x, y, z = np.array([8.0, 11.85]), np.array([9.0, 9.0]), np.array([10.0, 10.0])
+    v, zero = np.array([-0.05, 0.05]), np.zeros(2)
+    box, sp = np.full(3, 20.0), np.array([0, 1], np.uint8)
+    d = dict(x=x, y=y, z=z, box=box, species=sp, vx=v, vy=zero, vz=zero)
+    g = gpu_context(d, pot, velocities=True)
+    g.md(1.0, 1)
+    assert g.info()["md_pairs"] == 2
+    g.md(1.0, 11)
+    assert g.info()["md_rebuilds"] > 1
+    assert g.info()["md_pairs"] == 0
+    out = O.md(x, y, z, v, zero, zero, sp, box, pot, 1.0, 12)
+    assert np.array_equal(g.x.cpu().numpy(), out[0])
+    g.close()
+
+
 @pytest.mark.parametrize("path", ["pipeline", "da_perfect", "chain3", "persistent", "batch",
                                   "da_batch"])
 def test_sweep_paths_after_md(torch_cuda, oracle_mod, path):
