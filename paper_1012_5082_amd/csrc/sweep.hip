@@ -927,6 +927,7 @@ __global__ void __launch_bounds__(BLOCK) k_commit_chain(SweepArgs a, uint64_t w_
 //   SM_TRIAL  (w, s): trials of (w, s)                         -> SM_DECIDE (w, s)
 //   SM_DECIDE (w, s): global test of (w, s); accepted: commit  -> SM_TRIAL next
 //                                  otherwise: trials of next   -> SM_DECIDE next
+//                                  (sweeps of a single stage: none -> SM_TRIAL next)
 // and the stage after the last one of the call leads to SM_DONE (kernels
 // launched beyond that do nothing).  The draws are those of the per-stage
 // path, so both give the same chain.  The site table of sweep w + 1, stage s
@@ -1300,6 +1301,9 @@ __global__ void __launch_bounds__(BLOCK) k_stage(SweepArgs a, int par) {
     s2 = 0;
   }
   const bool more = w2 < w_end;
+  // sweeps of one stage (grown domains of no more atoms than cells): the next
+  // stage's sites are drawn by this kernel, so its trials take one of their own
+  const bool ahead = more && S > 1;
   // the trial blocks' counts of (w, s) and ln u_g first: their reads then
   // overlap the trial reads below
   const double lnug = a.stage_lnug[(int64_t)(m.w & 1) * S + m.s];
@@ -1315,7 +1319,7 @@ __global__ void __launch_bounds__(BLOCK) k_stage(SweepArgs a, int par) {
   v.m = 0;
   v.s = 0;
   v.ri = 0.0;
-  if (!DA && more) pipe_trials_load<F>(a, w2, s2, t, lane, i2, lnu2, v);
+  if (!DA && ahead) pipe_trials_load<F>(a, w2, s2, t, lane, i2, lnu2, v);
   // global test of (w, s) (Eq. trans_vcsgc_par2) from the trial blocks' counts
   block_sums<3, false>(c3, shd);
   const long long n_valid = c3[0] & 0xffffffffll, n_plus = c3[0] >> 32;
@@ -1339,7 +1343,7 @@ __global__ void __launch_bounds__(BLOCK) k_stage(SweepArgs a, int par) {
       const int32_t i = a.rec[(gs & 1) * rstride + t];
       if (i >= 0) pipe_commit<F>(a, i, lane);
     }
-  } else if (more) {
+  } else if (ahead) {
     if constexpr (DA)
       pipe_trials_da<F>(a, w2, s2, t, lane, a.rec + ((gs + 1) & 1) * rstride,
                         a.part + ((gs + 1) & 1) * pstride + NPW * blockIdx.x, sh,
@@ -1383,7 +1387,7 @@ __global__ void __launch_bounds__(BLOCK) k_stage(SweepArgs a, int par) {
     n.w = w2;
     n.s = s2;
     n.nb = nb_new;
-    n.phase = !more ? SM_DONE : (gacc == 1 ? SM_TRIAL : SM_DECIDE);
+    n.phase = !more ? SM_DONE : (gacc == 1 || !ahead ? SM_TRIAL : SM_DECIDE);
     n.pad = 0;
     ds->pipe.sm[par ^ 1] = n;
     ds->pipe.used += 1;
@@ -1875,9 +1879,9 @@ static hipError_t pipe_launch(vcsgc_ctx *c, const SweepArgs &a, unsigned grid, i
 
 // Sweeps w .. w + n_sweeps - 1 through the fused pipeline (a.D = 0: one
 // stage per kernel; the kernels a call needs are one per stage, plus one,
-// plus one per accepted stage) or the batched pipeline (a.D stages per
-// kernel; about one kernel per D stages plus one per accepted stage).  The
-// host launches its estimate, reads the pipeline's progress and launches
+// plus one per accepted stage, or two per stage where a sweep has a single
+// one) or the batched pipeline (a.D stages per kernel; about one kernel per D
+// stages plus one per accepted stage).  The host launches its estimate, reads the pipeline's progress and launches
 // more until the last stage has been decided.
 static hipError_t launch_pipeline(vcsgc_ctx *c, SweepArgs a, double dmu0, double kappa,
                                   double cbar, double T, int64_t n_sweeps, bool use_graph,

@@ -144,6 +144,49 @@ def test_grown_perfect_surrogate_equals_plain(torch_cuda, oracle_mod):
         g.close()
 
 
+def _gas(n=24):
+    """n atoms anywhere in a box of 4 x 3 x 2 cells, no two closer than 2 A:
+    no more atoms than cells, so a sweep has one stage."""
+    r = np.random.default_rng(77)
+    box = np.array([60.0, 45.0, 38.0])
+    pts = []
+    while len(pts) < n:
+        q = r.uniform(0.0, 1.0, 3) * box
+        if all(np.linalg.norm((q - p + box / 2) % box - box / 2) > 2.0 for p in pts):
+            pts.append(q)
+    pts = np.array(pts)
+    return dict(x=pts[:, 0].copy(), y=pts[:, 1].copy(), z=pts[:, 2].copy(), box=box,
+                species=I.initial_species(n, 0.4, 78))
+
+
+GAS_ARGS = (0.0, 1.0, 0.4, 900.0)
+
+
+@pytest.mark.parametrize("path", ["stage", "logged", "batch", "perfect"])
+def test_grown_one_stage_sweeps(torch_cuda, oracle_mod, path):
+    """A sweep of one stage: the sites of the next sweep are drawn by the
+    kernel that tests this one, and its trials are made after that."""
+    O = oracle_mod
+    pot = I.params("FS-P1")
+    d = _gas()
+    g = _ctx(d, pot, 14.5)
+    assert g.info()["stages_per_sweep"] == 1 and tuple(g.info()["n_cells"]) == (4, 3, 2)
+    g.set_tuning("batch" if path == "batch" else "stage", 3)
+    if path == "logged":
+        g.enable_log(40 * 24, 40)
+    if path == "perfect":
+        g.set_surrogate("perfect")
+    print(f"[grown] one stage per sweep, {path}", flush=True)
+    st = O.SweepState(d["x"], d["y"], d["z"], d["box"], d["species"], pot)
+    for n in (1, 2, 37):
+        sg = g.sweep(*GAS_ARGS, n, 99)
+        so, _, _ = O.sweep(st, *GAS_ARGS, n, 99, grow_edge=14.5)
+        for key in ("trials", "local_accepts", "stages", "stage_accepts", "flips", "n_final"):
+            assert sg[key] == so[key], key
+    _check(O, g, st, sg, so)
+    g.close()
+
+
 def test_grown_argument_checks(torch_cuda):
     from paper_1012_5082_amd.binding import VcsgcError
     pot = I.params("FS-P1")
