@@ -388,8 +388,13 @@ __global__ void k_set_sweep(DevState *ds, unsigned long long w) {
   if (threadIdx.x == 0 && blockIdx.x == 0) ds->wcur = w;
 }
 
+// (a replay's first stage has parity 0, also where the sweep before it ended
+// at parity 0: an odd number of stages)
 __global__ void k_next_sweep(DevState *ds) {
-  if (threadIdx.x == 0 && blockIdx.x == 0) ds->wcur += 1ull;
+  if (threadIdx.x == 0 && blockIdx.x == 0) {
+    ds->wcur += 1ull;
+    ds->n_b[0] = ds->n_b_cur;
+  }
 }
 
 // The trials of a whole sweep: for stage s and active cell t, the site drawn

@@ -1164,3 +1164,32 @@ def test_persistent_batches(torch_cuda, oracle_mod, nx, colours, kappa, tpg):
     assert np.array_equal(g.species.cpu().numpy(), st.species)
     assert np.array_equal(g.rho().cpu().numpy(), st.rho)
     g.close()
+
+
+@pytest.mark.parametrize("k", [2, 5])
+def test_local_chains_odd_stages(torch_cuda, oracle_mod, k):
+    """Local chains over sweeps of an odd number of stages (27 colours): n_B
+    after the last stage of a sweep is the one that the next sweep starts
+    from, also between the sweeps of one call."""
+    O = oracle_mod
+    from paper_1012_5082_amd.binding import VCSGC
+    pot = I.params("FS-P1")
+    x, y, z, box = I.bcc(12, 12, 12)
+    x, y, z = I.thermalize(x, y, z, box, 0.05, 5)
+    sp = I.initial_species(x.size, 0.1, 6)
+    args = (-0.3, 1.0, 0.1, 600.0)
+    g = VCSGC(x, y, z, box, sp, pot, colours=27)
+    g.set_local_steps(k)
+    S = g.info()["stages_per_sweep"]
+    assert S % 2 == 1
+    sg = g.sweep(*args, 4, 313)
+    st = O.SweepState(x, y, z, box, sp, pot)
+    so, _, sl = O.sweep(st, *args, 4, 313, local_steps=k, colour_period=3, log_stages=4 * S)
+    last = [sl[S * (q + 1) - 1] for q in range(3)]
+    assert any(r[5] == 1.0 and r[3] != 0.0 for r in last)  # n_B changes in a last stage
+    for key in ("trials", "local_accepts", "stages", "stage_accepts", "flips", "n_final",
+                "sum_n", "sum_n2"):
+        assert sg[key] == so[key], key
+    assert np.array_equal(g.species.cpu().numpy(), st.species)
+    assert np.array_equal(g.rho().cpu().numpy(), st.rho)
+    g.close()
