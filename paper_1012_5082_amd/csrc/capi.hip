@@ -1130,8 +1130,10 @@ vcsgc_status md_nvt_steps(vcsgc_ctx *c, double dt_fs, int64_t n_steps, bool dev)
   VC_CHECK(c, hipMemsetAsync(c->ds->rebuild, 0, 2 * sizeof(int), c->stream), "reset");
   VC_CHECK(c, vc::launch_pack(c), "pack");
   VC_CHECK(c, vc::launch_forces(c), "forces");
-  VC_CHECK(c, vc::launch_nvt_ke(c, dt_fs, false), "thermostat");
-  VC_CHECK(c, vc::launch_nvt_thermo(c, dt_fs, 2), "thermostat");
+  if (n_steps > 0) {  // a call of no steps leaves xi and eta
+    VC_CHECK(c, vc::launch_nvt_ke(c, dt_fs, false), "thermostat");
+    VC_CHECK(c, vc::launch_nvt_thermo(c, dt_fs, 2), "thermostat");
+  }
   for (int64_t k = 0; k < n_steps; ++k) {
     const int par = dev ? (int)(k & 1) : 0;
     VC_CHECK(c, vc::launch_nvt_kick_drift(c, dt_fs, par), "kick-drift");

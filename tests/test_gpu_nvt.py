@@ -58,6 +58,25 @@ def test_nvt_parity(torch_cuda, oracle_mod, n, T):
     g.close()
 
 
+def test_nvt_call_of_no_steps(torch_cuda, oracle_mod):
+    """md(dt, 0) evaluates the forces and leaves the trajectory and the
+    thermostat's state as they are."""
+    O = oracle_mod
+    pot = I.params("FS-P1")
+    d = _md_system(n=8, T=700.0, seed=48)
+    g = gpu_context(d, pot, velocities=True)
+    g.set_thermostat(1200.0, 40.0, xi=0.001, eta=0.25)
+    g.md(2.5, 0)
+    assert g.thermostat() == (0.001, 0.25)
+    g.md(2.5, 7)
+    out, th = O.md_nvt(d["x"], d["y"], d["z"], d["vx"], d["vy"], d["vz"], d["species"], d["box"],
+                       pot, 2.5, 7, 1200.0, 40.0, xi=0.001, eta=0.25)
+    assert g.thermostat() == tuple(th)
+    for nm, want in zip(NAMES, out[:9]):
+        assert np.array_equal(getattr(g, nm).cpu().numpy(), want), nm
+    g.close()
+
+
 def test_nvt_infinite_coupling_time_is_nve(torch_cuda):
     """tau = infinity: the thermostat's kernels leave the NVE trajectory of
     the fused NVE passes unchanged, bit for bit."""
