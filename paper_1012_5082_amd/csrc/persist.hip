@@ -1,6 +1,6 @@
 // Persistent parallel VC-SGC sweep for a batch of independent replicas
-// (a single system is a batch of one), one cooperative launch for all
-// sweeps of a call.
+// (a single system is a batch of one), one launch for all sweeps of a call,
+// a cooperative one where workgroups wait for each other.
 //
 // Replica r owns workgroups [g0, g0 + G) of the grid, each a contiguous share
 // of the replica's active cells.  A stage whose global test fails changes
